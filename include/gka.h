@@ -92,8 +92,9 @@ typedef enum { GKA_STATE_FULL = 0, GKA_STATE_H_LOWER_BLOCKS = 1 } gka_state_layo
  * GKA_PATH_RECURRENT: Eq. (CH) token by token, one workgroup per (batch, head) pair with the states in registers (the
  *                     kernel of gka_decode_tokens), float32 arithmetic whatever p->compute says. Every head dimension,
  *                     dtype, stride and variant, with xhat_out and fro_out; GKA_PHASE_ALL only. It is the only path
- *                     for d = 256 and for float32 tensors or operands at d = 16 and 32 (what GKA_PATH_AUTO selects
- *                     there) and its parallelism is the number of pairs: meant for short sequences over many heads
+ *                     for float32 tensors or operands at d = 16 and 32 and for d = 256 up to 128 tokens (what
+ *                     GKA_PATH_AUTO selects there; longer sequences at d = 256 run chunk-wise with float32 products)
+ *                     and its parallelism is the number of pairs: meant for short sequences over many heads
  *                     and as a float32 cross-check of the chunk-wise kernels, not for long sequences over few
  *                     pairs. Gates are used as given (no floor at exp(-100)). */
 typedef enum { GKA_PATH_AUTO = 0, GKA_PATH_TWO_PHASE = 1, GKA_PATH_FUSED = 2, GKA_PATH_RECURRENT = 3 } gka_path;
@@ -148,7 +149,8 @@ typedef struct {
  * states; p->slab_state_bytes overrides that budget). The fused kernel (gka_path) needs only the segment summaries
  * of its chunk walk; the query returns the larger of the two sizes. The chunk-wise kernels of d = 16 and 32 keep four
  * d x d float32 states per chunk. The token-by-token path (GKA_PATH_RECURRENT) keeps
- * its states in registers: 256 bytes, plus one U state per pair at d = 256. Its contents after a call are unspecified. */
+ * its states in registers: 256 bytes, plus one U state per pair at d = 256 (above 128 tokens d = 256 runs chunk-wise, its
+ * chunk states bounded by the same 1 GiB). Its contents after a call are unspecified. */
 size_t gka_forward_workspace_bytes(const gka_params *p);
 
 /* Whole-sequence forward, Eq. (CH).

@@ -18,6 +18,7 @@ struct Plan {
     int pairs_per_batch;          // (batch, head) pairs per launch
     int slab_chunks;              // chunks of every pair per launch
     bool recurrent;               // token-by-token kernel: no chunks, no launch plan
+    bool wide;                    // d = 256 chunk-wise: the two-phase kernels with float32 products
     bool small;                   // chunk-wise kernels of the head dimensions 16 and 32 (bf16 tensors and operands)
     bool split;                   // GKA_COMPUTE_BF16_SPLIT (fused kernel only)
     bool fused_shape;             // dtype, operands and head dimension of the fused kernel
@@ -34,6 +35,9 @@ constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walk
 constexpr size_t kDefaultSlabStateBytes = (size_t)1 << 30;
 // Workgroups the fused kernel should at least have: one per compute unit.
 constexpr int kFusedMinWorkgroups = 256;
+// Above this length d = 256 runs chunk-wise (300 tokens of 4 pairs: 0.13 ms against 4.6 ms token by token; the chunk states
+// need a workspace that shorter sequences are not asked for).
+constexpr int kWideMinTokens = 2 * gka::kChunk;
 constexpr size_t kMaxPairsPerBatch = 1024;
 constexpr size_t kMinSlabChunks = 4;
 
@@ -76,7 +80,10 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     // GKA_PATH_TWO_PHASE select there), else token by token
     pl->small = pl->d <= 32 && pl->io_bf16 && p->compute == GKA_COMPUTE_BF16 && !readout_only &&
                 (p->path == GKA_PATH_AUTO || p->path == GKA_PATH_TWO_PHASE);
-    pl->recurrent = !pl->small && (p->path == GKA_PATH_RECURRENT || !chunked_dim(pl->d));
+    // d = 256: GKA_PATH_AUTO takes the chunk-wise kernels with float32 products (the token-by-token kernel's arithmetic)
+    // above kWideMinTokens
+    pl->wide = pl->d == 256 && p->path == GKA_PATH_AUTO && p->T > kWideMinTokens && !pl->split && !readout_only;
+    pl->recurrent = !pl->small && !pl->wide && (p->path == GKA_PATH_RECURRENT || !chunked_dim(pl->d));
     if (pl->recurrent && (p->path == GKA_PATH_TWO_PHASE || p->path == GKA_PATH_FUSED || readout_only))
         return GKA_ERR_UNSUPPORTED;
     if ((int64_t)pl->n_pairs * pl->n_chunks > (int64_t)0x7fffffff) return GKA_ERR_SHAPE;
@@ -95,6 +102,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
         pl->stride_t = p->stride_t;
         pl->stride_h = p->stride_h;
     }
+    if (pl->wide) pl->compute_bf16 = false;
     if (pl->small) {
         if ((int64_t)pl->n_pairs * pl->n_chunks > (int64_t)0x7fffffff / 4) return GKA_ERR_SHAPE;
         pl->fused_shape = false;
@@ -258,6 +266,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     }
     const bool fused_ok = pl.fused_shape && !p->xhat_out && !solve_only && !q_lo && p->phase == GKA_PHASE_ALL;
     if ((p->path == GKA_PATH_FUSED || pl.split) && !fused_ok) return GKA_ERR_UNSUPPORTED;
+    if (pl.wide && p->phase != GKA_PHASE_ALL) return GKA_ERR_UNSUPPORTED;
     if (pl.split && p->path == GKA_PATH_TWO_PHASE) return GKA_ERR_UNSUPPORTED;     // only the fused kernel splits
     if (fused_ok && p->path != GKA_PATH_TWO_PHASE) {
         gka::FusedArgs fa = {};
@@ -300,6 +309,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     so.ws_H = sa.ws_H; so.ws_U = sa.ws_U; so.ws_hn = sa.ws_hn;
     so.stride_b = pl.stride_b; so.stride_t = pl.stride_t; so.stride_h = pl.stride_h;
     so.H = p->H; so.T = p->T; so.n_iter = p->n_iter;
+    so.init_states = H_init != nullptr;
     const bool one_launch = pl.pairs_per_batch >= pl.n_pairs && pl.slab_chunks >= pl.n_chunks;
     // With a single phase requested the workspace must cover the whole problem.
     if (p->phase != GKA_PHASE_ALL && !one_launch) return GKA_ERR_UNSUPPORTED;

@@ -1,4 +1,4 @@
-// Per-chunk solve: chunk-wise Frobenius norms (Section 4.2.1), the fused Chebyshev driver
+// Per-chunk solve with bf16 products (float32 products: gka_solve_f32.hip): chunk-wise Frobenius norms (Section 4.2.1), the fused Chebyshev driver
 // (Algorithm 1 on all tokens of the chunk at once) and the readout y_c = U_c xhat_c of Eq. (CH).
 //
 // One workgroup = one chunk of one (batch, head) pair = four waves. Wave w owns the token block tw = w & 1
@@ -243,23 +243,16 @@ __device__ __forceinline__ void build_row_frags(typename MMA::frag *sK, const ty
                                                 int lane)
 {
     typedef SolveShape<MMA, D> SH;
-    constexpr int VEC = MMA::VEC, HS = MMA::HS, NB = SH::NB;
+    constexpr int HS = MMA::HS, NB = SH::NB;
     const typename SH::Rows at;
     const int n = lane & 31, g = lane >> 5;
     for (int f = w; f < SH::K_FRAGS; f += 4) {
         const int hh = f % HS, blk = (f / HS) % NB, jt = f / (HS * NB);
-        if constexpr (VEC == 8) {
-            // kidx(8*hh + p, g) = 16*hh + 8*(p/4) + 4*g + p%4: two runs of four consecutive features
-            const int col = 32 * blk + 16 * hh + 4 * g;
-            u16x4 lo = *(const u16x4 *)(sRow + at(32 * jt + n, col)), hi = *(const u16x4 *)(sRow + at(32 * jt + n, col + 8));
-            u16x8 u = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            sK[f * 64 + lane] = __builtin_bit_cast(typename MMA::frag, u);
-        } else {
-            typename MMA::elem_t e[VEC];
-#pragma unroll
-            for (int p = 0; p < VEC; ++p) e[p] = sRow[at(32 * jt + n, 32 * blk + kidx(hh * VEC + p, g))];
-            sK[f * 64 + lane] = MMA::pack_elems(e);
-        }
+        // kidx(8*hh + p, g) = 16*hh + 8*(p/4) + 4*g + p%4: two runs of four consecutive features
+        const int col = 32 * blk + 16 * hh + 4 * g;
+        u16x4 lo = *(const u16x4 *)(sRow + at(32 * jt + n, col)), hi = *(const u16x4 *)(sRow + at(32 * jt + n, col + 8));
+        u16x8 u = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        sK[f * 64 + lane] = __builtin_bit_cast(typename MMA::frag, u);
     }
 }
 
@@ -270,20 +263,15 @@ __device__ __forceinline__ void build_transposed_frags(typename MMA::frag *sAT, 
                                                        int w, int lane)
 {
     typedef SolveShape<MMA, D> SH;
-    constexpr int VEC = MMA::VEC, HS = MMA::HS;
+    constexpr int HS = MMA::HS;
     const typename SH::Rows at;
-    const int n = lane & 31, g = lane >> 5;
+    const int g = lane >> 5;
     for (int f = w; f < SH::KT_FRAGS; f += 4) {
         const int hh = f % HS, jt = (f / HS) % 2, mt = f / (2 * HS);
-        if constexpr (VEC == 8) {
-            const int t0 = 32 * jt + 16 * hh + 4 * g;       // kidx(8*hh + p, g) = 16*hh + 8*(p/4) + 4*g + p%4
-            const int col16 = 32 * mt + 16 * ((lane >> 4) & 1);
-            sAT[f * 64 + lane] = UNTRACKED ? gather_transposed_bf16_untracked(sRow, at, col16, lane, t0, t0 + 8)
-                                           : gather_transposed_bf16(sRow, at, col16, lane, t0, t0 + 8);
-        } else {
-            auto tok_of = [&](int p) { return 32 * jt + kidx(hh * VEC + p, g); };
-            sAT[f * 64 + lane] = gather_transposed<MMA>(sRow, at, 32 * mt + n, tok_of);
-        }
+        const int t0 = 32 * jt + 16 * hh + 4 * g;           // kidx(8*hh + p, g) = 16*hh + 8*(p/4) + 4*g + p%4
+        const int col16 = 32 * mt + 16 * ((lane >> 4) & 1);
+        sAT[f * 64 + lane] = UNTRACKED ? gather_transposed_bf16_untracked(sRow, at, col16, lane, t0, t0 + 8)
+                                       : gather_transposed_bf16(sRow, at, col16, lane, t0, t0 + 8);
     }
 }
 
@@ -535,12 +523,7 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
                 if (idx < TOTAL) xi[idx / 16][idx % 16] += dl[idx / 16][idx % 16];
             }
         };
-        if constexpr (MMA::kFusedPassSweep) {
-            fused_pass_sweep<MMA, NSTEPS, NJ, NBH>(Kset, Hset, myX, pacc, gS, lane, add_delta);
-        } else {
-            fused_gemm<MMA, NSTEPS, NJ, decltype(add_delta), NJ>(Kset, myX, pacc, lane, add_delta);
-            fused_gemm<MMA, NSTEPS, NBH>(Hset, myX, gS, lane);
-        }
+        fused_pass_sweep<MMA, NSTEPS, NJ, NBH>(Kset, Hset, myX, pacc, gS, lane, add_delta);
         frag pm[NJ][HS];
         mask_p<MMA, TW>(pacc, mreg, pm);
         lds_barrier();                       // the exchange region may be overwritten from here on
@@ -549,26 +532,15 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
         // -r_{i-1} = zeta gS + gI + lam xi; delta_i = cm delta_{i-1} - omega s0 r_{i-1}: the gS term is formed while the
         // MFMAs that finish gI are in flight
         constexpr int TOTAL = NBH * 16, NM = NBH * (TW + 1) * HS, PERM = (TOTAL + NM - 1) / NM;
-        if constexpr (MMA::kFusedPassSweep) {
-            gemm_intra<MMA, NBH, TW>(sKT, mt0, pm, gI, lane, [&](auto step) {
-                constexpr int S = decltype(step)::value;
-                const float ncz = ncs * zeta;
-#pragma unroll
-                for (int e = 0; e < PERM; ++e) {
-                    const int idx = S * PERM + e;
-                    if (idx < TOTAL)
-                        dl[idx / 16][idx % 16] = cm * dl[idx / 16][idx % 16] + ncz * gS[idx / 16][idx % 16];
-                }
-            });
-        } else {
-            // many short MFMAs per product: the compiler's own schedule is better than a pinned interleaving
-            gemm_intra<MMA, NBH, TW>(sKT, mt0, pm, gI, lane);
+        gemm_intra<MMA, NBH, TW>(sKT, mt0, pm, gI, lane, [&](auto step) {
+            constexpr int S = decltype(step)::value;
             const float ncz = ncs * zeta;
 #pragma unroll
-            for (int i = 0; i < NBH; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) dl[i][r] = cm * dl[i][r] + ncz * gS[i][r];
-        }
+            for (int e = 0; e < PERM; ++e) {
+                const int idx = S * PERM + e;
+                if (idx < TOTAL) dl[idx / 16][idx % 16] = cm * dl[idx / 16][idx % 16] + ncz * gS[idx / 16][idx % 16];
+            }
+        });
         const float ncl = ncs * lam;
 #pragma unroll
         for (int i = 0; i < NBH; ++i)
@@ -601,8 +573,7 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
         for (int r = 0; r < 16; ++r) xi[i][r] += dl[i][r];                               // xi_r
 
     // ---------------- readout y_c = zeta_c U_[n] xhat_c + sum_{j<=c} M[j,c] v_j (k_j . xhat_c) ----------------
-    constexpr int NSPL = MMA::kSplitReadout ? 2 : 1;
-    const frag *Uw = (const frag *)a.ws_U + chunk_id * (NSPL * SH::H_FRAGS * 64);
+    const frag *Uw = (const frag *)a.ws_U + chunk_id * (2 * SH::H_FRAGS * 64);    // value and remainder
     RowStage<MMA, IO, D> vrows;
     // The addresses of the readout's loads and staging stores are formed here, from a copy of the thread index that
     // the compiler cannot trace back past this point: formed before the passes (where it would hoist them, or keep
@@ -635,32 +606,27 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
                     xi[i][4 * q4 + e] = al * xi[i][4 * q4 + e] + (1.0f - al) * (valid ? qv4[e] : 0.0f);
             }
     }
-    // the operand of the readout as B operand: the rounded value and, on the bf16 path, the rounding remainder as a
-    // second operand
+    // the operand of the readout as B operand: the rounded value and the rounding remainder as a second operand
     frag ownlo[NBH][HS];
 #pragma unroll
     for (int i = 0; i < NBH; ++i)
 #pragma unroll
         for (int hh = 0; hh < HS; ++hh) {
             own[i][hh] = MMA::pack(&xi[i][hh * VEC]);
-            if (NSPL == 2) {
-                float lo[VEC], back[VEC];
-                MMA::unpack(own[i][hh], back);
+            float lo[VEC], back[VEC];
+            MMA::unpack(own[i][hh], back);
 #pragma unroll
-                for (int p = 0; p < VEC; ++p) lo[p] = xi[i][hh * VEC + p] - back[p];
-                ownlo[i][hh] = MMA::pack(lo);
-            }
+            for (int p = 0; p < VEC; ++p) lo[p] = xi[i][hh * VEC + p] - back[p];
+            ownlo[i][hh] = MMA::pack(lo);
         }
     // The rounding remainder of U_[n] is used once, against the rounded xhat: its fragments go from global memory
     // straight into registers (the passes' registers are free by now) and never pass through LDS.
     frag ulo[NBH][NSTEPS];
-    if (NSPL == 2) {
-        const frag *Ulo = Uw + SH::H_FRAGS * 64;
+    const frag *Ulo = Uw + SH::H_FRAGS * 64;
 #pragma unroll
-        for (int i = 0; i < NBH; ++i)
+    for (int i = 0; i < NBH; ++i)
 #pragma unroll
-            for (int st = 0; st < NSTEPS; ++st) ulo[i][st] = Ulo[((mt0 + i) * NSTEPS + st) * 64 + lane_late];
-    }
+        for (int st = 0; st < NSTEPS; ++st) ulo[i][st] = Ulo[((mt0 + i) * NSTEPS + st) * 64 + lane_late];
     lds_barrier();                           // every wave is done with H_[n], K^T and the exchange region
     async_block_copy<H16>(sH, Uw, w, lane_late);    // U_[n] (rounded part) replaces H_[n]
     vrows.store(sRow, tok0, a.T, tid_late);
@@ -672,19 +638,17 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
     lds_barrier();
     f32x16 acc[NJ + NBH];
     fused_gemm<MMA, NSTEPS, NJ + NBH, NoFill, NJ + NBH>(Aset, myX, acc, lane);   // K xhat^T and U xhat
-    if (NSPL == 2) {
-        // remainder of U_[n] (registers) times the rounded xhat (still published)
+    // remainder of U_[n] (registers) times the rounded xhat (still published)
 #pragma unroll
-        for (int st = 0; st < NSTEPS; ++st) {
-            const frag bx = myX[st * 64 + lane];
+    for (int st = 0; st < NSTEPS; ++st) {
+        const frag bx = myX[st * 64 + lane];
 #pragma unroll
-            for (int i = 0; i < NBH; ++i) acc[NJ + i] = MMA::mma(ulo[i][st], bx, acc[NJ + i]);
-        }
-        lds_barrier();
-        publish_operand<MMA, NB>(sX, ownlo, TW, mt0, lane);
-        lds_barrier();
-        fused_gemm<MMA, NSTEPS, NJ + NBH>(Aset, myX, acc, lane);      // K and rounded U on the remainder of xhat
+        for (int i = 0; i < NBH; ++i) acc[NJ + i] = MMA::mma(ulo[i][st], bx, acc[NJ + i]);
     }
+    lds_barrier();
+    publish_operand<MMA, NB>(sX, ownlo, TW, mt0, lane);
+    lds_barrier();
+    fused_gemm<MMA, NSTEPS, NJ + NBH>(Aset, myX, acc, lane);      // K and rounded U on the remainder of xhat
     frag pm[NJ][HS];
     f32x16 y[NBH];
     {
@@ -728,29 +692,11 @@ __global__ __launch_bounds__(kSolveThreads) __attribute__((amdgpu_waves_per_eu(2
     chunk_solve_body<MmaBF16, IO, D, GATED>(a);
 }
 
-// fp32 path: its fragments are twice as large, one workgroup per CU.
 template <class IO, int D, bool GATED>
-__global__ __launch_bounds__(kSolveThreads) void chunk_solve_kernel_f32(SolveArgs a)
+static hipError_t launch_chunk_solve_g(const SolveArgs &a, hipStream_t stream)
 {
-    chunk_solve_body<MmaF32, IO, D, GATED>(a);
-}
-
-template <class MMA, class IO, int D, bool GATED>
-struct SolveKernel;
-template <class IO, int D, bool GATED>
-struct SolveKernel<MmaBF16, IO, D, GATED> {
-    static constexpr auto fn = chunk_solve_kernel_bf16<IO, D, GATED>;
-};
-template <class IO, int D, bool GATED>
-struct SolveKernel<MmaF32, IO, D, GATED> {
-    static constexpr auto fn = chunk_solve_kernel_f32<IO, D, GATED>;
-};
-
-template <class MMA, class IO, int D, bool GATED>
-static hipError_t launch_chunk_solve_g(const SolveArgs &a, int n_pairs, hipStream_t stream)
-{
-    typedef SolveShape<MMA, D> SH;
-    auto kern = SolveKernel<MMA, IO, D, GATED>::fn;
+    typedef SolveShape<MmaBF16, D> SH;
+    auto kern = chunk_solve_kernel_bf16<IO, D, GATED>;
     // (set once per kernel instantiation and device, not per launch)
     static bool attr_set_on[64] = {};
     int dev = 0;
@@ -761,34 +707,26 @@ static hipError_t launch_chunk_solve_g(const SolveArgs &a, int n_pairs, hipStrea
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_set_on[dev] = true;
     }
-    SolveArgs args = a;
-    args.n_pairs = n_pairs;
-    dim3 grid((unsigned)(n_pairs * a.n_chunks)), block(kSolveThreads);
-    const size_t lds = SH::lds_bytes;
-    hipLaunchKernelGGL(kern, grid, block, lds, stream, args);
+    dim3 grid((unsigned)(a.n_pairs * a.n_chunks)), block(kSolveThreads);
+    hipLaunchKernelGGL(kern, grid, block, SH::lds_bytes, stream, a);
     return hipGetLastError();
 }
 
-template <class MMA, class IO, int D>
-static hipError_t launch_chunk_solve_t(const SolveArgs &a, int n_pairs, hipStream_t stream)
+template <class IO, int D>
+static hipError_t launch_chunk_solve_t(const SolveArgs &a, hipStream_t stream)
 {
-    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_chunk_solve_g<MMA, IO, D, true>(a, n_pairs, stream);
-    return launch_chunk_solve_g<MMA, IO, D, false>(a, n_pairs, stream);
+    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_chunk_solve_g<IO, D, true>(a, stream);
+    return launch_chunk_solve_g<IO, D, false>(a, stream);
 }
 
 hipError_t launch_chunk_solve(const SolveArgs &a, int n_pairs, int d, bool io_bf16, bool compute_bf16,
                               hipStream_t stream)
 {
-    if (compute_bf16) {
-        if (d == 128) return launch_chunk_solve_t<MmaBF16, IOBF16, 128>(a, n_pairs, stream);
-        return launch_chunk_solve_t<MmaBF16, IOBF16, 64>(a, n_pairs, stream);
-    }
-    if (io_bf16) {
-        if (d == 128) return launch_chunk_solve_t<MmaF32, IOBF16, 128>(a, n_pairs, stream);
-        return launch_chunk_solve_t<MmaF32, IOBF16, 64>(a, n_pairs, stream);
-    }
-    if (d == 128) return launch_chunk_solve_t<MmaF32, IOF32, 128>(a, n_pairs, stream);
-    return launch_chunk_solve_t<MmaF32, IOF32, 64>(a, n_pairs, stream);
+    SolveArgs args = a;
+    args.n_pairs = n_pairs;
+    if (!compute_bf16) return launch_solve_f32(args, d, io_bf16, stream);
+    if (d == 128) return launch_chunk_solve_t<IOBF16, 128>(args, stream);
+    return launch_chunk_solve_t<IOBF16, 64>(args, stream);
 }
 
 size_t ws_H_bytes_per_chunk(int d, bool compute_bf16) { return (size_t)d * d * (compute_bf16 ? 2 : 4); }

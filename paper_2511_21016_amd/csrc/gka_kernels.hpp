@@ -53,6 +53,7 @@ struct SolveArgs {
     int pair0;                    // first (batch, head) pair of this launch; workspace is indexed from 0
     bool readout_only;            // variants' kernel: no solve (its result is discarded by alpha = 0): H_[n] is not read
     bool solve_only;              // variants' kernel: xhat_out is all the caller wants: U_[n] is not read, o not written
+    bool init_states;             // the sequence starts from given states (else the states before chunk 0 are zero)
 };
 
 struct DecodeArgs {
@@ -186,6 +187,8 @@ hipError_t launch_state_pass(const StatePassArgs &a, int n_pairs, int d, bool io
 int state_pass_workgroups_per_segment(int n_pairs, int d, bool compute_bf16);
 hipError_t launch_chunk_solve(const SolveArgs &a, int n_pairs, int d, bool io_bf16, bool compute_bf16,
                               hipStream_t stream);
+// The same with float32 products (gka_solve_f32.hip; d = 64, 128, 256): what launch_chunk_solve calls for float32 operands.
+hipError_t launch_solve_f32(const SolveArgs &a, int d, bool io_bf16, hipStream_t stream);
 hipError_t launch_decode_step(const DecodeArgs &a, int n_pairs, int d, bool io_bf16, hipStream_t stream);
 
 // Forward pass in one kernel with the states in registers (bf16 tensors and operands, d = 128, Eq. (CH) as printed).

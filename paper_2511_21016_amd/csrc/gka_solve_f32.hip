@@ -1,0 +1,500 @@
+// Per-chunk solve with float32 products (v_mfma_f32_16x16x4_f32): chunk-wise Frobenius norms (Section 4.2.1), Algorithm
+// 1 on all tokens of the chunk at once and the readout of Eq. (CH), for d = 64, 128 and 256, float32 or bf16 tensors.
+// The mathematics is that of gka_chunk_solve.hip (bf16 products), whose header derives the split
+//
+//   (H_c x_c) = zeta_c (H_[n] x_c) + sum_{j<=c} M[j,c] k_j (k_j . x_c)
+//
+// and the residual form of the recurrence. What differs is the shape: a float32 product takes sixteen times the matrix
+// pipe's time of a bf16 one, so everything here serves the pipe.
+//   * A workgroup takes TT tiles of 16 tokens of one chunk (TT = 4: the whole chunk; 4 / TT workgroups per chunk).
+//     Wave w owns the feature rows 16 RT w .. of every vector, for all of the workgroup's tokens: no product is
+//     computed twice, and the state's rows of a wave stay in its registers for all passes (RT D / 4 registers; a pass
+//     reads no state from memory or LDS).
+//   * Tokens sit on the N dimension: lane (n, kg) = (lane & 15, lane >> 4) holds rows 4 kg .. + 3 of token n of a tile,
+//     so per-token scalars are per-lane scalars. Vectors cross waves through LDS rows [token][feature]; a lane reads
+//     four consecutive features 16 s + 4 kg .. + 3 at once and uses them in four products (the contraction index is
+//     enumerated in that order by both operands).
+//   * Key products P = K delta^T are dealt out by 16 x 16 tiles (causal ones only) over the waves ahead of the state
+//     product, which does not need them: the barrier that publishes P waits for no one.
+// Bound: the matrix pipe (157 TFLOP/s in float32). Measured, microseconds per forward pass, against 32 x 32 x 2 products
+// with two waves per token block that each formed all of P, H_[n] in LDS, one workgroup per chunk: d = 64, 1 pair x 256
+// tokens 62 -> 35; d = 64, 64 x 1024 205 -> 181; d = 128, 16 x 1500 309 -> 210; d = 128, 64 x 1024 665 -> 477
+// (90 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16230 -> 784, of which this kernel 702.
+#include "gka_device.hpp"
+#include "gka_kernels.hpp"
+
+namespace gka {
+
+template <int D, int TT>
+struct SolveF32Shape {
+    static constexpr int NW = D == 64 ? 4 : 8;         // waves
+    static constexpr int NTHR = 64 * NW;
+    static constexpr int RT = D / (16 * NW);           // row tiles of 16 features per wave
+    static constexpr int KS = D / 16;                  // steps of 16 features (four products) of a contraction
+    static constexpr int TB = 4 / TT;                  // workgroups per chunk
+    static constexpr int NUNITS = TT == 4 ? 10 : TT == 2 ? 7 : 4;   // causal (key tile, token tile) pairs, at most
+    static constexpr int MAXU = (NUNITS + NW - 1) / NW;             // ... per wave
+    static constexpr size_t k_bytes = (size_t)kChunk * D * 4;
+    static constexpr size_t x_bytes = (size_t)16 * TT * D * 4;
+    static constexpr size_t p_bytes = (size_t)16 * TT * kChunk * 4;
+    static constexpr size_t lds_bytes = k_bytes + x_bytes + p_bytes;
+    static_assert((2 * NW + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand rows");
+};
+
+// float4 index of columns 4 c4 .. + 3 of a row in a tile of rows of W floats: 16-byte granules XOR-swizzled with the row
+// number, so that sixteen rows at the same columns, or a row's sixteen columns, fall into different banks
+template <int W>
+__device__ __forceinline__ int row4(int row, int c4) { return row * (W / 4) + (c4 ^ (row & 15)); }
+template <int W>
+__device__ __forceinline__ int row1(int row, int col) { return 4 * row4<W>(row, col >> 2) + (col & 3); }
+
+__device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
+// sum over the four lanes that hold the rows of one token
+__device__ __forceinline__ float sum_kg(float x)
+{
+    x += __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
+}
+
+template <class IO, int D, int TT, bool GATED>
+__device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
+{
+    typedef SolveF32Shape<D, TT> SH;
+    constexpr int NW = SH::NW, NTHR = SH::NTHR, RT = SH::RT, KS = SH::KS, TB = SH::TB, MAXU = SH::MAXU;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    f32x4 *sK = (f32x4 *)smem;                         // k rows (later v rows) of the chunk, [64][D]
+    f32x4 *sX = (f32x4 *)(smem + SH::k_bytes);         // operand rows [16 TT][D]
+    f32x4 *sP = (f32x4 *)(smem + SH::k_bytes + SH::x_bytes);   // masked key products [16 TT][64]
+    // scratch of the norm, in the operand rows
+    float *sA = (float *)sX;                           // [NW][64] k_j^T H k_j, a wave's rows
+    float *sB = sA + NW * 64;                          // [4][64]  sum of m[i,j] G_ij^2 over a tile of i
+    float *sDg = sB + 4 * 64;                          // [64]     G_jj^2
+    float *sW = sDg + 64;                              // [64]     w_j
+    float *sF = sW + 64;                               // [NW][64] sum of m[j,c]^2 w_j over a wave's share of j
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kg = lane >> 4;
+    // the later token tiles of a chunk see more keys: their workgroups start first. Consecutive workgroups take the
+    // same chunk of consecutive pairs (in the [B,T,H,d] layout the heads of a token are adjacent).
+    const int per_tb = a.n_pairs * a.n_chunks;
+    const int tb = TB - 1 - (int)blockIdx.x / per_tb;
+    const int within = (int)blockIdx.x % per_tb;
+    const int pair = within % a.n_pairs, chunk_local = within / a.n_pairs;
+    const int chunk = a.chunk0 + chunk_local;
+    const int b = (a.pair0 + pair) / a.H, h = (a.pair0 + pair) % a.H;
+    const int64_t chunk_id = (int64_t)chunk_local * a.n_pairs + pair;
+    const int64_t base_bh = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
+    const int64_t gate_base = (int64_t)b * a.T * a.H + h;
+    const int tok0 = chunk * kChunk;
+    if (tok0 + 16 * TT * tb >= a.T) return;            // (whole workgroup) only padding
+    const int JT = TT * (tb + 1);                      // key tiles in sight
+    const bool solve = !(GATED && a.readout_only);
+    const bool stated = chunk > 0 || a.init_states;    // else H_[n] = U_[n] = 0: nothing to read or multiply
+
+    // ---------------- requests: gates, k rows, state rows, q ----------------
+    const int64_t gate_at = gate_base + (int64_t)min(tok0 + lane, a.T - 1) * a.H;
+    const float gm = a.gate[gate_at];
+    float ball = 1.0f;                                 // lane j: write gate beta_j
+    if constexpr (GATED) {
+        const float raw = (a.beta ? a.beta : a.gate)[gate_at];
+        ball = a.beta ? raw : 1.0f;
+    }
+    constexpr int RPI = NTHR / (D / 4), NP = kChunk / RPI;      // rows per sweep of the workgroup, sweeps
+    typename IO::raw4 rows[NP];
+    auto load_rows = [&](const void *x) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            if (i * RPI < 16 * JT)
+                rows[i] = IO::load_raw4(x, base_bh + (int64_t)min(tok0 + i * RPI + tid / (D / 4), a.T - 1) * a.stride_t +
+                                               4 * (tid % (D / 4)));
+    };
+    auto store_rows = [&]() {                          // rows beyond the sequence are zero
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            if (i * RPI < 16 * JT) {
+                const int row = i * RPI + tid / (D / 4);
+                f32x4 x = IO::cvt4(rows[i]);
+                if (tok0 + row >= a.T) x = zero4();
+                sK[row4<D>(row, tid % (D / 4))] = x;
+            }
+    };
+    load_rows(a.k);
+    // A fragments of this wave's rows of a state: element [16 rt + n][16 s + 4 kg + e] of the state in sreg[rt][s][e]
+    f32x4 sreg[RT][KS];
+    auto load_state = [&](const void *ws) {
+        const f32x4 *src = (const f32x4 *)ws + chunk_id * (D * D / 4) + (int64_t)w * RT * KS * 64 + lane;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) sreg[rt][s] = stated ? src[(rt * KS + s) * 64] : zero4();
+    };
+    int c_loc[TT];                                     // this lane's tokens
+    int64_t tok_off[TT];
+    bool valid[TT];
+    f32x4 qv[RT][TT];
+    float lam[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        c_loc[tt] = 16 * (TT * tb + tt) + n;
+        valid[tt] = tok0 + c_loc[tt] < a.T;
+        const int tok = min(tok0 + c_loc[tt], a.T - 1);
+        tok_off[tt] = base_bh + (int64_t)tok * a.stride_t + 16 * RT * w + 4 * kg;
+        lam[tt] = ((!GATED || a.lambda) ? a.lambda : a.gate)[gate_base + (int64_t)tok * a.H];
+    }
+    auto load_q = [&](const void *x, int rt, int tt) {
+        const f32x4 v = IO::load4(x, tok_off[tt] + 16 * rt);
+        return valid[tt] ? v : zero4();
+    };
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            qv[rt][tt] = load_q(a.q, rt, tt);
+            if constexpr (GATED) {
+                if (a.q_lo) qv[rt][tt] += load_q(a.q_lo, rt, tt);
+            }
+        }
+    float hn2 = 0.0f;
+    if (solve) {
+        load_state(a.ws_H);
+        constexpr int NHN = (D / 32) * (D / 32);       // partial sums of ||H_[n]||^2
+        if (stated) hn2 = wave_sum(lane < NHN ? a.ws_hn[chunk_id * NHN + lane] : 0.0f);
+    }
+
+    // ---------------- decays (Section 4.2.1; log-space form of Appendix B.2, base 2) ----------------
+    const float Gall = wave_inclusive_scan((tok0 + lane < a.T) ? log2_gate(gm) : 0.0f, lane);
+    float zeta[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) zeta[tt] = exp2f(__shfl(Gall, c_loc[tt], 64));
+    // beta_j M[j,c] for rows j = 16 jt + 4 kg + r and the column c; strict: j < c
+    auto mask4 = [&](int jt, int c, bool strict) {
+        const float Gc = __shfl(Gall, c, 64);
+        f32x4 m;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = 16 * jt + 4 * kg + r;
+            float x = __builtin_amdgcn_exp2f(Gc - __shfl(Gall, j, 64));
+            if constexpr (GATED) x *= __shfl(ball, j, 64);
+            m[r] = (strict ? j < c : j <= c) ? x : 0.0f;
+        }
+        return m;
+    };
+    // this wave's (key tile, token tile) pairs of the masked key products
+    int unit_j[MAXU], unit_t[MAXU];                    // token tile TT: no such pair
+    f32x4 unit_m[MAXU];
+#pragma unroll
+    for (int i = 0; i < MAXU; ++i) {
+        int u = i * NW + w, tt = 0, len = TT * tb + 1;
+        while (tt < TT && u >= len) { u -= len; ++tt; ++len; }
+        unit_j[i] = u;
+        unit_t[i] = tt;
+        unit_m[i] = tt < TT ? mask4(u, 16 * (TT * tb + tt) + n, false) : zero4();
+    }
+    store_rows();
+    lds_barrier();
+
+    // [16 rows of K, tile jt] x [16 rows of X, tile xt]^T over all features
+    auto key_product = [&](int jt, const f32x4 *X, int xt) {
+        f32x4 c0 = zero4(), c1 = zero4();              // two chains of dependent products
+#pragma unroll 4
+        for (int s = 0; s < KS; ++s) {
+            const f32x4 ka = sK[row4<D>(16 * jt + n, 4 * s + kg)], xb = X[row4<D>(16 * xt + n, 4 * s + kg)];
+            c0 = mma4(ka[0], xb[0], c0);
+            c1 = mma4(ka[1], xb[1], c1);
+            c0 = mma4(ka[2], xb[2], c0);
+            c1 = mma4(ka[3], xb[3], c1);
+        }
+        return c0 + c1;
+    };
+
+    // ---------------- chunk-wise Frobenius norm ----------------
+    // ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} m[j,c]^2 w_j,
+    // w_j = 2 (zeta_j k_j^T H_[n] k_j + sum_{i<j} m[i,j] G_ij^2) / beta_j + G_jj^2,  G = K K^T
+    // (the folded three-term expansion, see gka_chunk_solve.hip)
+    float fro[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) fro[tt] = 0.0f;
+    if (solve) {
+        for (int jt = 0; jt < JT; ++jt) {
+            float part = 0.0f;
+            if (stated) {
+                f32x4 acc[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = zero4();
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const f32x4 kb = sK[row4<D>(16 * jt + n, 4 * s + kg)];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) acc[rt] = mma4(sreg[rt][s][e], kb[e], acc[rt]);
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const f32x4 kr = sK[row4<D>(16 * jt + n, 4 * (RT * w + rt) + kg)];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part += acc[rt][r] * kr[r];
+                }
+                part = sum_kg(part);
+            }
+            if (kg == 0) sA[w * 64 + 16 * jt + n] = part;
+        }
+        for (int u0 = w; u0 < JT * (JT + 1) / 2; u0 += NW) {
+            int it = u0, jt = 0;
+            while (it > jt) { ++jt; it -= jt; }        // tile it <= jt of the lower triangle, row by row
+            const f32x4 G = key_product(it, sK, jt);
+            const f32x4 m = mask4(it, 16 * jt + n, true);
+            float bp = 0.0f, dp = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float g2 = G[r] * G[r];
+                bp += m[r] * g2;
+                dp += (4 * kg + r == n) ? g2 : 0.0f;
+            }
+            bp = sum_kg(bp);
+            dp = sum_kg(dp);
+            if (kg == 0) {
+                sB[it * 64 + 16 * jt + n] = bp;
+                if (it == jt) sDg[16 * jt + n] = dp;
+            }
+        }
+        lds_barrier();
+        if (tid < 16 * JT) {                           // (the first wave: lane j = token j)
+            float as = 0.0f, bs = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) as += sA[i * 64 + tid];
+            for (int i = 0; i <= tid >> 4; ++i) bs += sB[i * 64 + tid];
+            const float cross = 2.0f * (exp2f(Gall) * as + bs);
+            sW[tid] = GATED ? (ball > 0.0f ? cross / ball + sDg[tid] : 0.0f) : cross + sDg[tid];
+        }
+        lds_barrier();
+        float f = 0.0f;                                // lane c = token c; keys dealt out over the waves
+#pragma unroll
+        for (int i = 0; i < 64 / NW; ++i) {
+            const int j = i * NW + w;
+            if (j < 16 * JT) {
+                float m = __builtin_amdgcn_exp2f(Gall - lane_value(Gall, j));
+                if constexpr (GATED) m *= lane_value(ball, j);
+                m = j <= lane ? m : 0.0f;
+                f += m * m * sW[j];
+            }
+        }
+        sF[w * 64 + lane] = f;
+        lds_barrier();
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            float fs = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) fs += sF[i * 64 + c_loc[tt]];
+            fro[tt] = sqrtf(fmaxf(zeta[tt] * zeta[tt] * hn2 + fs, 0.0f));
+            if (a.fro_out && valid[tt] && w == 0 && kg == 0)
+                a.fro_out[gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H] = fro[tt];
+        }
+        lds_barrier();                                 // the scratch becomes the operand rows
+    }
+
+    // ---------------- Chebyshev iteration (Algorithm 1), residual form ----------------
+    float s0[TT], rho2[TT], omega[TT];
+    f32x4 xi[RT][TT], dl[RT][TT], gS[RT][TT], gI[RT][TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        if (GATED && !a.lambda) lam[tt] = a.lambda_scale * fro[tt];     // Section 4.1: lambda_t = a ||H_t||_F
+        if (!valid[tt] || !solve) lam[tt] = 1.0f;
+        const float L = fro[tt] + lam[tt], mu = lam[tt];                // Section 4.1
+        s0[tt] = 2.0f / (L + mu);
+        const float rho = (L - mu) / (L + mu);
+        rho2[tt] = rho * rho;
+        omega[tt] = 2.0f;
+    }
+    auto publish = [&](const f32x4 (&x)[RT][TT]) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) sX[row4<D>(16 * tt + n, 4 * (RT * w + rt) + kg)] = x[rt][tt];
+    };
+    // acc += S X^T for this wave's rows of the state in sreg
+    auto state_product = [&](f32x4 (&acc)[RT][TT]) {
+        if (!stated) return;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            f32x4 xb[TT];
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) xb[tt] = sX[row4<D>(16 * tt + n, 4 * s + kg)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mma4(sreg[rt][s][e], xb[tt][e], acc[rt][tt]);
+        }
+    };
+    auto masked_key_products = [&]() {
+#pragma unroll
+        for (int i = 0; i < MAXU; ++i)
+            if (unit_t[i] < TT)
+                sP[row4<kChunk>(16 * unit_t[i] + n, 4 * unit_j[i] + kg)] =
+                    key_product(unit_j[i], sX, unit_t[i]) * unit_m[i];
+    };
+    // acc += A^T (P o M) for this wave's rows, A = the rows in sK
+    auto intra_product = [&](f32x4 (&acc)[RT][TT]) {
+        const float *rowsf = (const float *)sK;
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) {
+            if (jt >= JT) break;
+            float at[RT][4];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) at[rt][e] = rowsf[row1<D>(16 * jt + 4 * kg + e, 16 * (RT * w + rt) + n)];
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+                if (jt <= TT * tb + tt) {
+                    const f32x4 pb = sP[row4<kChunk>(16 * tt + n, 4 * jt + kg)];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) acc[rt][tt] = mma4(at[rt][e], pb[e], acc[rt][tt]);
+                }
+        }
+    };
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            gS[rt][tt] = zero4();
+            gI[rt][tt] = -qv[rt][tt];
+            dl[rt][tt] = xi[rt][tt] = s0[tt] * qv[rt][tt];              // xi_0 = 2 q / (L + mu)
+        }
+    for (int it = 0; it < a.n_iter; ++it) {
+        publish(dl);
+        lds_barrier();                                 // delta visible; the masked products of the last pass are used up
+        masked_key_products();
+        state_product(gS);
+        lds_barrier();
+        intra_product(gI);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            omega[tt] = 4.0f / (4.0f - rho2[tt] * omega[tt]);           // weight schedule
+            const float cm = omega[tt] - 1.0f, cs = -omega[tt] * s0[tt];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float res = zeta[tt] * gS[rt][tt][r] + gI[rt][tt][r] + lam[tt] * xi[rt][tt][r];   // -r_{i-1}
+                    dl[rt][tt][r] = cm * dl[rt][tt][r] + cs * res;
+                    xi[rt][tt][r] += dl[rt][tt][r];
+                }
+        }
+    }
+
+    // ---------------- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c) ----------------
+    if (GATED && a.xhat_out) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+                if (valid[tt])
+                    *(f32x4 *)(a.xhat_out + (gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H) * D + 16 * (RT * w + rt) +
+                               4 * kg) = xi[rt][tt];
+    }
+    if (GATED && a.solve_only) return;                 // (whole workgroup)
+    load_state(a.ws_U);
+    load_rows(a.v);
+    if (GATED && a.alpha) {                            // alpha-connection (Section 4.3)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            const float al = a.alpha[gate_base + (int64_t)min(tok0 + c_loc[tt], a.T - 1) * a.H];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) xi[rt][tt] = al * xi[rt][tt] + (1.0f - al) * load_q(a.q, rt, tt);
+        }
+    }
+    publish(xi);
+    lds_barrier();
+    masked_key_products();
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) gS[rt][tt] = zero4();
+    state_product(gS);
+    lds_barrier();                                     // every wave is done with the keys
+    store_rows();
+    lds_barrier();
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) gS[rt][tt] *= zeta[tt];
+    intra_product(gS);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+            if (valid[tt])
+                IO::store4(a.o, tok_off[tt] + 16 * rt, gS[rt][tt][0], gS[rt][tt][1], gS[rt][tt][2], gS[rt][tt][3]);
+}
+
+template <class IO, int D, int TT, bool GATED>
+__global__ __launch_bounds__((SolveF32Shape<D, TT>::NTHR)) __attribute__((amdgpu_waves_per_eu(2))) void
+solve_f32_kernel(SolveArgs a)
+{
+    solve_f32_body<IO, D, TT, GATED>(a);
+}
+
+template <class IO, int D, int TT, bool GATED>
+static hipError_t launch_solve_f32_t(const SolveArgs &a, hipStream_t stream)
+{
+    typedef SolveF32Shape<D, TT> SH;
+    auto kern = solve_f32_kernel<IO, D, TT, GATED>;
+    // (set once per kernel instantiation and device, not per launch)
+    static bool attr_set_on[64] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64 || !attr_set_on[dev]) {
+        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::lds_bytes);
+        if (e != hipSuccess) return e;
+        if (dev >= 0 && dev < 64) attr_set_on[dev] = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_pairs * a.n_chunks * SH::TB)), dim3(SH::NTHR), SH::lds_bytes, stream, a);
+    return hipGetLastError();
+}
+
+template <class IO, int D, bool GATED>
+static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
+{
+    // Tokens per workgroup (16 TT): small workgroups spread a small problem over the chip, large ones repeat less of the
+    // norm and share operand reads. Measured (whole forward pass, microseconds, TT = 1 / 2 / 4): d = 128: 20 chunks
+    // 56 / 76 / 106, 160 chunks 115 / 112 / 118, 384 chunks 236 / 210 / 228, 1024 chunks 612 / 518 / 477; d = 64: 64
+    // chunks 36 / 47 / 60, 256 chunks 63 / 63 / 70, 1024 chunks 189 / 181 / 187; d = 256 (where the state rows leave
+    // no registers for TT = 4): 20 chunks 130 / 200, 88 chunks 222 / 233, 256 chunks 440 / 392.
+    const int64_t chunks = (int64_t)a.n_pairs * a.n_chunks;
+    if (chunks <= 128) return launch_solve_f32_t<IO, D, 1, GATED>(a, stream);
+    if (D != 128 || chunks <= 512) return launch_solve_f32_t<IO, D, 2, GATED>(a, stream);
+    if constexpr (D == 128) return launch_solve_f32_t<IO, D, 4, GATED>(a, stream);
+    return hipErrorInvalidValue;
+}
+
+template <class IO, int D>
+static hipError_t launch_solve_f32_g(const SolveArgs &a, hipStream_t stream)
+{
+    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_solve_f32_d<IO, D, true>(a, stream);
+    return launch_solve_f32_d<IO, D, false>(a, stream);
+}
+
+hipError_t launch_solve_f32(const SolveArgs &a, int d, bool io_bf16, hipStream_t stream)
+{
+    if (io_bf16) {
+        if (d == 256) return launch_solve_f32_g<IOBF16, 256>(a, stream);
+        if (d == 128) return launch_solve_f32_g<IOBF16, 128>(a, stream);
+        return launch_solve_f32_g<IOBF16, 64>(a, stream);
+    }
+    if (d == 256) return launch_solve_f32_g<IOF32, 256>(a, stream);
+    if (d == 128) return launch_solve_f32_g<IOF32, 128>(a, stream);
+    return launch_solve_f32_g<IOF32, 64>(a, stream);
+}
+
+}  // namespace gka

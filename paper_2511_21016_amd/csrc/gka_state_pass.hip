@@ -4,7 +4,7 @@
 // U0[32*rb .. +32][:], held as fp32 MFMA accumulators (wave w owns columns 32*w .. +32 of the slab),
 // and walks a contiguous run of the pair's chunks in order. Per chunk it
 //   1. (if asked) writes the slab, as it stands before the chunk, to the workspace in the fragment order
-//      the solve kernel consumes (H: bf16 or fp32 operands plus the slab's share of ||H_[n]||_F^2; U: the operand
+//      its solve kernel consumes (H: bf16 or fp32 operands plus the slab's share of ||H_[n]||_F^2; U: the operand
 //      and, for bf16, what the rounding left over as a second operand),
 //   2. applies the chunk: S <- zeta_C S + sum_j (zeta_C / zeta_j) a_j k_j^T  (a = k for H, a = v for U),
 //      the decay weights built in log space (Appendix B.2), as one MFMA contraction over the chunk's tokens.
@@ -91,7 +91,6 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
 {
     constexpr int NB = D / 32;
     constexpr int VEC = MMA::VEC;
-    constexpr int HS = MMA::HS;
     constexpr int STEPS = kChunk / (2 * VEC);     // MFMA steps over the chunk's tokens
     constexpr int NT = D * 2;                     // threads
     constexpr int RS = D + MMA::kRowPad;
@@ -195,37 +194,22 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
         // ---- write the state before the chunk, fragment order
         if (WRITE) {
             const int64_t chunk_id = (int64_t)(c - a.chunk0) * a.n_pairs + pair;   // chunk-major: pairs adjacent
-            float vals[16];
+            // the order in which gka_solve_f32.hip reads A fragments of 16 x 16 x 4 products: block (row tile of 16, 16
+            // columns) of 64 float4, row m and columns 4 kg .. + 3 at 16 kg + m. This lane holds columns 8 q + 4 g .. + 3
+            // of row n of the block row rb, block column w.
+            f32x4 *Sw = (f32x4 *)(doH ? a.ws_H : a.ws_U) + chunk_id * (D * D / 4);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) vals[r] = acc[r];
+            for (int q = 0; q < 4; ++q) {
+                const int rt = 2 * rb + (n >> 4), s = 2 * w + (q >> 1), kg = 2 * (q & 1) + g;
+                store_once(&Sw[(rt * (D / 16) + s) * 64 + 16 * kg + (n & 15)],
+                           f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]});
+            }
             if (doH) {
-                frag *Hw = (frag *)a.ws_H + chunk_id * (NB * NB * HS * 64);
                 float ss = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) ss += acc[r] * acc[r];
-#pragma unroll
-                for (int hh = 0; hh < HS; ++hh)
-                    store_once(&Hw[((rb * NB + w) * HS + hh) * 64 + lane], MMA::pack(vals + hh * VEC));
                 ss = wave_sum(ss);
                 if (lane == 0) a.ws_hn[chunk_id * (NB * NB) + rb * NB + w] = ss;
-            } else {
-                constexpr int NSPL = MMA::kSplitReadout ? 2 : 1;
-                frag *Uw = (frag *)a.ws_U + chunk_id * (NSPL * NB * NB * HS * 64);
-                float lo[16];
-#pragma unroll
-                for (int hh = 0; hh < HS; ++hh) {
-                    frag fr = MMA::pack(vals + hh * VEC);
-                    store_once(&Uw[((rb * NB + w) * HS + hh) * 64 + lane], fr);
-                    if (NSPL == 2) {
-#pragma unroll
-                        for (int p = 0; p < VEC; ++p) lo[hh * VEC + p] = vals[hh * VEC + p] - MMA::elem(fr, p);
-                    }
-                }
-                if (NSPL == 2) {
-#pragma unroll
-                    for (int hh = 0; hh < HS; ++hh)
-                        Uw[(NB * NB * HS + (rb * NB + w) * HS + hh) * 64 + lane] = MMA::pack(lo + hh * VEC);
-                }
             }
         }
         lds_barrier();                          // s_k, s_v visible
@@ -371,7 +355,7 @@ __device__ __forceinline__ void state_pass_body_bf16_tile(const StatePassArgs &a
     constexpr int RPI = 64 / LPR;                 // rows per wave-wide copy instruction
     constexpr int PPR = D / 4;                    // 4-element pieces per row of the B tile
     constexpr int VP = kChunk * PPR / NT;         // pieces of the B tile per thread
-    constexpr int NSPL = MMA::kSplitReadout ? 2 : 1;
+    constexpr int NSPL = 2;                       // U as value and remainder
     constexpr int NS = WRITE ? NB * (DOH ? HS + 1 : HS * NSPL) : 0;   // state stores per chunk
     static_assert(NW == NB && STEPS == 4, "one wave per column block, four MFMA steps per chunk");
     static_assert(NA + NS < 64, "the counted wait below fits the counter");
@@ -484,12 +468,10 @@ __device__ __forceinline__ void state_pass_body_bf16_tile(const StatePassArgs &a
 #pragma unroll
                         for (int p = 0; p < MMA::VEC; ++p) lo[hh * MMA::VEC + p] = vals[hh * MMA::VEC + p] - back[p];
                     }
-                    if (NSPL == 2) {
 #pragma unroll
-                        for (int hh = 0; hh < HS; ++hh)
-                            store_once(&Uw[(NB * NB * HS + (rb * NB + w) * HS + hh) * 64 + lane],
-                                       MMA::pack(lo + hh * MMA::VEC));
-                    }
+                    for (int hh = 0; hh < HS; ++hh)
+                        store_once(&Uw[(NB * NB * HS + (rb * NB + w) * HS + hh) * 64 + lane],
+                                   MMA::pack(lo + hh * MMA::VEC));
                 }
             }
         }
@@ -683,9 +665,11 @@ hipError_t launch_state_pass(const StatePassArgs &a, int n_pairs, int d, bool io
         return launch_state_pass_t<MmaBF16, IOBF16, 64>(a, n_pairs, stream);
     }
     if (io_bf16) {
+        if (d == 256) return launch_state_pass_t<MmaF32, IOBF16, 256>(a, n_pairs, stream);
         if (d == 128) return launch_state_pass_t<MmaF32, IOBF16, 128>(a, n_pairs, stream);
         return launch_state_pass_t<MmaF32, IOBF16, 64>(a, n_pairs, stream);
     }
+    if (d == 256) return launch_state_pass_t<MmaF32, IOF32, 256>(a, n_pairs, stream);
     if (d == 128) return launch_state_pass_t<MmaF32, IOF32, 128>(a, n_pairs, stream);
     return launch_state_pass_t<MmaF32, IOF32, 64>(a, n_pairs, stream);
 }
