@@ -3,223 +3,330 @@
 // all arithmetic fp32. The states are read once, advanced by a.T tokens in registers and written once, so the state
 // traffic of a call does not grow with the number of tokens. The same kernel is gka_forward's recurrent path (any
 // number of tokens, separate initial and final states, ||H_t||_F and the solve's result as optional outputs), the
-// only one for the head dimension 256 and for float32 tensors at 16 and 32.
+// only one for float32 tensors at the head dimensions 16 and 32 and for short sequences at 256.
 //
-// The d x d states are distributed as float4 pieces in flat row-major order, piece (it*NTHR + t) on thread
-// t, so that state reads and writes are fully coalesced: thread t holds, for each of its ITS pieces, row
-// i = it*RPI + t / C4 and columns 4*(t % C4) .. +3 (C4 = d/4 pieces per row, RPI = NTHR/C4 rows per sweep).
-// H is symmetric, so H x is evaluated column-wise, (H x)_j = sum_i H[i][j] x_i: every thread accumulates
-// its rows into its four columns, and the NTHR/C4 partial sums per column are combined through LDS.
-// NTHR = 256 threads (d = 16 has a kernel of its own below); 1024 for d = 256, where a thread holds 16 pieces of H and U does
-// not fit beside them: U is then streamed, each piece read, advanced, used for the readout and written back
-// once per token (STREAM_U).
+// Layout. NW waves; wave w owns D / NW rows of both states. Lane (rg, cg) = (lane / 8, lane % 8) of a wave holds, of the R
+// rows D / NW w + 8 rr + rg (rr < R = D / (8 NW)), the float4 pieces cg + 8 i (i < D / 32): eight lanes read a whole
+// 128-byte line, a wave's pieces i = 0, 1, .. eight whole rows, and i is the 32-column block. A product S x is formed by
+// rows: a lane takes the D / 8 components of x under its pieces from LDS (D / 32 reads of 16 bytes, one line per wave),
+// and the R partial sums are added over the eight lanes of a row by three DPP moves that also deal the rows out, so
+// that every lane ends up with one complete row sum (lanes whose cg differs in bit 1 only with the same one). That
+// lane then owns the row's component of xi, delta and the residual: a pass is one LDS write, one barrier, D / 32 LDS
+// reads, the multiply-adds and three DPP steps. Barriers order LDS only: the stores of the advanced states drain
+// while the token is solved.
+// What bounds it: few pairs, the latency of that chain (about 0.25 us per pass); many pairs, HBM for single tokens, and the
+// vector units for several tokens per call.
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
 namespace gka {
 
-template <int D>
+template <int D, int NW_>
 struct DecodeShape {
-    static constexpr int NTHR = D == 256 ? 1024 : 256;
-    static constexpr int C4 = D / 4, RPI = NTHR / C4, ITS = D / RPI, NW = NTHR / 64;
-    static constexpr bool STREAM_U = D == 256;
-    static_assert(ITS * NTHR * 4 == D * D && ITS >= 1 && RPI * C4 == NTHR, "every thread holds ITS pieces of a state");
+    static constexpr int NW = NW_, NTHR = 64 * NW;
+    static constexpr int R = D / (8 * NW), NI = D / 32;      // rows and float4 pieces per row of a lane
+    static_assert(R * 8 * NW == D && (R == 1 || R == 2 || R == 4), "every lane holds R whole rows' pieces");
+    static constexpr bool STREAM_U = D == 256;               // H fills the registers
+    static constexpr int G = R == 4 ? 2 : 1;                 // groups of rows whose ||.||^2 is summed apart
 };
+
+// The sums over the eight lanes cg of R row sums each: this lane's share is row 8 rr + rg with rr = row_share<R>(lane).
+template <int R>
+__device__ __forceinline__ int row_share(int lane)
+{
+    return R == 4 ? ((lane >> 1) & 2) | (lane & 1) : R == 2 ? (lane >> 2) & 1 : 0;
+}
+template <int R>
+__device__ __forceinline__ float sum_rows(const float (&p)[R], int lane)
+{
+    auto dpp = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF,
+                                                                  0xF, true));
+    };
+    constexpr std::integral_constant<int, 0x141> half_mirror;     // lane cg <-> 7 - cg
+    constexpr std::integral_constant<int, 0xB1> xor1;             // quad_perm [1,0,3,2]
+    constexpr std::integral_constant<int, 0x4E> xor2;             // quad_perm [2,3,0,1]
+    const bool b2 = lane & 4, b0 = lane & 1;
+    float t;
+    if constexpr (R == 4) {
+        // rows 2 b2, 2 b2 + 1 stay, the others go to the mirror lane; then row b0 of the two stays
+        const float k0 = b2 ? p[2] : p[0], k1 = b2 ? p[3] : p[1];
+        const float a0 = k0 + dpp(b2 ? p[0] : p[2], half_mirror), a1 = k1 + dpp(b2 ? p[1] : p[3], half_mirror);
+        t = (b0 ? a1 : a0) + dpp(b0 ? a0 : a1, xor1);
+    } else if constexpr (R == 2) {
+        t = (b2 ? p[1] : p[0]) + dpp(b2 ? p[0] : p[1], half_mirror);
+        t += dpp(t, xor1);
+    } else {
+        t = p[0] + dpp(p[0], half_mirror);
+        t += dpp(t, xor1);
+    }
+    return t + dpp(t, xor2);
+}
 
 // MULTI = false: the single-step kernel, a.T == 1 known at compile time.
 // LOWER: of H_in / H_state only the 32 x 32 blocks on and below the block diagonal are read and written; the blocks
 // above are rebuilt in registers from their mirror images (through LDS, once per call), so the arithmetic is the same.
-// STREAM: U is streamed (as always at d = 256) although it would fit: the single-token kernel at d = 128, which
-// then has room for a fourth workgroup per CU.
-template <class IO, int D, bool MULTI, bool LOWER, bool STREAM = false>
-__global__ __launch_bounds__(DecodeShape<D>::NTHR) void decode_step_kernel(DecodeArgs a)
+// STREAM: U is streamed (as always at d = 256) although it would fit: each piece is read, advanced, used for the
+// readout and written back after the solve. For single tokens of many pairs: fewer registers, four workgroups per CU.
+template <class IO, int D, int NW, bool MULTI, bool LOWER, bool STREAM>
+__global__ __launch_bounds__(64 * NW)
+void decode_step_kernel(DecodeArgs a)
 {
-    typedef DecodeShape<D> SH;
+    typedef DecodeShape<D, NW> SH;
     const int T = MULTI ? a.T : 1;
-    constexpr int NTHR = SH::NTHR, C4 = SH::C4, RPI = SH::RPI, ITS = SH::ITS, NW = SH::NW;
+    constexpr int NTHR = SH::NTHR, R = SH::R, NI = SH::NI, C4 = D / 4;
     constexpr bool STREAM_U = SH::STREAM_U || STREAM;
     static_assert(!STREAM || !MULTI, "U is streamed once per token: at d < 256 only where a call is one token");
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int rg = lane >> 3, cg = lane & 7;
     const int pair = blockIdx.x;
-    const int col4 = t % C4, rgrp = t / C4;
 
-    __shared__ float s_q[D], s_k[D], s_v[D];
-    __shared__ float s_x[D];                 // operand of the current product (delta_i or xhat)
-    __shared__ float s_part[RPI][D];         // per row-group partial column sums
-    __shared__ float s_red[NW];
+    __shared__ __attribute__((aligned(16))) float s_in[3][D];     // q, k, v of the token
+    __shared__ __attribute__((aligned(16))) float s_x[2][D];      // operand of the product (delta_i or xhat), alternating
+    // ||H||^2 by groups of 16 rows (R >= 2): the order of the sum does not depend on NW, single and multi-token calls
+    // stay bit-identical
+    constexpr int G = SH::G;
+    __shared__ float s_red[NW * G];
 
-    const int64_t state_off = (int64_t)pair * D * D;
+    const int row0 = w * (D / NW) + rg;                           // row 8 rr + row0
+    const int my = 8 * row_share<R>(lane) + row0;                 // the component this lane owns in the solve
+    const bool writer = !(lane & 2) && (R == 4 || !(lane & 1)) && (R != 1 || !(lane & 4));   // one of the lanes that own it
+    const int64_t state_off = (int64_t)pair * D * D + (int64_t)row0 * D + 4 * cg;
+    auto piece = [&](int rr, int i) { return 8 * rr * D + 32 * i; };   // its offset from the lane's base
     const float *Hin = a.H_in ? a.H_in + state_off : nullptr;      // nullptr: zero initial states
     const float *Uin = a.U_in ? a.U_in + state_off : nullptr;
     float *Hs = a.H_state ? a.H_state + state_off : nullptr;       // nullptr: the final states are not wanted
     float *Us = a.U_state ? a.U_state + state_off : nullptr;
     const int b = pair / a.H, h = pair - b * a.H;
-    f32x4 hreg[ITS], ureg[STREAM_U ? 1 : ITS];
-    // piece `it` of this thread lies in block row (it * RPI) / 32 (RPI divides 32) and block column bj
-    const int bj = col4 / 8;
-    auto held = [&](int it) { return !LOWER || bj <= (it * RPI) / 32; };
+
+    // a token's q, k, v (one component per thread, the three arrays dealt out over the threads) and scalars, fetched
+    // while the token before it is solved
+    constexpr int NIN = (3 * D + NTHR - 1) / NTHR;
+    struct TokenIn { float x[NIN], gamma, beta, alpha, lam; };
+    auto fetch = [&](int tok) {
+        TokenIn in;
+        const int64_t bth = ((int64_t)b * T + tok) * a.H + h;      // [B,T,H] index of the token
+        const int64_t at = b * a.stride_b + tok * a.stride_t + h * a.stride_h;   // its row of q, k, v, o
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-        hreg[it] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (Hin && held(it)) hreg[it] = __builtin_nontemporal_load((const f32x4 *)(Hin + (int64_t)(it * NTHR + t) * 4));
-        if constexpr (!STREAM_U) {
-            ureg[it] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (Uin) ureg[it] = __builtin_nontemporal_load((const f32x4 *)(Uin + (int64_t)(it * NTHR + t) * 4));
+        for (int i = 0; i < NIN; ++i) {
+            const int e = i * NTHR + t, which = min(e / D, 2);
+            in.x[i] = IO::load(which == 0 ? a.q : which == 1 ? a.k : a.v, at + e % D);
         }
+        in.gamma = a.gate[bth];
+        in.beta = a.beta ? a.beta[bth] : 1.0f;                     // write gate (Remark in Section 4.1)
+        in.alpha = a.alpha ? a.alpha[bth] : 1.0f;                  // alpha-connection (Section 4.3)
+        in.lam = a.lambda ? a.lambda[bth] : 0.0f;
+        return in;
+    };
+    TokenIn next = fetch(0);
+
+    f32x4 hreg[R][NI], ureg[STREAM_U ? 1 : R][NI];
+    // row block of the lane's row 8 rr + row0 (a wave's eight rows lie in one 32-row block)
+    auto held = [&](int rr, int i) { return !LOWER || i <= (w * (D / NW) + 8 * rr) / 32; };
+#pragma unroll
+    for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            hreg[rr][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (Hin && held(rr, i)) hreg[rr][i] = __builtin_nontemporal_load((const f32x4 *)(Hin + piece(rr, i)));
+        }
+    if constexpr (!STREAM_U) {
+#pragma unroll
+        for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                ureg[rr][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (Uin) ureg[rr][i] = __builtin_nontemporal_load((const f32x4 *)(Uin + piece(rr, i)));
+            }
+    }
+    // the first row's pieces of a streamed U are on their way during the solve
+    f32x4 upre[STREAM ? NI : 1];
+    if constexpr (STREAM) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) upre[i] = __builtin_nontemporal_load((const f32x4 *)((Uin ? Uin : Us) + piece(0, i)));
     }
     if constexpr (LOWER) {
-        constexpr int NBLK = D / 32, NOFF = NBLK * (NBLK - 1) / 2;
-        __shared__ float s_tr[NOFF][32][33];         // the blocks below the diagonal, block (bi, bj) at bi (bi - 1) / 2 + bj
+        constexpr int NOFF = NI * (NI - 1) / 2;
+        // the blocks below the diagonal, block (bi, bj) at bi (bi - 1) / 2 + bj
+        __shared__ __attribute__((aligned(16))) float s_tr[NOFF][32][36];
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int bi = (it * RPI) / 32, row = it * RPI + rgrp;
-            if (bj < bi) {
+        for (int rr = 0; rr < R; ++rr)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s_tr[bi * (bi - 1) / 2 + bj][row % 32][(4 * col4) % 32 + e] = hreg[it][e];
+            for (int i = 0; i < NI; ++i) {
+                const int bi = (w * (D / NW) + 8 * rr) / 32, row = 8 * rr + row0;
+                if (i < bi) *(f32x4 *)&s_tr[bi * (bi - 1) / 2 + i][row % 32][4 * cg] = hreg[rr][i];
             }
-        }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int bi = (it * RPI) / 32, row = it * RPI + rgrp;
-            if (bj > bi) {
+        for (int rr = 0; rr < R; ++rr)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) hreg[it][e] = s_tr[bj * (bj - 1) / 2 + bi][(4 * col4 + e) % 32][row % 32];
+            for (int i = 0; i < NI; ++i) {
+                const int bi = (w * (D / NW) + 8 * rr) / 32, row = 8 * rr + row0;
+                if (i > bi) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) hreg[rr][i][e] = s_tr[i * (i - 1) / 2 + bi][4 * cg + e][row % 32];
+                }
             }
-        }
     }
     // H is written in full where the caller of the forward pass wants the final state (valid under either layout)
-    auto stored = [&](int it) { return held(it) || a.h_out_full; };
+    auto stored = [&](int rr, int i) { return held(rr, i) || a.h_out_full; };
+    // the components of a vector in LDS under this lane's pieces i
+    auto columns = [&](const float *x, int i) { return *(const f32x4 *)(x + 4 * cg + 32 * i); };
+    auto row_sums = [&](const f32x4 (&acc)[R]) {
+        float p[R];
+#pragma unroll
+        for (int rr = 0; rr < R; ++rr) p[rr] = (acc[rr][0] + acc[rr][1]) + (acc[rr][2] + acc[rr][3]);
+        return sum_rows<R>(p, lane);
+    };
     for (int tok = 0; tok < T; ++tok) {
-        const int64_t bth = ((int64_t)b * T + tok) * a.H + h;      // [B,T,H] index of this token
-        // d = 256: addresses of the state pieces are recomputed per token (hoisted out of the loop they would take
-        // registers that H needs)
-        int tv = t;
-        if constexpr (STREAM_U) asm volatile("" : "+v"(tv));
-        const int64_t row0 = b * a.stride_b + tok * a.stride_t + h * a.stride_h;   // its row of q, k, v, o
-        if (t < D) {
-            s_q[t] = IO::load(a.q, row0 + t);
-            s_k[t] = IO::load(a.k, row0 + t);
-            s_v[t] = IO::load(a.v, row0 + t);
-        }
-        const float gamma = a.gate[bth];
-        const float beta = a.beta ? a.beta[bth] : 1.0f;        // write gate (Remark in Section 4.1)
-        const float alpha = a.alpha ? a.alpha[bth] : 1.0f;     // alpha-connection (Section 4.3)
-        __syncthreads();
+        const int64_t bth = ((int64_t)b * T + tok) * a.H + h;
+        const int64_t at = b * a.stride_b + tok * a.stride_t + h * a.stride_h;
+        // addresses of state pieces are recomputed per token (hoisted out of the loop they would take registers that the
+        // states need)
+        int voff = 0;
+        if constexpr (MULTI || STREAM_U) asm volatile("" : "+v"(voff));
+        const TokenIn in = next;
+#pragma unroll
+        for (int i = 0; i < NIN; ++i)
+            if (i * NTHR + t < 3 * D) (&s_in[0][0])[i * NTHR + t] = in.x[i];
+        const float gamma = in.gamma, beta = in.beta, alpha = in.alpha;
+        lds_barrier();
+        if constexpr (MULTI) next = fetch(min(tok + 1, T - 1));
 
         // ---- state update (Eq. (CH)) and ||H_t||_F^2
-        float kc[4];
+        const float qr = s_in[0][my];
+        float kr[R], vr[R], ss[G] = {};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) kc[e] = s_k[4 * col4 + e];
-        float ss = 0.0f;
+        for (int rr = 0; rr < R; ++rr) {
+            kr[rr] = s_in[1][8 * rr + row0];
+            vr[rr] = beta * s_in[2][8 * rr + row0];
+        }
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int row = it * RPI + rgrp;
-            const float kr = s_k[row], vr = beta * s_v[row];
+        for (int i = 0; i < NI; ++i) {
+            const f32x4 kc = columns(s_in[1], i);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // beta (k_i k_j): the product of the two k components first, so that both mirror images of an
-                // element get the same bits
-                hreg[it][e] = gamma * hreg[it][e] + beta * (kr * kc[e]);
-                // (the multiply-add written out: held or streamed, U gets the same bits)
-                if constexpr (!STREAM_U) ureg[it][e] = __builtin_fmaf(gamma, ureg[it][e], vr * kc[e]);
-                ss += hreg[it][e] * hreg[it][e];
-            }
-            if (tok == T - 1) {              // the stores drain while the last token is solved
-                if (Hs && stored(it)) __builtin_nontemporal_store(hreg[it], (f32x4 *)(Hs + (int64_t)(it * NTHR + tv) * 4));
-                if constexpr (!STREAM_U) {
-                    if (Us) __builtin_nontemporal_store(ureg[it], (f32x4 *)(Us + (int64_t)(it * NTHR + t) * 4));
+            for (int rr = 0; rr < R; ++rr) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // beta (k_i k_j): the product of the two k components first, so that both mirror images of an
+                    // element get the same bits
+                    hreg[rr][i][e] = gamma * hreg[rr][i][e] + beta * (kr[rr] * kc[e]);
+                    // (the multiply-add written out: held or streamed, U gets the same bits)
+                    if constexpr (!STREAM_U) ureg[rr][i][e] = __builtin_fmaf(gamma, ureg[rr][i][e], vr[rr] * kc[e]);
+                    ss[G * rr / R] += hreg[rr][i][e] * hreg[rr][i][e];
                 }
             }
         }
-        ss = wave_sum(ss);
-        if ((t & 63) == 0) s_red[t >> 6] = ss;
-        __syncthreads();
+        if (tok == T - 1) {                      // the stores drain while the last token is solved
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    if (Hs && stored(rr, i)) __builtin_nontemporal_store(hreg[rr][i], (f32x4 *)(Hs + voff + piece(rr, i)));
+                    if constexpr (!STREAM_U) {
+                        if (Us) __builtin_nontemporal_store(ureg[rr][i], (f32x4 *)(Us + voff + piece(rr, i)));
+                    }
+                }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float total = wave_inclusive_scan(ss[g], lane);
+            if (lane == 63) s_red[w * G + g] = total;
+        }
+        lds_barrier();
         float fro2 = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) fro2 += s_red[w];
+        for (int i = 0; i < NW * G; ++i) fro2 += s_red[i];
         const float fro = sqrtf(fro2);
-        const float lam = a.lambda ? a.lambda[bth] : a.lambda_scale * fro;   // Section 4.1: lambda_t = a ||H_t||_F
+        const float lam = a.lambda ? in.lam : a.lambda_scale * fro;          // Section 4.1: lambda_t = a ||H_t||_F
         if (a.fro_out && t == 0) a.fro_out[bth] = fro;
 
-        // ---- Algorithm 1 in residual form; thread j < D owns component j of xi, delta, r
+        // ---- Algorithm 1 in residual form
         const float L = fro + lam, mu = lam;
         const float s0 = 2.0f / (L + mu);
         const float rho = (L - mu) / (L + mu);
         const float rho2 = rho * rho;
-        float xi = 0.0f, dl = 0.0f, rs = 0.0f;
-        if (t < D) {
-            xi = s0 * s_q[t];
-            dl = xi;
-            rs = s_q[t];
-            s_x[t] = dl;
-        }
+        float xi = s0 * qr, dl = xi, rs = qr;
         float omega = 2.0f;
-        __syncthreads();
-        for (int i = 0; i < a.n_iter; ++i) {
-            float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int it = 0; it < ITS; ++it) {
-                const float xr = s_x[it * RPI + rgrp];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] += hreg[it][e] * xr;
-            }
-            *(f32x4 *)&s_part[rgrp][4 * col4] = f32x4{p[0], p[1], p[2], p[3]};
-            __syncthreads();
+        int buf = 0;
+        for (int it = 0; it < a.n_iter; ++it) {
+            // (the buffer of the pass before last: every wave has read it before it passed the last barrier)
+            if (writer) s_x[buf][my] = dl;
             omega = 4.0f / (4.0f - rho2 * omega);
-            if (t < D) {
-                float hx = 0.0f;
+            lds_barrier();
+            f32x4 acc[R];                          // (four chains per row)
 #pragma unroll
-                for (int rg = 0; rg < RPI; ++rg) hx += s_part[rg][t];
-                rs -= hx + lam * dl;
-                dl = (omega - 1.0f) * dl + omega * s0 * rs;
-                xi += dl;
-                s_x[t] = dl;
+            for (int i = 0; i < NI; ++i) {
+                const f32x4 xc = columns(s_x[buf], i);
+#pragma unroll
+                for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[rr][e] = i == 0 ? hreg[rr][i][e] * xc[e] : acc[rr][e] + hreg[rr][i][e] * xc[e];
             }
-            __syncthreads();
+            const float hx = row_sums(acc);
+            rs -= hx + lam * dl;
+            dl = (omega - 1.0f) * dl + omega * s0 * rs;
+            xi += dl;
+            buf ^= 1;
         }
 
-        // ---- readout y = U (alpha xhat + (1 - alpha) q) (rows of U are not symmetric: reduce each row over its
-        // C4 lanes)
-        if (t < D) {
-            s_x[t] = alpha * xi + (1.0f - alpha) * s_q[t];
-            if (a.xhat_out) a.xhat_out[bth * D + t] = xi;
+        // ---- readout y = U (alpha xhat + (1 - alpha) q)
+        if (writer) {
+            s_x[buf][my] = alpha * xi + (1.0f - alpha) * qr;
+            if (a.xhat_out) a.xhat_out[bth * D + my] = xi;
         }
-        __syncthreads();
-        float xc[4];
+        lds_barrier();
+        f32x4 acc[R];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) xc[e] = s_x[4 * col4 + e];
-        // (streamed U: four pieces in flight at d = 256, where all sixteen would not fit beside H; eight at d = 128)
-        constexpr int kReadoutUnroll = SH::STREAM_U ? 4 : STREAM ? 8 : ITS;
-#pragma unroll kReadoutUnroll
-        for (int it = 0; it < ITS; ++it) {
-            f32x4 u;
-            if constexpr (STREAM_U) {
-                // this thread's piece of U: from the caller's initial state at the first token, afterwards what this
-                // same thread stored at the previous token
-                const int64_t at = (int64_t)(it * NTHR + tv) * 4;
-                u = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                if constexpr (MULTI) {
-                    if (tok > 0) u = *(const f32x4 *)(Us + at);
-                    else if (Uin) u = *(const f32x4 *)(Uin + at);
-                } else {
-                    if (Uin) u = __builtin_nontemporal_load((const f32x4 *)(Uin + at));
+        for (int rr = 0; rr < R; ++rr) acc[rr] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (STREAM_U) {
+            // four pieces at a time: read, advanced, used and written back. From the caller's initial state at the first
+            // token, afterwards what this same lane stored at the previous token. (A zero initial state: the loads, from
+            // the final state's buffer, are replaced by zeros; no branch around a load.)
+            const bool zero = tok == 0 && !Uin;
+            const float *Usrc = (tok > 0 || !Uin ? Us : Uin) + voff;
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+                for (int i0 = 0; i0 < NI; i0 += 4) {
+                    if constexpr (SH::STREAM_U) __builtin_amdgcn_sched_barrier(0);   // (d = 256: no room for more at once)
+                    const float vs = beta * s_in[2][8 * rr + row0];
+                    f32x4 u[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const f32x4 *src = (const f32x4 *)(Usrc + piece(rr, i0 + i));
+                        if (STREAM && rr == 0) u[i] = upre[i0 + i];
+                        else u[i] = MULTI ? *src : __builtin_nontemporal_load(src);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const f32x4 kc = columns(s_in[1], i0 + i), xc = columns(s_x[buf], i0 + i);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            u[i][e] = __builtin_fmaf(gamma, zero ? 0.0f : u[i][e], vs * kc[e]);
+                            acc[rr][e] += u[i][e] * xc[e];
+                        }
+                        f32x4 *dst = (f32x4 *)(Us + voff + piece(rr, i0 + i));
+                        if constexpr (MULTI) *dst = u[i];
+                        else __builtin_nontemporal_store(u[i], dst);
+                    }
                 }
-                const float vr = beta * s_v[it * RPI + rgrp];
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) u[e] = __builtin_fmaf(gamma, u[e], vr * kc[e]);
-                if constexpr (MULTI) *(f32x4 *)(Us + at) = u;
-                else __builtin_nontemporal_store(u, (f32x4 *)(Us + at));
-            } else {
-                u = ureg[it];
+            for (int i = 0; i < NI; ++i) {
+                const f32x4 xc = columns(s_x[buf], i);
+#pragma unroll
+                for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[rr][e] += ureg[rr][i][e] * xc[e];
             }
-            float y = u[0] * xc[0] + u[1] * xc[1] + u[2] * xc[2] + u[3] * xc[3];
-#pragma unroll
-            for (int off = C4 / 2; off > 0; off >>= 1) y += __shfl_xor(y, off, 64);
-            if (col4 == 0) IO::store1(a.o, row0 + it * RPI + rgrp, y);
         }
-        // the next token overwrites s_q, s_k, s_v and (two barriers later) s_x: every thread must be done with xc
-        __syncthreads();
+        const float y = row_sums(acc);
+        if (writer) IO::store1(a.o, at + my, y);
+        // (the next token overwrites s_in, and two of its barriers later s_x: every wave must be done with s_in)
+        if constexpr (MULTI) lds_barrier();
     }
 }
 
@@ -318,21 +425,31 @@ __global__ __launch_bounds__(256) void decode_step_kernel_d16(DecodeArgs a, int 
     if (a.U_state) *(f32x4 *)(a.U_state + state_off) = ureg;
 }
 
+constexpr int kDecodeHoldPairs = 256;
+
+template <class IO, int D, int NW, bool MULTI, bool LOWER, bool STREAM = false>
+static void launch_nw(const DecodeArgs &a, int n_pairs, hipStream_t stream)
+{
+    hipLaunchKernelGGL((decode_step_kernel<IO, D, NW, MULTI, LOWER, STREAM>), dim3((unsigned)n_pairs), dim3(64 * NW), 0,
+                       stream, a);
+}
+
 template <class IO, int D, bool MULTI, bool LOWER>
 static void launch_one(const DecodeArgs &a, int n_pairs, hipStream_t stream)
 {
-    // One token at d = 128: U is streamed through the readout instead of being held beside H (102 registers instead
-    // of 158: four workgroups per CU instead of three). Measured on two boxes of the pool, 8192 pairs: full layout
-    // 0.380 / 0.389 ms against 0.423 / 0.386 ms, block-lower layout 0.310 / 0.313 ms against 0.368 / 0.330 ms.
-    if constexpr (D == 128 && !MULTI) {
-        if (a.U_state) {
-            hipLaunchKernelGGL((decode_step_kernel<IO, D, MULTI, LOWER, true>), dim3((unsigned)n_pairs),
-                               dim3(DecodeShape<D>::NTHR), 0, stream, a);
-            return;
+    if constexpr (D == 256) {
+        launch_nw<IO, D, 16, MULTI, LOWER>(a, n_pairs, stream);
+    } else if constexpr (D == 128) {
+        if constexpr (!MULTI) {
+            if (a.U_state && n_pairs > kDecodeHoldPairs) {
+                launch_nw<IO, D, 4, MULTI, LOWER, true>(a, n_pairs, stream);
+                return;
+            }
         }
+        launch_nw<IO, D, 8, MULTI, LOWER>(a, n_pairs, stream);
+    } else {
+        launch_nw<IO, D, 4, MULTI, LOWER>(a, n_pairs, stream);
     }
-    hipLaunchKernelGGL((decode_step_kernel<IO, D, MULTI, LOWER>), dim3((unsigned)n_pairs), dim3(DecodeShape<D>::NTHR), 0,
-                       stream, a);
 }
 
 template <class IO, bool MULTI>
