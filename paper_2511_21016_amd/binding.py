@@ -58,11 +58,13 @@ class GkaError(RuntimeError):
 
 
 _lib = None
+_raw_stream = None          # device index -> hipStream_t of torch's current stream there
+_io_of = {}                 # torch dtype -> gka_dtype
 
 
 def load_library():
     """Load libgka.so once; raise if it has not been built."""
-    global _lib
+    global _lib, _raw_stream, _io_of
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -70,7 +72,7 @@ def load_library():
         # PyTorch ships its own HIP runtime (SONAME libamdhip64.so.7). Importing torch first makes libgka
         # bind to that same copy; loading libgka first would bring a second runtime into the process and
         # kernels launched on torch's streams would fail.
-        import torch  # noqa: F401
+        import torch
         lib = ctypes.CDLL(LIB_PATH)
         vp, fp = ctypes.c_void_p, ctypes.c_void_p
         lib.gka_forward_workspace_bytes.argtypes = [ctypes.POINTER(GkaParams)]
@@ -105,6 +107,12 @@ def load_library():
         lib.gka_status_string.restype = ctypes.c_char_p
         lib.gka_version.argtypes = []
         lib.gka_version.restype = ctypes.c_int
+        # (a decode step of few sequences lasts as long as the Python that enqueues it: the stream's handle is asked for
+        # without the Stream object around it where torch offers that, 0.1 us instead of 1.9 us)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if _raw_stream is None:
+            _raw_stream = lambda index: torch.cuda.current_stream(index).cuda_stream
+        _io_of = {torch.float32: GKA_F32, torch.bfloat16: GKA_BF16}
         _lib = lib
     return _lib
 
@@ -121,11 +129,8 @@ def make_params(B, H, T, d, n_iter, io_dtype, compute, chunk=64, d_v=None, strid
                 lambda_scale=0.0, beta=None, alpha=None, state_layout=0, xhat_out=None, slab_state_bytes=0,
                 walk_chunks=0, path=0):
     """beta, alpha, xhat_out: device addresses (ints) of the optional per-token gates / solve output, or None."""
-    return GkaParams(B=B, H=H, T=T, d_k=d, d_v=d if d_v is None else d_v, chunk=chunk, n_iter=n_iter,
-                     io_dtype=io_dtype, compute=compute, phase=phase,
-                     stride_b=strides[0], stride_t=strides[1], stride_h=strides[2],
-                     lambda_scale=lambda_scale, state_layout=state_layout, beta=beta, alpha=alpha, xhat_out=xhat_out,
-                     slab_state_bytes=slab_state_bytes, walk_chunks=walk_chunks, path=path)
+    return GkaParams(B, H, T, d, d if d_v is None else d_v, chunk, n_iter, io_dtype, compute, phase, *strides,
+                     lambda_scale, state_layout, beta, alpha, xhat_out, slab_state_bytes, walk_chunks, path)
 
 
 def forward_workspace_bytes(params):
@@ -173,12 +178,11 @@ def _check(status):
 
 
 def _io_dtype(t):
-    import torch
-    if t.dtype == torch.float32:
-        return GKA_F32
-    if t.dtype == torch.bfloat16:
-        return GKA_BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    load_library()
+    io = _io_of.get(t.dtype)
+    if io is None:
+        raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    return io
 
 
 def _ptr(t):
@@ -204,11 +208,11 @@ def gka_forward(q, k, v, gate, lam, n_iter, *, compute=None, chunk=64, H_init=No
     params = make_params(B, H, T, d, n_iter, io, compute, chunk=chunk, d_v=v.shape[-1], phase=phase,
                          lambda_scale=lambda_scale, beta=_ptr(beta), alpha=_ptr(alpha), state_layout=state_layout,
                          xhat_out=_ptr(xhat), slab_state_bytes=slab_state_bytes, walk_chunks=walk_chunks, path=path)
-    nbytes = forward_workspace_bytes(params)
-    if nbytes == 0:
-        # let the library name the error
-        _check(forward_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(q)))
     if workspace is None:
+        nbytes = forward_workspace_bytes(params)
+        if nbytes == 0:
+            # let the library name the error
+            _check(forward_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(q)))
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
     o = torch.empty_like(v) if out is None else out
     extras = {}
@@ -222,7 +226,7 @@ def gka_forward(q, k, v, gate, lam, n_iter, *, compute=None, chunk=64, H_init=No
         extras["fro"] = fro
     if return_xhat:
         extras["xhat"] = xhat
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream = _raw_stream(q.get_device())
     _check(forward_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(o), _ptr(H_init),
                        _ptr(U_init), _ptr(Hf), _ptr(Uf), _ptr(fro), _ptr(workspace), workspace.numel(), stream))
     return (o, extras) if extras else o
@@ -232,13 +236,15 @@ def gka_decode_step(H_state, U_state, q, k, v, gate, lam, n_iter, *, out=None, b
                     lambda_scale=0.0, state_layout=GKA_STATE_FULL):
     """gka_decode_step on torch CUDA tensors: states [B,H,d,d] float32 (updated in place), q, k, v [B,H,d],
     gate, lam [B,H] float32 (lam None: lambda_scale * ||H||_F); beta, alpha: optional [B,H] float32."""
-    import torch
     B, H, d = q.shape
     io = _io_dtype(q)
     params = make_params(B, H, 1, d, n_iter, io, GKA_COMPUTE_F32, lambda_scale=lambda_scale, beta=_ptr(beta),
                          alpha=_ptr(alpha), state_layout=state_layout)
-    o = torch.empty_like(v) if out is None else out
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    o = out
+    if o is None:
+        import torch
+        o = torch.empty_like(v)
+    stream = _raw_stream(q.get_device())
     _check(decode_step_raw(params, _ptr(H_state), _ptr(U_state), _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam),
                            _ptr(o), stream))
     return o
@@ -257,7 +263,7 @@ def gka_decode_tokens(H_state, U_state, q, k, v, gate, lam, n_iter, *, out=None,
     params = make_params(B, H, T, d, n_iter, io, GKA_COMPUTE_F32, lambda_scale=lambda_scale, beta=_ptr(beta),
                          alpha=_ptr(alpha), state_layout=state_layout)
     o = torch.empty_like(v) if out is None else out
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream = _raw_stream(q.get_device())
     _check(decode_tokens_raw(params, _ptr(H_state), _ptr(U_state), _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam),
                              _ptr(o), stream))
     return o
@@ -303,8 +309,8 @@ def gka_backward(q, k, v, gate, lam, dy, n_iter, *, compute=None, beta=None, alp
         compute = GKA_COMPUTE_BF16 if io == GKA_BF16 else GKA_COMPUTE_F32
     params = make_params(B, H, T, d, n_iter, io, compute, lambda_scale=lambda_scale, beta=_ptr(beta),
                          alpha=_ptr(alpha), strides=strides)
-    nbytes = backward_workspace_bytes(params)
     if workspace is None:
+        nbytes = backward_workspace_bytes(params)
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=q.device)
     f32 = dict(dtype=torch.float32, device=q.device)
     out = {"dq": torch.empty((B, T, H, d), **f32), "dk": torch.empty((B, T, H, d), **f32),
@@ -315,7 +321,7 @@ def gka_backward(q, k, v, gate, lam, dy, n_iter, *, compute=None, beta=None, alp
         out["dbeta"] = torch.empty((B, T, H), **f32)
     if alpha is not None:
         out["dalpha"] = torch.empty((B, T, H), **f32)
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream = _raw_stream(q.get_device())
     if H_init is not None or return_state_grads:
         if return_state_grads:
             out["dH_init"] = torch.empty((B, H, d, d), **f32)
@@ -354,11 +360,11 @@ def gka_forward_sketched(q, k, v, gate, lam, S, n_iter, *, beta=None, lambda_sca
     d_s = S.shape[-2]
     params = make_params(B, H, T, d, n_iter, _io_dtype(q), GKA_COMPUTE_BF16, lambda_scale=lambda_scale,
                          beta=_ptr(beta))
-    nbytes = forward_sketched_workspace_bytes(params, d_s)
     if workspace is None:
+        nbytes = forward_sketched_workspace_bytes(params, d_s)
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=q.device)
     o = torch.empty_like(v) if out is None else out
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream = _raw_stream(q.get_device())
     _check(forward_sketched_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(S), d_s, per_head,
                                 _ptr(o), _ptr(workspace), workspace.numel(), stream))
     return o
