@@ -28,7 +28,11 @@ struct Plan {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-constexpr int kStateMinWorkgroups = 512;   // two state-pass workgroups per CU
+constexpr int kStateMinWorkgroups = 512;   // two state-pass workgroups per CU (bf16 operands)
+constexpr int kStateMinWorkgroupsF32 = 256;
+// Up to this many chunks a state pass is one launch: the second launch that segments need costs as much as walking them
+// (d = 64, 5 chunks: 27.8 us per forward pass in two segments, 23.3 us in one; float32, 4 chunks 34.6 and 32.1 us).
+constexpr int kStateSingleWalk = 5;
 constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walks before segments are added
 // Chunk states one launch pair keeps in the workspace unless gka_params::slab_state_bytes says otherwise (tests use
 // that to force several slabs on small problems).
@@ -142,7 +146,8 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     // (a plain readout walks U only: half the workgroups of a segment have nothing to do)
     int wg_per_seg = gka::state_pass_workgroups_per_segment(pl->pairs_per_batch, pl->d, pl->compute_bf16);
     if (readout_only && wg_per_seg > 1) wg_per_seg /= 2;
-    int n_segs = (kStateMinWorkgroups + wg_per_seg - 1) / wg_per_seg;
+    int n_segs = ((pl->compute_bf16 ? kStateMinWorkgroups : kStateMinWorkgroupsF32) + wg_per_seg - 1) / wg_per_seg;
+    if (pl->slab_chunks <= kStateSingleWalk) n_segs = 1;
     if (n_segs < pl->slab_chunks / kStateMaxWalk) n_segs = pl->slab_chunks / kStateMaxWalk;
     if (n_segs > pl->slab_chunks / 2) n_segs = pl->slab_chunks / 2;
     if (n_segs < 1) n_segs = 1;
