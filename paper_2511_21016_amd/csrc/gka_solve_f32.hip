@@ -6,8 +6,7 @@
 //
 // and the residual form of the recurrence. What differs is the shape: a float32 product takes sixteen times the matrix
 // pipe's time of a bf16 one, so everything here serves the pipe.
-//   * A workgroup takes TT tiles of 16 tokens of one chunk (TT = 4: the whole chunk; 4 / TT workgroups per chunk).
-//     Wave w owns the feature rows 16 RT w .. of every vector, for all of the workgroup's tokens: no product is
+//   * A workgroup takes TT = 1 or 2 tiles of 16 tokens of one chunk (4 / TT workgroups per chunk). Wave w owns the feature rows 16 RT w .. of every vector, for all of the workgroup's tokens: no product is
 //     computed twice, and the state's rows of a wave stay in its registers for all passes (RT D / 4 registers; a pass
 //     reads no state from memory or LDS).
 //   * Tokens sit on the N dimension: lane (n, kg) = (lane & 15, lane >> 4) holds rows 4 kg .. + 3 of token n of a tile,
@@ -18,8 +17,8 @@
 //     product, which does not need them: the barrier that publishes P waits for no one.
 // Bound: the matrix pipe (157 TFLOP/s in float32). Measured, microseconds per forward pass, against 32 x 32 x 2 products
 // with two waves per token block that each formed all of P, H_[n] in LDS, one workgroup per chunk: d = 64, 1 pair x 256
-// tokens 62 -> 35; d = 64, 64 x 1024 205 -> 181; d = 128, 16 x 1500 309 -> 210; d = 128, 64 x 1024 665 -> 477
-// (90 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16230 -> 784, of which this kernel 702.
+// tokens 62 -> 32; d = 64, 64 x 1024 205 -> 163; d = 128, 16 x 1500 309 -> 197; d = 128, 64 x 1024 664 -> 436
+// (98 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16220 -> 724, of which this kernel 600.
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
@@ -32,21 +31,23 @@ struct SolveF32Shape {
     static constexpr int RT = D / (16 * NW);           // row tiles of 16 features per wave
     static constexpr int KS = D / 16;                  // steps of 16 features (four products) of a contraction
     static constexpr int TB = 4 / TT;                  // workgroups per chunk
-    static constexpr int NUNITS = TT == 4 ? 10 : TT == 2 ? 7 : 4;   // causal (key tile, token tile) pairs, at most
+    static constexpr int NUNITS = TT == 2 ? 7 : 4;   // causal (key tile, token tile) pairs, at most
     static constexpr int MAXU = (NUNITS + NW - 1) / NW;             // ... per wave
-    static constexpr size_t k_bytes = (size_t)kChunk * D * 4;
-    static constexpr size_t x_bytes = (size_t)16 * TT * D * 4;
-    static constexpr size_t p_bytes = (size_t)16 * TT * kChunk * 4;
+    static constexpr size_t k_bytes = (size_t)kChunk * (D + 4) * 4;
+    static constexpr size_t x_bytes = (size_t)16 * TT * (D + 4) * 4;
+    static constexpr size_t p_bytes = (size_t)16 * TT * (kChunk + 4) * 4;
     static constexpr size_t lds_bytes = k_bytes + x_bytes + p_bytes;
     static_assert((2 * NW + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand rows");
 };
 
-// float4 index of columns 4 c4 .. + 3 of a row in a tile of rows of W floats: 16-byte granules XOR-swizzled with the row
-// number, so that sixteen rows at the same columns, or a row's sixteen columns, fall into different banks
+// float4 index of columns 4 c4 .. + 3 of a row in a tile of rows of W floats. Rows are padded by 16 bytes: sixteen rows at
+// the same columns, or four rows' sixteen columns, fall into different banks, and every access of a lane is an
+// immediate offset from one address (an XOR swizzle made the compiler keep fifty addresses in registers: 162 of them
+// at d = 128 with TT = 2, one workgroup per CU).
 template <int W>
-__device__ __forceinline__ int row4(int row, int c4) { return row * (W / 4) + (c4 ^ (row & 15)); }
+__device__ __forceinline__ int row4(int row, int c4) { return row * (W / 4 + 1) + c4; }
 template <int W>
-__device__ __forceinline__ int row1(int row, int col) { return 4 * row4<W>(row, col >> 2) + (col & 3); }
+__device__ __forceinline__ int row1(int row, int col) { return row * (W + 4) + col; }
 
 __device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c)
 {
@@ -150,15 +151,18 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
         const f32x4 v = IO::load4(x, tok_off[tt] + 16 * rt);
         return valid[tt] ? v : zero4();
     };
+    auto load_rhs = [&]() {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-            qv[rt][tt] = load_q(a.q, rt, tt);
-            if constexpr (GATED) {
-                if (a.q_lo) qv[rt][tt] += load_q(a.q_lo, rt, tt);
+            for (int tt = 0; tt < TT; ++tt) {
+                qv[rt][tt] = load_q(a.q, rt, tt);
+                if constexpr (GATED) {
+                    if (a.q_lo) qv[rt][tt] += load_q(a.q_lo, rt, tt);
+                }
             }
-        }
+    };
+    if constexpr (D != 256) load_rhs();                // (d = 256: the norm needs the registers)
     float hn2 = 0.0f;
     if (solve) {
         load_state(a.ws_H);
@@ -299,6 +303,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
     }
 
     // ---------------- Chebyshev iteration (Algorithm 1), residual form ----------------
+    if constexpr (D == 256) load_rhs();
     float s0[TT], rho2[TT], omega[TT];
     f32x4 xi[RT][TT], dl[RT][TT], gS[RT][TT], gI[RT][TT];
 #pragma unroll
@@ -438,7 +443,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
 }
 
 template <class IO, int D, int TT, bool GATED>
-__global__ __launch_bounds__((SolveF32Shape<D, TT>::NTHR)) __attribute__((amdgpu_waves_per_eu(2))) void
+__global__ __launch_bounds__((SolveF32Shape<D, TT>::NTHR)) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void
 solve_f32_kernel(SolveArgs a)
 {
     solve_f32_body<IO, D, TT, GATED>(a);
@@ -467,15 +472,13 @@ template <class IO, int D, bool GATED>
 static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
 {
     // Tokens per workgroup (16 TT): small workgroups spread a small problem over the chip, large ones repeat less of the
-    // norm and share operand reads. Measured (whole forward pass, microseconds, TT = 1 / 2 / 4): d = 128: 20 chunks
-    // 56 / 76 / 106, 160 chunks 115 / 112 / 118, 384 chunks 236 / 210 / 228, 1024 chunks 612 / 518 / 477; d = 64: 64
-    // chunks 36 / 47 / 60, 256 chunks 63 / 63 / 70, 1024 chunks 189 / 181 / 187; d = 256 (where the state rows leave
-    // no registers for TT = 4): 20 chunks 130 / 200, 88 chunks 222 / 233, 256 chunks 440 / 392.
+    // norm and share operand reads. Measured (whole forward pass, microseconds, TT = 1 / 2): d = 64: 64 chunks 35 / 46,
+    // 256 chunks 62 / 64, 512 chunks 112 / 104; d = 128: 20 chunks 49 / 71, 160 chunks 102 / 112, 256 chunks 141 / 129,
+    // 1024 chunks 472 / 436; d = 256: 20 chunks 119 / 181, 88 chunks 210 / 209, 160 chunks 240 / 227, 512 chunks 834 / 724.
+    // (TT = 4 at d = 128, 1024 chunks: 460; at d = 256 the state rows leave no registers for it.)
     const int64_t chunks = (int64_t)a.n_pairs * a.n_chunks;
-    if (chunks <= 128) return launch_solve_f32_t<IO, D, 1, GATED>(a, stream);
-    if (D != 128 || chunks <= 512) return launch_solve_f32_t<IO, D, 2, GATED>(a, stream);
-    if constexpr (D == 128) return launch_solve_f32_t<IO, D, 4, GATED>(a, stream);
-    return hipErrorInvalidValue;
+    if (chunks <= (D == 256 ? 96 : 192)) return launch_solve_f32_t<IO, D, 1, GATED>(a, stream);
+    return launch_solve_f32_t<IO, D, 2, GATED>(a, stream);
 }
 
 template <class IO, int D>

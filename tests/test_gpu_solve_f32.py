@@ -1,6 +1,6 @@
 """GPU parity of the per-chunk solve with float32 products (d = 64, 128 and, on GKA_PATH_AUTO, 256) against the fp64
-oracle, at the edges of its token tiles (16 tokens) and on problems large enough for each of its workgroup sizes (16, 32
-and 64 tokens)."""
+oracle, at the edges of its token tiles (16 tokens) and on problems large enough for each of its workgroup sizes (16 and 32
+tokens)."""
 import numpy as np
 import pytest
 
