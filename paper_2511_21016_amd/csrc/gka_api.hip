@@ -220,7 +220,8 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
                         const float *lambda, void *o, const float *H_init, const float *U_init, float *H_final,
                         float *U_final, float *fro_out, void *workspace, size_t workspace_bytes,
                         void *hip_stream, PhaseEvents *prof, bool readout_only = false, bool solve_only = false,
-                        const void *q_lo = nullptr)
+                        const void *q2 = nullptr, const void *q2_lo = nullptr,
+                        float *xhat2_out = nullptr)
 {
     Plan pl;
     gka_status s = make_plan(p, &pl, readout_only);
@@ -234,7 +235,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     char *ws = (char *)workspace;
 
     if (pl.small) {
-        if (p->phase != GKA_PHASE_ALL || solve_only || q_lo) return GKA_ERR_UNSUPPORTED;
+        if (p->phase != GKA_PHASE_ALL || solve_only) return GKA_ERR_UNSUPPORTED;
         gka::SmallArgs sm = {};
         sm.q = q; sm.k = k; sm.v = v; sm.o = o;
         sm.stride_b = pl.stride_b; sm.stride_t = pl.stride_t; sm.stride_h = pl.stride_h;
@@ -251,7 +252,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
         return GKA_OK;
     }
     if (pl.recurrent) {
-        if (p->phase != GKA_PHASE_ALL || pl.split || solve_only || q_lo) return GKA_ERR_UNSUPPORTED;
+        if (p->phase != GKA_PHASE_ALL || pl.split || solve_only) return GKA_ERR_UNSUPPORTED;
         gka::DecodeArgs da = {};
         da.H_in = H_init; da.U_in = U_init;
         da.H_state = H_final;
@@ -269,7 +270,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
         if (prof) prof->mark(stream);
         return GKA_OK;
     }
-    const bool fused_ok = pl.fused_shape && !p->xhat_out && !solve_only && !q_lo && p->phase == GKA_PHASE_ALL;
+    const bool fused_ok = pl.fused_shape && !p->xhat_out && !solve_only && p->phase == GKA_PHASE_ALL;
     if ((p->path == GKA_PATH_FUSED || pl.split) && !fused_ok) return GKA_ERR_UNSUPPORTED;
     if (pl.wide && p->phase != GKA_PHASE_ALL) return GKA_ERR_UNSUPPORTED;
     if (pl.split && p->path == GKA_PATH_TWO_PHASE) return GKA_ERR_UNSUPPORTED;     // only the fused kernel splits
@@ -304,7 +305,8 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     sa.seg_buf = (float *)(ws + pl.off_seg); sa.seg_logdecay = (float *)(ws + pl.off_segdecay);
     sa.init_mode = 0; sa.final_mode = 0; sa.write_frags = 1;
     gka::SolveArgs so = {};
-    so.q = q; so.q_lo = q_lo; so.k = k; so.v = v; so.gate = gate; so.lambda = lambda; so.o = o; so.fro_out = fro_out;
+    so.q = q; so.k = k; so.v = v; so.gate = gate; so.lambda = lambda; so.o = o; so.fro_out = fro_out;
+    so.q2 = q2; so.q2_lo = q2_lo; so.xhat2_out = xhat2_out;
     so.beta = p->beta; so.alpha = p->alpha; so.lambda_scale = p->lambda_scale;
     so.xhat_out = p->xhat_out;
     // plain readout y_t = U_t q_t (used by the backward pass): needs alpha = 0 from the caller; no H states, no solve
@@ -489,15 +491,24 @@ void plan_readout_segments(int n_pairs, int n_chunks, int *n_segs, int *seg_len)
     *n_segs = (n_chunks + *seg_len - 1) / *seg_len;
 }
 
+// ... of the reverse recurrences' walk: one workgroup per CU
+constexpr int kReverseMinWorkgroups = 256;
+void plan_reverse_segments(int n_pairs, int n_chunks, int *n_segs, int *seg_len)
+{
+    int ns = (kReverseMinWorkgroups + n_pairs - 1) / n_pairs;
+    if (ns > n_chunks / 2) ns = n_chunks / 2;
+    if (ns < 1) ns = 1;
+    *seg_len = (n_chunks + ns - 1) / ns;
+    *n_segs = (n_chunks + *seg_len - 1) / *seg_len;
+}
+
 struct BackwardPlan {
     size_t n_elems, n_tokens, esz;
-    size_t off_f32[9];        // xhat, p; with the fused readouts also y, H x, A k, A^T k, Ubar k, U^T dy, Ubar^T v
+    size_t off_f32[3];        // xhat, p; bf16 tensors: U^T dy
     size_t off_io[23];
-    size_t off_m[6];          // gate_rev, zeros, s, fro, c, C
+    size_t off_m[9];          // gate_rev, zeros, s, fro, c, C, p . H x, k . dk / beta, v . dv / beta
     size_t off_fin[3];        // final states of three reverse readouts (gradients at the initial states)
     size_t off_fwd, fwd_bytes, total;
-    bool reuse_states;        // the second solve runs on the chunk states of the first
-    size_t off_rws;           // scratch of the readouts (the forward workspace itself unless reuse_states)
     bool strided;             // q, k, v, dy come with explicit strides
     size_t off_pack[4];       // their packed copies
 };
@@ -524,9 +535,9 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
         if (p->stride_b % align || p->stride_t % align || p->stride_h % align) return GKA_ERR_SHAPE;
         for (int i = 0; i < 4; ++i) { bp->off_pack[i] = off; off = align_up(off + bp->n_elems * bp->esz, 256); }
     }
-    for (int i = 0; i < 9; ++i) { bp->off_f32[i] = off; off = align_up(off + bp->n_elems * 4, 256); }
+    for (int i = 0; i < 3; ++i) { bp->off_f32[i] = off; off = align_up(off + bp->n_elems * 4, 256); }
     for (int i = 0; i < 23; ++i) { bp->off_io[i] = off; off = align_up(off + bp->n_elems * bp->esz, 256); }
-    for (int i = 0; i < 6; ++i) { bp->off_m[i] = off; off = align_up(off + bp->n_tokens * 4, 256); }
+    for (int i = 0; i < 9; ++i) { bp->off_m[i] = off; off = align_up(off + bp->n_tokens * 4, 256); }
     for (int i = 0; i < 3; ++i) {
         bp->off_fin[i] = off;
         off = align_up(off + (size_t)p->B * p->H * p->d_k * p->d_k * 4, 256);
@@ -541,17 +552,11 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
     int rs_n, rs_len;
     plan_readout_segments(p->B * p->H, (p->T + gka::kChunk - 1) / gka::kChunk, &rs_n, &rs_len);
     const size_t rbytes = align_up(gka::gla_readout_workspace_bytes(p->B * p->H, rs_n, p->d_k, p->d_v), 256);
-    // bf16 tensors, one launch per phase: the second solve reuses the chunk states H_[n] that the first one left in the
-    // forward workspace (the same H_t), so the readouts in between get a scratch region of their own
-    bp->reuse_states = p->io_dtype == GKA_BF16 && full.pairs_per_batch >= full.n_pairs && full.slab_chunks >= full.n_chunks;
-    if (bp->reuse_states) {
-        bp->off_rws = off + bp->fwd_bytes;
-        bp->total = bp->off_rws + rbytes;
-    } else {
-        if (rbytes > bp->fwd_bytes) bp->fwd_bytes = rbytes;
-        bp->off_rws = bp->off_fwd;
-        bp->total = off + bp->fwd_bytes;
-    }
+    if (rbytes > bp->fwd_bytes) bp->fwd_bytes = rbytes;
+    plan_reverse_segments(p->B * p->H, (p->T + gka::kChunk - 1) / gka::kChunk, &rs_n, &rs_len);
+    const size_t vbytes = align_up(gka::reverse_workspace_bytes(p->B * p->H, rs_n, p->d_k), 256);
+    if (vbytes > bp->fwd_bytes) bp->fwd_bytes = vbytes;
+    bp->total = off + bp->fwd_bytes;
     return GKA_OK;
 }
 }  // namespace
@@ -608,6 +613,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     float *xf = (float *)(ws + bp.off_f32[0]), *pf32 = (float *)(ws + bp.off_f32[1]);
     auto f32buf = [&](int i) { return (float *)(ws + bp.off_f32[i]); };
     float *gate_rev = (float *)(ws + bp.off_m[0]), *zeros = (float *)(ws + bp.off_m[1]), *sbuf = (float *)(ws + bp.off_m[2]);
+    float *phx = (float *)(ws + bp.off_m[6]);
     float *fro = (float *)(ws + bp.off_m[3]), *cbuf = (float *)(ws + bp.off_m[4]), *Cbuf = (float *)(ws + bp.off_m[5]);
     void *fws = ws + bp.off_fwd;
     const bool io_bf16 = p->io_dtype == GKA_BF16;
@@ -630,17 +636,21 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     // a forward pass with the roles given; alpha = zeros makes it the plain readout y_t = U_t q_t of the gated
     // recurrence U_t = gate_t U_{t-1} + beta_t v_t k_t^T (the solve is reduced to its starting point and discarded)
     auto fwd = [&](const void *qq, const void *kk, const void *vv, const float *gg, const float *beta,
-                   const float *alpha, int n_iter, void *out, float *xhat, float *fro_out = nullptr,
-                   bool solve_only = false, const void *q_lo = nullptr, int phase = GKA_PHASE_ALL) {
+                   const float *alpha, int n_iter, void *out, float *xhat, float *fro_out = nullptr) {
         gka_params pp = *p;                      // lambda (or its rule) as given: only the two solves use it
-        pp.beta = beta; pp.alpha = alpha; pp.n_iter = n_iter; pp.xhat_out = xhat; pp.phase = phase;
+        pp.beta = beta; pp.alpha = alpha; pp.n_iter = n_iter; pp.xhat_out = xhat;
         pp.state_layout = GKA_STATE_FULL;
-        const bool plain_readout = alpha == zeros;
-        // (initial states reach the two solves; the composition of plain readouts for float32 tensors has none)
-        const bool is_solve = xhat != nullptr;
-        return forward_impl(&pp, qq, kk, vv, gg, lambda, out, is_solve ? H_init : nullptr, is_solve ? U_init : nullptr,
-                            nullptr, nullptr, fro_out, fws, bp.fwd_bytes, hip_stream, nullptr, plain_readout, solve_only,
-                            q_lo);
+        return forward_impl(&pp, qq, kk, vv, gg, lambda, out, nullptr, nullptr, nullptr, nullptr, fro_out, fws,
+                            bp.fwd_bytes, hip_stream, nullptr, alpha == zeros);
+    };
+    // bf16 tensors: both solves in one pass over the chunks (the second right-hand side does not depend on the first
+    // solve), without U states and readout
+    auto solve_both = [&](const void *q2, const void *q2_lo, float *fro_out) {
+        gka_params pp = *p;
+        pp.alpha = nullptr; pp.xhat_out = xf;
+        pp.state_layout = GKA_STATE_FULL;
+        return forward_impl(&pp, q, k, v, gate, lambda, io(IO_Y), H_init, U_init, nullptr, nullptr, fro_out, fws,
+                            bp.fwd_bytes, hip_stream, nullptr, false, true, q2, q2_lo, pf32);
     };
     auto glue = [&](int which) {
         return gka::launch_backward_glue(g, which, io_bf16, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
@@ -650,60 +660,61 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     // (bf16 tensors: whatever operands the two solves use, the readouts take the stored bf16 tensors as they are)
     const bool fused = io_bf16;
     // out_f32: the output in float32 (the pieces of the gate gradient's sum), else in the tensors' dtype
-    // q_lo, k_lo, v_lo: the bf16 remainder of an operand that was computed in float32 (x, xt), or nullptr
+    // q_lo, k_lo: the bf16 remainder of an operand that was computed in float32 (x), or nullptr
     // init / init_transposed: the state before the first token (forward readouts); fin: where the state after the last
     // token of the walk goes (reverse readouts: the accumulated gradient at the initial state)
     auto readout = [&](const void *qq, const void *kk, const void *vv, const float *beta, bool reverse, void *out,
                        int seg_mode = 0, float *out_f32 = nullptr, const void *q_lo = nullptr,
-                       const void *k_lo = nullptr, const void *v_lo = nullptr, const float *init = nullptr,
-                       bool init_transposed = false, float *fin = nullptr) {
+                       const void *k_lo = nullptr, const float *init = nullptr,
+                       bool init_transposed = false, float *fin = nullptr, const float *dot_with = nullptr,
+                       float *dot_out = nullptr) {
         gka::ReadoutArgs r = {};                     // (optional pointers default to nullptr)
         r.init_state = init; r.init_transposed = init_transposed; r.final_state = fin;
-        r.q = qq; r.q_lo = q_lo; r.k_lo = k_lo; r.v_lo = v_lo; r.q_is_f32 = false; r.k = kk; r.v = vv; r.o = out;
+        r.dot_with = dot_with; r.dot_out = dot_out;
+        r.q = qq; r.q_lo = q_lo; r.k_lo = k_lo; r.q_is_f32 = false; r.k = kk; r.v = vv; r.o = out;
         r.o_f32 = out_f32;
         r.gate = gate; r.beta = beta;
         r.stride_h = p->d_k; r.stride_t = (int64_t)p->H * p->d_k; r.stride_b = (int64_t)p->T * p->H * p->d_k;
         r.qk_stride_h = r.stride_h; r.qk_stride_t = r.stride_t; r.qk_stride_b = r.stride_b;
         r.H = p->H; r.T = p->T; r.n_pairs = p->B * p->H;
         plan_readout_segments(r.n_pairs, (p->T + gka::kChunk - 1) / gka::kChunk, &r.n_segs, &r.seg_len);
-        r.seg_buf = (float *)(ws + bp.off_rws);
+        r.seg_buf = (float *)fws;
         r.seg_logdecay = r.seg_buf + (size_t)r.n_pairs * r.n_segs * p->d_k * p->d_v;
         r.reverse = reverse; r.seg_mode = seg_mode;
         return gka::launch_gla_readout(r, p->d_k, p->d_v, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
     g.natural_order = fused;
-    if (fused) {                                  // these seven arrive in float32 (see the combine kernel)
-        g.y_io = f32buf(2); g.hx_io = f32buf(3); g.r1 = f32buf(4); g.r2 = f32buf(5); g.r4 = f32buf(6);
-        g.dxt_io = f32buf(7); g.r3 = f32buf(8);
+    if (fused) {
+        g.dxt_io = f32buf(2);                     // (float32)
+        g.phx = phx; g.kd = (float *)(ws + bp.off_m[7]); g.vd = (float *)(ws + bp.off_m[8]);
         // bf16 tensors: the second solve takes alpha dxt, and the readouts take x and xt, as value + remainder
         g.rhs_lo_io = io(IO_RHS_LO); g.x_lo_io = io(IO_X_LO); g.xt_lo_io = io(IO_XT_LO);
     }
 #define GKA_TRY(expr) do { gka_status e_ = (expr); if (e_ != GKA_OK) return e_; } while (0)
-    // the forward solve and output; then x, xt in the tensors' dtype, the all-zero alpha and the reversed gates
-    // (with the fused readouts y is read out again below, and the solves run without U states and readout)
-    GKA_TRY(fwd(q, k, v, gate, p->beta, p->alpha, p->n_iter, io(IO_Y), xf, rule ? fro : nullptr, fused));
-    GKA_TRY(glue(0));
-    // y_t again, from the stored xt (see the combine kernel)
-    if (fused) GKA_TRY(readout(io(IO_XT), k, v, p->beta, false, nullptr, 0, f32buf(2), io(IO_XT_LO), nullptr, nullptr,
-                               U_init));
-    // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy
-    // (its state is the transpose of the one just read out: the segment summaries are reused)
-    if (fused) GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, 2, f32buf(7), nullptr, nullptr, nullptr, U_init, true));
-    else GKA_TRY(fwd(dy, v, k, gate, p->beta, zeros, 0, io(IO_DXT), nullptr));
-    GKA_TRY(glue(1));
-    // p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
-    // (the chunk states H_[n] of the first solve are still in the forward workspace where the plan says so)
-    GKA_TRY(fwd(io(IO_RHS), k, v, gate, p->beta, nullptr, p->n_iter, io(IO_SCRATCH), pf32, nullptr, fused,
-                fused ? io(IO_RHS_LO) : nullptr, fused && bp.reuse_states ? GKA_PHASE_SOLVE : GKA_PHASE_ALL));
-    // H_t x_t
-    if (fused) GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, 0, f32buf(3), io(IO_X_LO), nullptr, nullptr,
-                               H_init));
-    else GKA_TRY(fwd(io(IO_X), k, k, gate, p->beta, zeros, 0, io(IO_HX), nullptr));
+    if (fused) {
+        // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy
+        GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, 0, f32buf(2), nullptr, nullptr, U_init, true));
+        GKA_TRY(glue(1));
+        // x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
+        GKA_TRY(solve_both(io(IO_RHS), io(IO_RHS_LO), rule ? fro : nullptr));
+        // x, xt in the tensors' dtype; p_t . H_t x_t
+        GKA_TRY(glue(0));
+        GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
+                        nullptr, pf32, phx));
+    } else {
+        // the forward solve and output; then x, xt in the tensors' dtype, the all-zero alpha and the reversed gates
+        GKA_TRY(fwd(q, k, v, gate, p->beta, p->alpha, p->n_iter, io(IO_Y), xf, rule ? fro : nullptr));
+        GKA_TRY(glue(0));
+        GKA_TRY(fwd(dy, v, k, gate, p->beta, zeros, 0, io(IO_DXT), nullptr));
+        GKA_TRY(glue(1));
+        GKA_TRY(fwd(io(IO_RHS), k, v, gate, p->beta, nullptr, p->n_iter, io(IO_SCRATCH), pf32));
+        GKA_TRY(fwd(io(IO_X), k, k, gate, p->beta, zeros, 0, io(IO_HX), nullptr));
+    }
     // the rule's extra gradient -c_t H_t at every state: c_t, C_t = sum_{s>=t} M[t,s]^2 c_s, and H_t k_t
     if (rule) {
         GKA_TRY(glue(5));
         GKA_TRY(glue(6));
-        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), 1, nullptr, nullptr, nullptr, nullptr, H_init));
+        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), 1, nullptr, nullptr, nullptr, H_init));
         else GKA_TRY(fwd(k, k, k, gate, p->beta, zeros, 0, io(IO_HK), nullptr));
     }
     // reverse recurrences: A_t k_t, A_t^T k_t, Ubar_t^T v_t, Ubar_t k_t (no write gate inside them)
@@ -712,15 +723,29 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         float *fin_px = with_state ? (float *)(ws + bp.off_fin[0]) : nullptr;
         float *fin_xtdy = with_state ? (float *)(ws + bp.off_fin[1]) : nullptr;
         float *fin_ck = with_state && rule ? (float *)(ws + bp.off_fin[2]) : nullptr;
-        if (rule) GKA_TRY(readout(k, k, io(IO_VPR), nullptr, true, io(IO_R5), 0, nullptr, nullptr, nullptr, nullptr,
-                                  nullptr, false, fin_ck));
-        GKA_TRY(readout(k, io(IO_X), io(IO_PR), nullptr, true, nullptr, 0, f32buf(4), nullptr, io(IO_X_LO), nullptr,
-                        nullptr, false, fin_px));
-        GKA_TRY(readout(k, io(IO_PR), io(IO_X), nullptr, true, nullptr, 2, f32buf(5), nullptr, nullptr, io(IO_X_LO)));
-        GKA_TRY(readout(v, dy, io(IO_XT), nullptr, true, nullptr, 0, f32buf(8), nullptr, nullptr, io(IO_XT_LO),
-                        nullptr, false, fin_xtdy));
+        if (rule) GKA_TRY(readout(k, k, io(IO_VPR), nullptr, true, io(IO_R5), 0, nullptr, nullptr, nullptr, nullptr, false,
+                                  fin_ck));
         g.fin_px = fin_px; g.fin_xtdy = fin_xtdy; g.fin_ck = fin_ck;
-        GKA_TRY(readout(k, io(IO_XT), dy, nullptr, true, nullptr, 2, f32buf(6), nullptr, io(IO_XT_LO), nullptr));
+        // (the gradient at the initial H needs A_t = sum M[t,s] p_s x_s^T itself at token 0, not its symmetric part; the
+        // readout's output is not wanted)
+        if (dH_init) GKA_TRY(readout(k, io(IO_X), io(IO_PR), nullptr, true, io(IO_SCRATCH), 0, nullptr, nullptr, io(IO_X_LO),
+                                     nullptr, false, fin_px));
+        gka::ReverseArgs rv = {};
+        rv.k = k; rv.v = v; rv.dy = dy; rv.p = io(IO_PR); rv.x = io(IO_X); rv.x_lo = io(IO_X_LO);
+        rv.gate = gate; rv.beta = p->beta;
+        rv.dk = dk; rv.dv = dv; rv.kd = (float *)(ws + bp.off_m[7]); rv.vd = (float *)(ws + bp.off_m[8]);
+        rv.fin_xtdy = fin_xtdy;
+        rv.H = p->H; rv.T = p->T; rv.n_pairs = p->B * p->H;
+        plan_reverse_segments(rv.n_pairs, (p->T + gka::kChunk - 1) / gka::kChunk, &rv.n_segs, &rv.seg_len);
+        rv.seg_buf = (float *)fws;
+        rv.seg_logdecay = rv.seg_buf + (size_t)rv.n_pairs * rv.n_segs * 2 * p->d_k * p->d_k;
+        if (!p->alpha) {                          // xt = x
+            if (gka::launch_reverse(rv, p->d_k, 3, stream) != hipSuccess) return GKA_ERR_LAUNCH;
+        } else {
+            if (gka::launch_reverse(rv, p->d_k, 1, stream) != hipSuccess) return GKA_ERR_LAUNCH;
+            rv.x = io(IO_XT); rv.x_lo = io(IO_XT_LO);
+            if (gka::launch_reverse(rv, p->d_k, 2, stream) != hipSuccess) return GKA_ERR_LAUNCH;
+        }
     } else {
         if (rule) GKA_TRY(fwd(io(IO_KR), io(IO_KR), io(IO_VPR), gate_rev, nullptr, zeros, 0, io(IO_R5), nullptr));
         GKA_TRY(fwd(io(IO_KR), io(IO_XR), io(IO_PR), gate_rev, nullptr, zeros, 0, io(IO_R1), nullptr));
@@ -839,7 +864,7 @@ gka_status gka_forward_sketched(const gka_params *p, const void *q, const void *
         if (st != GKA_OK) return st;
     }
     gka::ReadoutArgs r = {};                     // (optional pointers default to nullptr)
-    r.k_lo = nullptr; r.v_lo = nullptr;
+    r.k_lo = nullptr;
     r.v = v; r.o = o; r.o_f32 = nullptr; r.gate = gate; r.beta = p->beta;
     r.stride_h = p->d_v; r.stride_t = (int64_t)p->H * p->d_v; r.stride_b = (int64_t)p->T * p->H * p->d_v;
     r.H = p->H; r.T = p->T; r.n_pairs = n_pairs;

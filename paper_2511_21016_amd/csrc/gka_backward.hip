@@ -152,9 +152,6 @@ __global__ __launch_bounds__(64) void bwd_rule_scan_kernel(BackwardGlueArgs a)
 //   dq = p + (1 - alpha) dxt,  dk = beta (-A k - A^T k + Ubar^T v),  dv = beta Ubar k,
 //   dalpha = dxt . (x - q),  dlambda = -x . p,  dbeta = k^T Abar k + v . (Ubar k)  (Abar = -A without the rule),
 //   s = -p . (H x) + dy . y - beta dbeta      (the gate gradient is the reverse cumulative sum of s over gamma),
-//   with y = U_t xt_t read out from the stored (rounded) xt where the tensors are bf16: the sum telescopes against
-//   v . (Ubar k), which the reversed passes form from that same xt; with the forward pass's own y (formed from the
-//   unrounded xhat) the mismatch accumulates along the sequence
 // With the rule lambda_t = a ||H_t||_F the gradient at every H_t gets the term -c_t H_t (Appendix B.2,
 // Eq. (dH_t-implicit)); summed over the later states it is C_t H_t for the keys up to t (C_t = sum_{s>=t} M[t,s]^2 c_s)
 // plus a reverse recurrence over the later keys, both read from plain readouts.
@@ -172,7 +169,7 @@ __global__ __launch_bounds__(256) void bwd_combine_kernel(BackwardGlueArgs a)
     const int64_t bt = tok / a.H, h = tok - bt * a.H;
     const int64_t b = bt / a.T, t = bt - b * a.T;
     // the same token in the results of the reversed passes
-    const int64_t rtok = a.natural_order ? tok : (b * a.T + (a.T - 1 - t)) * a.H + h;
+    const int64_t rtok = (b * a.T + (a.T - 1 - t)) * a.H + h;
     const int64_t i = tok * D + sub * 4, ri = rtok * D + sub * 4;
     auto group_sum = [](float x) {
 #pragma unroll
@@ -187,12 +184,8 @@ __global__ __launch_bounds__(256) void bwd_combine_kernel(BackwardGlueArgs a)
     f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
     if (a.dalpha) q = IO::load4(a.q, i);         // q enters dalpha only
     const f32x4 k = IO::load4(a.k, i), v = IO::load4(a.v, i), dy = IO::load4(a.dy, i);
-    // with the fused readouts (natural_order) the pieces of the gate gradient's sum arrive in float32
-    auto piece = [&](const void *ptr, int64_t idx) {
-        return a.natural_order ? load_f32x4((const float *)ptr, idx) : IO::load4(ptr, idx);
-    };
-    const f32x4 dxt = piece(a.dxt_io, i), y = piece(a.y_io, i), hx = piece(a.hx_io, i);
-    const f32x4 a1 = piece(a.r1, ri), a2 = piece(a.r2, ri), u1 = piece(a.r3, ri), d4 = piece(a.r4, ri);
+    const f32x4 dxt = IO::load4(a.dxt_io, i), y = IO::load4(a.y_io, i), hx = IO::load4(a.hx_io, i);
+    const f32x4 a1 = IO::load4(a.r1, ri), a2 = IO::load4(a.r2, ri), u1 = IO::load4(a.r3, ri), d4 = IO::load4(a.r4, ri);
     f32x4 hk = {0.0f, 0.0f, 0.0f, 0.0f}, r5 = hk;
     float kk = 0.0f;                             // k_t . k_t (the rule's diagonal term)
     if (rule) {
@@ -230,6 +223,70 @@ __global__ __launch_bounds__(256) void bwd_combine_kernel(BackwardGlueArgs a)
         if (a.dlambda && !rule) a.dlambda[tok] = s_dlam;
         if (a.dbeta) a.dbeta[tok] = dbeta;
         float D_t = s_dyy - s_phx;
+        if (rule) D_t -= a.c[tok] * a.fro[tok] * a.fro[tok];
+        a.s[tok] = D_t - be * dbeta;
+    }
+}
+
+// The same for bf16 tensors, whose reverse recurrences (gka_reverse.hip) leave dk and dv themselves and the dots
+// kd = k . dk / beta, vd = v . dv / beta: dq, the scalars and, with the rule, its share of dk. (k . Ubar^T v = v . Ubar k,
+// so k^T Abar k + v . Ubar k = (kd + vd) / 2.)
+template <int D>
+__global__ __launch_bounds__(256) void bwd_combine_natural_kernel(BackwardGlueArgs a)
+{
+    typedef IOBF16 IO;
+    constexpr int LPT = D / 4, TPW = 64 / LPT;   // lanes per token, four features each; tokens per wave
+    const int lane = threadIdx.x & 63;
+    const int sub = lane % LPT;
+    const int64_t tok_raw = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TPW + lane / LPT;   // index into [B,T,H]
+    const bool live = tok_raw < a.n_tokens;      // a dead group computes on the last token and stores nothing
+    const int64_t tok = live ? tok_raw : a.n_tokens - 1;
+    const int64_t i = tok * D + sub * 4;
+    auto group_sum = [](float x) {
+#pragma unroll
+        for (int off = LPT / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        return x;
+    };
+    const float al = a.alpha ? a.alpha[tok] : 1.0f;
+    const float be = a.beta ? a.beta[tok] : 1.0f;
+    const bool rule = a.rule_a > 0.0f;
+    const f32x4 x = load_f32x4(a.x_f32, i), p = load_f32x4(a.p_f32, i), dxt = load_f32x4((const float *)a.dxt_io, i);
+    f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.alpha) q = IO::load4(a.q, i);
+    float kd = a.kd[tok];
+    if (rule) {
+        // dk -= 2 beta (C_t H_t k_t + sum_{j>t} M[t,j] beta_j C_j k_j (k_j . k_t)); r5 holds the sum with its j = t term
+        const f32x4 k = IO::load4(a.k, i), hk = IO::load4(a.hk_io, i), r5 = IO::load4(a.r5, i);
+        const float Ct = a.C[tok];
+        const float kk = group_sum(k[0] * k[0] + k[1] * k[1] + k[2] * k[2] + k[3] * k[3]);
+        f32x4 dk = load_f32x4(a.dk, i);
+        float dot = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float extra = -2.0f * (Ct * hk[e] + (r5[e] - be * Ct * k[e] * kk));
+            dk[e] += be * extra;
+            dot += k[e] * extra;
+        }
+        if (live) *(f32x4 *)(a.dk + i) = dk;
+        kd += group_sum(dot);
+    }
+    float s_dalpha = 0.0f, s_dlam = 0.0f, s_dyy = 0.0f;
+    f32x4 o_dq;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        o_dq[e] = p[e] + (1.0f - al) * dxt[e];
+        s_dalpha += dxt[e] * (x[e] - q[e]);
+        s_dlam -= x[e] * p[e];
+        s_dyy += dxt[e] * (al * x[e] + (1.0f - al) * q[e]);      // dy . U xt = (U^T dy) . xt
+    }
+    if (live) *(f32x4 *)(a.dq + i) = o_dq;
+    s_dalpha = group_sum(s_dalpha); s_dlam = group_sum(s_dlam); s_dyy = group_sum(s_dyy);
+    if (live && sub == 0) {
+        const float dbeta = 0.5f * (a.vd[tok] + kd);
+        if (a.dalpha) a.dalpha[tok] = s_dalpha;
+        if (a.dlambda && !rule) a.dlambda[tok] = s_dlam;
+        if (a.dbeta) a.dbeta[tok] = dbeta;
+        float D_t = s_dyy - a.phx[tok];
         if (rule) D_t -= a.c[tok] * a.fro[tok] * a.fro[tok];
         a.s[tok] = D_t - be * dbeta;
     }
@@ -307,8 +364,13 @@ static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stre
     case 3: {
         const int64_t per_block = 4 * (256 / a.d);         // 4 waves of 64 / (d / 4) tokens
         const unsigned tb = (unsigned)((a.n_tokens + per_block - 1) / per_block);
-        if (a.d == 128) hipLaunchKernelGGL((bwd_combine_kernel<IO, 128>), dim3(tb), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((bwd_combine_kernel<IO, 64>), dim3(tb), dim3(256), 0, stream, a);
+        if constexpr (std::is_same<IO, IOBF16>::value) {
+            if (a.d == 128) hipLaunchKernelGGL((bwd_combine_natural_kernel<128>), dim3(tb), dim3(256), 0, stream, a);
+            else hipLaunchKernelGGL((bwd_combine_natural_kernel<64>), dim3(tb), dim3(256), 0, stream, a);
+        } else {
+            if (a.d == 128) hipLaunchKernelGGL((bwd_combine_kernel<IO, 128>), dim3(tb), dim3(256), 0, stream, a);
+            else hipLaunchKernelGGL((bwd_combine_kernel<IO, 64>), dim3(tb), dim3(256), 0, stream, a);
+        }
         break;
     }
     case 4:

@@ -288,12 +288,14 @@ __device__ __forceinline__ void publish_operand(typename MMA::frag *sX, const ty
 
 // The work of one wave. TW (token block) is a template parameter so that the causal structure (key blocks
 // jt <= TW) is resolved at compile time; fh (feature half) only enters through mt0.
-// GATED: the layer's variants (write gate, alpha-connection, lambda_t = a ||H_t||_F) are compiled in; the plain
-// kernel carries none of their loads, registers or branches.
-template <class MMA, class IO, int D, int TW, bool GATED>
+// MODE 1 (GATED): the layer's variants (write gate, alpha-connection, lambda_t = a ||H_t||_F) are compiled in; the plain
+// kernel (MODE 0) carries none of their loads, registers or branches. MODE 2: solve only, for two right-hand sides one
+// after the other (the backward pass: x_t and p_t): everything in front of the passes is paid for once.
+template <class MMA, class IO, int D, int TW, int MODE>
 __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned char *smem, int w)
 {
     typedef SolveShape<MMA, D> SH;
+    constexpr bool GATED = MODE != 0, DUAL = MODE == 2;
     constexpr int NB = SH::NB, NBH = SH::NBH;
     constexpr int VEC = MMA::VEC, HS = MMA::HS;
     constexpr int NSTEPS = NB * HS;            // MFMA steps of a contraction over all D features
@@ -344,7 +346,7 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
         ball = a.beta ? bm_raw : 1.0f;
     }
     // plain readout (variants' kernel only): no solve, so neither H_[n] nor its norm is read
-    const bool solve = !(GATED && a.readout_only);
+    const bool solve = !(GATED && !DUAL && a.readout_only);
     if (solve) async_block_copy<H16>(sH, (const frag *)a.ws_H + chunk_id * (SH::H_FRAGS * 64), w, lane);   // H_[n] -> LDS
     RowStage<MMA, IO, D> krows;
     krows.load(a.k, base_bh, a.stride_t, tok0, a.T, tid);
@@ -353,18 +355,7 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
             qraw[i][q4] = IO::load_raw4(a.q, tok_off + 32 * (mt0 + i) + 8 * q4 + 4 * g);
-    typename IO::raw4 qlo[GATED ? NBH : 1][4];   // remainder of the right-hand side (variants' kernel), if given
-    bool has_qlo = false;
-    if constexpr (GATED) {
-        has_qlo = a.q_lo != nullptr;
-        if (has_qlo) {
-#pragma unroll
-            for (int i = 0; i < NBH; ++i)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    qlo[i][q4] = IO::load_raw4(a.q_lo, tok_off + 32 * (mt0 + i) + 8 * q4 + 4 * g);
-        }
-    }
+    typename IO::raw4 qlo[DUAL ? NBH : 1][4];  // remainder of the second right-hand side
     lam = ((!GATED || a.lambda) ? a.lambda : a.gate)[gate_base + (int64_t)min(tok, a.T - 1) * a.H];
     float hn[NB * NB];
 #pragma unroll
@@ -478,15 +469,25 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
     float xi[NBH][16], dl[NBH][16];
     f32x16 gS[NBH], gI[NBH];
     frag own[NBH][HS];
+    const frag *myX = sX + (TW * NSTEPS) * 64;         // this token block's operand in the exchange region
+#pragma unroll
+    for (int rhs = 0; rhs < (DUAL ? 2 : 1); ++rhs) {
+    if (DUAL && rhs == 1) {
+#pragma unroll
+        for (int i = 0; i < NBH; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                qraw[i][q4] = IO::load_raw4(a.q2, tok_off + 32 * (mt0 + i) + 8 * q4 + 4 * g);
+                qlo[i][q4] = IO::load_raw4(a.q2_lo, tok_off + 32 * (mt0 + i) + 8 * q4 + 4 * g);
+            }
+    }
 #pragma unroll
     for (int i = 0; i < NBH; ++i) {
         gS[i] = zero16();
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             f32x4 qv4 = IO::cvt4(qraw[i][q4]);
-            if constexpr (GATED) {
-                if (has_qlo) qv4 += IO::cvt4(qlo[i][q4]);
-            }
+            if (DUAL && rhs == 1) qv4 += IO::cvt4(qlo[i][q4]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float qv = valid ? qv4[e] : 0.0f;
@@ -497,7 +498,6 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
 #pragma unroll
         for (int hh = 0; hh < HS; ++hh) own[i][hh] = MMA::pack(&dl[i][hh * VEC]);
     }
-    const frag *myX = sX + (TW * NSTEPS) * 64;         // this token block's operand in the exchange region
     float omega = 2.0f;
     // xi lags one update behind: xi += delta is applied while the next pass's first sweep runs (and once after the
     // last pass), so it starts from xi_{-1} = 0
@@ -571,6 +571,20 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
     for (int i = 0; i < NBH; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) xi[i][r] += dl[i][r];                               // xi_r
+
+    if constexpr (DUAL) {
+        if (valid) {
+            float *xo = (rhs == 0 ? a.xhat_out : a.xhat2_out) + (gate_base + (int64_t)tok * a.H) * D;
+#pragma unroll
+            for (int i = 0; i < NBH; ++i)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *(f32x4 *)(xo + 32 * (mt0 + i) + 8 * q4 + 4 * g) =
+                        f32x4{xi[i][4 * q4], xi[i][4 * q4 + 1], xi[i][4 * q4 + 2], xi[i][4 * q4 + 3]};
+        }
+    }
+    }                                              // (right-hand sides)
+    if constexpr (DUAL) return;
 
     // ---------------- readout y_c = zeta_c U_[n] xhat_c + sum_{j<=c} M[j,c] v_j (k_j . xhat_c) ----------------
     const frag *Uw = (const frag *)a.ws_U + chunk_id * (2 * SH::H_FRAGS * 64);    // value and remainder
@@ -672,31 +686,31 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
     }
 }
 
-template <class MMA, class IO, int D, bool GATED>
+template <class MMA, class IO, int D, int MODE>
 __device__ __forceinline__ void chunk_solve_body(const SolveArgs &a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // wave-uniform: token block and feature half of this wave
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w & 1)
-        chunk_solve_wave<MMA, IO, D, 1, GATED>(a, smem, w);
+        chunk_solve_wave<MMA, IO, D, 1, MODE>(a, smem, w);
     else
-        chunk_solve_wave<MMA, IO, D, 0, GATED>(a, smem, w);
+        chunk_solve_wave<MMA, IO, D, 0, MODE>(a, smem, w);
 }
 
 // bf16 path: capped at 256 registers so that two workgroups (two waves per SIMD) share a CU.
-template <class IO, int D, bool GATED>
+template <class IO, int D, int MODE>
 __global__ __launch_bounds__(kSolveThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_solve_kernel_bf16(
     SolveArgs a)
 {
-    chunk_solve_body<MmaBF16, IO, D, GATED>(a);
+    chunk_solve_body<MmaBF16, IO, D, MODE>(a);
 }
 
-template <class IO, int D, bool GATED>
+template <class IO, int D, int MODE>
 static hipError_t launch_chunk_solve_g(const SolveArgs &a, hipStream_t stream)
 {
     typedef SolveShape<MmaBF16, D> SH;
-    auto kern = chunk_solve_kernel_bf16<IO, D, GATED>;
+    auto kern = chunk_solve_kernel_bf16<IO, D, MODE>;
     // (set once per kernel instantiation and device, not per launch)
     static bool attr_set_on[64] = {};
     int dev = 0;
@@ -715,8 +729,9 @@ static hipError_t launch_chunk_solve_g(const SolveArgs &a, hipStream_t stream)
 template <class IO, int D>
 static hipError_t launch_chunk_solve_t(const SolveArgs &a, hipStream_t stream)
 {
-    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_chunk_solve_g<IO, D, true>(a, stream);
-    return launch_chunk_solve_g<IO, D, false>(a, stream);
+    if (a.q2) return launch_chunk_solve_g<IO, D, 2>(a, stream);
+    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_chunk_solve_g<IO, D, 1>(a, stream);
+    return launch_chunk_solve_g<IO, D, 0>(a, stream);
 }
 
 hipError_t launch_chunk_solve(const SolveArgs &a, int n_pairs, int d, bool io_bf16, bool compute_bf16,

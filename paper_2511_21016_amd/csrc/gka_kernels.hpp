@@ -36,8 +36,6 @@ struct StatePassArgs {
 
 struct SolveArgs {
     const void *q, *k, *v;
-    const void *q_lo;             // variants' kernel: optional remainder of q in the tensors' dtype (the right-hand side
-                                  // of the solve is q + q_lo), or nullptr
     const float *gate, *lambda;   // lambda nullptr: lambda_t = lambda_scale ||H_t||_F
     const float *beta, *alpha;    // [B,T,H] write gate / alpha-connection, each nullptr (= 1)
     float lambda_scale;
@@ -53,6 +51,10 @@ struct SolveArgs {
     int pair0;                    // first (batch, head) pair of this launch; workspace is indexed from 0
     bool readout_only;            // variants' kernel: no solve (its result is discarded by alpha = 0): H_[n] is not read
     bool solve_only;              // variants' kernel: xhat_out is all the caller wants: U_[n] is not read, o not written
+    // a second right-hand side for the same systems (solve_only; the backward pass): CH(H_t + lambda_t I, q2_t + q2_lo_t, r)
+    // goes to xhat2_out. nullptr: none
+    const void *q2, *q2_lo;
+    float *xhat2_out;
     bool init_states;             // the sequence starts from given states (else the states before chunk 0 are zero)
 };
 
@@ -84,7 +86,9 @@ struct BackwardGlueArgs {
     void *x_io, *xt_io, *rhs_io;  // x, alpha x + (1 - alpha) q, alpha dxt
     void *rhs_lo_io;              // bf16 tensors: what rounding alpha dxt to rhs_io left over (nullptr: not kept)
     void *x_lo_io, *xt_lo_io;     // likewise for x_io and xt_io
-    const void *dxt_io, *y_io, *hx_io;                     // U_t^T dy_t, forward output, H_t x_t
+    const void *dxt_io, *y_io, *hx_io;                     // U_t^T dy_t; float32 tensors: forward output, H_t x_t
+    const float *phx;             // bf16 tensors: p_t . H_t x_t,
+    const float *kd, *vd;         //   k . dk / beta, v . dv / beta (gka_reverse.hip)
     void *k_rev, *v_rev, *dy_rev, *x_rev, *p_rev, *xt_rev; // time-reversed copies
     float *gate_rev, *zeros;      // gates of the reverse recurrences; an all-zero alpha
     const void *r1, *r2, *r3, *r4;                         // reversed passes: A k, A^T k, Ubar^T v, Ubar k
@@ -94,9 +98,8 @@ struct BackwardGlueArgs {
     const float *fro;             // ||H_t||_F of the forward pass
     float *c, *C;                 // c_t and C_t = sum_{s>=t} M[t,s]^2 c_s
     void *vp_rev;                 // time-reversed beta_t C_t k_t
-    bool natural_order;           // the reversed passes read and write the tensors in place (gla_readout `reverse`):
-                                  // nothing is reversed here, p_rev and vp_rev are plain conversions, and dxt_io, y_io,
-                                  // hx_io, r1, r2, r3, r4 are float32
+    bool natural_order;           // bf16 tensors: the reversed passes read and write the tensors in place: nothing is reversed
+                                  // here, p_rev and vp_rev are plain conversions, dxt_io is float32
     const void *hk_io, *r5;       // H_t k_t; reversed pass sum_{j>=t} M[t,j] beta_j C_j k_j (k_j . k_t)
     // gradients at the initial states (which = 7): the final states of three reverse readouts, each [pairs, d, d]
     const float *H_init;          // the caller's initial H (the rule's term needs it)
@@ -117,9 +120,8 @@ hipError_t launch_pack_rows(const void *src, void *dst, int B, int T, int H, int
 struct ReadoutArgs {
     const void *q, *k, *v;        // q, k: [B,T,H,dk]; v: [B,T,H,dv]
     const void *q_lo;             // optional bf16 remainder of q (y_t = U_t (q_t + q_lo_t)), or nullptr
-    const void *k_lo, *v_lo;      // optional bf16 remainder of k or of v (at most one of the two; dk = dv only), laid out
-                                  // like k / v: the recurrence is that of k + k_lo (v + v_lo). For operands that were
-                                  // computed in float32 (the solves' results in the backward pass)
+    const void *k_lo;             // optional bf16 remainder of k (dk = dv only), laid out like k: the recurrence is that of
+                                  // k + k_lo. For operands that were computed in float32 (the solves' results)
     bool q_is_f32;                // q is float32 (split into value + remainder inside); dk = 64, dv = 128 only
     void *o;                      // [B,T,H,dv]
     float *o_f32;                 // if not nullptr the output goes here in float32 instead (same strides)
@@ -132,15 +134,35 @@ struct ReadoutArgs {
     float *seg_buf;               // [pairs, n_segs, dv*dk] segment summaries
     float *seg_logdecay;          // [pairs, n_segs]
     int seg_mode;                 // 0: the summaries are computed by this call; 1: they are in seg_buf already (the call
-                                  // before had the same k, v, gate, beta, direction); 2: likewise, with k and v exchanged
-                                  // (the transposed state; dk = dv only)
+                                  // before had the same k, v, gate, beta, direction)
     bool reverse;
     const float *init_state;      // [pairs, dv, dk] float32 or nullptr (zero): the state before the first token of the walk
     bool init_transposed;         // init_state holds the transposed state, [pairs, dk, dv] (dk = dv only)
+    const float *dot_with;        // q_lo given, dk = dv: not the output itself is wanted but dot_out_t = dot_with_t . y_t,
+    float *dot_out;               // dot_with float32 like q, dot_out [B,T,H]; o and o_f32 are ignored. nullptr: no
     float *final_state;           // [pairs, dv, dk] float32 or nullptr: the state after the last token of the walk
 };
 hipError_t launch_gla_readout(const ReadoutArgs &a, int dk, int dv, hipStream_t stream);
 size_t gla_readout_workspace_bytes(int n_pairs, int n_segs, int dk, int dv);
+
+// Reverse recurrences of the backward pass in one walk (gka_reverse.hip). Packed bf16 [B,T,H,d] tensors unless named
+// otherwise; x, x_lo stand for xt, xt_lo in a call for the Ubar parts alone.
+struct ReverseArgs {
+    const void *k, *v, *dy, *p;   // p, the second solve's result, in bf16
+    const void *x, *x_lo;
+    const float *gate, *beta;     // [B,T,H]; beta nullptr (= 1)
+    float *dk, *dv;               // float32 [B,T,H,d]
+    float *kd, *vd;               // [B,T,H]: k . dk / beta, v . dv / beta
+    float *fin_xtdy;              // [pairs, d, d] or nullptr: sum_t M[0,t] xt_t dy_t^T
+    int H, T, n_pairs;
+    int n_segs, seg_len;          // segments of the chunk scan per pair, chunks per segment
+    float *seg_buf;               // [pairs, n_segs, 2 d*d] segment summaries
+    float *seg_logdecay;          // [pairs, n_segs]
+};
+// part: 3 everything (no alpha-connection: xt = x), 1 dk = -S k only (not scaled, kd not written), 2 the rest, added to
+// what part 1 left in dk.
+hipError_t launch_reverse(const ReverseArgs &a, int d, int part, hipStream_t stream);
+size_t reverse_workspace_bytes(int n_pairs, int n_segs, int d);
 
 // Projections of latent sketching: down (qs = S q, ks = S k, 64 sketched features stored, zeros above d_s) and up
 // (xhat = S^T z as bf16 value and optional remainder). Packed bf16 tensors [B,T,H,d]; z float32 [B,T,H,64].

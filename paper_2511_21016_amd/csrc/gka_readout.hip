@@ -1,6 +1,6 @@
 // Gated-linear-attention readout y_t = U_t q_t, U_t = gamma_t U_{t-1} + beta_t v_t k_t^T, with the state kept in
-// registers: the reverse recurrences of the backward pass (Section 4.2.2, Eq. (Ai) and its counterpart for U) and its
-// plain forward readouts (U_t^T dy_t, H_t xhat_t, H_t k_t) are all of this form. Unlike the forward pass of the layer
+// registers: the plain forward readouts of the backward pass (U_t^T dy_t, p_t . H_t xhat_t, H_t k_t), the rule's reverse
+// recurrence and latent sketching's readout are of this form (the other reverse recurrences: gka_reverse.hip). Unlike the forward pass of the layer
 // there is no solve between the state and its readout, so nothing forces the chunk states through memory: one
 // workgroup walks a segment of a pair's chunks, as the state pass does, and produces the chunk's outputs on the way,
 //   y_c = zeta_c U_[n] q_c + sum_{s<=c} M[s,c] beta_s v_s (k_s . q_c)          (chunk-wise form, Section 4.2.1),
@@ -47,7 +47,7 @@ struct ReadoutShape {
     static constexpr size_t tab_bytes = 3 * kChunk * sizeof(float);   // per-token G, state weight, beta of the chunk
     static constexpr size_t lds_bytes = (q_elems + k_elems + v_elems) * 2 + p_frags * sizeof(frag) + tab_bytes;
     static constexpr size_t lds_bytes_qlo = lds_bytes + q_elems * 2;   // with the remainder of q as a second tile
-    static constexpr size_t lds_bytes_kvlo = lds_bytes + k_elems * 2;  // ... of k or v (square states: same size)
+    static constexpr size_t lds_bytes_klo = lds_bytes + k_elems * 2;   // ... of k
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -77,22 +77,22 @@ __device__ __forceinline__ float *summary_tile(const ReadoutArgs &a, int pair, i
 // Waves per SIMD a variant is compiled for: two (256 registers each), but one (512 registers, half of them
 // accumulation registers that the compiler uses as a second file) for the d = 128 variants with a second operand
 // tensor, whose prefetch registers do not fit beside the state otherwise (they spilled 20-37 registers to memory).
-constexpr int readout_waves_per_simd(int dk, bool summary, int qmode, int kvlo)
+constexpr int readout_waves_per_simd(int dk, bool summary, int qmode, bool klo)
 {
-    return (dk == 128 && !summary && (qmode == 1 || kvlo != 0)) ? 1 : 2;
+    return (dk == 128 && !summary && (qmode == 1 || klo)) ? 1 : 2;
 }
 
 // QMODE: 0 q in bf16; 1 q as bf16 value + bf16 remainder (q_lo); 2 q in float32, split into value + remainder here.
-// KVLO: 0 k and v as they are; 1 k comes with a remainder tensor (k_lo); 2 v does (v_lo). Not combined with QMODE != 0.
-template <int DK, int DV, bool GATED, bool SUMMARY, int QMODE, int KVLO = 0>
+// KLO: k comes with a remainder tensor (k_lo). Not combined with QMODE != 0.
+// DOT: y_t itself is not wanted, only dot_with_t . y_t (the backward pass's p_t . H_t x_t).
+template <int DK, int DV, bool GATED, bool SUMMARY, int QMODE, bool KLO = false, bool DOT = false>
 __global__ __launch_bounds__(DV * 2)
-    __attribute__((amdgpu_waves_per_eu(readout_waves_per_simd(DK, SUMMARY, QMODE, KVLO), readout_waves_per_simd(DK, SUMMARY, QMODE, KVLO))))
+    __attribute__((amdgpu_waves_per_eu(readout_waves_per_simd(DK, SUMMARY, QMODE, KLO), readout_waves_per_simd(DK, SUMMARY, QMODE, KLO))))
     void gla_readout_kernel(ReadoutArgs a)
 {
     typedef ReadoutShape<DK, DV> SH;
     constexpr bool QLO = QMODE != 0, QF32 = QMODE == 2;
-    constexpr bool KLO = KVLO == 1, VLO = KVLO == 2;
-    static_assert(KVLO == 0 || (QMODE == 0 && DK == DV), "remainders of k / v: square states, plain q");
+    static_assert(!KLO || (QMODE == 0 && DK == DV), "remainder of k: square states, plain q");
     // PRECISE: P and the weighted v rows enter their products as value + remainder, so that the outputs carry the
     // rounding of the tensors they are given and nothing else of that size: the gate gradient of the backward pass is
     // a long cumulative sum of differences of such outputs, and only errors common to all of them cancel in it
@@ -104,9 +104,10 @@ __global__ __launch_bounds__(DV * 2)
     uint16_t *sK = sQ + SH::q_elems;
     uint16_t *sV = sK + SH::k_elems;
     frag *sP = (frag *)(sV + SH::v_elems);
+    float *sDot = (float *)sP;                        // (DOT: [NB][64], in place of P)
     float *sG = (float *)(sP + SH::p_frags), *sW = sG + kChunk, *sB = sW + kChunk;
     uint16_t *sQ2 = (uint16_t *)(sB + kChunk);        // (QLO only)
-    uint16_t *sKV2 = sQ2;                             // (KVLO only: the remainder rows of k or v, laid out like them)
+    uint16_t *sK2 = sQ2;                              // (KLO only: the remainder rows of k, laid out like them)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -147,26 +148,16 @@ __global__ __launch_bounds__(DV * 2)
             }
             for (int sg = 0; sg < seg; ++sg) {
                 const float decay = exp2f(a.seg_logdecay[pair * a.n_segs + sg]);
-                if (DK == DV && a.seg_mode == 2) {
-                    // summaries of the transposed recurrence (k and v exchanged), left by the readout before this one:
-                    // U[32w + n][32jb + kidx(r, g)] is its element [32jb + kidx(r, g)][32w + n], i.e. tile (jb, w),
-                    // lane (kidx(r, g), g'), register r' with kidx(r', g') = n
-                    const float *t = summary_tile<DK, DV>(a, pair, sg, jb, w);
-                    const int gp = (n >> 2) & 1, rp = 4 * (n >> 3) + (n & 3);
+                const float *t = summary_tile<DK, DV>(a, pair, sg, w, jb);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[jb][r] = decay * acc[jb][r] + t[rp * 64 + 32 * gp + kidx(r, g)];
-                } else {
-                    const float *t = summary_tile<DK, DV>(a, pair, sg, w, jb);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[jb][r] = decay * acc[jb][r] + t[r * 64 + lane];
-                }
+                for (int r = 0; r < 16; ++r) acc[jb][r] = decay * acc[jb][r] + t[r * 64 + lane];
             }
         }
     }
 
     // ---- rows of a chunk: global -> registers (one chunk ahead) -> LDS
     struct Rows {
-        u32x4_t q[PQ], k[PK], v[PV], q2[QMODE == 1 ? PK : 1], kv2[KVLO != 0 ? PK : 1];
+        u32x4_t q[PQ], k[PK], v[PV], q2[QMODE == 1 ? PK : 1], k2[KLO ? PK : 1];
         float gate, beta;
     };
     auto fetch = [&](Rows &f, int c) {
@@ -178,7 +169,7 @@ __global__ __launch_bounds__(DV * 2)
             if (!SUMMARY && !QF32) f.q[i] = *(const u32x4_t *)((const uint16_t *)a.q + off);
             if (QMODE == 1) f.q2[i] = *(const u32x4_t *)((const uint16_t *)a.q_lo + off);
             f.k[i] = *(const u32x4_t *)((const uint16_t *)a.k + off);
-            if (KLO) f.kv2[i] = *(const u32x4_t *)((const uint16_t *)a.k_lo + off);
+            if (KLO) f.k2[i] = *(const u32x4_t *)((const uint16_t *)a.k_lo + off);
         }
         if (QF32) {
 #pragma unroll
@@ -195,7 +186,6 @@ __global__ __launch_bounds__(DV * 2)
             const int64_t off = base_v + (int64_t)tensor_token(c * kChunk + piece / (DV / 8)) * a.stride_t +
                                 8 * (piece % (DV / 8));
             f.v[i] = *(const u32x4_t *)((const uint16_t *)a.v + off);
-            if (VLO) f.kv2[i] = *(const u32x4_t *)((const uint16_t *)a.v_lo + off);
         }
         const int tau = min(c * kChunk + lane, a.T - 1);
         if (a.reverse) f.gate = tau == 0 ? 1.0f : a.gate[gate_base + (int64_t)(a.T - tau) * a.H];
@@ -211,7 +201,7 @@ __global__ __launch_bounds__(DV * 2)
             if (!SUMMARY && !QF32) *(u32x4_t *)(sQ + row * RSQ + col) = f.q[i];
             if (QMODE == 1) *(u32x4_t *)(sQ2 + row * RSQ + col) = f.q2[i];
             *(u32x4_t *)(sK + row * RSK + col) = f.k[i];
-            if (KLO) *(u32x4_t *)(sKV2 + row * RSK + col) = f.kv2[i];
+            if (KLO) *(u32x4_t *)(sK2 + row * RSK + col) = f.k2[i];
         }
         if (QF32) {
 #pragma unroll
@@ -231,7 +221,6 @@ __global__ __launch_bounds__(DV * 2)
             const int piece = i * NT + tid;
             const int row = piece / (DV / 8), col = 8 * (piece % (DV / 8));
             *(u32x4_t *)(sV + row * RSV + col) = f.v[i];
-            if (VLO) *(u32x4_t *)(sKV2 + row * RSV + col) = f.kv2[i];
         }
     };
 
@@ -257,17 +246,26 @@ __global__ __launch_bounds__(DV * 2)
             if (GATED) sB[lane] = bj;
         }
         if (c + 1 < chunk_end) fetch(rows, c + 1);
+        f32x4 dw[DOT ? 2 : 1][4];                  // dot_with at this lane's features 32 w + 8 q4 + 4 g of tokens 32 tb + n
+        if (DOT) {
+#pragma unroll
+            for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    dw[tb][q4] = *(const f32x4 *)(a.dot_with + base_v +
+                                                  (int64_t)tensor_token(c * kChunk + 32 * tb + n) * a.stride_t + 32 * w +
+                                                  4 * g + 8 * q4);
+        }
         lds_barrier();                             // (no wait for the rows in flight)
 
         // V^T fragments, tokens of step (sb, h2) in kidx order: runs at 32 sb + 16 h2 + 4 g and 8 further
-        frag vt[2][2], vt2[2][2];                  // (vt2: the remainder rows, VLO only)
+        frag vt[2][2];
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2) {
                 const int t0 = 32 * sb + 16 * h2 + 4 * g;
                 vt[sb][h2] = gather_transposed_bf16(sV, PaddedTile{RSV}, 32 * w + sub16, lane, t0, t0 + 8);
-                if (VLO) vt2[sb][h2] = gather_transposed_bf16(sKV2, PaddedTile{RSV}, 32 * w + sub16, lane, t0, t0 + 8);
             }
 
         if (!SUMMARY) {
@@ -283,7 +281,7 @@ __global__ __launch_bounds__(DV * 2)
                     const frag kf = row_runs(krow, 16 * st + 4 * g);
                     pacc = MMA::mma(kf, row_runs(qrow, 16 * st + 4 * g), pacc);
                     if (KLO)
-                        pacc = MMA::mma(row_runs(sKV2 + (32 * sb + n) * RSK, 16 * st + 4 * g),
+                        pacc = MMA::mma(row_runs(sK2 + (32 * sb + n) * RSK, 16 * st + 4 * g),
                                         row_runs(qrow, 16 * st + 4 * g), pacc);
                     if (QLO) pacc = MMA::mma(kf, row_runs(sQ2 + (32 * tb + n) * RSQ, 16 * st + 4 * g), pacc);
                 }
@@ -356,10 +354,29 @@ __global__ __launch_bounds__(DV * 2)
                 for (int h2 = 0; h2 < 2; ++h2) {
                     y[tb] = MMA::mma(vt[sb][h2], sP[(tile * 2 + h2) * 64 + lane], y[tb]);
                     if (PRECISE) y[tb] = MMA::mma(vt[sb][h2], sP[(6 + tile * 2 + h2) * 64 + lane], y[tb]);
-                    if (VLO) y[tb] = MMA::mma(vt2[sb][h2], sP[(tile * 2 + h2) * 64 + lane], y[tb]);
+                }
+            }
+            if constexpr (DOT) {
+                lds_barrier();                     // P has been read
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) {
+                    float dot = 0.0f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) dot += dw[tb][r >> 2][r & 3] * y[tb][r];
+                    dot += __shfl_xor(dot, 32, 64);
+                    if (g == 0) sDot[w * kChunk + 32 * tb + n] = dot;
+                }
+                lds_barrier();
+                const int tau = c * kChunk + lane;
+                if (w == 0 && tau < a.T) {
+                    float dot = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) dot += sDot[i * kChunk + lane];
+                    a.dot_out[gate_base + (int64_t)tensor_token(tau) * a.H] = dot;
                 }
             }
             // ---- store: lane (n, g) holds features 32 w + kidx(r, g) of token 32 tb + n
+            if constexpr (!DOT) {
 #pragma unroll
             for (int tb = 0; tb < 2; ++tb) {
                 const int tau = c * kChunk + 32 * tb + n;
@@ -376,6 +393,7 @@ __global__ __launch_bounds__(DV * 2)
                     }
                 }
             }
+            }
         }
 
         // ---- U <- zeta_C U + sum_s w_s v_s k_s^T: tile jb gets K^T (block jb) times the weighted V^T fragments
@@ -386,12 +404,6 @@ __global__ __launch_bounds__(DV * 2)
             for (int h2 = 0; h2 < 2; ++h2) {
                 float x[8];
                 MMA::unpack(vt[sb][h2], x);
-                if (VLO) {
-                    float x2[8];
-                    MMA::unpack(vt2[sb][h2], x2);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] += x2[e];
-                }
                 const int t0 = 32 * sb + 16 * h2 + 4 * g;
                 const f32x4 w0 = *(const f32x4 *)(sW + t0), w1 = *(const f32x4 *)(sW + t0 + 8);
 #pragma unroll
@@ -421,7 +433,7 @@ __global__ __launch_bounds__(DV * 2)
                     acc[jb] = MMA::mma(kt, vw[sb][h2], acc[jb]);
                     if (PRECISE) acc[jb] = MMA::mma(kt, vwlo[sb][h2], acc[jb]);
                     if (KLO)
-                        acc[jb] = MMA::mma(gather_transposed_bf16(sKV2, PaddedTile{RSK}, 32 * jb + sub16, lane, t0, t0 + 8),
+                        acc[jb] = MMA::mma(gather_transposed_bf16(sK2, PaddedTile{RSK}, 32 * jb + sub16, lane, t0, t0 + 8),
                                            vw[sb][h2], acc[jb]);
                 }
         }
@@ -448,31 +460,31 @@ __global__ __launch_bounds__(DV * 2)
     }
 }
 
-template <int DK, int DV, bool GATED, int QMODE, int KVLO = 0>
+template <int DK, int DV, bool GATED, int QMODE, bool KLO = false, bool DOT = false>
 static hipError_t launch_readout_d(const ReadoutArgs &a0, hipStream_t stream)
 {
     typedef ReadoutShape<DK, DV> SH;
     ReadoutArgs a = a0;
-    constexpr size_t lds_sum = KVLO != 0 ? SH::lds_bytes_kvlo : SH::lds_bytes;
+    constexpr size_t lds_sum = KLO ? SH::lds_bytes_klo : SH::lds_bytes;
     constexpr size_t lds_main = QMODE != 0 ? SH::lds_bytes_qlo : lds_sum;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, false, QMODE, KVLO>,
+        hipError_t e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, false, QMODE, KLO, DOT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_main);
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, true, 0, KVLO>,
+        e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, true, 0, KLO>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_sum);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     if (a.n_segs > 1 && a.seg_mode == 0) {
         // summaries of every segment but the last, each from a zero state
-        hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, true, 0, KVLO>), dim3(a.n_pairs * (a.n_segs - 1)),
+        hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, true, 0, KLO>), dim3(a.n_pairs * (a.n_segs - 1)),
                            dim3(SH::NT), lds_sum, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, false, QMODE, KVLO>), dim3(a.n_pairs * a.n_segs), dim3(SH::NT),
+    hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, false, QMODE, KLO, DOT>), dim3(a.n_pairs * a.n_segs), dim3(SH::NT),
                        lds_main, stream, a);
     return hipGetLastError();
 }
@@ -480,10 +492,14 @@ static hipError_t launch_readout_d(const ReadoutArgs &a0, hipStream_t stream)
 template <int D>
 static hipError_t launch_readout_square(const ReadoutArgs &a, hipStream_t stream)
 {
-    if (a.k_lo || a.v_lo) {
-        // (the reverse recurrences of the backward pass: no write gate inside them)
-        if (a.q_lo || a.beta || (a.k_lo && a.v_lo)) return hipErrorInvalidValue;
-        return a.k_lo ? launch_readout_d<D, D, false, 0, 1>(a, stream) : launch_readout_d<D, D, false, 0, 2>(a, stream);
+    if (a.k_lo) {
+        // (a reverse recurrence of the backward pass: no write gate inside it)
+        if (a.q_lo || a.beta) return hipErrorInvalidValue;
+        return launch_readout_d<D, D, false, 0, true>(a, stream);
+    }
+    if (a.dot_with) {
+        if (!a.q_lo) return hipErrorInvalidValue;
+        return a.beta ? launch_readout_d<D, D, true, 1, false, true>(a, stream) : launch_readout_d<D, D, false, 1, false, true>(a, stream);
     }
     if (a.q_lo)
         return a.beta ? launch_readout_d<D, D, true, 1>(a, stream) : launch_readout_d<D, D, false, 1>(a, stream);
@@ -493,7 +509,7 @@ static hipError_t launch_readout_square(const ReadoutArgs &a, hipStream_t stream
 hipError_t launch_gla_readout(const ReadoutArgs &a, int dk, int dv, hipStream_t stream)
 {
     if (a.q_is_f32) {                          // the sketched readout: float32 q, 64 or 32 sketched features, full v
-        if ((dk != 64 && dk != 32) || dv != 128 || a.q_lo || a.k_lo || a.v_lo) return hipErrorInvalidValue;
+        if ((dk != 64 && dk != 32) || dv != 128 || a.q_lo || a.k_lo) return hipErrorInvalidValue;
         if (dk == 32)
             return a.beta ? launch_readout_d<32, 128, true, 2>(a, stream) : launch_readout_d<32, 128, false, 2>(a, stream);
         return a.beta ? launch_readout_d<64, 128, true, 2>(a, stream) : launch_readout_d<64, 128, false, 2>(a, stream);

@@ -61,10 +61,13 @@ __device__ __forceinline__ float sum_kg(float x)
     return x + __shfl_xor(x, 32, 64);
 }
 
-template <class IO, int D, int TT, bool GATED>
+// MODE as in gka_chunk_solve.hip: 0 plain, 1 (GATED) with the layer's variants, 2 (DUAL) solve only for two right-hand
+// sides one after the other (the backward pass).
+template <class IO, int D, int TT, int MODE>
 __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
 {
     typedef SolveF32Shape<D, TT> SH;
+    constexpr bool GATED = MODE != 0, DUAL = MODE == 2;
     constexpr int NW = SH::NW, NTHR = SH::NTHR, RT = SH::RT, KS = SH::KS, TB = SH::TB, MAXU = SH::MAXU;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     f32x4 *sK = (f32x4 *)smem;                         // k rows (later v rows) of the chunk, [64][D]
@@ -94,7 +97,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
     const int tok0 = chunk * kChunk;
     if (tok0 + 16 * TT * tb >= a.T) return;            // (whole workgroup) only padding
     const int JT = TT * (tb + 1);                      // key tiles in sight
-    const bool solve = !(GATED && a.readout_only);
+    const bool solve = !(GATED && !DUAL && a.readout_only);
     const bool stated = chunk > 0 || a.init_states;    // else H_[n] = U_[n] = 0: nothing to read or multiply
 
     // ---------------- requests: gates, k rows, state rows, q ----------------
@@ -155,12 +158,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                qv[rt][tt] = load_q(a.q, rt, tt);
-                if constexpr (GATED) {
-                    if (a.q_lo) qv[rt][tt] += load_q(a.q_lo, rt, tt);
-                }
-            }
+            for (int tt = 0; tt < TT; ++tt) qv[rt][tt] = load_q(a.q, rt, tt);
     };
     if constexpr (D != 256) load_rhs();                // (d = 256: the norm needs the registers)
     float hn2 = 0.0f;
@@ -367,6 +365,16 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
                 }
         }
     };
+    for (int rhs = 0; rhs < (DUAL ? 2 : 1); ++rhs) {
+    if (DUAL && rhs == 1) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                qv[rt][tt] = load_q(a.q2, rt, tt) + load_q(a.q2_lo, rt, tt);
+                omega[tt] = 2.0f;
+            }
+    }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -396,17 +404,19 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
                 }
         }
     }
-
-    // ---------------- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c) ----------------
     if (GATED && a.xhat_out) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
                 if (valid[tt])
-                    *(f32x4 *)(a.xhat_out + (gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H) * D + 16 * (RT * w + rt) +
+                    *(f32x4 *)((DUAL && rhs == 1 ? a.xhat2_out : a.xhat_out) + (gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H) * D + 16 * (RT * w + rt) +
                                4 * kg) = xi[rt][tt];
     }
+    }                                                  // (right-hand sides)
+    if constexpr (DUAL) return;
+
+    // ---------------- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c) ----------------
     if (GATED && a.solve_only) return;                 // (whole workgroup)
     load_state(a.ws_U);
     load_rows(a.v);
@@ -442,18 +452,18 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
                 IO::store4(a.o, tok_off[tt] + 16 * rt, gS[rt][tt][0], gS[rt][tt][1], gS[rt][tt][2], gS[rt][tt][3]);
 }
 
-template <class IO, int D, int TT, bool GATED>
+template <class IO, int D, int TT, int MODE>
 __global__ __launch_bounds__((SolveF32Shape<D, TT>::NTHR)) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void
 solve_f32_kernel(SolveArgs a)
 {
-    solve_f32_body<IO, D, TT, GATED>(a);
+    solve_f32_body<IO, D, TT, MODE>(a);
 }
 
-template <class IO, int D, int TT, bool GATED>
+template <class IO, int D, int TT, int MODE>
 static hipError_t launch_solve_f32_t(const SolveArgs &a, hipStream_t stream)
 {
     typedef SolveF32Shape<D, TT> SH;
-    auto kern = solve_f32_kernel<IO, D, TT, GATED>;
+    auto kern = solve_f32_kernel<IO, D, TT, MODE>;
     // (set once per kernel instantiation and device, not per launch)
     static bool attr_set_on[64] = {};
     int dev = 0;
@@ -468,7 +478,7 @@ static hipError_t launch_solve_f32_t(const SolveArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <class IO, int D, bool GATED>
+template <class IO, int D, int MODE>
 static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
 {
     // Tokens per workgroup (16 TT): small workgroups spread a small problem over the chip, large ones repeat less of the
@@ -477,15 +487,18 @@ static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
     // 1024 chunks 472 / 436; d = 256: 20 chunks 119 / 181, 88 chunks 210 / 209, 160 chunks 240 / 227, 512 chunks 834 / 724.
     // (TT = 4 at d = 128, 1024 chunks: 460; at d = 256 the state rows leave no registers for it.)
     const int64_t chunks = (int64_t)a.n_pairs * a.n_chunks;
-    if (chunks <= (D == 256 ? 96 : 192)) return launch_solve_f32_t<IO, D, 1, GATED>(a, stream);
-    return launch_solve_f32_t<IO, D, 2, GATED>(a, stream);
+    if (chunks <= (D == 256 ? 96 : 192)) return launch_solve_f32_t<IO, D, 1, MODE>(a, stream);
+    return launch_solve_f32_t<IO, D, 2, MODE>(a, stream);
 }
 
 template <class IO, int D>
 static hipError_t launch_solve_f32_g(const SolveArgs &a, hipStream_t stream)
 {
-    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_solve_f32_d<IO, D, true>(a, stream);
-    return launch_solve_f32_d<IO, D, false>(a, stream);
+    if constexpr (D != 256) {
+        if (a.q2) return launch_solve_f32_d<IO, D, 2>(a, stream);
+    }
+    if (a.beta || a.alpha || !a.lambda || a.xhat_out) return launch_solve_f32_d<IO, D, 1>(a, stream);
+    return launch_solve_f32_d<IO, D, 0>(a, stream);
 }
 
 hipError_t launch_solve_f32(const SolveArgs &a, int d, bool io_bf16, hipStream_t stream)
