@@ -140,6 +140,17 @@ __device__ __forceinline__ bf16x8 gather_transposed_bf16(const uint16_t *tile, L
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// One such run of four tokens (t0 .. t0+3) at the lane's column of a 16-column tile, as raw bits.
+template <class Layout>
+__device__ __forceinline__ u16x4 transposed_run(const uint16_t *tile, Layout at, int lane, int t0)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const int i = lane & 15;
+    return __builtin_bit_cast(u16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (lds_s16x4 *)(tile + at(t0 + (i >> 2), 4 * (i & 3)))));
+}
+
 // The same two transpose reads written as assembly, including the wait for their data. The compiler orders every
 // LDS read it knows of behind all copies into LDS (below) that are in flight, whichever part of LDS they fill; a
 // read it does not see is not held back. For tiles that no copy in flight writes to.

@@ -3,22 +3,22 @@
 //     and the readout y_t = U_t xhat_t;
 //   * the solve of latent sketching (appendix "Latent Sketching for Approximate Solutions") in d_s <= 32 sketched
 //     dimensions, z_t = CH(S H_t S^T + lambda_t I, S q_t, r), on the sketched keys and queries (no values, no readout).
-// At these sizes a state is a 32 x 32 matrix (zero beyond d): one pair of accumulator tiles of the 16x16x32 matrix
-// instruction, and a contraction over the features is a single 32-deep step. Every operand of a pass of Algorithm 1
-// then lives in registers: a pass touches no memory at all. Three launches:
+// At these sizes a state is one or four accumulator tiles of the matrix instructions, and a contraction over the features
+// a single step. Every operand of a pass of Algorithm 1 then lives in registers: a pass touches no memory at all.
+//   small_walk_kernel: a wave walks the sequence of a (batch, head) pair, or a segment of it, 16 tokens at a time with the
+//      states in registers; the 16 tokens sit on the output lanes of the products (per-token scalars are per-lane
+//      scalars): chunk-wise Frobenius norm, all passes in residual form, the readout, then the states after the tile.
+// Where pairs are few and sequences long, two launches before it compute the states before every chunk of 64 tokens:
 //   1. small_chunk_delta_kernel: per chunk, Delta H = sum_j w_j k_j k_j^T and Delta U = sum_j w_j v_j k_j^T (w_j: decay
 //      from token j to the chunk's end, times the write gate) and the chunk's log2 decay; one wave per chunk.
 //   2. small_state_scan_kernel: per pair, the states before every chunk, S_[n+1] = zeta_n S_[n] + Delta_n (elementwise
 //      in float32, one float4 per thread and state, sixteen chunks in flight), from the caller's initial states if
 //      given; the states after the last chunk are the final states.
-//   3. small_solve_kernel: per chunk one workgroup of four waves, wave w = the 16 tokens 16 w .. 16 w + 15 on the
-//      output lanes of the products (per-token scalars are per-lane scalars, the iterate stays in registers):
-//      chunk-wise Frobenius norm, all passes of Algorithm 1 in residual form, then the readout.
-// The arithmetic of 3 is that of the 128-dimensional kernels: the token's system is taken divided by its zeta_c,
+// The arithmetic of the walk is that of the 128-dimensional kernels: the token's system is taken divided by its zeta_c,
 //   g / zeta_c = H_[n] xi + K^T ((M / zeta_c) o (K xi)) - q / zeta_c,
 //   delta' = (omega - 1) delta - omega s0 (zeta_c (g / zeta_c) + lambda xi'),  xi' = xi + delta,
-// with bf16 operands (H_[n], K, the update delta, the masked products) and float32 accumulation; in the readout
-// U_[n] and xhat enter as bf16 value + remainder.
+// with bf16 operands (K, the update delta, the masked products; H_[n] as value + remainder) and float32 accumulation; in
+// the readout U_[n] and xhat enter as bf16 value + remainder.
 //
 // Fragment conventions (v_mfma_f32_16x16x32_bf16, lane l = 16 kg + n): an accumulator tile holds rows 4 kg + r
 // (r = 0..3) of column n; an operand fragment holds eight contraction values of row (A) or column (B) n. Two
@@ -31,9 +31,25 @@ namespace gka {
 
 namespace {
 
-constexpr int kDs = 32;                    // features a fragment covers (rows of 16 features: the upper half is zero)
-constexpr int kRow = 40;                   // LDS row of a key in 2-byte elements: 64 B of features + 16 B of padding
+constexpr int kDs = 32;                    // features of a sketched row that are computed
+constexpr int kRowPad = 8;                 // padding of an LDS row of keys or values, 2-byte elements
 constexpr float kMinZeta = 0x1p-60f;       // floor of zeta_c where the system is divided by it
+// How the walks are cut (us per forward pass, bf16, r = 10):
+// * One walk per pair, without the two launches that compute the states before every chunk: with many pairs, which fill
+//   the SIMDs (d = 16, 6144 pairs x 197 tokens 98 against 140 chunk by chunk, 2400 x 400 98 and 98, 1200 x 785 143 and 96;
+//   d = 32, 3072 x 300 137 and 240, 1200 x 785 235 and 252, 768 x 785 162 and 150), and with up to two chunks (d = 16,
+//   768 x 128: 20 against 27).
+// * At most kFewChunks chunks in all leave SIMDs empty: a wave per tile, which advances the states over the tiles between
+//   the last known ones and its own (a sixth of the work of solving them; d = 16, 24 x 128: 9 against 18 with a wave per
+//   chunk). A short sequence is then walked from its start, too, while the waves are few (24 x 197: 11 against 17; d = 16,
+//   192 x 250, 768 chunks: 22 against 18.5; d = 32: 27.5 and 29).
+template <int D>
+struct WalkRule {
+    static constexpr int many_pairs = D == 16 ? 2048 : 1024;
+    static constexpr int short_chunks = 2;
+    static constexpr int few_walk_chunks = D == 16 ? 5 : 4, few_walk_units = D == 16 ? 512 : 1024;
+};
+constexpr int kFewChunks = 1024;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c)
@@ -67,45 +83,44 @@ __device__ __forceinline__ void split8(f32x4 lo, f32x4 hi, bf16x8 &val, bf16x8 &
     unpack8(val, bl, bh);
     rem = pack8(lo - bl, hi - bh);
 }
+// sum over the four lanes that share n: rows of 16 lanes are exchanged in the register file (as shuffles they would be
+// two LDS round trips)
 __device__ __forceinline__ float sum_over_kg(float x)
 {
-    x += __shfl_xor(x, 16, 64);
-    x += __shfl_xor(x, 32, 64);
-    return x;
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// the 32 features of one row (of 2-byte elements) in slot order, for the lane's kg; of a row that holds only 16
-// features the upper half reads as zero
-__device__ __forceinline__ bf16x8 row_in_slot_order(const uint16_t *row, int kg, bool upper = true)
+// The lane's number, formed anew wherever it is asked for: values derived from it are then not kept (or spilled)
+// across the code in between.
+__device__ __forceinline__ int fresh_lane()
 {
-    const u16x4 lo = *(const u16x4 *)(row + 4 * kg);
-    u16x4 hi = {0, 0, 0, 0};
-    if (upper) hi = *(const u16x4 *)(row + 16 + 4 * kg);
-    const u16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-}
-// feature `col` of the eight keys 32 ks + (slot order) of an LDS tile of rows
-__device__ __forceinline__ bf16x8 keys_in_slot_order(const uint16_t *rows, int ks, int kg, int col)
-{
-    u16x8 v;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = rows[(32 * ks + 16 * (s >> 2) + 4 * kg + (s & 3)) * kRow + col];
-    return __builtin_bit_cast(bf16x8, v);
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
 }
 __device__ __forceinline__ int64_t row_offset(const SmallArgs &a, int b, int h, int tok)
 {
     return b * a.stride_b + (int64_t)min(tok, a.T - 1) * a.stride_t + h * a.stride_h;
 }
-// The chunk's 64 rows of x (first 32 features; zeros from feature a.d on) into an LDS tile: 256 pieces of 16 bytes,
-// `n_threads` at work. Rows past the end of the sequence repeat the last one (finite values that only meet zero
-// weights and masked products).
-__device__ __forceinline__ void stage_rows(const SmallArgs &a, const void *x, uint16_t *rows, int b, int h, int tok0, int t,
-                                           int n_threads)
+// The chunk's 64 rows of x into a wave's LDS tile, 16 bytes at a time. Rows past the end of the sequence repeat the last
+// one (finite values that only meet zero weights).
+template <int D>
+__device__ __forceinline__ void stage_rows(const SmallArgs &a, const void *x, uint16_t *rows, int b, int h, int tok0,
+                                           int lane)
 {
-    for (int piece = t; piece < 256; piece += n_threads) {
-        const int row = piece >> 2, part = piece & 3;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (8 * part < a.d) v = *(const u32x4 *)((const uint16_t *)x + row_offset(a, b, h, tok0 + row) + 8 * part);
-        *(u32x4 *)(rows + row * kRow + 8 * part) = v;
+    constexpr int PPR = D / 8;                 // pieces of 16 bytes per row
+    u32x4 v[PPR];
+#pragma unroll
+    for (int i = 0; i < PPR; ++i) {
+        const int piece = i * 64 + lane;
+        v[i] = *(const u32x4 *)((const uint16_t *)x + row_offset(a, b, h, tok0 + piece / PPR) + 8 * (piece % PPR));
+    }
+#pragma unroll
+    for (int i = 0; i < PPR; ++i) {
+        const int piece = i * 64 + lane;
+        *(u32x4 *)(rows + (piece / PPR) * (D + kRowPad) + 8 * (piece % PPR)) = v[i];
     }
 }
 
@@ -120,9 +135,9 @@ template <bool WITH_U, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void small_chunk_delta_kernel(SmallArgs a)
 {
     constexpr int NF = D / 16;                 // feature tiles that exist; a state is stored as D x D
-
-    __shared__ __attribute__((aligned(16))) uint16_t s_k[4][64 * kRow];
-    __shared__ __attribute__((aligned(16))) uint16_t s_v[WITH_U ? 4 : 1][WITH_U ? 64 * kRow : 8];
+    const PaddedRows at = {D + kRowPad};
+    __shared__ __attribute__((aligned(16))) uint16_t s_k[4][64 * (D + kRowPad)];
+    __shared__ __attribute__((aligned(16))) uint16_t s_v[WITH_U ? 4 : 1][WITH_U ? 64 * (D + kRowPad) : 8];
     __shared__ __attribute__((aligned(16))) float s_w[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int n = lane & 15, kg = lane >> 4;
@@ -133,8 +148,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     const int pair = (int)(unit % a.n_pairs), chunk = (int)(unit / a.n_pairs);
     const int b = pair / a.H, h = pair % a.H;
     const int tok0 = chunk * kChunk;
-    stage_rows(a, a.k, s_k[w], b, h, tok0, lane, 64);
-    if constexpr (WITH_U) stage_rows(a, a.v, s_v[w], b, h, tok0, lane, 64);
+    stage_rows<D>(a, a.k, s_k[w], b, h, tok0, lane);
+    if constexpr (WITH_U) stage_rows<D>(a, a.v, s_v[w], b, h, tok0, lane);
     const bool valid = tok0 + lane < a.T;
     const int64_t gi = (b * (int64_t)a.T + min(tok0 + lane, a.T - 1)) * a.H + h;
     const float G = wave_inclusive_scan(valid ? log2_gate(a.gate[gi]) : 0.0f, lane);
@@ -150,11 +165,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             f32x4 lo, hi;
-            kt[f] = keys_in_slot_order(s_k[w], ks, kg, 16 * f + n);
+            kt[f] = gather_transposed_bf16(s_k[w], at, 16 * f, lane, 32 * ks + 4 * kg, 32 * ks + 16 + 4 * kg);
             unpack8(kt[f], lo, hi);
             wk[f] = pack8(lo * w0, hi * w1);
             if constexpr (WITH_U) {
-                unpack8(keys_in_slot_order(s_v[w], ks, kg, 16 * f + n), lo, hi);
+                unpack8(gather_transposed_bf16(s_v[w], at, 16 * f, lane, 32 * ks + 4 * kg, 32 * ks + 16 + 4 * kg), lo,
+                        hi);
                 wv[f] = pack8(lo * w0, hi * w1);
             }
         }
@@ -221,273 +237,368 @@ __global__ __launch_bounds__(D * D / 4) void small_state_scan_kernel(SmallArgs a
     if (WITH_U && a.U_final) *(f32x4 *)(a.U_final + ext) = U;
 }
 
-// ---- 3. solve and readout ----------------------------------------------------------------------------------------
+// ---- 3. walk: solve and readout ----------------------------------------------------------------------------------
 namespace {
 
-// What a wave fetches from global memory before the workgroup's first barrier (the rows are on their way then).
-struct TileInputs {
-    f32x4 h[2][2];             // the state before the chunk: rows 16 fo + n, columns 4 kg .. and 16 + 4 kg ..
-    bf16x8 qB;                 // the query of this lane's token as a B fragment
-    float lam;                 // lambda of this lane's token (if given)
-    int64_t ti;                // index of the token into [B,T,H]
-    int64_t row;               // offset of its row in q, k, v, o
-    bool valid;
+// The per-token inputs of a tile as a lane (n, kg) holds them: token n of the tile, features 4 kg .. of each block of 16.
+template <bool WITH_U, int NF>
+struct TileRows {
+    u16x4 k[NF], q[NF], v[WITH_U ? NF : 1];
+    float gate, lam, beta, alpha;
 };
-// rows 16 fo + n of a D x D float32 state as the two runs of four columns a lane holds of them (zero beyond D)
-template <int D>
-__device__ __forceinline__ void state_row_runs(const float *S, int fo, int n, int kg, f32x4 &lo, f32x4 &hi)
+// Wave-uniform bases and 32-bit lane offsets (a row of the tile is at most 15 stride_t away).
+template <bool WITH_U, int NF>
+__device__ __forceinline__ TileRows<WITH_U, NF> fetch_tile(const SmallArgs &a, int b, int h, int tile, int n, int kg)
 {
-    const float *row = S + (16 * fo + n) * D;
-    lo = *(const f32x4 *)(row + 4 * kg);
-    hi = zero4();
-    if constexpr (D > 16) hi = *(const f32x4 *)(row + 16 + 4 * kg);
-}
-template <int D>
-__device__ __forceinline__ TileInputs fetch_tile_inputs(const SmallArgs &a, int pair, int chunk, int w, int lane)
-{
-    const int n = lane & 15, kg = lane >> 4;
-    const int b = pair / a.H, h = pair % a.H;
-    const int tok = chunk * kChunk + 16 * w + n;
-    TileInputs in;
-    in.valid = tok < a.T;
-    in.ti = (b * (int64_t)a.T + min(tok, a.T - 1)) * a.H + h;
-    in.row = row_offset(a, b, h, tok);
-    const float *Hn = a.sH + (pair * (int64_t)a.n_chunks + chunk) * (D * D);
+    TileRows<WITH_U, NF> in;
+    const int64_t base = b * a.stride_b + 16 * (int64_t)tile * a.stride_t + h * a.stride_h;
+    const int64_t ti = (b * (int64_t)a.T + 16 * tile) * a.H + h;
+    const uint32_t i = min(n, a.T - 1 - 16 * tile);          // (rows past the end repeat the last one)
+    const uint32_t at = 2 * (i * (uint32_t)a.stride_t + 4 * kg), at_t = 4 * (i * (uint32_t)a.H);     // bytes
 #pragma unroll
-    for (int fo = 0; fo < D / 16; ++fo) state_row_runs<D>(Hn, fo, n, kg, in.h[fo][0], in.h[fo][1]);
-    in.qB = row_in_slot_order((const uint16_t *)a.q + in.row, kg, D > 16);
-    in.lam = a.lambda ? a.lambda[in.ti] : 0.0f;
+    for (int f = 0; f < NF; ++f) {
+        in.k[f] = *(const u16x4 *)((const char *)((const uint16_t *)a.k + base + 16 * f) + at);
+        in.q[f] = *(const u16x4 *)((const char *)((const uint16_t *)a.q + base + 16 * f) + at);
+        if constexpr (WITH_U) in.v[f] = *(const u16x4 *)((const char *)((const uint16_t *)a.v + base + 16 * f) + at);
+    }
+    in.gate = *(const float *)((const char *)(a.gate + ti) + at_t);
+    in.lam = a.lambda ? *(const float *)((const char *)(a.lambda + ti) + at_t) : 0.0f;
+    in.beta = a.beta ? *(const float *)((const char *)(a.beta + ti) + at_t) : 1.0f;
+    in.alpha = WITH_U && a.alpha ? *(const float *)((const char *)(a.alpha + ti) + at_t) : 1.0f;
     return in;
 }
 
-// The work of the wave that owns token tile TT of the chunk: key tiles 0 .. TT are visible to it.
-template <int TT, bool WITH_U, int D>
-__device__ __forceinline__ void small_solve_tile(const SmallArgs &a, const TileInputs &in, const uint16_t *rows,
-                                                 const uint16_t *vrows, const float *Gtab, const float *Btab, float *Wtab,
-                                                 int64_t unit, int lane)
+// fragment halves: a fragment of 32 contraction values is two runs of four per lane
+__device__ __forceinline__ bf16x8 join(u16x4 lo, u16x4 hi)
 {
-    constexpr int NJ = TT + 1;                 // key tiles
-    constexpr int NKS = (TT + 2) / 2;          // steps of 32 keys in the products over keys
-    constexpr int NF = D / 16;                 // feature tiles that exist (the second half of a fragment is zero at 16)
-    const int n = lane & 15, kg = lane >> 4;
-    const int c_local = 16 * TT + n;
-    const bool valid = in.valid;
-    const int64_t ti = in.ti;
-
-    // ---- operands
-    // the state before the chunk, rows as A fragments, and its squared norm
-    bf16x8 Hf[NF];
-    float hn2 = 0.0f;
-#pragma unroll
-    for (int fo = 0; fo < NF; ++fo) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hn2 += in.h[fo][0][e] * in.h[fo][0][e] + in.h[fo][1][e] * in.h[fo][1][e];
-        Hf[fo] = pack8(in.h[fo][0], in.h[fo][1]);
-    }
-    hn2 = wave_sum(hn2);
-    const bf16x8 qB = in.qB;
-    // decay mask of Section 4.2.1 (log-space form of Appendix B.2, base 2) with the write gate folded in:
-    // m[j,c] = 2^(G_c - G_j) beta_j for j <= c; lane element (js, r) <-> key j = 16 js + 4 kg + r
-    const float Gc = Gtab[c_local];
-    float zeta = exp2f(Gc);
-    const float beta_c = Btab[c_local];
-    f32x4 mreg[NJ];
-#pragma unroll
-    for (int js = 0; js < NJ; ++js) {
-        const f32x4 Gj = *(const f32x4 *)(Gtab + 16 * js + 4 * kg), bj = *(const f32x4 *)(Btab + 16 * js + 4 * kg);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 16 * js + 4 * kg + r;
-            // hardware exp2: decays under 2^-126 are flushed to zero
-            mreg[js][r] = (j <= c_local) ? __builtin_amdgcn_exp2f(Gc - Gj[r]) * bj[r] : 0.0f;
-        }
-    }
-    // keys: rows as A fragments (products K x), columns as A fragments (products K^T p), this lane's own key as B
-    bf16x8 kA[NJ], kT[NF][NKS];
-#pragma unroll
-    for (int js = 0; js < NJ; ++js) kA[js] = row_in_slot_order(rows + (16 * js + n) * kRow, kg);
-#pragma unroll
-    for (int fo = 0; fo < NF; ++fo)
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) kT[fo][ks] = keys_in_slot_order(rows, ks, kg, 16 * fo + n);
-    const bf16x8 kB = kA[TT];                  // (row 16 TT + n: the same fragment read as a column of the B operand)
-
-    // ---- chunk-wise Frobenius norm (Section 4.2.1, the double sum folded by M[i,c] M[j,c] = M[j,c]^2 M[i,j]):
-    //   ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} m[j,c]^2 w_j,
-    //   w_j = 2 (zeta_j k_j^T H_[n] k_j + sum_{i<j} m[i,j] G_ij^2) / beta_j + G_jj^2   (G = K K^T; w_j = 0 for beta_j = 0)
-    {
-        f32x4 kc[2];
-        unpack8(kB, kc[0], kc[1]);
-        float a_part = 0.0f;
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo) {
-            const f32x4 hk = mma16(Hf[fo], kB, zero4());
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a_part += hk[r] * kc[fo][r];
-        }
-        float b_part = 0.0f, d_part = 0.0f;
-#pragma unroll
-        for (int js = 0; js < NJ; ++js) {
-            const f32x4 G = mma16(kA[js], kB, zero4());
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                b_part += mreg[js][r] * (G[r] * G[r]);
-                if (js == TT && 4 * kg + r == n) d_part = G[r] * G[r];
-            }
-        }
-        a_part = sum_over_kg(a_part);
-        b_part = sum_over_kg(b_part);
-        d_part = sum_over_kg(d_part);
-        b_part -= beta_c * d_part;             // the sum runs over i < c: the diagonal term (m[c,c] = beta_c) is taken out
-        const float wc = beta_c > 0.0f ? 2.0f * (zeta * a_part + b_part) / beta_c + d_part : 0.0f;
-        if (kg == 0) Wtab[c_local] = wc;
-    }
-    __syncthreads();                           // every wave of the workgroup comes through here, whatever its TT
-    float fro;
-    {
-        float f = 0.0f;
-#pragma unroll
-        for (int js = 0; js < NJ; ++js) {
-            const f32x4 wv = *(const f32x4 *)(Wtab + 16 * js + 4 * kg);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) f += mreg[js][r] * mreg[js][r] * wv[r];
-        }
-        f = sum_over_kg(f);
-        fro = sqrtf(fmaxf(zeta * zeta * hn2 + f, 0.0f));
-    }
-    if (a.fro_out && valid && kg == 0) a.fro_out[ti] = fro;
-    float lam = a.lambda ? in.lam : a.lambda_scale * fro;                // Section 4.1: lambda_t = a ||H_t||_F
-    if (!valid) lam = 1.0f;
-
-    // ---- Algorithm 1 in residual form; Section 4.1: L = ||H_t||_F + lambda_t, mu = lambda_t
-    const float L = fro + lam, mu = lam;
-    const float rcp = __builtin_amdgcn_rcpf(L + mu);
-    const float s0 = 2.0f * rcp;
-    const float rho = (L - mu) * rcp, rho2 = rho * rho;
-    zeta = fmaxf(zeta, kMinZeta);
-    const float rz = 1.0f / zeta;
-#pragma unroll
-    for (int js = 0; js < NJ; ++js) mreg[js] *= rz;
-    f32x4 xi[NF], dl[NF], gn[NF];
-    {
-        f32x4 qv[2];
-        unpack8(qB, qv[0], qv[1]);
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float qe = valid ? qv[fo][r] : 0.0f;
-                xi[fo][r] = 0.0f;
-                dl[fo][r] = s0 * qe;
-                gn[fo][r] = -qe * rz;
-            }
-    }
-    float omega = 2.0f;
-    for (int it = 0; it < a.n_iter; ++it) {
-        omega = 4.0f * __builtin_amdgcn_rcpf(4.0f - rho2 * omega);      // weight schedule
-        const float cm = omega - 1.0f, ncs = -omega * s0 * zeta, ncl = -omega * s0 * lam;
-        const bf16x8 dB = pack8(dl[0], NF > 1 ? dl[NF - 1] : zero4());
-        f32x4 P[2 * NKS];                      // masked key products; a key tile beyond the token tile counts as zero
-#pragma unroll
-        for (int js = NJ; js < 2 * NKS; ++js) P[js] = zero4();
-#pragma unroll
-        for (int js = 0; js < NJ; ++js) P[js] = mma16(kA[js], dB, zero4()) * mreg[js];
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo) {
-            gn[fo] = mma16(Hf[fo], dB, gn[fo]);
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) gn[fo] = mma16(kT[fo][ks], pack8(P[2 * ks], P[2 * ks + 1]), gn[fo]);
-        }
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo) {
-            xi[fo] += dl[fo];
-            dl[fo] = cm * dl[fo] + ncs * gn[fo] + ncl * xi[fo];
-        }
-    }
-    f32x4 x[NF];
-#pragma unroll
-    for (int fo = 0; fo < NF; ++fo) x[fo] = xi[fo] + dl[fo];
-    if (a.xhat_out && valid) {
-        float *z = a.xhat_out + ti * a.xhat_row;
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo) {
-            *(f32x4 *)(z + 16 * fo + 4 * kg) = x[fo];
-            if (a.xhat_zero_upper) *(f32x4 *)(z + kDs + 16 * fo + 4 * kg) = zero4();   // (a reader of 64 stored features)
-        }
-    }
-    if constexpr (WITH_U) {
-        // ---- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c), x = alpha xhat + (1 - alpha) q
-        // (Section 4.3), formed with the mask divided by zeta_c and multiplied by zeta_c at the end
-        if (a.alpha) {
-            const float al = valid ? a.alpha[ti] : 1.0f;
-            f32x4 qv[2];
-            unpack8(qB, qv[0], qv[1]);
-#pragma unroll
-            for (int fo = 0; fo < NF; ++fo)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[fo][r] = al * x[fo][r] + (1.0f - al) * (valid ? qv[fo][r] : 0.0f);
-        }
-        bf16x8 xv, xr;
-        split8(x[0], NF > 1 ? x[NF - 1] : zero4(), xv, xr);
-        f32x4 P[2 * NKS];
-#pragma unroll
-        for (int js = NJ; js < 2 * NKS; ++js) P[js] = zero4();
-#pragma unroll
-        for (int js = 0; js < NJ; ++js) P[js] = mma16(kA[js], xr, mma16(kA[js], xv, zero4())) * mreg[js];
-        const float *Un = a.sU + unit * (D * D);
-        const int64_t orow = in.row;
-#pragma unroll
-        for (int fo = 0; fo < NF; ++fo) {
-            f32x4 ulo, uhi;
-            state_row_runs<D>(Un, fo, n, kg, ulo, uhi);
-            bf16x8 Uv, Ur;
-            split8(ulo, uhi, Uv, Ur);
-            f32x4 y = mma16(Uv, xr, mma16(Ur, xv, mma16(Uv, xv, zero4())));
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-                y = mma16(keys_in_slot_order(vrows, ks, kg, 16 * fo + n), pack8(P[2 * ks], P[2 * ks + 1]), y);
-            y *= zeta;
-            if (valid) IOBF16::store4(a.o, orow + 16 * fo + 4 * kg, y[0], y[1], y[2], y[3]);
-        }
-    }
+    const u16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
 }
+__device__ __forceinline__ u16x4 pack4(f32x4 x)
+{
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    bf16x4 v;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = (__bf16)x[p];
+    u32x2 b = __builtin_bit_cast(u32x2, v);
+    asm("" : "+v"(b));                         // (two conversions of pairs: seen through, they become four and merges)
+    return __builtin_bit_cast(u16x4, b);
+}
+// rounded value and what the rounding left over
+__device__ __forceinline__ void split4(f32x4 x, u16x4 &val, u16x4 &rem)
+{
+    val = pack4(x);
+    rem = pack4(x - IOBF16::cvt4(val));
+}
+
+// Products, c + X Y. An operand of 16 contraction values is one run of four per lane, which is also how an accumulator
+// tile packs: 16 features take the 16-deep product. With 32 features everything is 32-deep, also over the tile's 16 keys
+// (their second half of the slots is empty or carries a remainder): a 16-deep product that accumulates onto the result
+// of a 32-deep one a few instructions earlier has read its accumulator before it was written.
+template <int NF>
+struct Products {                              // NF = 2
+    static __device__ __forceinline__ f32x4 features(const u16x4 (&x)[2], const u16x4 (&y)[2], f32x4 c)
+    {
+        return mma16(join(x[0], x[1]), join(y[0], y[1]), c);
+    }
+    static __device__ __forceinline__ f32x4 keys(u16x4 x, u16x4 y, f32x4 c)
+    {
+        return mma16(join(x, x), join(y, u16x4{0, 0, 0, 0}), c);
+    }
+    static __device__ __forceinline__ f32x4 keys(u16x4 x, u16x4 val, u16x4 rem, f32x4 c)
+    {
+        return mma16(join(x, x), join(val, rem), c);
+    }
+};
+template <>
+struct Products<1> {
+    static __device__ __forceinline__ f32x4 keys(u16x4 x, u16x4 y, f32x4 c)
+    {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, x), __builtin_bit_cast(s16x4, y), c, 0, 0,
+                                                         0);
+    }
+    static __device__ __forceinline__ f32x4 keys(u16x4 x, u16x4 val, u16x4 rem, f32x4 c)
+    {
+        return keys(x, rem, keys(x, val, c));
+    }
+    static __device__ __forceinline__ f32x4 features(const u16x4 (&x)[1], const u16x4 (&y)[1], f32x4 c)
+    {
+        return keys(x[0], y[0], c);
+    }
+};
+
+// sum over the 16 lanes of a row, inclusive prefix
+__device__ __forceinline__ float row_inclusive_scan(float x)
+{
+    auto add = [](float v, auto ctrl) {
+        return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf,
+                                                              false));
+    };
+    x = add(x, std::integral_constant<int, 0x111>{});
+    x = add(x, std::integral_constant<int, 0x112>{});
+    x = add(x, std::integral_constant<int, 0x114>{});
+    return add(x, std::integral_constant<int, 0x118>{});
+}
+// LDS that only one wave writes and reads: its accesses keep their order in the LDS queue, the compiler has to as well
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
 
 }  // namespace
 
-// (the occupancy bound keeps the register budget at 128, within which the matrix instructions write plain vector
-// registers; with the default budget of 512 the compiler gives them the accumulation file and a third of the pass
-// loop is moves between the two files)
+// One wave per (pair, segment of the sequence, part of the segment): it walks tiles of 16 tokens with H and U^T in
+// accumulator tiles. A tile's solve needs its own 16 keys and nothing else of the sequence but the states before it: a pass
+// has one key product, 4 masked elements per lane and 1 + 2 .. products for the gradient (with the four token tiles of a
+// chunk of 64 solved against the state before the chunk, up to four key tiles and 16 masked elements). By symmetry an
+// accumulator tile of H is the A operand of the solve, and U^T that of the readout: no transposition. H, U, x and the
+// weighted rows enter products as bf16 value + remainder: the matrix pipe is idle most of the time. Bounded by instruction
+// issue (36 vector instructions of a wave per pass at d = 16, some 300 per tile around them) and, where waves are few, by
+// the chain of dependent products (0.11 us per pass, 1 us per tile). No barrier: LDS holds a wave's own 16 rows, for the
+// transposed reads, and per-token scalars. d = 16, 6144 pairs x 197 tokens: 235 us for the whole forward pass with states
+// per chunk of 64 in memory and four key tiles, 98 us now; d = 32, 3072 x 300: 306 and 138 us.
+// Registers: 80 per lane at d = 16 (six waves per SIMD, which 6144 pairs fill), 128 or 168 at d = 32.
 template <bool WITH_U, int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void small_solve_kernel(SmallArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 16 ? 6 : WITH_U ? 3 : 4, 8)))
+void small_walk_kernel(SmallArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t s_rows[64 * kRow];
-    __shared__ __attribute__((aligned(16))) uint16_t s_vrows[WITH_U ? 64 * kRow : 8];
-    __shared__ __attribute__((aligned(16))) float s_G[64], s_B[64], s_W[64];
-    const int lane = threadIdx.x & 63;
+    constexpr int NF = D / 16;                 // feature tiles
+    typedef Products<NF> MM;
+    __shared__ __attribute__((aligned(16))) uint16_t s_k[4][NF * 256];
+    __shared__ __attribute__((aligned(16))) uint16_t s_v[4][WITH_U ? NF * 256 : 8];
+    __shared__ __attribute__((aligned(16))) float s_tab[4][3 * 16];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // consecutive workgroups: the same chunk of consecutive pairs (adjacent memory in the [B,T,H,d] layout)
-    const int pair = blockIdx.x % a.n_pairs, chunk = blockIdx.x / a.n_pairs;
+    // consecutive waves: the same segment of consecutive pairs (adjacent memory in the [B,T,H,d] layout)
+    const unsigned unit = blockIdx.x * 4 + w;
+    if (unit >= (unsigned)a.n_pairs * a.n_segs * a.n_subs) return;
+    const int pair = unit % (unsigned)a.n_pairs, part = unit / (unsigned)a.n_pairs;
+    const int seg = part / a.n_subs, sub = part - seg * a.n_subs;
     const int b = pair / a.H, h = pair % a.H;
-    const int tok0 = chunk * kChunk;
-    stage_rows(a, a.k, s_rows, b, h, tok0, threadIdx.x, 256);
-    if constexpr (WITH_U) stage_rows(a, a.v, s_vrows, b, h, tok0, threadIdx.x, 256);
-    const TileInputs in = fetch_tile_inputs<D>(a, pair, chunk, w, lane);
-    if (w == 0) {
-        const int64_t gi = (b * (int64_t)a.T + min(tok0 + lane, a.T - 1)) * a.H + h;
-        s_G[lane] = wave_inclusive_scan(tok0 + lane < a.T ? log2_gate(a.gate[gi]) : 0.0f, lane);
-        s_B[lane] = a.beta ? a.beta[gi] : 1.0f;
+    // the states are known at tile_begin; tiles from solve_begin on are this wave's
+    const int seg_tiles = a.seg_chunks * (kChunk / 16), n_tiles = (a.T + 15) / 16;
+    const int tile_begin = seg * seg_tiles, solve_begin = tile_begin + sub * (seg_tiles / a.n_subs);
+    const int tile_end = min(solve_begin + seg_tiles / a.n_subs, n_tiles);
+    if (solve_begin >= n_tiles) return;
+    const bool finishes = a.n_segs == 1 && tile_end == n_tiles;
+    uint16_t *rows = s_k[w], *vrows = s_v[w];
+    float *Gtab = s_tab[w], *Btab = Gtab + 16, *Wtab = Gtab + 32;
+    const PaddedRows at = {16};                // tiles of 16 rows x 16 features
+
+    // ---- states before the segment: accumulator tile (fi, fj) holds S[16 fj + n][16 fi + 4 kg + r]
+    f32x4 H[NF][NF], U[NF][NF];
+    TileRows<WITH_U, NF> next;
+    {
+        const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
+        const bool first = a.n_segs == 1;
+        const int64_t s0 = first ? (int64_t)pair * (D * D) : (pair * (int64_t)a.n_chunks + seg * a.seg_chunks) * (D * D);
+        const float *Hs = first ? a.H_init : a.sH, *Us = first ? a.U_init : a.sU;
+#pragma unroll
+        for (int fi = 0; fi < NF; ++fi)
+#pragma unroll
+            for (int fj = 0; fj < NF; ++fj) {
+                const int64_t e = s0 + (16 * fj + n) * D + 16 * fi + 4 * kg;
+                H[fi][fj] = Hs ? *(const f32x4 *)(Hs + e) : zero4();
+                U[fi][fj] = WITH_U && Us ? *(const f32x4 *)(Us + e) : zero4();
+            }
+        next = fetch_tile<WITH_U, NF>(a, b, h, tile_begin, n, kg);
     }
-    __syncthreads();
-    if (tok0 + 16 * w >= a.T) {                // none of this wave's tokens exists (the sequence's last chunk):
-        __syncthreads();                       // the barrier that the other waves pass inside their tile's work
-        return;
+    for (int tile = tile_begin; tile < tile_end; ++tile) {
+        // (lane-derived values formed anew in every tile: kept over the loop they would be spilled)
+        const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
+        const TileRows<WITH_U, NF> in = next;
+        next = fetch_tile<WITH_U, NF>(a, b, h, min(tile + 1, tile_end - 1), n, kg);
+        const bool valid = 16 * tile + n < a.T;
+        const int64_t ti0 = (b * (int64_t)a.T + 16 * tile) * a.H + h;    // the tile's first token in [B,T,H]
+
+        // ---- per-token scalars and rows through the wave's LDS
+        const float Gc = row_inclusive_scan(valid ? log2_gate(in.gate) : 0.0f);
+        const float Gt = lane_value(Gc, 15);
+        const float beta_c = valid ? in.beta : 0.0f;         // (tokens past the end weigh nothing)
+        if (kg == 0) {
+            Gtab[n] = Gc;
+            Btab[n] = beta_c;
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            *(u16x4 *)(rows + f * 256 + 16 * n + 4 * kg) = in.k[f];
+            if constexpr (WITH_U) *(u16x4 *)(vrows + f * 256 + 16 * n + 4 * kg) = in.v[f];
+        }
+        wave_lds_order();
+        const f32x4 Gj = *(const f32x4 *)(Gtab + 4 * kg), bj = *(const f32x4 *)(Btab + 4 * kg);
+        u16x4 kT[NF];                          // column 16 f + n of the keys 4 kg .. 4 kg + 3
+#pragma unroll
+        for (int f = 0; f < NF; ++f) kT[f] = transposed_run(rows + f * 256, at, lane, 4 * kg);
+        // decay mask of Section 4.2.1 (log-space form of Appendix B.2, base 2) with the write gate folded in:
+        // m[j,c] = 2^(G_c - G_j) beta_j for j <= c; lane element r <-> key j = 4 kg + r
+        if (tile >= solve_begin) {
+            // (hardware exp2 here and below: decays under 2^-126 are flushed to zero)
+            float zeta = __builtin_amdgcn_exp2f(Gc);
+            f32x4 m;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m[r] = (4 * kg + r <= n) ? __builtin_amdgcn_exp2f(Gc - Gj[r]) * bj[r] : 0.0f;
+
+            // ---- H as A operand, value and remainder
+            u16x4 Hv[NF][NF], Hr[NF][NF];          // [row block][contraction block]
+            float hn2 = 0.0f;
+#pragma unroll
+            for (int fo = 0; fo < NF; ++fo)
+#pragma unroll
+                for (int fi = 0; fi < NF; ++fi) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) hn2 += H[fi][fo][r] * H[fi][fo][r];
+                    split4(H[fi][fo], Hv[fo][fi], Hr[fo][fi]);
+                }
+
+            // ---- Frobenius norm at every token (Section 4.2.1, the double sum folded by M[i,c] M[j,c] = M[j,c]^2 M[i,j]):
+            //   ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} m[j,c]^2 w_j,
+            //   w_j = 2 (zeta_j k_j^T H_[n] k_j + sum_{i<=j} m[i,j] G_ij^2) / beta_j - G_jj^2
+            // (G = K K^T; w_j = 0 for beta_j = 0)
+            float fro;
+            {
+                float w_part = 0.0f, diag = 0.0f;
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) {
+                    const f32x4 hk = MM::features(Hr[fo], in.k, MM::features(Hv[fo], in.k, zero4()));
+                    const f32x4 kc = IOBF16::cvt4(in.k[fo]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) w_part += hk[r] * kc[r];
+                }
+                w_part *= zeta;
+                const f32x4 G = MM::features(in.k, in.k, zero4());
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float g2 = G[r] * G[r];
+                    w_part += m[r] * g2;
+                    diag = 4 * kg + r == n ? g2 : diag;
+                }
+                const float wc = sum_over_kg(2.0f * __builtin_amdgcn_rcpf(beta_c) * w_part - diag);
+                if (kg == 0) Wtab[n] = beta_c > 0.0f ? wc : 0.0f;
+                wave_lds_order();
+                const f32x4 wv = *(const f32x4 *)(Wtab + 4 * kg);
+                float f = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f += m[r] * m[r] * wv[r];
+                hn2 = lane_value(wave_inclusive_scan(hn2, lane), 63);
+                fro = __builtin_amdgcn_sqrtf(fmaxf(zeta * zeta * hn2 + sum_over_kg(f), 0.0f));
+            }
+            if (a.fro_out && valid && kg == 0) (a.fro_out + ti0)[(uint32_t)n * a.H] = fro;
+            const float lam = a.lambda ? in.lam : a.lambda_scale * fro;      // Section 4.1: lambda_t = a ||H_t||_F
+
+            // ---- Algorithm 1 in residual form; Section 4.1: L = ||H_t||_F + lambda_t, mu = lambda_t
+            const float L = fro + lam, mu = lam;
+            const float rcp = __builtin_amdgcn_rcpf(L + mu);
+            const float s0 = 2.0f * rcp;
+            const float rho = (L - mu) * rcp, rho2 = rho * rho;
+            zeta = fmaxf(zeta, kMinZeta);
+            const float rz = __builtin_amdgcn_rcpf(zeta);
+            m *= rz;
+            f32x4 xi[NF], dl[NF], gn[NF];
+#pragma unroll
+            for (int fo = 0; fo < NF; ++fo) {
+                const f32x4 qv = IOBF16::cvt4(in.q[fo]);         // (columns of tokens past the end go nowhere)
+                xi[fo] = zero4();
+                dl[fo] = s0 * qv;
+                gn[fo] = -rz * qv;
+            }
+            // weight schedule omega' = 4 / (4 - rho^2 omega) as wr = omega / 4
+            float wr = 0.5f;
+            const float w_rho = -4.0f * rho2, w_g = -4.0f * s0 * zeta, w_x = -4.0f * s0 * lam;
+            for (int it = 0; it < a.n_iter; ++it) {
+                wr = __builtin_amdgcn_rcpf(4.0f + w_rho * wr);
+                const float cm = 4.0f * wr - 1.0f, ncs = w_g * wr, ncl = w_x * wr;
+                u16x4 d[NF];
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) d[fo] = pack4(dl[fo]);
+                const u16x4 p = pack4(MM::features(in.k, d, zero4()) * m);
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) {
+                    gn[fo] = MM::features(Hr[fo], d, MM::features(Hv[fo], d, gn[fo]));
+                    gn[fo] = MM::keys(kT[fo], p, gn[fo]);
+                }
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) {
+                    xi[fo] += dl[fo];
+                    dl[fo] = cm * dl[fo] + ncs * gn[fo] + ncl * xi[fo];
+                }
+            }
+            f32x4 x[NF];
+#pragma unroll
+            for (int fo = 0; fo < NF; ++fo) x[fo] = xi[fo] + dl[fo];
+            if (a.xhat_out && valid) {
+                float *z = a.xhat_out + ti0 * a.xhat_row + (int64_t)n * a.H * a.xhat_row;
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) {
+                    *(f32x4 *)(z + 16 * fo + 4 * kg) = x[fo];
+                    if (!WITH_U && a.xhat_zero_upper)            // (a reader of 64 stored features)
+                        *(f32x4 *)(z + kDs + 16 * fo + 4 * kg) = zero4();
+                }
+            }
+            // the next tile's rows are awaited here, where they have had the passes to arrive: behind the conditional store of
+            // the outputs the wait would be for that store too
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                asm volatile("" : "+v"(next.k[f]), "+v"(next.q[f]));
+                if constexpr (WITH_U) asm volatile("" : "+v"(next.v[f]));
+            }
+            asm volatile("" : "+v"(next.gate), "+v"(next.lam), "+v"(next.beta), "+v"(next.alpha));
+            if constexpr (WITH_U) {
+                // ---- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c), x = alpha xhat + (1 - alpha) q
+                // (Section 4.3), formed with the mask divided by zeta_c and multiplied by zeta_c at the end
+                if (a.alpha) {
+#pragma unroll
+                    for (int fo = 0; fo < NF; ++fo) x[fo] = in.alpha * x[fo] + (1.0f - in.alpha) * IOBF16::cvt4(in.q[fo]);
+                }
+                u16x4 xv[NF], xr[NF];
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) split4(x[fo], xv[fo], xr[fo]);
+                const u16x4 p = pack4(MM::features(in.k, xr, MM::features(in.k, xv, zero4())) * m);
+#pragma unroll
+                for (int fo = 0; fo < NF; ++fo) {
+                    u16x4 Uv[NF], Ur[NF];
+#pragma unroll
+                    for (int fi = 0; fi < NF; ++fi) split4(U[fi][fo], Uv[fi], Ur[fi]);
+                    f32x4 y = MM::features(Uv, xr, MM::features(Ur, xv, MM::features(Uv, xv, zero4())));
+                    const u16x4 vT = transposed_run(vrows + fo * 256, at, lane, 4 * kg);
+                    y = zeta * MM::keys(vT, p, y);
+                    if (valid) {
+                        const int64_t base = b * a.stride_b + 16 * (int64_t)tile * a.stride_t + h * a.stride_h;
+                        char *o = (char *)((uint16_t *)a.o + base + 16 * fo);
+                        IOBF16::store4(o + 2 * ((uint32_t)n * (uint32_t)a.stride_t + 4 * kg), 0, y[0], y[1], y[2], y[3]);
+                    }
+                }
+            }
+        }
+        if (tile + 1 == tile_end && !finishes) break;
+        // ---- states after the tile: H <- zeta_T H + K^T (w o K), U^T <- zeta_T U^T + K^T (w o V)
+        wave_lds_order();                      // (scalars and rows are read again: registers are short during the passes)
+        const float zt = __builtin_amdgcn_exp2f(Gt);
+        f32x4 wj;                              // weights of the keys 4 kg + r in the states after the tile
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wj[r] = __builtin_amdgcn_exp2f(Gt - Gtab[4 * kg + r]) * Btab[4 * kg + r];
+#pragma unroll
+        for (int fj = 0; fj < NF; ++fj) {
+            u16x4 wkv, wkr;
+            split4(IOBF16::cvt4(kT[fj]) * wj, wkv, wkr);
+#pragma unroll
+            for (int fi = 0; fi < NF; ++fi) H[fi][fj] = MM::keys(kT[fi], wkv, wkr, zt * H[fi][fj]);
+            if constexpr (WITH_U) {
+                split4(IOBF16::cvt4(transposed_run(vrows + fj * 256, at, lane, 4 * kg)) * wj, wkv, wkr);
+#pragma unroll
+                for (int fi = 0; fi < NF; ++fi) U[fi][fj] = MM::keys(kT[fi], wkv, wkr, zt * U[fi][fj]);
+            }
+        }
+        wave_lds_order();                      // the next tile's rows replace these
     }
-    const int64_t unit = pair * (int64_t)a.n_chunks + chunk;
-    switch (w) {
-    case 0: small_solve_tile<0, WITH_U, D>(a, in, s_rows, s_vrows, s_G, s_B, s_W, unit, lane); break;
-    case 1: small_solve_tile<1, WITH_U, D>(a, in, s_rows, s_vrows, s_G, s_B, s_W, unit, lane); break;
-    case 2: small_solve_tile<2, WITH_U, D>(a, in, s_rows, s_vrows, s_G, s_B, s_W, unit, lane); break;
-    default: small_solve_tile<3, WITH_U, D>(a, in, s_rows, s_vrows, s_G, s_B, s_W, unit, lane); break;
+    // (with several segments the scan has written the final states)
+    if (finishes && a.H_final) {
+        const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
+#pragma unroll
+        for (int fi = 0; fi < NF; ++fi)
+#pragma unroll
+            for (int fj = 0; fj < NF; ++fj) {
+                const int64_t e = (int64_t)pair * (D * D) + (16 * fj + n) * D + 16 * fi + 4 * kg;
+                *(f32x4 *)(a.H_final + e) = H[fi][fj];
+                if (WITH_U) *(f32x4 *)(a.U_final + e) = U[fi][fj];
+            }
     }
 }
 
@@ -497,12 +608,23 @@ size_t state_array_bytes(int n_pairs, int n_chunks, int d)
     return ((size_t)n_pairs * n_chunks * d * d * sizeof(float) + 255) & ~(size_t)255;
 }
 template <bool WITH_U, int D>
-void launch_all(const SmallArgs &a, hipStream_t stream)
+void launch_all(SmallArgs a, hipStream_t stream)
 {
     const int64_t n_units = (int64_t)a.n_pairs * a.n_chunks;
-    hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D>), dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL((small_state_scan_kernel<WITH_U, D>), dim3((unsigned)a.n_pairs), dim3(D * D / 4), 0, stream, a);
-    hipLaunchKernelGGL((small_solve_kernel<WITH_U, D>), dim3((unsigned)n_units), dim3(256), 0, stream, a);
+    const bool few = n_units <= kFewChunks;
+    typedef WalkRule<D> Rule;
+    const bool whole = a.n_pairs >= Rule::many_pairs || a.n_chunks <= Rule::short_chunks ||
+                       (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units);
+    a.seg_chunks = whole ? a.n_chunks : 1;
+    a.n_segs = whole ? 1 : a.n_chunks;
+    a.n_subs = few ? a.seg_chunks * (kChunk / 16) : !whole && n_units <= 2 * kFewChunks ? 2 : 1;
+    if (!whole) {
+        hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D>), dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, stream,
+                           a);
+        hipLaunchKernelGGL((small_state_scan_kernel<WITH_U, D>), dim3((unsigned)a.n_pairs), dim3(D * D / 4), 0, stream, a);
+    }
+    const int64_t n_waves = (int64_t)a.n_pairs * a.n_segs * a.n_subs;
+    hipLaunchKernelGGL((small_walk_kernel<WITH_U, D>), dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, stream, a);
 }
 }  // namespace
 
