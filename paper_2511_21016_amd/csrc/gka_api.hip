@@ -216,12 +216,19 @@ struct PhaseEvents {
     }
 };
 
+// A second right-hand side (value + remainder) for the systems of a solve, and where its and the first one's results go
+// besides p->xhat_out.
+struct SecondRhs {
+    const void *q, *q_lo;
+    float *xhat;
+    void *first_hi, *first_lo, *hi;          // bf16: value and remainder of the first result, value of the second
+};
+
 gka_status forward_impl(const gka_params *p, const void *q, const void *k, const void *v, const float *gate,
                         const float *lambda, void *o, const float *H_init, const float *U_init, float *H_final,
                         float *U_final, float *fro_out, void *workspace, size_t workspace_bytes,
                         void *hip_stream, PhaseEvents *prof, bool readout_only = false, bool solve_only = false,
-                        const void *q2 = nullptr, const void *q2_lo = nullptr,
-                        float *xhat2_out = nullptr)
+                        const SecondRhs *second = nullptr)
 {
     Plan pl;
     gka_status s = make_plan(p, &pl, readout_only);
@@ -306,7 +313,10 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     sa.init_mode = 0; sa.final_mode = 0; sa.write_frags = 1;
     gka::SolveArgs so = {};
     so.q = q; so.k = k; so.v = v; so.gate = gate; so.lambda = lambda; so.o = o; so.fro_out = fro_out;
-    so.q2 = q2; so.q2_lo = q2_lo; so.xhat2_out = xhat2_out;
+    if (second) {
+        so.q2 = second->q; so.q2_lo = second->q_lo; so.xhat2_out = second->xhat;
+        so.xhat_hi = second->first_hi; so.xhat_lo = second->first_lo; so.xhat2_hi = second->hi;
+    }
     so.beta = p->beta; so.alpha = p->alpha; so.lambda_scale = p->lambda_scale;
     so.xhat_out = p->xhat_out;
     // plain readout y_t = U_t q_t (used by the backward pass): needs alpha = 0 from the caller; no H states, no solve
@@ -610,7 +620,9 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         p = &packed_params;
     }
     auto io = [&](int i) { return (void *)(ws + bp.off_io[i]); };
-    float *xf = (float *)(ws + bp.off_f32[0]), *pf32 = (float *)(ws + bp.off_f32[1]);
+    // (bf16 tensors without an alpha-connection: dq_t = p_t, and the solve writes it there)
+    float *xf = (float *)(ws + bp.off_f32[0]);
+    float *pf32 = p->io_dtype == GKA_BF16 && !p->alpha ? dq : (float *)(ws + bp.off_f32[1]);
     auto f32buf = [&](int i) { return (float *)(ws + bp.off_f32[i]); };
     float *gate_rev = (float *)(ws + bp.off_m[0]), *zeros = (float *)(ws + bp.off_m[1]), *sbuf = (float *)(ws + bp.off_m[2]);
     float *phx = (float *)(ws + bp.off_m[6]);
@@ -649,8 +661,9 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         gka_params pp = *p;
         pp.alpha = nullptr; pp.xhat_out = xf;
         pp.state_layout = GKA_STATE_FULL;
+        const SecondRhs second = {q2, q2_lo, pf32, io(IO_X), io(IO_X_LO), io(IO_PR)};
         return forward_impl(&pp, q, k, v, gate, lambda, io(IO_Y), H_init, U_init, nullptr, nullptr, fro_out, fws,
-                            bp.fwd_bytes, hip_stream, nullptr, false, true, q2, q2_lo, pf32);
+                            bp.fwd_bytes, hip_stream, nullptr, false, true, &second);
     };
     auto glue = [&](int which) {
         return gka::launch_backward_glue(g, which, io_bf16, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
@@ -688,17 +701,18 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         g.dxt_io = f32buf(2);                     // (float32)
         g.phx = phx; g.kd = (float *)(ws + bp.off_m[7]); g.vd = (float *)(ws + bp.off_m[8]);
         // bf16 tensors: the second solve takes alpha dxt, and the readouts take x and xt, as value + remainder
-        g.rhs_lo_io = io(IO_RHS_LO); g.x_lo_io = io(IO_X_LO); g.xt_lo_io = io(IO_XT_LO);
+        g.rhs_lo_io = io(IO_RHS_LO); g.xt_lo_io = io(IO_XT_LO);
     }
 #define GKA_TRY(expr) do { gka_status e_ = (expr); if (e_ != GKA_OK) return e_; } while (0)
     if (fused) {
-        // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy
+        // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy. (alpha_t dxt_t in bf16 from
+        // the readout itself: 97 -> 152 us at 64 pairs x 4096 tokens, its own pass over memory takes 41.)
         GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, 0, f32buf(2), nullptr, nullptr, U_init, true));
         GKA_TRY(glue(1));
         // x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
         GKA_TRY(solve_both(io(IO_RHS), io(IO_RHS_LO), rule ? fro : nullptr));
-        // x, xt in the tensors' dtype; p_t . H_t x_t
-        GKA_TRY(glue(0));
+        // xt in the tensors' dtype (x and p have been written so by the solve); p_t . H_t x_t
+        if (p->alpha) GKA_TRY(glue(0));
         GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
                         nullptr, pf32, phx));
     } else {
@@ -718,7 +732,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         else GKA_TRY(fwd(k, k, k, gate, p->beta, zeros, 0, io(IO_HK), nullptr));
     }
     // reverse recurrences: A_t k_t, A_t^T k_t, Ubar_t^T v_t, Ubar_t k_t (no write gate inside them)
-    GKA_TRY(glue(2));
+    if (!fused || rule) GKA_TRY(glue(2));
     if (fused) {
         float *fin_px = with_state ? (float *)(ws + bp.off_fin[0]) : nullptr;
         float *fin_xtdy = with_state ? (float *)(ws + bp.off_fin[1]) : nullptr;

@@ -17,7 +17,8 @@ namespace gka {
 __device__ __forceinline__ f32x4 load_f32x4(const float *p, int64_t i) { return *(const f32x4 *)(p + i); }
 
 // After the forward solve: x in the tensors' dtype, the readout operand xt = alpha x + (1 - alpha) q, and the
-// per-token constants of the later passes.
+// per-token constants of the later passes. (bf16 tensors: the solve writes x and p as bf16 itself, 27 us more for it at
+// 64 pairs x 4096 tokens, d = 128, against 79 + 34 us of passes over memory for them; xt is left, where it is not x.)
 template <class IO>
 __global__ __launch_bounds__(256) void bwd_mix_kernel(BackwardGlueArgs a)
 {
@@ -27,17 +28,14 @@ __global__ __launch_bounds__(256) void bwd_mix_kernel(BackwardGlueArgs a)
     const float al = a.alpha ? a.alpha[tok] : 1.0f;
     const f32x4 x = load_f32x4(a.x_f32, i);
     const f32x4 q = IO::load4(a.q, i);
+    if (a.natural_order) {                       // (with an alpha-connection only; the solve has written x)
+        store_value_remainder((void *)a.xt_io, a.xt_lo_io, i, al * x + (1.0f - al) * q);
+        return;
+    }
     const f32x4 xt = {al * x[0] + (1.0f - al) * q[0], al * x[1] + (1.0f - al) * q[1],
                       al * x[2] + (1.0f - al) * q[2], al * x[3] + (1.0f - al) * q[3]};
     IO::store4(a.x_io, i, x[0], x[1], x[2], x[3]);
     IO::store4(a.xt_io, i, xt[0], xt[1], xt[2], xt[3]);
-    if (a.x_lo_io) {
-        // bf16 tensors: the gradients at k and at the gates are small differences of sums over these operands, so
-        // what their rounding leaves over goes along as a second operand
-        const f32x4 xh = IO::load4(a.x_io, i), xth = IO::load4(a.xt_io, i);
-        IO::store4(a.x_lo_io, i, x[0] - xh[0], x[1] - xh[1], x[2] - xh[2], x[3] - xh[3]);
-        IO::store4(a.xt_lo_io, i, xt[0] - xth[0], xt[1] - xth[1], xt[2] - xth[2], xt[3] - xth[3]);
-    }
     // once per token: the all-zero alpha of the plain readouts and the gates of the reverse recurrences,
     // gate'_tau = gate_{T - tau} for tau >= 1 (gate'_0 multiplies a zero state: 1)
     if (i - tok * a.d == 0) {
@@ -57,12 +55,9 @@ __global__ __launch_bounds__(256) void bwd_rhs_kernel(BackwardGlueArgs a)
     const float al = a.alpha ? a.alpha[i / a.d] : 1.0f;
     const f32x4 g = a.natural_order ? load_f32x4((const float *)a.dxt_io, i) : IO::load4(a.dxt_io, i);
     const f32x4 rhs = {al * g[0], al * g[1], al * g[2], al * g[3]};
-    IO::store4(a.rhs_io, i, rhs[0], rhs[1], rhs[2], rhs[3]);
-    if (a.rhs_lo_io) {
-        // the solve amplifies a perturbation of its right-hand side: the rounding remainder goes along
-        const f32x4 hi = IO::load4(a.rhs_io, i);
-        IO::store4(a.rhs_lo_io, i, rhs[0] - hi[0], rhs[1] - hi[1], rhs[2] - hi[2], rhs[3] - hi[3]);
-    }
+    // (the solve amplifies a perturbation of its right-hand side: the rounding remainder goes along)
+    if (a.rhs_lo_io) store_value_remainder(a.rhs_io, a.rhs_lo_io, i, rhs);
+    else IO::store4(a.rhs_io, i, rhs[0], rhs[1], rhs[2], rhs[3]);
 }
 
 // Time reversal tau = T - 1 - t of k, v, dy, x, p, xt (p converted from float32 on the way).
@@ -71,15 +66,11 @@ __global__ __launch_bounds__(256) void bwd_reverse_kernel(BackwardGlueArgs a)
 {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= a.n_elems) return;
-    if (a.natural_order) {                       // nothing to reverse: p in the tensors' dtype and beta C k
-        const f32x4 pv = load_f32x4(a.p_f32, i);
-        IO::store4(a.p_rev, i, pv[0], pv[1], pv[2], pv[3]);
-        if (a.rule_a > 0.0f) {
-            const int64_t tok = i / a.d;
-            const float bc = (a.beta ? a.beta[tok] : 1.0f) * a.C[tok];
-            const f32x4 kv = IO::load4(a.k, i);
-            IO::store4(a.vp_rev, i, bc * kv[0], bc * kv[1], bc * kv[2], bc * kv[3]);
-        }
+    if (a.natural_order) {                       // nothing to reverse: beta C k (with the rule only)
+        const int64_t tok = i / a.d;
+        const float bc = (a.beta ? a.beta[tok] : 1.0f) * a.C[tok];
+        const f32x4 kv = IO::load4(a.k, i);
+        IO::store4(a.vp_rev, i, bc * kv[0], bc * kv[1], bc * kv[2], bc * kv[3]);
         return;
     }
     const int64_t hd = (int64_t)a.H * a.d;
@@ -118,34 +109,6 @@ __global__ __launch_bounds__(256) void bwd_rule_scalar_kernel(BackwardGlueArgs a
     for (int e = 0; e < E; ++e) dot += a.x_f32[tok * D + lane * E + e] * a.p_f32[tok * D + lane * E + e];
     dot = wave_sum(dot);
     if (lane == 0) a.c[tok] = a.rule_a * dot / a.fro[tok];
-}
-
-// C_t = c_t + gate_{t+1}^2 C_{t+1}: one wave per (batch, head) pair walks its sequence backwards 64 tokens at a time;
-// inside a block the affine maps C -> c + w C are composed by a Hillis-Steele scan over the lanes (lane 0 the latest
-// token).
-__global__ __launch_bounds__(64) void bwd_rule_scan_kernel(BackwardGlueArgs a)
-{
-    const int lane = threadIdx.x;
-    const int64_t b = blockIdx.x / a.H, h = blockIdx.x - b * a.H;
-    auto index = [&](int64_t t) { return (b * a.T + (t >= 0 ? t : 0)) * a.H + h; };
-    auto next_gate = [&](int64_t t) { return (t >= 0 && t + 1 < a.T) ? a.gate[index(t + 1)] : 0.0f; };
-    float carry = 0.0f;
-    float c_next = a.c[index(a.T - 1 - lane)], g_next = next_gate(a.T - 1 - lane);   // read one block ahead
-    for (int64_t t0 = a.T - 1; t0 >= 0; t0 -= 64) {
-        const int64_t t = t0 - lane;
-        float c = t >= 0 ? c_next : 0.0f;
-        float w = g_next * g_next;
-        c_next = a.c[index(t - 64)];
-        g_next = next_gate(t - 64);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const float cp = __shfl_up(c, off, 64), wp = __shfl_up(w, off, 64);
-            if (lane >= off) { c = c + w * cp; w = w * wp; }
-        }
-        const float run = c + w * carry;
-        if (t >= 0) a.C[index(t)] = run;
-        carry = lane_value(run, 63);
-    }
 }
 
 // d / 4 lanes per token: the pieces are combined into the gradients (Section 4.2.2, Appendix B.2):
@@ -279,7 +242,7 @@ __global__ __launch_bounds__(256) void bwd_combine_natural_kernel(BackwardGlueAr
         s_dlam -= x[e] * p[e];
         s_dyy += dxt[e] * (al * x[e] + (1.0f - al) * q[e]);      // dy . U xt = (U^T dy) . xt
     }
-    if (live) *(f32x4 *)(a.dq + i) = o_dq;
+    if (live && a.alpha) *(f32x4 *)(a.dq + i) = o_dq;       // (without alpha dq = p: already there)
     s_dalpha = group_sum(s_dalpha); s_dlam = group_sum(s_dlam); s_dyy = group_sum(s_dyy);
     if (live && sub == 0) {
         const float dbeta = 0.5f * (a.vd[tok] + kd);
@@ -292,41 +255,80 @@ __global__ __launch_bounds__(256) void bwd_combine_natural_kernel(BackwardGlueAr
     }
 }
 
-// One wave per (batch, head) pair: dgate_t = (sum_{s>=t} s_s) / gate_t, walking the sequence backwards 64 tokens at a
-// time. A gate of 0 starts a new packed sequence (it wipes the state): everything after it sums to gamma dgamma = 0
-// exactly, so the sum restarts there instead of carrying that zero as rounding noise, G_t = s_t + w_t G_{t+1} with
-// w_t = 0 where gate_{t+1} = 0; the gradient at such a gate itself is reported as 0. Inside a block the affine maps
-// are composed by a Hillis-Steele scan over the lanes (lane 0 the latest token).
-__global__ __launch_bounds__(64) void bwd_gate_scan_kernel(BackwardGlueArgs a)
+// The two reverse scans over a pair's tokens, one workgroup of up to kScanWaves waves per (batch, head) pair:
+//   RULE: C_t = c_t + gate_{t+1}^2 C_{t+1};
+//   else the gate gradient dgate_t = (sum_{s>=t} s_s) / gate_t. A gate of 0 starts a new packed sequence (it wipes the
+//   state): everything after it sums to gamma dgamma = 0 exactly, so the sum restarts there instead of carrying that zero
+//   as rounding noise, G_t = s_t + w_t G_{t+1} with w_t = 0 where gate_{t+1} = 0; the gradient at such a gate itself is
+//   reported as 0.
+// A wave takes consecutive blocks of 64 tokens, the latest first, and composes the affine maps G -> c + w G inside a block
+// by a Hillis-Steele scan over the lanes (lane 0 the latest token): once for its range's map, which every wave folds over
+// the waves before it, and once more (from the caches) for the outputs. One wave per pair waited for a memory round trip
+// per block: 61 us at 64 pairs x 4096 tokens, 22 now.
+constexpr int kScanWaves = 16;
+template <bool RULE>
+__global__ __launch_bounds__(64 * kScanWaves) void bwd_scan_kernel(BackwardGlueArgs a)
 {
-    const int lane = threadIdx.x;
+    __shared__ float s_c[kScanWaves], s_w[kScanWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int64_t b = blockIdx.x / a.H, h = blockIdx.x - b * a.H;
-    auto index = [&](int64_t t) { return (b * a.T + (t >= 0 ? t : 0)) * a.H + h; };
-    auto gate_at = [&](int64_t t) { return (t >= 0 && t < a.T) ? a.gate[index(t)] : 1.0f; };
-    float carry = 0.0f;
-    // the next block's values are read before this block's scan, so that the walk does not pay a memory round trip
-    // per block
-    float sv_next = a.s[index(a.T - 1 - lane)], g_next = gate_at(a.T - 1 - lane), gn_next = gate_at(a.T - lane);
-    for (int64_t t0 = a.T - 1; t0 >= 0; t0 -= 64) {
-        const int64_t t = t0 - lane;                       // lane 0 takes the latest token of the block
-        float c = t >= 0 ? sv_next : 0.0f;
-        const float gv = g_next;
-        float w = (t >= 0 && gn_next > 0.0f) ? 1.0f : 0.0f; // does the sum of the later tokens reach this one?
-        sv_next = a.s[index(t - 64)];
-        g_next = gate_at(t - 64);
-        gn_next = gate_at(t - 63);
-        float run;
-        if (__ballot(t >= 0 && w == 0.0f) == 0) {          // (wave-uniform) no restart in this block: a plain prefix sum
-            run = wave_inclusive_scan(c, lane) + carry;
-        } else {
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const float cp = __shfl_up(c, off, 64), wp = __shfl_up(w, off, 64);
-                if (lane >= off) { c = c + w * cp; w = w * wp; }
-            }
-            run = c + w * carry;
+    const float *src = RULE ? a.c : a.s;
+    const int n_blocks = (a.T + 63) / 64, per_wave = (n_blocks + n_waves - 1) / n_waves;
+    const int begin = wave * per_wave, end = min(begin + per_wave, n_blocks);
+    auto index = [&](int t) { return (b * a.T + max(t, 0)) * a.H + h; };
+    // the map of the token: c and w, and the gate itself (the gate gradient divides by it)
+    struct Item { float c, w, gate; };
+    auto load = [&](int block) {
+        const int t = a.T - 1 - 64 * block - lane;
+        Item it;
+        it.c = src[index(t)];
+        it.gate = RULE ? 0.0f : a.gate[index(t)];
+        const float after = t + 1 < a.T ? a.gate[index(t + 1)] : RULE ? 0.0f : 1.0f;
+        it.w = RULE ? after * after : after > 0.0f ? 1.0f : 0.0f;
+        if (t < 0) { it.c = 0.0f; it.w = 0.0f; }
+        return it;
+    };
+    auto compose = [&](float &c, float &w) {
+        if (!RULE && __ballot(w == 0.0f) == 0) {           // (wave-uniform) no restart in this block: a plain prefix sum
+            c = wave_inclusive_scan(c, lane);
+            return;
         }
-        if (t >= 0) a.dgate[index(t)] = gv > 0.0f ? run / gv : 0.0f;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const float cp = __shfl_up(c, off, 64), wp = __shfl_up(w, off, 64);
+            if (lane >= off) { c = c + w * cp; w = w * wp; }
+        }
+    };
+    if (n_waves > 1) {
+        float C = 0.0f, W = 1.0f;
+        if (begin < end) {
+            Item next = load(begin);                       // (one block ahead of the scan)
+            for (int block = begin; block < end; ++block) {
+                Item it = next;
+                next = load(min(block + 1, end - 1));
+                compose(it.c, it.w);
+                const float w63 = lane_value(it.w, 63);
+                C = lane_value(it.c, 63) + w63 * C;
+                W *= w63;
+            }
+        }
+        if (lane == 0) { s_c[wave] = C; s_w[wave] = W; }
+        __syncthreads();
+    }
+    float carry = 0.0f;
+    for (int i = 0; i < wave; ++i) carry = s_c[i] + s_w[i] * carry;
+    if (begin >= end) return;
+    Item next = load(begin);
+    for (int block = begin; block < end; ++block) {
+        Item it = next;
+        next = load(min(block + 1, end - 1));
+        compose(it.c, it.w);
+        const float run = it.c + it.w * carry;
+        const int t = a.T - 1 - 64 * block - lane;
+        if (t >= 0) {
+            if (RULE) a.C[index(t)] = run;
+            else a.dgate[index(t)] = it.gate > 0.0f ? run / it.gate : 0.0f;
+        }
         carry = lane_value(run, 63);
     }
 }
@@ -357,6 +359,8 @@ template <class IO>
 static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((a.n_elems / 4 + 255) / 256);
+    const int scan_blocks = (a.T + 63) / 64;
+    const dim3 scan_block(64 * (scan_blocks < kScanWaves ? scan_blocks : kScanWaves));
     switch (which) {
     case 0: hipLaunchKernelGGL((bwd_mix_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;
     case 1: hipLaunchKernelGGL((bwd_rhs_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;
@@ -374,7 +378,7 @@ static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stre
         break;
     }
     case 4:
-        hipLaunchKernelGGL(bwd_gate_scan_kernel, dim3((unsigned)(a.n_tokens / a.T)), dim3(64), 0, stream, a);
+        hipLaunchKernelGGL(bwd_scan_kernel<false>, dim3((unsigned)(a.n_tokens / a.T)), scan_block, 0, stream, a);
         break;
     case 5: {
         const unsigned tb = (unsigned)((a.n_tokens + 3) / 4);
@@ -383,7 +387,7 @@ static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stre
         break;
     }
     case 6:
-        hipLaunchKernelGGL(bwd_rule_scan_kernel, dim3((unsigned)(a.n_tokens / a.T)), dim3(64), 0, stream, a);
+        hipLaunchKernelGGL(bwd_scan_kernel<true>, dim3((unsigned)(a.n_tokens / a.T)), scan_block, 0, stream, a);
         break;
     default: {
         const int64_t n = (int64_t)a.n_pairs * a.d * a.d;

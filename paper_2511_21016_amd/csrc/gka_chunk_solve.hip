@@ -576,11 +576,16 @@ __device__ __forceinline__ void chunk_solve_wave(const SolveArgs &a, unsigned ch
         if (valid) {
             float *xo = (rhs == 0 ? a.xhat_out : a.xhat2_out) + (gate_base + (int64_t)tok * a.H) * D;
 #pragma unroll
-            for (int i = 0; i < NBH; ++i)
+            for (int i = 0; i < NBH; ++i) {
+                f32x4 x[4];
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    *(f32x4 *)(xo + 32 * (mt0 + i) + 8 * q4 + 4 * g) =
-                        f32x4{xi[i][4 * q4], xi[i][4 * q4 + 1], xi[i][4 * q4 + 2], xi[i][4 * q4 + 3]};
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    x[q4] = f32x4{xi[i][4 * q4], xi[i][4 * q4 + 1], xi[i][4 * q4 + 2], xi[i][4 * q4 + 3]};
+                    *(f32x4 *)(xo + 32 * (mt0 + i) + 8 * q4 + 4 * g) = x[q4];
+                }
+                store_block_value_remainder(rhs == 0 ? a.xhat_hi : a.xhat2_hi, rhs == 0 ? a.xhat_lo : nullptr,
+                                            (gate_base + (int64_t)tok * a.H) * D + 32 * (mt0 + i), g, x);
+            }
         }
     }
     }                                              // (right-hand sides)

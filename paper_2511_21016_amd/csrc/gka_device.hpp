@@ -88,6 +88,47 @@ struct IOBF16 {
     }
 };
 
+// Four elements as bf16 value and, where asked for, what the rounding left over.
+__device__ __forceinline__ void store_value_remainder(void *hi, void *lo, int64_t i, f32x4 x)
+{
+    const u16x4 v = {f32_to_bf16_bits(x[0]), f32_to_bf16_bits(x[1]), f32_to_bf16_bits(x[2]), f32_to_bf16_bits(x[3])};
+    *(u16x4 *)((uint16_t *)hi + i) = v;
+    if (lo) {
+        const f32x4 rem = x - IOBF16::cvt4(v);
+        IOBF16::store4(lo, i, rem[0], rem[1], rem[2], rem[3]);
+    }
+}
+
+// The same for a lane's 16 values of a 32-feature block in the 32x32 accumulator layout (x[q4]: features 8 q4 + 4 g .. + 3, g
+// the half of the wave; both halves hold the same token): the halves exchange runs, so that a lane stores eight features at
+// once (8-byte stores: twice the instructions, each to 32 rows; +94 us in the solve of 64 pairs x 4096 tokens instead of
+// +27). i: the block's first feature.
+__device__ __forceinline__ void store_block_bf16(void *dst, int64_t i, int g, const u16x4 (&x)[4])
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const u32x2 even = __builtin_bit_cast(u32x2, x[2 * p]), odd = __builtin_bit_cast(u32x2, x[2 * p + 1]);
+        const auto r0 = __builtin_amdgcn_permlane32_swap(even[0], odd[0], false, false);
+        const auto r1 = __builtin_amdgcn_permlane32_swap(even[1], odd[1], false, false);
+        *(u32x4 *)((uint16_t *)dst + i + 16 * p + 8 * g) = u32x4{r0[0], r1[0], r0[1], r1[1]};
+    }
+}
+__device__ __forceinline__ void store_block_value_remainder(void *hi, void *lo, int64_t i, int g, const f32x4 (&x)[4])
+{
+    u16x4 v[4], rem[4];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        v[q4] = u16x4{f32_to_bf16_bits(x[q4][0]), f32_to_bf16_bits(x[q4][1]), f32_to_bf16_bits(x[q4][2]),
+                      f32_to_bf16_bits(x[q4][3])};
+        const f32x4 d = x[q4] - IOBF16::cvt4(v[q4]);
+        rem[q4] = u16x4{f32_to_bf16_bits(d[0]), f32_to_bf16_bits(d[1]), f32_to_bf16_bits(d[2]), f32_to_bf16_bits(d[3])};
+    }
+    store_block_bf16(hi, i, g, v);
+    if (lo) store_block_bf16(lo, i, g, rem);
+}
+
 // Row-major LDS tiles of k or v rows (features contiguous) come in two layouts, both a functor (row, col) ->
 // element offset: rows padded so that consecutive rows start 32 bytes apart modulo 256, or unpadded rows whose
 // 32-byte granules are XOR-swizzled with the row number. Either way the four rows addressed by a 16-lane block of

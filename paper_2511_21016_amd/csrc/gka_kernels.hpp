@@ -55,6 +55,9 @@ struct SolveArgs {
     // goes to xhat2_out. nullptr: none
     const void *q2, *q2_lo;
     float *xhat2_out;
+    // with q2: the results as the readouts of the backward pass take them, bf16 value and remainder of the first, value of the
+    // second (packed [B,T,H,d])
+    void *xhat_hi, *xhat_lo, *xhat2_hi;
     bool init_states;             // the sequence starts from given states (else the states before chunk 0 are zero)
 };
 
@@ -85,7 +88,7 @@ struct BackwardGlueArgs {
     const float *x_f32, *p_f32;   // results of the two solves
     void *x_io, *xt_io, *rhs_io;  // x, alpha x + (1 - alpha) q, alpha dxt
     void *rhs_lo_io;              // bf16 tensors: what rounding alpha dxt to rhs_io left over (nullptr: not kept)
-    void *x_lo_io, *xt_lo_io;     // likewise for x_io and xt_io
+    void *xt_lo_io;               // likewise for xt_io
     const void *dxt_io, *y_io, *hx_io;                     // U_t^T dy_t; float32 tensors: forward output, H_t x_t
     const float *phx;             // bf16 tensors: p_t . H_t x_t,
     const float *kd, *vd;         //   k . dk / beta, v . dv / beta (gka_reverse.hip)

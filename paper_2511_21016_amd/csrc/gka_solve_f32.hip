@@ -409,9 +409,12 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                if (valid[tt])
-                    *(f32x4 *)((DUAL && rhs == 1 ? a.xhat2_out : a.xhat_out) + (gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H) * D + 16 * (RT * w + rt) +
-                               4 * kg) = xi[rt][tt];
+                if (valid[tt]) {
+                    const int64_t e = (gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H) * D + 16 * (RT * w + rt) + 4 * kg;
+                    *(f32x4 *)((DUAL && rhs == 1 ? a.xhat2_out : a.xhat_out) + e) = xi[rt][tt];
+                    if constexpr (DUAL)
+                        store_value_remainder(rhs == 0 ? a.xhat_hi : a.xhat2_hi, rhs == 0 ? a.xhat_lo : nullptr, e, xi[rt][tt]);
+                }
     }
     }                                                  // (right-hand sides)
     if constexpr (DUAL) return;
