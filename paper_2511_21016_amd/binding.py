@@ -189,6 +189,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _stream_of(t):
+    """Handle of torch's current stream on the tensor's GPU. Raises for a tensor that is not on one: its index is -1, which
+    the stream query would take as the current device."""
+    index = t.get_device()
+    if index < 0:
+        raise ValueError(f"expected tensors on a CUDA device, got {t.device}")
+    return _raw_stream(index)
+
+
 def gka_forward(q, k, v, gate, lam, n_iter, *, compute=None, chunk=64, H_init=None, U_init=None,
                 return_state=False, return_fro=False, workspace=None, out=None, phase=GKA_PHASE_ALL,
                 beta=None, alpha=None, lambda_scale=0.0, state_layout=GKA_STATE_FULL, return_xhat=False,
@@ -226,7 +235,7 @@ def gka_forward(q, k, v, gate, lam, n_iter, *, compute=None, chunk=64, H_init=No
         extras["fro"] = fro
     if return_xhat:
         extras["xhat"] = xhat
-    stream = _raw_stream(q.get_device())
+    stream = _stream_of(q)
     _check(forward_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(o), _ptr(H_init),
                        _ptr(U_init), _ptr(Hf), _ptr(Uf), _ptr(fro), _ptr(workspace), workspace.numel(), stream))
     return (o, extras) if extras else o
@@ -244,7 +253,7 @@ def gka_decode_step(H_state, U_state, q, k, v, gate, lam, n_iter, *, out=None, b
     if o is None:
         import torch
         o = torch.empty_like(v)
-    stream = _raw_stream(q.get_device())
+    stream = _stream_of(q)
     _check(decode_step_raw(params, _ptr(H_state), _ptr(U_state), _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam),
                            _ptr(o), stream))
     return o
@@ -263,7 +272,7 @@ def gka_decode_tokens(H_state, U_state, q, k, v, gate, lam, n_iter, *, out=None,
     params = make_params(B, H, T, d, n_iter, io, GKA_COMPUTE_F32, lambda_scale=lambda_scale, beta=_ptr(beta),
                          alpha=_ptr(alpha), state_layout=state_layout)
     o = torch.empty_like(v) if out is None else out
-    stream = _raw_stream(q.get_device())
+    stream = _stream_of(q)
     _check(decode_tokens_raw(params, _ptr(H_state), _ptr(U_state), _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam),
                              _ptr(o), stream))
     return o
@@ -321,7 +330,7 @@ def gka_backward(q, k, v, gate, lam, dy, n_iter, *, compute=None, beta=None, alp
         out["dbeta"] = torch.empty((B, T, H), **f32)
     if alpha is not None:
         out["dalpha"] = torch.empty((B, T, H), **f32)
-    stream = _raw_stream(q.get_device())
+    stream = _stream_of(q)
     if H_init is not None or return_state_grads:
         if return_state_grads:
             out["dH_init"] = torch.empty((B, H, d, d), **f32)
@@ -364,7 +373,7 @@ def gka_forward_sketched(q, k, v, gate, lam, S, n_iter, *, beta=None, lambda_sca
         nbytes = forward_sketched_workspace_bytes(params, d_s)
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=q.device)
     o = torch.empty_like(v) if out is None else out
-    stream = _raw_stream(q.get_device())
+    stream = _stream_of(q)
     _check(forward_sketched_raw(params, _ptr(q), _ptr(k), _ptr(v), _ptr(gate), _ptr(lam), _ptr(S), d_s, per_head,
                                 _ptr(o), _ptr(workspace), workspace.numel(), stream))
     return o
