@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void bwd_combine_natural_kernel(BackwardGlueAr
     const bool rule = a.rule_a > 0.0f;
     const f32x4 x = load_f32x4(a.x_f32, i), p = load_f32x4(a.p_f32, i), dxt = load_f32x4((const float *)a.dxt_io, i);
     f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (a.alpha) q = IO::load4(a.q, i);
+    if (a.alpha || a.dalpha) q = IO::load4(a.q, i);      // (dalpha without alpha: the gradient at alpha = 1)
     float kd = a.kd[tok];
     if (rule) {
         // dk -= 2 beta (C_t H_t k_t + sum_{j>t} M[t,j] beta_j C_j k_j (k_j . k_t)); r5 holds the sum with its j = t term
