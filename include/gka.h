@@ -160,7 +160,9 @@ size_t gka_forward_workspace_bytes(const gka_params *p);
  *   o        [B,T,H,d_v]  io_dtype (written)
  *   H_init   [B,H,d_k,d_k], U_init [B,H,d_v,d_k] float32, or NULL for zero initial states;
  *            gamma of the first token multiplies the initial state
- *   H_final, U_final      same shapes, written if not NULL (state after the last token)
+ *   H_final, U_final      same shapes, written if not NULL (state after the last token). They may be the buffers of
+ *                         H_init, U_init at d = 16, 32 and 256 and on GKA_PATH_RECURRENT; elsewhere several workgroups
+ *                         read the initial states while one writes the final ones: separate buffers
  *   fro_out  [B,T,H] float32 ||H_t||_F, written if not NULL
  *   workspace, workspace_bytes: see gka_forward_workspace_bytes
  * gate and lambda are packed [B,T,H] regardless of the q/k/v strides. */

@@ -224,6 +224,12 @@ struct SecondRhs {
     void *first_hi, *first_lo, *hi;          // bf16: value and remainder of the first result, value of the second
 };
 
+// The final states replace the initial ones in the caller's buffers.
+bool states_in_place(const float *H_init, const float *U_init, const float *H_final, const float *U_final)
+{
+    return H_final && (H_final == H_init || U_final == U_init);
+}
+
 gka_status forward_impl(const gka_params *p, const void *q, const void *k, const void *v, const float *gate,
                         const float *lambda, void *o, const float *H_init, const float *U_init, float *H_final,
                         float *U_final, float *fro_out, void *workspace, size_t workspace_bytes,
@@ -327,6 +333,10 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     so.stride_b = pl.stride_b; so.stride_t = pl.stride_t; so.stride_h = pl.stride_h;
     so.H = p->H; so.T = p->T; so.n_iter = p->n_iter;
     so.init_states = H_init != nullptr;
+    // d = 256 with the final states in the buffers of the initial ones: one segment, whose workgroups read the part of a state
+    // that they write. (With several segments the last one's workgroups would write what the others may not have read yet;
+    // several slabs read and write them in different launches.)
+    if (pl.wide && states_in_place(H_init, U_init, H_final, U_final) && pl.slab_chunks >= pl.n_chunks) sa.n_segs = 1;
     const bool one_launch = pl.pairs_per_batch >= pl.n_pairs && pl.slab_chunks >= pl.n_chunks;
     // With a single phase requested the workspace must cover the whole problem.
     if (p->phase != GKA_PHASE_ALL && !one_launch) return GKA_ERR_UNSUPPORTED;

@@ -613,8 +613,12 @@ void launch_all(SmallArgs a, hipStream_t stream)
     const int64_t n_units = (int64_t)a.n_pairs * a.n_chunks;
     const bool few = n_units <= kFewChunks;
     typedef WalkRule<D> Rule;
-    const bool whole = a.n_pairs >= Rule::many_pairs || a.n_chunks <= Rule::short_chunks ||
-                       (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units);
+    // (final states in the buffers of the initial ones: not where several waves of a pair would start from the initial states
+    // while one of them writes the final ones; the scan reads and writes each of their elements in one thread)
+    const bool in_place = a.H_final && (a.H_final == a.H_init || a.U_final == a.U_init);
+    const bool whole = !(few && in_place) &&
+                       (a.n_pairs >= Rule::many_pairs || a.n_chunks <= Rule::short_chunks ||
+                        (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units));
     a.seg_chunks = whole ? a.n_chunks : 1;
     a.n_segs = whole ? 1 : a.n_chunks;
     a.n_subs = few ? a.seg_chunks * (kChunk / 16) : !whole && n_units <= 2 * kFewChunks ? 2 : 1;

@@ -1,0 +1,68 @@
+/* A stand-in for the HIP runtime that libgka links against, preloaded into a process without a GPU: it launches nothing
+ * and writes down what the library asked for. One line per call on the file of recorder_open():
+ *   launch <kernel's mangled name> <grid> <block> <dynamic LDS bytes>
+ *   attribute <kernel's mangled name> <attribute> <value> <device>
+ */
+#include <stdio.h>
+#include <stddef.h>
+#include <stdint.h>
+
+typedef struct { uint32_t x, y, z; } dim3_t;
+
+static struct { const void *host; const char *name; } kernels[4096];
+static int n_kernels, device;
+static FILE *out;
+static struct { dim3_t grid, block; size_t lds; void *stream; } pushed;
+
+void recorder_open(const char *path) { out = fopen(path, "w"); }
+void recorder_close(void) { if (out) fclose(out); out = NULL; }
+void recorder_set_device(int d) { device = d; }
+
+static const char *name_of(const void *host)
+{
+    for (int i = 0; i < n_kernels; ++i)
+        if (kernels[i].host == host) return kernels[i].name;
+    return "?";
+}
+
+void **__hipRegisterFatBinary(const void *data) { (void)data; static void *handle; return &handle; }
+void __hipUnregisterFatBinary(void **modules) { (void)modules; }
+void __hipRegisterFunction(void **modules, const void *host, char *device_function, const char *device_name,
+                           unsigned thread_limit, void *tid, void *bid, void *block, void *grid, int *wsize)
+{
+    (void)modules; (void)device_function; (void)thread_limit; (void)tid; (void)bid; (void)block; (void)grid; (void)wsize;
+    if (n_kernels < 4096) { kernels[n_kernels].host = host; kernels[n_kernels++].name = device_name; }
+}
+void __hipRegisterVar(void **modules, void *var, char *host, char *dev, int ext, size_t size, int constant, int global)
+{
+    (void)modules; (void)var; (void)host; (void)dev; (void)ext; (void)size; (void)constant; (void)global;
+}
+int __hipPushCallConfiguration(dim3_t grid, dim3_t block, size_t lds, void *stream)
+{
+    pushed.grid = grid; pushed.block = block; pushed.lds = lds; pushed.stream = stream;
+    return 0;
+}
+int __hipPopCallConfiguration(dim3_t *grid, dim3_t *block, size_t *lds, void **stream)
+{
+    *grid = pushed.grid; *block = pushed.block; *lds = pushed.lds; *stream = pushed.stream;
+    return 0;
+}
+int hipLaunchKernel(const void *host, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
+{
+    (void)args; (void)stream;
+    if (out) fprintf(out, "launch %s %u %u %zu\n", name_of(host), grid.x, block.x, lds);
+    return 0;
+}
+int hipFuncSetAttribute(const void *host, int attribute, int value)
+{
+    if (out) fprintf(out, "attribute %s %d %d %d\n", name_of(host), attribute, value, device);
+    return 0;
+}
+int hipGetDevice(int *d) { *d = device; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipGetSymbolAddress(void **p, const void *symbol) { (void)symbol; *p = (void *)0x100000; return 0; }
+int hipEventCreate(void **e) { *e = (void *)1; return 0; }
+int hipEventDestroy(void *e) { (void)e; return 0; }
+int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }
+int hipEventSynchronize(void *e) { (void)e; return 0; }
+int hipEventElapsedTime(float *ms, void *a, void *b) { (void)a; (void)b; *ms = 0; return 0; }
