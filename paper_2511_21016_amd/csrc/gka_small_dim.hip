@@ -621,7 +621,9 @@ void launch_all(SmallArgs a, hipStream_t stream)
                         (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units));
     a.seg_chunks = whole ? a.n_chunks : 1;
     a.n_segs = whole ? 1 : a.n_chunks;
-    a.n_subs = few ? a.seg_chunks * (kChunk / 16) : !whole && n_units <= 2 * kFewChunks ? 2 : 1;
+    // (outputs that replace the rows of k or v: no wave advances the states over tiles that another one solves)
+    const bool over_rows = a.o && (a.o == a.k || a.o == a.v);
+    a.n_subs = over_rows ? 1 : few ? a.seg_chunks * (kChunk / 16) : !whole && n_units <= 2 * kFewChunks ? 2 : 1;
     if (!whole) {
         hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D>), dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, stream,
                            a);

@@ -86,7 +86,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
     // the later token tiles of a chunk see more keys: their workgroups start first. Consecutive workgroups take the
     // same chunk of consecutive pairs (in the [B,T,H,d] layout the heads of a token are adjacent).
     const int per_tb = a.n_pairs * a.n_chunks;
-    const int tb = TB - 1 - (int)blockIdx.x / per_tb;
+    const int tb = TB - 1 - a.skip_blocks - (int)blockIdx.x / per_tb;
     const int within = (int)blockIdx.x % per_tb;
     const int pair = within % a.n_pairs, chunk_local = within / a.n_pairs;
     const int chunk = a.chunk0 + chunk_local;
@@ -477,8 +477,17 @@ static hipError_t launch_solve_f32_t(const SolveArgs &a, hipStream_t stream)
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_set_on[dev] = true;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_pairs * a.n_chunks * SH::TB)), dim3(SH::NTHR), SH::lds_bytes, stream, a);
-    return hipGetLastError();
+    // A workgroup reads the rows of k and v of its chunk up to its own tokens. Outputs that replace them: the token blocks of a
+    // chunk one launch after the other, the last ones first.
+    const bool over_rows = !a.solve_only && (a.o == a.v || a.o == a.k);
+    const int blocks = over_rows ? 1 : SH::TB;
+    SolveArgs args = a;
+    for (args.skip_blocks = 0; args.skip_blocks < SH::TB; args.skip_blocks += blocks) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_pairs * a.n_chunks * blocks)), dim3(SH::NTHR), SH::lds_bytes, stream, args);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <class IO, int D, int MODE>
