@@ -360,7 +360,9 @@ static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stre
 {
     const unsigned blocks = (unsigned)((a.n_elems / 4 + 255) / 256);
     const int scan_blocks = (a.T + 63) / 64;
-    const dim3 scan_block(64 * (scan_blocks < kScanWaves ? scan_blocks : kScanWaves));
+    // (gradients that replace the gates: one wave, which reads a block's gates before it stores the block ahead of it)
+    const int scan_waves = which == 4 && a.dgate == a.gate ? 1 : scan_blocks < kScanWaves ? scan_blocks : kScanWaves;
+    const dim3 scan_block(64 * scan_waves);
     switch (which) {
     case 0: hipLaunchKernelGGL((bwd_mix_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;
     case 1: hipLaunchKernelGGL((bwd_rhs_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;

@@ -53,3 +53,48 @@ def test_in_place_against_separate_outputs(d, dtype, B, H, T, name):
     # the same sums at float32 products; d = 16, 32: tiles solved against other (rounded) states, twice the rounding that the
     # outputs are allowed
     assert pair_rel_err(got, want) <= (0.0 if d >= 64 else 2e-2)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_gate_gradients_over_the_gates(dtype):
+    """The gate gradient's scan reads gates across the ranges of its waves: with dgate == gate it has one wave."""
+    call = """
+ptr = [n << 36 for n in range(1, 12)]
+p = binding.make_params(1, 2, 1000, 64, 5, binding.{io}, binding.{compute})
+q, k, v, gate, lam, dy, dq, dk, dv, ws, dgate = ptr
+st = binding.backward_raw(p, q, k, v, gate, lam, dy, dq, dk, dv, {dgate}, workspace=ws, workspace_bytes=1 << 42)
+assert st == binding.GKA_OK, binding.status_string(st)
+"""
+    io, compute = {"f32": ("GKA_F32", "GKA_COMPUTE_F32"), "bf16": ("GKA_BF16", "GKA_COMPUTE_BF16")}[dtype]
+    waves = lambda dgate: [c["block"] // 64 for c in record(call.format(io=io, compute=compute, dgate=dgate))
+                           if c["kernel"] == "bwd_scan_kernel"]
+    assert waves("dgate") == [16] and waves("gate") == [1]
+
+
+@pytest.mark.gpu
+def test_gate_gradients_over_the_gates_against_separate_ones():
+    import torch
+    from paper_2511_21016_amd import binding, synth
+    from gka_testutil import to_host, upload_inputs
+    w = synth.CFG1.scaled(B=1, H=2, T=1000, d=64, n_iter=5, seed=771)
+    x = synth.make_inputs(w)
+    x["gate"][0, 500, 1] = 0.0
+    dev = upload_inputs(x, "f32")
+    dy = torch.randn(dev["v"].shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    params = binding.make_params(1, 2, 1000, 64, w.n_iter, binding.GKA_F32, binding.GKA_COMPUTE_F32)
+    nbytes = binding.backward_workspace_bytes(params)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(dev["q"]) for _ in range(3)]
+    results = []
+    for in_place in (False, True):
+        gate = dev["gate"].clone()
+        dgate = gate if in_place else torch.empty_like(gate)
+        st = binding.backward_raw(params, dev["q"].data_ptr(), dev["k"].data_ptr(), dev["v"].data_ptr(), gate.data_ptr(),
+                                  dev["lam"].data_ptr(), dy.data_ptr(), *(g.data_ptr() for g in grads), dgate.data_ptr(),
+                                  workspace=ws.data_ptr(), workspace_bytes=nbytes,
+                                  stream=torch.cuda.current_stream().cuda_stream)
+        assert st == binding.GKA_OK, binding.status_string(st)
+        torch.cuda.synchronize()
+        results.append(to_host(dgate))
+    # float32 sums of 1000 terms in another order
+    assert abs(results[1] - results[0]).max() <= 1e-4 * abs(results[0]).max()
