@@ -149,8 +149,9 @@ typedef struct {
  * states; p->slab_state_bytes overrides that budget). The fused kernel (gka_path) needs only the segment summaries
  * of its chunk walk; the query returns the larger of the two sizes. The chunk-wise kernels of d = 16 and 32 keep four
  * d x d float32 states per chunk. The token-by-token path (GKA_PATH_RECURRENT) keeps
- * its states in registers: 256 bytes, plus one U state per pair at d = 256 (above 128 tokens d = 256 runs chunk-wise, its
- * chunk states bounded by the same 1 GiB). Its contents after a call are unspecified. */
+ * its states in registers: 256 bytes, plus one U state per pair at d = 256. Above 128 tokens d = 256 runs chunk-wise: at
+ * most 1 GiB of chunk states as well and, where a sequence takes several slabs, 1 MiB of carried states for each of the up to
+ * 512 pairs of a launch. Its contents after a call are unspecified. */
 size_t gka_forward_workspace_bytes(const gka_params *p);
 
 /* Whole-sequence forward, Eq. (CH).

@@ -130,6 +130,12 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
                              gka::ws_U_bytes_per_chunk(pl->d, pl->compute_bf16);
     size_t ppb = pl->n_pairs < kMaxPairsPerBatch ? pl->n_pairs : kMaxPairsPerBatch;
     const size_t budget = p->slab_state_bytes > 0 ? (size_t)p->slab_state_bytes : kDefaultSlabStateBytes;
+    if (pl->wide) {
+        // (512 KiB per chunk: kMinSlabChunks of 1024 pairs would take twice the budget)
+        const size_t least = (size_t)pl->n_chunks < kMinSlabChunks ? (size_t)pl->n_chunks : kMinSlabChunks;
+        const size_t fit = budget / (least * per_chunk);
+        if (ppb > fit) ppb = fit > 0 ? fit : 1;
+    }
     size_t slab = budget / (ppb * per_chunk);
     if (slab < kMinSlabChunks) slab = kMinSlabChunks;
     if (slab > (size_t)pl->n_chunks) slab = pl->n_chunks;
@@ -153,10 +159,13 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     if (n_segs < 1) n_segs = 1;
     pl->seg_len = (pl->slab_chunks + n_segs - 1) / n_segs;
     pl->n_segs = (pl->slab_chunks + pl->seg_len - 1) / pl->seg_len;
-    pl->off_segdecay = align_up(pl->off_seg + (size_t)pl->pairs_per_batch * pl->n_segs * 2 * pl->d * pl->d * sizeof(float), 256);
-    pl->off_carry = align_up(pl->off_segdecay + (size_t)pl->pairs_per_batch * pl->n_segs * sizeof(float), 256);
+    // (one segment needs no summaries, one slab carries nothing)
+    const size_t n_summaries = pl->n_segs > 1 ? (size_t)pl->pairs_per_batch * pl->n_segs : 0;
+    pl->off_segdecay = align_up(pl->off_seg + n_summaries * 2 * pl->d * pl->d * sizeof(float), 256);
+    pl->off_carry = align_up(pl->off_segdecay + n_summaries * sizeof(float), 256);
     // two ping-pong pairs of fp32 (H, U) carried from slab to slab
-    pl->total = align_up(pl->off_carry + (size_t)4 * pl->pairs_per_batch * pl->d * pl->d * sizeof(float), 256);
+    const size_t n_carried = pl->slab_chunks < pl->n_chunks ? (size_t)4 * pl->pairs_per_batch : 0;
+    pl->total = align_up(pl->off_carry + n_carried * pl->d * pl->d * sizeof(float), 256);
     // Fused kernel: one workgroup per (pair, segment of the chunk walk). As few segments as give every compute unit a
     // workgroup (every segment but the last costs a second read of its k and v rows for the summary launch); an even
     // number of chunks per segment, because a workgroup takes its chunks two at a time.
