@@ -3,9 +3,33 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace gka {
 
 constexpr int kChunk = 64;   // chunk size C of Section 4.2.1
+
+// Raises the limits of dynamic LDS of a launcher's kernels, once per device (the attribute is kept per device). `done`: the
+// launcher's record.
+constexpr int kMaxLdsDevices = 64;
+struct LdsLimit {
+    const void *kernel;
+    size_t bytes;
+};
+inline hipError_t raise_lds_limits(bool (&done)[kMaxLdsDevices], std::initializer_list<LdsLimit> limits)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const bool recorded = dev >= 0 && dev < kMaxLdsDevices;
+    if (recorded && done[dev]) return hipSuccess;
+    for (const LdsLimit &l : limits) {
+        e = hipFuncSetAttribute(l.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.bytes);
+        if (e != hipSuccess) return e;
+    }
+    if (recorded) done[dev] = true;
+    return hipSuccess;
+}
 
 struct StatePassArgs {
     const void *k, *v;            // [B,T,H,d] tensors (element strides below)

@@ -467,21 +467,16 @@ static hipError_t launch_readout_d(const ReadoutArgs &a0, hipStream_t stream)
     ReadoutArgs a = a0;
     constexpr size_t lds_sum = KLO ? SH::lds_bytes_klo : SH::lds_bytes;
     constexpr size_t lds_main = QMODE != 0 ? SH::lds_bytes_qlo : lds_sum;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, false, QMODE, KLO, DOT>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_main);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void *)gla_readout_kernel<DK, DV, GATED, true, 0, KLO>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_sum);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static bool lds_raised[kMaxLdsDevices] = {};
+    hipError_t e = raise_lds_limits(lds_raised,
+                                    {{(const void *)gla_readout_kernel<DK, DV, GATED, false, QMODE, KLO, DOT>, lds_main},
+                                     {(const void *)gla_readout_kernel<DK, DV, GATED, true, 0, KLO>, lds_sum}});
+    if (e != hipSuccess) return e;
     if (a.n_segs > 1 && a.seg_mode == 0) {
         // summaries of every segment but the last, each from a zero state
         hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, true, 0, KLO>), dim3(a.n_pairs * (a.n_segs - 1)),
                            dim3(SH::NT), lds_sum, stream, a);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((gla_readout_kernel<DK, DV, GATED, false, QMODE, KLO, DOT>), dim3(a.n_pairs * a.n_segs), dim3(SH::NT),

@@ -468,20 +468,14 @@ template <int D, int PART>
 hipError_t launch_reverse_t(const ReverseArgs &a, hipStream_t stream)
 {
     typedef ReverseShape<D, PART> SH;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)reverse_kernel<D, PART, false>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::lds_main);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void *)reverse_kernel<D, PART, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)SH::lds_summary);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static bool lds_raised[kMaxLdsDevices] = {};
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)reverse_kernel<D, PART, false>, SH::lds_main},
+                                                 {(const void *)reverse_kernel<D, PART, true>, SH::lds_summary}});
+    if (e != hipSuccess) return e;
     if (a.n_segs > 1) {                                // summaries of every segment but the last, from zero states
         hipLaunchKernelGGL((reverse_kernel<D, PART, true>), dim3(a.n_pairs * (a.n_segs - 1)), dim3(SH::NT), SH::lds_summary,
                            stream, a);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((reverse_kernel<D, PART, false>), dim3(a.n_pairs * a.n_segs), dim3(SH::NT), SH::lds_main, stream, a);
