@@ -246,15 +246,20 @@ struct TileRows {
     u16x4 k[NF], q[NF], v[WITH_U ? NF : 1];
     float gate, lam, beta, alpha;
 };
-// Wave-uniform bases and 32-bit lane offsets (a row of the tile is at most 15 stride_t away).
-template <bool WITH_U, int NF>
+// Wave-uniform bases and lane offsets in bytes (a row of the tile is at most 15 stride_t away): 32 bits, but for packed
+// tensors of 2^23 heads and more.
+template <bool FAR>
+using RowOffset = std::conditional_t<FAR, uint64_t, uint32_t>;
+inline bool far_rows(const SmallArgs &a) { return 2 * (15 * (uint64_t)a.stride_t + kDs) > 0xffffffffu; }
+template <bool WITH_U, int NF, bool FAR>
 __device__ __forceinline__ TileRows<WITH_U, NF> fetch_tile(const SmallArgs &a, int b, int h, int tile, int n, int kg)
 {
     TileRows<WITH_U, NF> in;
     const int64_t base = b * a.stride_b + 16 * (int64_t)tile * a.stride_t + h * a.stride_h;
     const int64_t ti = (b * (int64_t)a.T + 16 * tile) * a.H + h;
     const uint32_t i = min(n, a.T - 1 - 16 * tile);          // (rows past the end repeat the last one)
-    const uint32_t at = 2 * (i * (uint32_t)a.stride_t + 4 * kg), at_t = 4 * (i * (uint32_t)a.H);     // bytes
+    const RowOffset<FAR> at = 2 * (i * (RowOffset<FAR>)a.stride_t + 4 * kg);
+    const uint32_t at_t = 4 * (i * (uint32_t)a.H);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         in.k[f] = *(const u16x4 *)((const char *)((const uint16_t *)a.k + base + 16 * f) + at);
@@ -357,7 +362,7 @@ __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory")
 // transposed reads, and per-token scalars. d = 16, 6144 pairs x 197 tokens: 235 us for the whole forward pass with states
 // per chunk of 64 in memory and four key tiles, 98 us now; d = 32, 3072 x 300: 306 and 138 us.
 // Registers: 80 per lane at d = 16 (six waves per SIMD, which 6144 pairs fill), 128 or 168 at d = 32.
-template <bool WITH_U, int D>
+template <bool WITH_U, int D, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 16 ? 6 : WITH_U ? 3 : 4, 8)))
 void small_walk_kernel(SmallArgs a)
 {
@@ -399,13 +404,13 @@ void small_walk_kernel(SmallArgs a)
                 H[fi][fj] = Hs ? *(const f32x4 *)(Hs + e) : zero4();
                 U[fi][fj] = WITH_U && Us ? *(const f32x4 *)(Us + e) : zero4();
             }
-        next = fetch_tile<WITH_U, NF>(a, b, h, tile_begin, n, kg);
+        next = fetch_tile<WITH_U, NF, FAR>(a, b, h, tile_begin, n, kg);
     }
     for (int tile = tile_begin; tile < tile_end; ++tile) {
         // (lane-derived values formed anew in every tile: kept over the loop they would be spilled)
         const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
         const TileRows<WITH_U, NF> in = next;
-        next = fetch_tile<WITH_U, NF>(a, b, h, min(tile + 1, tile_end - 1), n, kg);
+        next = fetch_tile<WITH_U, NF, FAR>(a, b, h, min(tile + 1, tile_end - 1), n, kg);
         const bool valid = 16 * tile + n < a.T;
         const int64_t ti0 = (b * (int64_t)a.T + 16 * tile) * a.H + h;    // the tile's first token in [B,T,H]
 
@@ -562,7 +567,7 @@ void small_walk_kernel(SmallArgs a)
                     if (valid) {
                         const int64_t base = b * a.stride_b + 16 * (int64_t)tile * a.stride_t + h * a.stride_h;
                         char *o = (char *)((uint16_t *)a.o + base + 16 * fo);
-                        IOBF16::store4(o + 2 * ((uint32_t)n * (uint32_t)a.stride_t + 4 * kg), 0, y[0], y[1], y[2], y[3]);
+                        IOBF16::store4(o + 2 * ((RowOffset<FAR>)n * (RowOffset<FAR>)a.stride_t + 4 * kg), 0, y[0], y[1], y[2], y[3]);
                     }
                 }
             }
@@ -630,7 +635,9 @@ void launch_all(SmallArgs a, hipStream_t stream)
         hipLaunchKernelGGL((small_state_scan_kernel<WITH_U, D>), dim3((unsigned)a.n_pairs), dim3(D * D / 4), 0, stream, a);
     }
     const int64_t n_waves = (int64_t)a.n_pairs * a.n_segs * a.n_subs;
-    hipLaunchKernelGGL((small_walk_kernel<WITH_U, D>), dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, stream, a);
+    const dim3 grid((unsigned)((n_waves + 3) / 4));
+    if (far_rows(a)) hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, true>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, false>), grid, dim3(256), 0, stream, a);
 }
 }  // namespace
 
