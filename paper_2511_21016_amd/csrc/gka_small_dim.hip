@@ -437,9 +437,10 @@ void small_walk_kernel(SmallArgs a)
         if (tile >= solve_begin) {
             // (hardware exp2 here and below: decays under 2^-126 are flushed to zero)
             float zeta = __builtin_amdgcn_exp2f(Gc);
-            f32x4 m;
+            f32x4 decay;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) m[r] = (4 * kg + r <= n) ? __builtin_amdgcn_exp2f(Gc - Gj[r]) * bj[r] : 0.0f;
+            for (int r = 0; r < 4; ++r) decay[r] = (4 * kg + r <= n) ? __builtin_amdgcn_exp2f(Gc - Gj[r]) : 0.0f;
+            f32x4 m = decay * bj;
 
             // ---- H as A operand, value and remainder
             u16x4 Hv[NF][NF], Hr[NF][NF];          // [row block][contraction block]
@@ -454,9 +455,9 @@ void small_walk_kernel(SmallArgs a)
                 }
 
             // ---- Frobenius norm at every token (Section 4.2.1, the double sum folded by M[i,c] M[j,c] = M[j,c]^2 M[i,j]):
-            //   ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} m[j,c]^2 w_j,
-            //   w_j = 2 (zeta_j k_j^T H_[n] k_j + sum_{i<=j} m[i,j] G_ij^2) / beta_j - G_jj^2
-            // (G = K K^T; w_j = 0 for beta_j = 0)
+            //   ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} M[j,c]^2 w_j,
+            //   w_j = beta_j (2 (zeta_j k_j^T H_[n] k_j + sum_{i<=j} m[i,j] G_ij^2) - beta_j G_jj^2)
+            // (G = K K^T; M the decays without the write gate: no division by a gate, which may be as small as it likes)
             float fro;
             {
                 float w_part = 0.0f, diag = 0.0f;
@@ -475,15 +476,15 @@ void small_walk_kernel(SmallArgs a)
                     w_part += m[r] * g2;
                     diag = 4 * kg + r == n ? g2 : diag;
                 }
-                const float wc = sum_over_kg(2.0f * __builtin_amdgcn_rcpf(beta_c) * w_part - diag);
-                if (kg == 0) Wtab[n] = beta_c > 0.0f ? wc : 0.0f;
+                const float wc = beta_c * sum_over_kg(2.0f * w_part - beta_c * diag);
+                if (kg == 0) Wtab[n] = wc;
                 wave_lds_order();
                 const f32x4 wv = *(const f32x4 *)(Wtab + 4 * kg);
                 float f = 0.0f;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) f += m[r] * m[r] * wv[r];
+                for (int r = 0; r < 4; ++r) f += decay[r] * decay[r] * wv[r];
                 hn2 = lane_value(wave_inclusive_scan(hn2, lane), 63);
-                fro = __builtin_amdgcn_sqrtf(fmaxf(zeta * zeta * hn2 + sum_over_kg(f), 0.0f));
+                fro = sqrtf(fmaxf(zeta * zeta * hn2 + sum_over_kg(f), 0.0f));
             }
             if (a.fro_out && valid && kg == 0) (a.fro_out + ti0)[(uint32_t)n * a.H] = fro;
             const float lam = a.lambda ? in.lam : a.lambda_scale * fro;      // Section 4.1: lambda_t = a ||H_t||_F
@@ -494,7 +495,8 @@ void small_walk_kernel(SmallArgs a)
             const float s0 = 2.0f * rcp;
             const float rho = (L - mu) * rcp, rho2 = rho * rho;
             zeta = fmaxf(zeta, kMinZeta);
-            const float rz = __builtin_amdgcn_rcpf(zeta);
+            float rz = __builtin_amdgcn_rcpf(zeta);
+            rz += rz * (1.0f - zeta * rz);                       // (rounded as a division is)
             m *= rz;
             f32x4 xi[NF], dl[NF], gn[NF];
 #pragma unroll
