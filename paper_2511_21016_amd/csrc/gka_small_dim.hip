@@ -484,7 +484,10 @@ void small_walk_kernel(SmallArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) f += decay[r] * decay[r] * wv[r];
                 hn2 = lane_value(wave_inclusive_scan(hn2, lane), 63);
-                fro = sqrtf(fmaxf(zeta * zeta * hn2 + sum_over_kg(f), 0.0f));
+                // (the hardware's root takes a denormal argument for zero: the norm of a state below 1e-19)
+                const float fro2 = fmaxf(zeta * zeta * hn2 + sum_over_kg(f), 0.0f);
+                const bool tiny = fro2 < 0x1p-96f;
+                fro = __builtin_amdgcn_sqrtf(tiny ? 0x1p64f * fro2 : fro2) * (tiny ? 0x1p-32f : 1.0f);
             }
             if (a.fro_out && valid && kg == 0) (a.fro_out + ti0)[(uint32_t)n * a.H] = fro;
             const float lam = a.lambda ? in.lam : a.lambda_scale * fro;      // Section 4.1: lambda_t = a ||H_t||_F
@@ -495,8 +498,7 @@ void small_walk_kernel(SmallArgs a)
             const float s0 = 2.0f * rcp;
             const float rho = (L - mu) * rcp, rho2 = rho * rho;
             zeta = fmaxf(zeta, kMinZeta);
-            float rz = __builtin_amdgcn_rcpf(zeta);
-            rz += rz * (1.0f - zeta * rz);                       // (rounded as a division is)
+            const float rz = __builtin_amdgcn_rcpf(zeta);
             m *= rz;
             f32x4 xi[NF], dl[NF], gn[NF];
 #pragma unroll
