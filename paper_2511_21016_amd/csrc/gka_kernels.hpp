@@ -227,7 +227,8 @@ struct SmallArgs {
     float *H_final, *U_final;     // optional
     int T, H, n_pairs, n_chunks, n_iter;
     float *dH, *sH, *dU, *sU, *chunk_log2_decay;   // carved from the workspace by the launcher
-    int n_segs, seg_chunks, n_subs; // set by the launcher: segments of the walk, chunks each, waves per segment
+    bool whole;                   // set by the launcher: walks start at H_init, U_init (else at the states before a chunk);
+    int n_segs, seg_chunks, n_subs; // segments of the walk, chunks each, waves per segment
 };
 size_t small_dim_workspace_bytes(int n_pairs, int n_chunks, int d, bool with_readout);
 hipError_t launch_small_dim_forward(SmallArgs a, void *workspace, hipStream_t stream);

@@ -383,7 +383,7 @@ void small_walk_kernel(SmallArgs a)
     const int tile_begin = seg * seg_tiles, solve_begin = tile_begin + sub * (seg_tiles / a.n_subs);
     const int tile_end = min(solve_begin + seg_tiles / a.n_subs, n_tiles);
     if (solve_begin >= n_tiles) return;
-    const bool finishes = a.n_segs == 1 && tile_end == n_tiles;
+    const bool finishes = a.whole && tile_end == n_tiles;
     uint16_t *rows = s_k[w], *vrows = s_v[w];
     float *Gtab = s_tab[w], *Btab = Gtab + 16, *Wtab = Gtab + 32;
     const PaddedRows at = {16};                // tiles of 16 rows x 16 features
@@ -393,7 +393,7 @@ void small_walk_kernel(SmallArgs a)
     TileRows<WITH_U, NF> next;
     {
         const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
-        const bool first = a.n_segs == 1;
+        const bool first = a.whole;
         const int64_t s0 = first ? (int64_t)pair * (D * D) : (pair * (int64_t)a.n_chunks + seg * a.seg_chunks) * (D * D);
         const float *Hs = first ? a.H_init : a.sH, *Us = first ? a.U_init : a.sU;
 #pragma unroll
@@ -628,6 +628,7 @@ void launch_all(SmallArgs a, hipStream_t stream)
     const bool whole = !(few && in_place) &&
                        (a.n_pairs >= Rule::many_pairs || a.n_chunks <= Rule::short_chunks ||
                         (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units));
+    a.whole = whole;
     a.seg_chunks = whole ? a.n_chunks : 1;
     a.n_segs = whole ? 1 : a.n_chunks;
     // (outputs that replace the rows of k or v: no wave advances the states over tiles that another one solves)
