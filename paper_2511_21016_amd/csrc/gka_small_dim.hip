@@ -37,19 +37,24 @@ constexpr float kMinZeta = 0x1p-60f;       // floor of zeta_c where the system i
 // How the walks are cut (us per forward pass, bf16, r = 10):
 // * One walk per pair, without the two launches that compute the states before every chunk: with many pairs, which fill
 //   the SIMDs (d = 16, 6144 pairs x 197 tokens 98 against 140 chunk by chunk, 2400 x 400 98 and 98, 1200 x 785 143 and 96;
-//   d = 32, 3072 x 300 137 and 240, 1200 x 785 235 and 252, 768 x 785 162 and 150), and with up to two chunks (d = 16,
-//   768 x 128: 20 against 27).
-// * At most kFewChunks chunks in all leave SIMDs empty: a wave per tile, which advances the states over the tiles between
-//   the last known ones and its own (a sixth of the work of solving them; d = 16, 24 x 128: 9 against 18 with a wave per
-//   chunk). A short sequence is then walked from its start, too, while the waves are few (24 x 197: 11 against 17; d = 16,
-//   192 x 250, 768 chunks: 22 against 18.5; d = 32: 27.5 and 29).
+//   d = 32, 3072 x 300 137 and 240, 1024 x 400 84 and 103, 768 x 785 162 and 150), and with up to two chunks (d = 16,
+//   768 x 100: 17 against 19).
+// * Up to chunk_workgroups chunks in all the four waves of a workgroup take a chunk (d = 16, 192 x 500, 1536 chunks: 21.8
+//   against 22.9 with two waves that advance over each other's tiles, 384 x 500, 3072 chunks: 31.4 and 32.1, 768 x 300, 3840:
+//   35.0 and 33.9 with one wave; d = 32, 256 x 400, 1792 chunks: 37.2 and 40.5, 576 x 197, 2304 chunks: 43.1 and 41.7).
+// * Where such a sequence is short it is walked from its start all the same, in one launch, by a wave per tile that advances
+//   the states over the tiles before its own without solving them (d = 16, 13 tiles, 48 pairs: 11.4 against 12.3 by chunks,
+//   96 pairs 13.0 and 12.7, 10 tiles, 192 pairs 12.1 and 13.6, 256 pairs 14.3 and 14.1, 16 tiles, 48 pairs 13.0 and 12.3 to
+//   14.4 (what three launches take of the host), 96 pairs 15.7 and 12.7; d = 32, 10 tiles, 288 pairs 23.8 and 26.6, 13 tiles,
+//   96 pairs 20.5 and 19.2): few_walk_work bounds pairs x tiles^3, which these turning points have in common.
 template <int D>
 struct WalkRule {
     static constexpr int many_pairs = D == 16 ? 2048 : 1024;
     static constexpr int short_chunks = 2;
-    static constexpr int few_walk_chunks = D == 16 ? 5 : 4, few_walk_units = D == 16 ? 512 : 1024;
+    static constexpr int chunk_workgroups = D == 16 ? 3072 : 2048;
+    static constexpr int few_walk_tiles = D == 16 ? 16 : 10, few_walk_work = D == 16 ? 1 << 18 : 360000;
 };
-constexpr int kFewChunks = 1024;
+constexpr int kTileWaveChunks = 1024;      // up to this many chunks in all a walk from the start has a wave per tile
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c)
@@ -131,7 +136,9 @@ __device__ __forceinline__ void stage_rows(const SmallArgs &a, const void *x, ui
 // of K^T[fi] (w o K)[fj]: A = features x keys, B = keys x features, both gathered column-wise from the LDS tile of key
 // rows; stored transposed (Delta H is symmetric up to the rounding of w o K), so that a lane holds four consecutive
 // elements of a row. Delta U^T tile (fi, fj) = K^T[fi] (w o V)[fj], stored transposed likewise: row-major Delta U.
-template <bool WITH_U, int D>
+// REM: the weighted rows enter as bf16 value + remainder (the states are then as exact as those of a walk from the start; half as
+// long again where chunks are many).
+template <bool WITH_U, int D, bool REM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void small_chunk_delta_kernel(SmallArgs a)
 {
     constexpr int NF = D / 16;                 // feature tiles that exist; a state is stored as D x D
@@ -161,24 +168,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         const f32x4 w0 = *(const f32x4 *)&s_w[w][32 * ks + 4 * kg], w1 = *(const f32x4 *)&s_w[w][32 * ks + 16 + 4 * kg];
-        bf16x8 kt[2], wk[2], wv[2];
+        bf16x8 kt[2], wk[2], wk_rem[2], wv[2], wv_rem[2];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             f32x4 lo, hi;
             kt[f] = gather_transposed_bf16(s_k[w], at, 16 * f, lane, 32 * ks + 4 * kg, 32 * ks + 16 + 4 * kg);
             unpack8(kt[f], lo, hi);
-            wk[f] = pack8(lo * w0, hi * w1);
+            split8(lo * w0, hi * w1, wk[f], wk_rem[f]);
             if constexpr (WITH_U) {
                 unpack8(gather_transposed_bf16(s_v[w], at, 16 * f, lane, 32 * ks + 4 * kg, 32 * ks + 16 + 4 * kg), lo,
                         hi);
-                wv[f] = pack8(lo * w0, hi * w1);
+                split8(lo * w0, hi * w1, wv[f], wv_rem[f]);
             }
         }
 #pragma unroll
         for (int fi = 0; fi < NF; ++fi)
 #pragma unroll
             for (int fj = 0; fj < NF; ++fj) {
+                if constexpr (REM) accH[fi][fj] = mma16(kt[fi], wk_rem[fj], accH[fi][fj]);
                 accH[fi][fj] = mma16(kt[fi], wk[fj], accH[fi][fj]);
+                if constexpr (WITH_U && REM) accU[fi][fj] = mma16(kt[fi], wv_rem[fj], accU[fi][fj]);
                 if constexpr (WITH_U) accU[fi][fj] = mma16(kt[fi], wv[fj], accU[fi][fj]);
             }
     }
@@ -361,31 +370,55 @@ __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory")
 // the chain of dependent products (0.11 us per pass, 1 us per tile). No barrier: LDS holds a wave's own 16 rows, for the
 // transposed reads, and per-token scalars. d = 16, 6144 pairs x 197 tokens: 235 us for the whole forward pass with states
 // per chunk of 64 in memory and four key tiles, 98 us now; d = 32, 3072 x 300: 306 and 138 us.
-// Registers: 80 per lane at d = 16 (six waves per SIMD, which 6144 pairs fill), 128 or 168 at d = 32.
-template <bool WITH_U, int D, bool FAR>
+// Registers: 68 per lane at d = 16 (seven waves per SIMD; 6144 pairs fill six), at d = 32 110 without and 138 with the readout.
+// WALK_FAR: 64-bit row offsets. WALK_CHUNK: the four waves of a workgroup take the four tiles of one chunk, each from the states
+// before the chunk, which it advances over the tiles before its own from rows that the four waves have put into LDS (one
+// barrier). With a wave per tile that fetched those rows itself, memory was waited for at every tile: d = 32, 144 pairs x 300
+// tokens 32.3 us per forward pass, 23.2 now; sketched solve of 64 x 1000 tokens 65.0 and 56.2. (Four waves that solve against
+// the state before the chunk, up to four key tiles per pass, are as fast, 22.5 and 58.0, but round the masked products of 64
+// keys: 2.85e-3 from float64 instead of 2.60e-3.)
+enum { WALK_NEAR, WALK_FAR, WALK_CHUNK };
+template <bool WITH_U, int D, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 16 ? 6 : WITH_U ? 3 : 4, 8)))
 void small_walk_kernel(SmallArgs a)
 {
     constexpr int NF = D / 16;                 // feature tiles
+    constexpr bool FAR = MODE == WALK_FAR, CHUNK = MODE == WALK_CHUNK;
     typedef Products<NF> MM;
     __shared__ __attribute__((aligned(16))) uint16_t s_k[4][NF * 256];
     __shared__ __attribute__((aligned(16))) uint16_t s_v[4][WITH_U ? NF * 256 : 8];
     __shared__ __attribute__((aligned(16))) float s_tab[4][3 * 16];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // consecutive waves: the same segment of consecutive pairs (adjacent memory in the [B,T,H,d] layout)
-    const unsigned unit = blockIdx.x * 4 + w;
-    if (unit >= (unsigned)a.n_pairs * a.n_segs * a.n_subs) return;
+    // consecutive waves (CHUNK: workgroups): the same segment of consecutive pairs (adjacent memory in the [B,T,H,d] layout)
+    const unsigned unit = CHUNK ? blockIdx.x : blockIdx.x * 4 + w;
+    if (!CHUNK && unit >= (unsigned)a.n_pairs * a.n_segs * a.n_subs) return;
     const int pair = unit % (unsigned)a.n_pairs, part = unit / (unsigned)a.n_pairs;
-    const int seg = part / a.n_subs, sub = part - seg * a.n_subs;
+    const int seg = CHUNK ? part : part / a.n_subs, sub = CHUNK ? w : part - seg * a.n_subs;
     const int b = pair / a.H, h = pair % a.H;
     // the states are known at tile_begin; tiles from solve_begin on are this wave's
     const int seg_tiles = a.seg_chunks * (kChunk / 16), n_tiles = (a.T + 15) / 16;
-    const int tile_begin = seg * seg_tiles, solve_begin = tile_begin + sub * (seg_tiles / a.n_subs);
-    const int tile_end = min(solve_begin + seg_tiles / a.n_subs, n_tiles);
-    if (solve_begin >= n_tiles) return;
-    const bool finishes = a.whole && tile_end == n_tiles;
+    const int sub_tiles = CHUNK ? 1 : seg_tiles / a.n_subs;
+    const int tile_begin = seg * seg_tiles, solve_begin = tile_begin + sub * sub_tiles;
+    const int tile_end = min(solve_begin + sub_tiles, n_tiles);
+    if (!CHUNK && solve_begin >= n_tiles) return;
+    const bool finishes = !CHUNK && a.whole && tile_end == n_tiles;
     uint16_t *rows = s_k[w], *vrows = s_v[w];
     float *Gtab = s_tab[w], *Btab = Gtab + 16, *Wtab = Gtab + 32;
+    // a tile's rows and scalars into the wave's LDS; returns the decays before its tokens
+    auto publish = [&](const TileRows<WITH_U, NF> &in, int tile, int n, int kg) {
+        const bool valid = 16 * tile + n < a.T;
+        const float G = row_inclusive_scan(valid ? log2_gate(in.gate) : 0.0f);
+        if (kg == 0) {
+            Gtab[n] = G;
+            Btab[n] = valid ? in.beta : 0.0f;  // (tokens past the end weigh nothing)
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            *(u16x4 *)(rows + f * 256 + 16 * n + 4 * kg) = in.k[f];
+            if constexpr (WITH_U) *(u16x4 *)(vrows + f * 256 + 16 * n + 4 * kg) = in.v[f];
+        }
+        return G;
+    };
     const PaddedRows at = {16};                // tiles of 16 rows x 16 features
 
     // ---- states before the segment: accumulator tile (fi, fj) holds S[16 fj + n][16 fi + 4 kg + r]
@@ -393,7 +426,7 @@ void small_walk_kernel(SmallArgs a)
     TileRows<WITH_U, NF> next;
     {
         const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
-        const bool first = a.whole;
+        const bool first = !CHUNK && a.whole;
         const int64_t s0 = first ? (int64_t)pair * (D * D) : (pair * (int64_t)a.n_chunks + seg * a.seg_chunks) * (D * D);
         const float *Hs = first ? a.H_init : a.sH, *Us = first ? a.U_init : a.sU;
 #pragma unroll
@@ -404,29 +437,34 @@ void small_walk_kernel(SmallArgs a)
                 H[fi][fj] = Hs ? *(const f32x4 *)(Hs + e) : zero4();
                 U[fi][fj] = WITH_U && Us ? *(const f32x4 *)(Us + e) : zero4();
             }
-        next = fetch_tile<WITH_U, NF, FAR>(a, b, h, tile_begin, n, kg);
+        next = fetch_tile<WITH_U, NF, FAR>(a, b, h, CHUNK ? min(solve_begin, n_tiles - 1) : tile_begin, n, kg);
+        if constexpr (CHUNK) {
+            publish(next, solve_begin, n, kg);
+            __syncthreads();
+            if (solve_begin >= n_tiles) return;              // (none of the wave's tokens exists)
+        }
     }
     for (int tile = tile_begin; tile < tile_end; ++tile) {
         // (lane-derived values formed anew in every tile: kept over the loop they would be spilled)
         const int lane = fresh_lane(), n = lane & 15, kg = lane >> 4;
-        const TileRows<WITH_U, NF> in = next;
-        next = fetch_tile<WITH_U, NF, FAR>(a, b, h, min(tile + 1, tile_end - 1), n, kg);
+        const TileRows<WITH_U, NF> in = next;                // (CHUNK: of the wave's own tile, the last of its loop)
+        if constexpr (!CHUNK) next = fetch_tile<WITH_U, NF, FAR>(a, b, h, min(tile + 1, tile_end - 1), n, kg);
         const bool valid = 16 * tile + n < a.T;
         const int64_t ti0 = (b * (int64_t)a.T + 16 * tile) * a.H + h;    // the tile's first token in [B,T,H]
 
-        // ---- per-token scalars and rows through the wave's LDS
-        const float Gc = row_inclusive_scan(valid ? log2_gate(in.gate) : 0.0f);
+        // ---- per-token scalars and rows through LDS
+        float Gc;
+        if constexpr (CHUNK) {
+            rows = s_k[tile - tile_begin];
+            vrows = s_v[tile - tile_begin];
+            Gtab = s_tab[tile - tile_begin];
+            Btab = Gtab + 16;
+            Gc = Gtab[n];
+        } else {
+            Gc = publish(in, tile, n, kg);
+        }
         const float Gt = lane_value(Gc, 15);
-        const float beta_c = valid ? in.beta : 0.0f;         // (tokens past the end weigh nothing)
-        if (kg == 0) {
-            Gtab[n] = Gc;
-            Btab[n] = beta_c;
-        }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            *(u16x4 *)(rows + f * 256 + 16 * n + 4 * kg) = in.k[f];
-            if constexpr (WITH_U) *(u16x4 *)(vrows + f * 256 + 16 * n + 4 * kg) = in.v[f];
-        }
+        const float beta_c = valid ? in.beta : 0.0f;
         wave_lds_order();
         const f32x4 Gj = *(const f32x4 *)(Gtab + 4 * kg), bj = *(const f32x4 *)(Btab + 4 * kg);
         u16x4 kT[NF];                          // column 16 f + n of the keys 4 kg .. 4 kg + 3
@@ -543,12 +581,14 @@ void small_walk_kernel(SmallArgs a)
             }
             // the next tile's rows are awaited here, where they have had the passes to arrive: behind the conditional store of
             // the outputs the wait would be for that store too
+            if constexpr (!CHUNK) {
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                asm volatile("" : "+v"(next.k[f]), "+v"(next.q[f]));
-                if constexpr (WITH_U) asm volatile("" : "+v"(next.v[f]));
+                for (int f = 0; f < NF; ++f) {
+                    asm volatile("" : "+v"(next.k[f]), "+v"(next.q[f]));
+                    if constexpr (WITH_U) asm volatile("" : "+v"(next.v[f]));
+                }
+                asm volatile("" : "+v"(next.gate), "+v"(next.lam), "+v"(next.beta), "+v"(next.alpha));
             }
-            asm volatile("" : "+v"(next.gate), "+v"(next.lam), "+v"(next.beta), "+v"(next.alpha));
             if constexpr (WITH_U) {
                 // ---- readout y_c = zeta_c U_[n] x_c + sum_{j<=c} m[j,c] v_j (k_j . x_c), x = alpha xhat + (1 - alpha) q
                 // (Section 4.3), formed with the mask divided by zeta_c and multiplied by zeta_c at the end
@@ -620,29 +660,37 @@ template <bool WITH_U, int D>
 void launch_all(SmallArgs a, hipStream_t stream)
 {
     const int64_t n_units = (int64_t)a.n_pairs * a.n_chunks;
-    const bool few = n_units <= kFewChunks;
     typedef WalkRule<D> Rule;
+    const bool tile_waves = n_units <= kTileWaveChunks;
+    const int64_t n_tiles = (a.T + 15) / 16;
     // (final states in the buffers of the initial ones: not where several waves of a pair would start from the initial states
     // while one of them writes the final ones; the scan reads and writes each of their elements in one thread)
     const bool in_place = a.H_final && (a.H_final == a.H_init || a.U_final == a.U_init);
-    const bool whole = !(few && in_place) &&
+    const bool whole = !(tile_waves && in_place) &&
                        (a.n_pairs >= Rule::many_pairs || a.n_chunks <= Rule::short_chunks ||
-                        (a.n_chunks <= Rule::few_walk_chunks && n_units <= Rule::few_walk_units));
+                        (tile_waves && n_tiles <= Rule::few_walk_tiles &&
+                         a.n_pairs * n_tiles * n_tiles * n_tiles <= Rule::few_walk_work));
     a.whole = whole;
     a.seg_chunks = whole ? a.n_chunks : 1;
     a.n_segs = whole ? 1 : a.n_chunks;
     // (outputs that replace the rows of k or v: no wave advances the states over tiles that another one solves)
     const bool over_rows = a.o && (a.o == a.k || a.o == a.v);
-    a.n_subs = over_rows ? 1 : few ? a.seg_chunks * (kChunk / 16) : !whole && n_units <= 2 * kFewChunks ? 2 : 1;
+    a.n_subs = whole && tile_waves && !over_rows ? a.seg_chunks * (kChunk / 16) : 1;
+    const bool by_chunk = !whole && n_units <= Rule::chunk_workgroups;
     if (!whole) {
-        hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D>), dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, stream,
-                           a);
+        const dim3 grid((unsigned)((n_units + 3) / 4));
+        if (by_chunk) hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D, true>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((small_chunk_delta_kernel<WITH_U, D, false>), grid, dim3(256), 0, stream, a);
         hipLaunchKernelGGL((small_state_scan_kernel<WITH_U, D>), dim3((unsigned)a.n_pairs), dim3(D * D / 4), 0, stream, a);
+    }
+    if (by_chunk) {
+        hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, WALK_CHUNK>), dim3((unsigned)n_units), dim3(256), 0, stream, a);
+        return;
     }
     const int64_t n_waves = (int64_t)a.n_pairs * a.n_segs * a.n_subs;
     const dim3 grid((unsigned)((n_waves + 3) / 4));
-    if (far_rows(a)) hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, true>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, false>), grid, dim3(256), 0, stream, a);
+    if (far_rows(a)) hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, WALK_FAR>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((small_walk_kernel<WITH_U, D, WALK_NEAR>), grid, dim3(256), 0, stream, a);
 }
 }  // namespace
 

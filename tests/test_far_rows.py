@@ -16,8 +16,9 @@ assert st == binding.GKA_OK, binding.status_string(st)
 """)
     walk = calls[-1]
     assert walk["kernel"] == "small_walk_kernel"
-    # (the last template argument; rows of the tile are up to 15 H d elements of 2 bytes away, features up to 64 bytes)
-    assert walk["mangled"].split("EEE")[0].endswith("Lb1" if far else "Lb0")
+    # (the last template argument: WALK_NEAR, WALK_FAR; rows of the tile are up to 15 H d elements of 2 bytes away, features
+    # up to 64 bytes)
+    assert walk["mangled"].split("EEE")[0].endswith("Li1" if far else "Li0")
     assert far == (2 * (15 * H * d + 32) > 0xffffffff)
 
 

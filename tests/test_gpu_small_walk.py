@@ -1,7 +1,6 @@
 """GPU parity of the walk kernel of the head dimensions 16 and 32 (bf16 tensors and operands) against the fp64 oracle, at
 the edges of its tiles (16 tokens) and on problems of every way in which its walks are cut: a wave per tile from the
-sequence's start, a wave per tile from the states before its chunk, two waves per chunk, one wave per chunk, one walk per
-pair."""
+sequence's start, a workgroup of four waves per chunk, one wave per chunk, one walk per pair."""
 import numpy as np
 import pytest
 
@@ -15,9 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("variants", [False, True])
 @pytest.mark.parametrize("d,B,H,T", [
     (16, 2, 3, 1), (16, 2, 2, 17), (16, 1, 3, 64), (32, 2, 3, 15), (32, 1, 2, 128), (32, 2, 3, 250),     # tile by tile
-    (16, 2, 3, 321), (16, 32, 5, 257), (32, 1, 3, 257),              # tile by tile from the states before the chunk
-    (16, 15, 12, 390), (32, 10, 15, 401),                            # two waves per chunk
-    (16, 16, 12, 705), (32, 19, 10, 721),                            # one wave per chunk
+    (16, 2, 3, 321), (16, 32, 5, 257), (32, 1, 3, 257),              # four waves per chunk
+    (16, 15, 12, 390), (32, 10, 15, 401), (16, 16, 12, 705),
+    (32, 19, 10, 721), (16, 60, 10, 401), (32, 64, 10, 257),         # one wave per chunk
     (16, 41, 25, 65), (16, 128, 16, 145), (32, 64, 16, 129)])        # one walk per pair
 def test_small_walk(d, B, H, T, variants):
     import torch
@@ -42,7 +41,12 @@ def test_small_walk(d, B, H, T, variants):
                               return_xhat=variants, **kw)
     # Rounding to bf16 is uniform within 2^-9 of a value, 1.1e-3 in the 2-norm: the output once, the update delta of every
     # pass and the masked products, which the solve adds up and amplifies on some tokens (two times the output's share in
-    # all). A tile gone wrong in one of n pairs of m tiles shows as (n m)^-1/2, 7e-3 at the largest size here.
+    # all). A token gone wrong in one pair does not show in that norm of all of them: it does in the pair's own, as T^-1/2,
+    # 3.7e-2 at the longest here. (The largest difference of the worst of thousands of pairs would not do: it is that of the
+    # one token whose solve amplifies rounding most, 2.4e-2 of the pair's largest value here.)
+    diff = to_host(o) - ref
+    pair = np.sqrt((diff ** 2).sum(axis=(1, 3)) / (ref ** 2).sum(axis=(1, 3)))
+    assert pair.max() <= 2e-2, pair.max()
     assert np.linalg.norm(to_host(o) - ref) <= 6e-3 * np.linalg.norm(ref)
     assert np.abs(to_host(ex["fro"]) - rex["fro"]).max() <= 5e-3 * rex["fro"].max()
     if variants:

@@ -29,9 +29,12 @@ def test_float32_products(d, B, H, T, dtype, blocks, o):
 
 
 @pytest.mark.parametrize("o", ["V", "K"])
-@pytest.mark.parametrize("d,B,H,T", [(16, 2, 3, 128), (16, 4, 6, 197), (32, 2, 3, 500), (16, 15, 12, 390)])
+@pytest.mark.parametrize("d,B,H,T", [(16, 2, 3, 128), (16, 4, 6, 197), (32, 2, 3, 150), (32, 2, 3, 500), (16, 15, 12, 390)])
 def test_small_head_dims(d, B, H, T, o):
     plan = _launches(d, B, H, T, "bf16", o)
+    if plan[-1]["mangled"].split("EEE")[0].endswith("Li2"):    # WALK_CHUNK: a workgroup has read its chunk before it stores
+        assert plan[-1]["grid"] == B * H * ((T + 63) // 64)
+        return
     walks_per_pair = (T + 63) // 64 if "small_state_scan_kernel" in [c["kernel"] for c in plan] else 1
     assert plan[-1]["kernel"] == "small_walk_kernel" and plan[-1]["grid"] == (B * H * walks_per_pair + 3) // 4
 
