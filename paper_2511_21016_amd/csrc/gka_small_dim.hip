@@ -40,8 +40,8 @@ constexpr float kMinZeta = 0x1p-60f;       // floor of zeta_c where the system i
 //   d = 32, 3072 x 300 137 and 240, 1024 x 400 84 and 103, 768 x 785 162 and 150), and with up to two chunks (d = 16,
 //   768 x 100: 17 against 19).
 // * Up to chunk_workgroups chunks in all the four waves of a workgroup take a chunk (d = 16, 192 x 500, 1536 chunks: 21.8
-//   against 22.9 with two waves that advance over each other's tiles, 384 x 500, 3072 chunks: 31.4 and 32.1, 768 x 300, 3840:
-//   35.0 and 33.9 with one wave; d = 32, 256 x 400, 1792 chunks: 37.2 and 40.5, 576 x 197, 2304 chunks: 43.1 and 41.7).
+//   against 22.9 with two waves that advance over each other's tiles, 576 x 197, 2304 chunks: 24.5 and 25.6 with one wave,
+//   768 x 250, 3072: 31.3 and 29.6; d = 32, 256 x 400, 1792 chunks: 37.2 and 40.5, 576 x 197, 2304 chunks: 43.1 and 41.7).
 // * Where such a sequence is short it is walked from its start all the same, in one launch, by a wave per tile that advances
 //   the states over the tiles before its own without solving them (d = 16, 13 tiles, 48 pairs: 11.4 against 12.3 by chunks,
 //   96 pairs 13.0 and 12.7, 10 tiles, 192 pairs 12.1 and 13.6, 256 pairs 14.3 and 14.1, 16 tiles, 48 pairs 13.0 and 12.3 to
@@ -51,7 +51,7 @@ template <int D>
 struct WalkRule {
     static constexpr int many_pairs = D == 16 ? 2048 : 1024;
     static constexpr int short_chunks = 2;
-    static constexpr int chunk_workgroups = D == 16 ? 3072 : 2048;
+    static constexpr int chunk_workgroups = D == 16 ? 2560 : 2048;
     static constexpr int few_walk_tiles = D == 16 ? 16 : 10, few_walk_work = D == 16 ? 1 << 18 : 360000;
 };
 constexpr int kTileWaveChunks = 1024;      // up to this many chunks in all a walk from the start has a wave per tile
