@@ -144,7 +144,10 @@ void decode_step_kernel(DecodeArgs a)
     f32x4 upre[STREAM ? NI : 1];
     if constexpr (STREAM) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) upre[i] = __builtin_nontemporal_load((const f32x4 *)((Uin ? Uin : Us) + piece(0, i)));
+        for (int i = 0; i < NI; ++i) {
+            upre[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (Uin) upre[i] = __builtin_nontemporal_load((const f32x4 *)(Uin + piece(0, i)));
+        }
     }
     if constexpr (LOWER) {
         constexpr int NOFF = NI * (NI - 1) / 2;
@@ -283,10 +286,12 @@ void decode_step_kernel(DecodeArgs a)
         for (int rr = 0; rr < R; ++rr) acc[rr] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (STREAM_U) {
             // four pieces at a time: read, advanced, used and written back. From the caller's initial state at the first
-            // token, afterwards what this same lane stored at the previous token. (A zero initial state: the loads, from
-            // the final state's buffer, are replaced by zeros; no branch around a load.)
+            // token, afterwards what this same lane stored at the previous token. A zero initial state: a single token reads
+            // nothing (d = 256, one token of 256 pairs: 22.1 us, 32.2 with the loads replaced by zeros). With several tokens a
+            // branch around the loads makes the compiler spill 92 registers: there they go to a few rows of the final state,
+            // the same for all waves, and zeros take their place.
             const bool zero = tok == 0 && !Uin;
-            const float *Usrc = (tok > 0 || !Uin ? Us : Uin) + voff;
+            const float *Usrc = (zero ? Us - row0 * D : tok > 0 ? Us : Uin) + voff;
 #pragma unroll
             for (int rr = 0; rr < R; ++rr)
 #pragma unroll
@@ -298,14 +303,16 @@ void decode_step_kernel(DecodeArgs a)
                     for (int i = 0; i < 4; ++i) {
                         const f32x4 *src = (const f32x4 *)(Usrc + piece(rr, i0 + i));
                         if (STREAM && rr == 0) u[i] = upre[i0 + i];
-                        else u[i] = MULTI ? *src : __builtin_nontemporal_load(src);
+                        else if (MULTI) u[i] = *src;
+                        else if (zero) u[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                        else u[i] = __builtin_nontemporal_load(src);
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const f32x4 kc = columns(s_in[1], i0 + i), xc = columns(s_x[buf], i0 + i);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            u[i][e] = __builtin_fmaf(gamma, zero ? 0.0f : u[i][e], vs * kc[e]);
+                            u[i][e] = __builtin_fmaf(gamma, MULTI && zero ? 0.0f : u[i][e], vs * kc[e]);
                             acc[rr][e] += u[i][e] * xc[e];
                         }
                         f32x4 *dst = (f32x4 *)(Us + voff + piece(rr, i0 + i));
