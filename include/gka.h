@@ -252,12 +252,12 @@ gka_status gka_decode_tokens(const gka_params *p,
 /* Backward pass of the layer by implicit differentiation (Section 4.2.2 "Backward Pass", Appendix B.2): given
  * dy_t = dL/dy_t, the gradients at q, k, v, the gates and lambda (and at the write gate and the alpha-connection if
  * they are in use). The forward solve's result is treated as the exact solution of its system and both solves run
- * r passes of Algorithm 1 (dq_t = CH(H_t + lambda_t I, dxhat_t, r)), as in the paper. The two solves run on the
- * forward kernels; the reverse recurrences of Section 4.2.2 are six gated-linear-attention readouts (seven on bf16
- * tensors, where the output is read out again from the stored operand for the gate gradient), four of them
- * walking the sequence backwards (one kernel with the state in registers for GKA_BF16 tensors, the forward kernels
- * on reversed copies for GKA_F32 tensors), plus a few elementwise kernels: about five times the cost of gka_forward
- * with bf16 tensors and operands; the paper's chunk-wise backward kernels are not reproduced.
+ * r passes of Algorithm 1 (dq_t = CH(H_t + lambda_t I, dxhat_t, r)), as in the paper. GKA_BF16 tensors: both
+ * solves share one pass over the forward pass's chunk states, two gated-linear-attention readouts give U_t^T dy_t and
+ * p_t . H_t xhat_t (the rule for lambda: two more), and one walk over the sequence from its end forms the reverse
+ * recurrences of Section 4.2.2 (two walks with an alpha-connection). GKA_F32 tensors: the forward kernels for two solves
+ * and six readouts (eight with the rule), four of them on reversed copies. Either way a few elementwise kernels: about five
+ * times the cost of gka_forward with bf16 tensors and operands; the paper's chunk-wise backward kernels are not reproduced.
  *   Supported: lambda given or NULL with p->lambda_scale > 0 (the rule lambda_t = a ||H_t||_F, whose w_t H_t terms
  *   of the Lemma in Section 4.2.2 cost two more readouts), zero initial states (gka_backward_from_state takes
  *   others), p->beta and p->alpha as in gka_forward. Explicit strides apply to q, k, v and dy (multiples of 16
@@ -268,8 +268,8 @@ gka_status gka_decode_tokens(const gka_params *p,
  *   q, k, v, dy  [B,T,H,d] io_dtype, 16-byte aligned;  gate, lambda [B,T,H] float32
  *   dq, dk, dv   [B,T,H,d] float32, 16-byte aligned (written);  dgate [B,T,H] float32 (written)
  *   dlambda, dbeta, dalpha [B,T,H] float32, each written if not NULL (dlambda only when lambda is given)
- *   workspace: gka_backward_workspace_bytes(p) bytes, 256-byte aligned (about 24 tensors of the size of q in
- *   io_dtype plus the forward workspace); contents unspecified afterwards. */
+ *   workspace: gka_backward_workspace_bytes(p) bytes, 256-byte aligned (GKA_BF16 tensors: the size of 17 tensors like q,
+ *   GKA_F32 tensors: of 23, plus the forward workspace); contents unspecified afterwards. */
 size_t gka_backward_workspace_bytes(const gka_params *p);
 gka_status gka_backward(const gka_params *p,
                         const void *q, const void *k, const void *v,

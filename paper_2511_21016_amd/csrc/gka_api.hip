@@ -531,19 +531,21 @@ void plan_reverse_segments(int n_pairs, int n_chunks, int *n_segs, int *seg_len)
     *n_segs = (n_chunks + *seg_len - 1) / *seg_len;
 }
 
+// Tensors of the backward pass in the tensors' dtype: those of float32 tensors alone, those of both, those of bf16 tensors.
+enum { IO_Y, IO_DXT, IO_HX, IO_KR, IO_VR, IO_DYR, IO_XR, IO_XTR, IO_R1, IO_R2, IO_R3, IO_R4,
+       IO_RHS, IO_BF16_FIRST = IO_RHS, IO_X, IO_XT, IO_PR, IO_SCRATCH, IO_HK, IO_VPR, IO_R5,
+       IO_RHS_LO, IO_REMAINDERS = IO_RHS_LO, IO_X_LO, IO_XT_LO, IO_TENSORS };
+
 struct BackwardPlan {
     size_t n_elems, n_tokens, esz;
     size_t off_f32[3];        // xhat, p; bf16 tensors: U^T dy
-    size_t off_io[23];
+    size_t off_io[IO_TENSORS];
     size_t off_m[9];          // gate_rev, zeros, s, fro, c, C, p . H x, k . dk / beta, v . dv / beta
     size_t off_fin[3];        // final states of three reverse readouts (gradients at the initial states)
     size_t off_fwd, fwd_bytes, total;
     bool strided;             // q, k, v, dy come with explicit strides
     size_t off_pack[4];       // their packed copies
 };
-enum { IO_Y, IO_DXT, IO_RHS, IO_HX, IO_X, IO_XT, IO_KR, IO_VR, IO_DYR, IO_XR, IO_PR, IO_XTR, IO_R1, IO_R2, IO_R3, IO_R4,
-       IO_SCRATCH, IO_HK, IO_VPR, IO_R5, IO_RHS_LO, IO_X_LO, IO_XT_LO };
-
 gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
 {
     gka_status s = check_common(p, false);
@@ -565,7 +567,12 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
         for (int i = 0; i < 4; ++i) { bp->off_pack[i] = off; off = align_up(off + bp->n_elems * bp->esz, 256); }
     }
     for (int i = 0; i < 3; ++i) { bp->off_f32[i] = off; off = align_up(off + bp->n_elems * 4, 256); }
-    for (int i = 0; i < 23; ++i) { bp->off_io[i] = off; off = align_up(off + bp->n_elems * bp->esz, 256); }
+    for (int i = 0; i < IO_TENSORS; ++i) {
+        // (float32 tensors: everything but the remainders; bf16 tensors: what the solves and the readouts hand on)
+        const bool used = p->io_dtype == GKA_BF16 ? i >= IO_BF16_FIRST : i < IO_REMAINDERS;
+        bp->off_io[i] = off;
+        if (used) off = align_up(off + bp->n_elems * bp->esz, 256);
+    }
     for (int i = 0; i < 9; ++i) { bp->off_m[i] = off; off = align_up(off + bp->n_tokens * 4, 256); }
     for (int i = 0; i < 3; ++i) {
         bp->off_fin[i] = off;
@@ -681,7 +688,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         pp.alpha = nullptr; pp.xhat_out = xf;
         pp.state_layout = GKA_STATE_FULL;
         const SecondRhs second = {q2, q2_lo, pf32, io(IO_X), io(IO_X_LO), io(IO_PR)};
-        return forward_impl(&pp, q, k, v, gate, lambda, io(IO_Y), H_init, U_init, nullptr, nullptr, fro_out, fws,
+        return forward_impl(&pp, q, k, v, gate, lambda, io(IO_SCRATCH), H_init, U_init, nullptr, nullptr, fro_out, fws,
                             bp.fwd_bytes, hip_stream, nullptr, false, true, &second);
     };
     auto glue = [&](int which) {

@@ -496,8 +496,13 @@ static hipError_t launch_readout_square(const ReadoutArgs &a, hipStream_t stream
         if (!a.q_lo) return hipErrorInvalidValue;
         return a.beta ? launch_readout_d<D, D, true, 1, false, true>(a, stream) : launch_readout_d<D, D, false, 1, false, true>(a, stream);
     }
-    if (a.q_lo)
-        return a.beta ? launch_readout_d<D, D, true, 1>(a, stream) : launch_readout_d<D, D, false, 1>(a, stream);
+    if (a.q_lo) {
+        // (the readout of latent sketching at d = 64; at 128 it works in the sketched space)
+        if constexpr (D == 64)
+            return a.beta ? launch_readout_d<D, D, true, 1>(a, stream) : launch_readout_d<D, D, false, 1>(a, stream);
+        else
+            return hipErrorInvalidValue;
+    }
     return a.beta ? launch_readout_d<D, D, true, 0>(a, stream) : launch_readout_d<D, D, false, 0>(a, stream);
 }
 

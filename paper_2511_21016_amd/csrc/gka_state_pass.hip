@@ -77,8 +77,7 @@ __device__ __forceinline__ void store_end_state(const StatePassArgs &a, const f3
         float *t = segment_tile<D>(a, pair, seg, rb, w) + (DOH ? 0 : 1024);
 #pragma unroll
         for (int r = 0; r < 16; ++r) t[r * 64 + lane] = acc[r];
-        // (the H workgroup's job; in a launch without H workgroups the U workgroup's)
-        if (rb == 0 && (DOH || a.only_u) && threadIdx.x == 0) a.seg_logdecay[pair * a.n_segs + seg] = Gseg;
+        if (rb == 0 && DOH && threadIdx.x == 0) a.seg_logdecay[pair * a.n_segs + seg] = Gseg;
     }
 }
 
@@ -554,8 +553,7 @@ __global__ __launch_bounds__(D * 2) __attribute__((amdgpu_waves_per_eu(kStateWav
         sub = (id - full) % PER;
         group = full / PER + (id - full) / PER;
     }
-    if (a.only_u && !(sub & 1)) return;            // nobody reads the H states of this launch
-    if (a.only_h && (sub & 1)) return;             // ... or its U states
+    if (a.only_h && (sub & 1)) return;             // nobody reads the U states of this launch
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[2 * kChunk * D];
     __shared__ __attribute__((aligned(16))) uint16_t s_b[kChunk * (D + MmaBF16::kRowPad)];
     if (a.write_frags) {
