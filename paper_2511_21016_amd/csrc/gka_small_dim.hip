@@ -45,14 +45,15 @@ constexpr float kMinZeta = 0x1p-60f;       // floor of zeta_c where the system i
 // * Where such a sequence is short it is walked from its start all the same, in one launch, by a wave per tile that advances
 //   the states over the tiles before its own without solving them (d = 16, 13 tiles, 48 pairs: 11.4 against 12.3 by chunks,
 //   96 pairs 13.0 and 12.7, 10 tiles, 192 pairs 12.1 and 13.6, 256 pairs 14.3 and 14.1, 16 tiles, 48 pairs 13.0 and 12.3 to
-//   14.4 (what three launches take of the host), 96 pairs 15.7 and 12.7; d = 32, 10 tiles, 288 pairs 23.8 and 26.6, 13 tiles,
+//   14.4 (what three launches take of the host, which varies), 96 pairs 15.7 and 12.7, 19 tiles, 4 pairs 14.2 and 12.4
+//   to 16.6; d = 32, 10 tiles, 288 pairs 23.8 and 26.6, 13 tiles,
 //   96 pairs 20.5 and 19.2): few_walk_work bounds pairs x tiles^3, which these turning points have in common.
 template <int D>
 struct WalkRule {
     static constexpr int many_pairs = D == 16 ? 2048 : 1024;
     static constexpr int short_chunks = 2;
     static constexpr int chunk_workgroups = D == 16 ? 2560 : 2048;
-    static constexpr int few_walk_tiles = D == 16 ? 16 : 10, few_walk_work = D == 16 ? 1 << 18 : 360000;
+    static constexpr int few_walk_tiles = D == 16 ? 20 : 10, few_walk_work = D == 16 ? 1 << 18 : 360000;
 };
 constexpr int kTileWaveChunks = 1024;      // up to this many chunks in all a walk from the start has a wave per tile
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -9,12 +9,12 @@ from paper_2511_21016_amd import binding, synth
 from gka_testutil import pair_rel_err, to_device, to_host, upload_inputs
 from hip_recorder import record
 
-CHUNKS = [(16, 25, 5, 209), (16, 1, 4, 257), (16, 2, 2, 271), (16, 1, 1, 288), (16, 1, 3, 1000), (16, 20, 10, 305),
+CHUNKS = [(16, 25, 5, 209), (16, 60, 1, 257), (16, 10, 6, 271), (16, 10, 5, 288), (16, 1, 3, 1000), (16, 20, 10, 305),
           (32, 2, 3, 161), (32, 1, 4, 193), (32, 2, 2, 207), (32, 1, 1, 256), (32, 1, 3, 1000), (32, 30, 8, 497)]
 
 
 @pytest.mark.parametrize("d,B,H,T,by_chunk", [(*s, True) for s in CHUNKS] + [
-    (16, 1, 1, 256, False), (16, 8, 15, 197, True), (16, 16, 16, 150, False), (32, 1, 1, 160, False), (16, 60, 10, 400, False),
+    (16, 1, 1, 256, False), (16, 2, 2, 305, False), (16, 8, 15, 197, True), (16, 16, 16, 150, False), (32, 1, 1, 160, False), (16, 60, 10, 400, False),
     (32, 64, 10, 257, False), (16, 4, 4, 128, False)])
 def test_kernel_choice(d, B, H, T, by_chunk):
     calls = record(f"""
