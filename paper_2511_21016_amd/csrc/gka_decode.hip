@@ -3,7 +3,7 @@
 // all arithmetic fp32. The states are read once, advanced by a.T tokens in registers and written once, so the state
 // traffic of a call does not grow with the number of tokens. The same kernel is gka_forward's recurrent path (any
 // number of tokens, separate initial and final states, ||H_t||_F and the solve's result as optional outputs), the
-// only one for float32 tensors at the head dimensions 16 and 32 and for short sequences at 256.
+// only one for float32 tensors at the head dimensions 16 and 32 and for sequences of up to 128 tokens at 256.
 //
 // Layout. NW waves; wave w owns D / NW rows of both states. Lane (rg, cg) = (lane / 8, lane % 8) of a wave holds, of the R
 // rows D / NW w + 8 rr + rg (rr < R = D / (8 NW)), the float4 pieces cg + 8 i (i < D / 32): eight lanes read a whole
@@ -14,8 +14,9 @@
 // lane then owns the row's component of xi, delta and the residual: a pass is one LDS write, one barrier, D / 32 LDS
 // reads, the multiply-adds and three DPP steps. Barriers order LDS only: the stores of the advanced states drain
 // while the token is solved.
-// What bounds it: few pairs, the latency of that chain (about 0.25 us per pass); many pairs, HBM for single tokens, and the
-// vector units for several tokens per call.
+// What bounds it: few pairs, the latency of that chain (about 0.25 us per pass; d = 128, 32 pairs 8.4 us); many pairs, HBM for
+// single tokens (d = 128, 8192 pairs, 10 passes: 376 us for 2.16 GB, 5.7 TB/s), and the vector units for several tokens
+// per call (4 tokens of 1536 pairs, block-lower H: 105 us).
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
@@ -287,39 +288,62 @@ void decode_step_kernel(DecodeArgs a)
         if constexpr (STREAM_U) {
             // four pieces at a time: read, advanced, used and written back. From the caller's initial state at the first
             // token, afterwards what this same lane stored at the previous token. A zero initial state: a single token reads
-            // nothing (d = 256, one token of 256 pairs: 22.1 us, 32.2 with the loads replaced by zeros). With several tokens a
-            // branch around the loads makes the compiler spill 92 registers: there they go to a few rows of the final state,
-            // the same for all waves, and zeros take their place.
+            // nothing (d = 256, one token of 256 pairs: 21.1 us, 32.2 with the loads replaced by zeros), by a branch around
+            // the whole walk over U (branches around the loads leave one of them in flight). With several tokens a branch
+            // makes the compiler spill 92 registers: there the loads go to a few rows of the final state, the same for all
+            // waves, and zeros take their place.
             const bool zero = tok == 0 && !Uin;
             const float *Usrc = (zero ? Us - row0 * D : tok > 0 ? Us : Uin) + voff;
+            enum { FROM_ZERO, LOADED, FROM_MEMORY };
+            auto four_pieces = [&](int rr, int i0, auto from) {
+                constexpr int FROM = decltype(from)::value;
+                if constexpr (SH::STREAM_U) __builtin_amdgcn_sched_barrier(0);   // (d = 256: no room for more at once)
+                const float vs = beta * s_in[2][8 * rr + row0];
+                f32x4 u[4];
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-                for (int i0 = 0; i0 < NI; i0 += 4) {
-                    if constexpr (SH::STREAM_U) __builtin_amdgcn_sched_barrier(0);   // (d = 256: no room for more at once)
-                    const float vs = beta * s_in[2][8 * rr + row0];
-                    f32x4 u[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const f32x4 *src = (const f32x4 *)(Usrc + piece(rr, i0 + i));
-                        if (STREAM && rr == 0) u[i] = upre[i0 + i];
-                        else if (MULTI) u[i] = *src;
-                        else if (zero) u[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                        else u[i] = __builtin_nontemporal_load(src);
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const f32x4 kc = columns(s_in[1], i0 + i), xc = columns(s_x[buf], i0 + i);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            u[i][e] = __builtin_fmaf(gamma, MULTI && zero ? 0.0f : u[i][e], vs * kc[e]);
-                            acc[rr][e] += u[i][e] * xc[e];
-                        }
-                        f32x4 *dst = (f32x4 *)(Us + voff + piece(rr, i0 + i));
-                        if constexpr (MULTI) *dst = u[i];
-                        else __builtin_nontemporal_store(u[i], dst);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const f32x4 *src = (const f32x4 *)(Usrc + piece(rr, i0 + i));
+                    if constexpr (FROM == FROM_ZERO) u[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    else if constexpr (FROM == LOADED) u[i] = upre[i0 + i];
+                    else if constexpr (MULTI) u[i] = *src;
+                    else u[i] = __builtin_nontemporal_load(src);
                 }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const f32x4 kc = columns(s_in[1], i0 + i), xc = columns(s_x[buf], i0 + i);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        u[i][e] = __builtin_fmaf(gamma, MULTI && zero ? 0.0f : u[i][e], vs * kc[e]);
+                        acc[rr][e] += u[i][e] * xc[e];
+                    }
+                    f32x4 *dst = (f32x4 *)(Us + voff + piece(rr, i0 + i));
+                    if constexpr (MULTI) *dst = u[i];
+                    else __builtin_nontemporal_store(u[i], dst);
+                }
+            };
+            auto all_pieces = [&](auto first, auto from) {
+                if constexpr (STREAM) {            // (no condition on rr around the loads: it costs them their non-temporal
+                    static_assert(NI == 4);        // hint, d = 128, 8192 pairs 388 us instead of 380)
+                    four_pieces(0, 0, first);
+                }
+#pragma unroll
+                for (int rr = STREAM; rr < R; ++rr)
+#pragma unroll
+                    for (int i0 = 0; i0 < NI; i0 += 4) four_pieces(rr, i0, from);
+            };
+            constexpr std::integral_constant<int, FROM_ZERO> zeros;
+            constexpr std::integral_constant<int, LOADED> loaded;
+            constexpr std::integral_constant<int, FROM_MEMORY> memory;
+            if constexpr (MULTI) {
+#pragma unroll
+                for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+                    for (int i0 = 0; i0 < NI; i0 += 4) four_pieces(rr, i0, memory);
+            } else if (zero) {
+                all_pieces(zeros, zeros);
+            } else {
+                all_pieces(loaded, memory);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -432,6 +456,11 @@ __global__ __launch_bounds__(256) void decode_step_kernel_d16(DecodeArgs a, int 
     if (a.U_state) *(f32x4 *)(a.U_state + state_off) = ureg;
 }
 
+// Single tokens at d = 128: up to this many pairs one workgroup per CU is all there is, and eight waves that hold both
+// states finish a token's chain sooner; above it several workgroups of four waves share a CU, which holding U would not
+// let them (us, held with eight waves / streamed with four, full H: 64 pairs 10.0 / 11.7, 192 11.7 / 12.9, 256 12.8 / 14.3,
+// 288 19.4 / 17.8, 512 23.8 / 23.3, 1024 50.5 / 47.4, 8192 383 / 377; H on and below the block diagonal: 256 11.8 / 13.9,
+// 288 17.0 / 16.9, 1024 42.1 / 38.5, 2048 80.1 / 78.4, 8192 309 / 318; 384 pairs of full H 20.9 / 19.9).
 constexpr int kDecodeHoldPairs = 256;
 
 template <class IO, int D, int NW, bool MULTI, bool LOWER, bool STREAM = false>
