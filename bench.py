@@ -3,7 +3,7 @@
 One step = one gka_forward over the single-layer bf16 workload (B=4, H=16, T=4096, d=128, chunk 64,
 n_iter=10), inputs resident in HBM. Prints one JSON line: layer tokens/s, the roofline of the dominant
 kernel (the fused chunk-walk kernel, bf16 MFMA bound) from HIP-event timings taken on the launch stream,
-and the fp64 CPU oracle timed on this machine's host cores on the same workload.
+and the fp64 CPU oracle timed on the host's cores on the same workload.
 """
 import argparse
 import json
@@ -255,7 +255,7 @@ def main():
         torch.cuda.synchronize()
         ms_decode = d0.elapsed_time(d1) / d_steps
         state_bytes = dB * dH * 2 * dd * dd * 4 * 2          # H and U, read and written
-        dk = "decode_step_kernel<IOBF16,128,false,false,true>"
+        dk = "decode_step_kernel<IOBF16,128,4,false,false,true>"
         result["decode"] = {"workload": f"{w5.name}: {dB} seq x {dH} heads, d={dd}, n_iter={w5.n_iter}, states prefilled "
                                         f"from {w5.T} tokens by gka_forward ({ms_prefill:.1f} ms), {d_steps} steps",
                             "ms_per_step": ms_decode, "sequence_tokens_per_s": dB / (ms_decode * 1e-3),
@@ -281,10 +281,10 @@ def main():
         lower_bytes = dB * dH * (dd * dd + 10 * 32 * 32) * 4 * 2
         result["decode"]["h_lower_blocks"] = {
             "ms_per_step": ms_lower, "sequence_tokens_per_s": dB / (ms_lower * 1e-3),
-            "roofline": {"kernel": "decode_step_kernel<IOBF16,128,false,true,true>", "bound": "hbm",
+            "roofline": {"kernel": "decode_step_kernel<IOBF16,128,4,false,true,true>", "bound": "hbm",
                          "achieved": lower_bytes / (ms_lower * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": lower_bytes / (ms_lower * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                         "traffic": committed_traffic("decode_step_kernel<IOBF16,128,false,true,true>")}}
+                         "traffic": committed_traffic("decode_step_kernel<IOBF16,128,4,false,true,true>")}}
         # several tokens per call (gka_decode_tokens): the states still cross HBM once per call
         multi = {}
         for nt in (4, 8):
@@ -362,16 +362,16 @@ def main():
                                       "times_forward": ms_sk / ms_per_step, "workspace_bytes": sws.numel()}
         del sws, so, S
 
-    # ---- other head dimensions (extra information): the token-by-token path of gka_forward, synthetic inputs of the
-    # workload's distributions. d = 16 on the shape of a vision model (Appendix L: 197 tokens, many short sequences);
+    # ---- other head dimensions (extra information): the library's choice and, at d = 16, the token-by-token path of
+    # gka_forward, synthetic inputs of the workload's distributions. d = 16 on the shape of a vision model (Appendix L: 197 tokens, many short sequences);
     # d = 256 at the model width of the headline workload.
     if not args.no_head_dims:
         result["other_head_dims"] = {}
         rec = binding.GKA_PATH_RECURRENT
         for name, shape, path, kernel in (
-                ("d16_197_tokens", dict(B=256, H=24, T=197, d=16), binding.GKA_PATH_AUTO, "small_solve_kernel (chunk-wise, d <= 32)"),
+                ("d16_197_tokens", dict(B=256, H=24, T=197, d=16), binding.GKA_PATH_AUTO, "small_walk_kernel (one wave per pair, 16 tokens at a time)"),
                 ("d16_197_tokens_recurrent", dict(B=256, H=24, T=197, d=16), rec, "decode_step_kernel_d16 (path recurrent)"),
-                ("d256", dict(B=4, H=8, T=1024, d=256), binding.GKA_PATH_AUTO, "decode_step_kernel (path recurrent)")):
+                ("d256", dict(B=4, H=8, T=1024, d=256), binding.GKA_PATH_AUTO, "solve_f32_kernel (chunk-wise, float32 products)")):
             wd = w.scaled(seed=w.seed + 50, **shape)
             xd = upload_inputs(synth.make_inputs(wd), "bf16")
             od = torch.empty_like(xd["v"])

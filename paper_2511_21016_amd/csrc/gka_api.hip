@@ -39,8 +39,11 @@ constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walk
 constexpr size_t kDefaultSlabStateBytes = (size_t)1 << 30;
 // Workgroups the fused kernel should at least have: one per compute unit.
 constexpr int kFusedMinWorkgroups = 256;
-// Above this length d = 256 runs chunk-wise (300 tokens of 4 pairs: 0.13 ms against 4.6 ms token by token; the chunk states
-// need a workspace that shorter sequences are not asked for).
+// Above this length d = 256 runs chunk-wise. The line is what callers are asked for, not speed: the chunk states need a
+// workspace, and calls of up to two chunks have always run without one (sizes queried and allocated once by a program
+// would no longer do). Chunk by chunk would be the faster way from 4 to 8 tokens on (us, chunk-wise against token by
+// token: 4 pairs, 4 tokens 36 / 55, 16 tokens 36 / 202, 64 tokens 50 / 789, 128 tokens 113 / 1573; 64 pairs, 4 tokens
+// 50 / 57, 128 tokens 204 / 1591; 512 pairs, 2 tokens 216 / 110, 4 tokens 213 / 199, 128 tokens 1140 / 5287).
 constexpr int kWideMinTokens = 2 * gka::kChunk;
 constexpr size_t kMaxPairsPerBatch = 1024;
 constexpr size_t kMinSlabChunks = 4;

@@ -1,5 +1,6 @@
-// Per-chunk solve with bf16 products (float32 products: gka_solve_f32.hip): chunk-wise Frobenius norms (Section 4.2.1), the fused Chebyshev driver
-// (Algorithm 1 on all tokens of the chunk at once) and the readout y_c = U_c xhat_c of Eq. (CH).
+// Per-chunk solve with bf16 products (float32 products: gka_solve_f32.hip): chunk-wise Frobenius norms (Section 4.2.1),
+// the fused Chebyshev driver (Algorithm 1 on all tokens of the chunk at once) and the readout y_c = U_c xhat_c of
+// Eq. (CH).
 //
 // One workgroup = one chunk of one (batch, head) pair = four waves. Wave w owns the token block tw = w & 1
 // (tokens 32 tw .. 32 tw + 31) and the feature half fh = w >> 1 (rows 32 mt .., mt in its half of the D / 32

@@ -6,9 +6,9 @@
 //
 // and the residual form of the recurrence. What differs is the shape: a float32 product takes sixteen times the matrix
 // pipe's time of a bf16 one, so everything here serves the pipe.
-//   * A workgroup takes TT = 1 or 2 tiles of 16 tokens of one chunk (4 / TT workgroups per chunk). Wave w owns the feature rows 16 RT w .. of every vector, for all of the workgroup's tokens: no product is
-//     computed twice, and the state's rows of a wave stay in its registers for all passes (RT D / 4 registers; a pass
-//     reads no state from memory or LDS).
+//   * A workgroup takes TT = 1 or 2 tiles of 16 tokens of one chunk (4 / TT workgroups per chunk). Wave w owns the feature
+//     rows 16 RT w .. of every vector, for all of the workgroup's tokens: no product is computed twice, and the state's
+//     rows of a wave stay in its registers for all passes (RT D / 4 registers; a pass reads no state from memory or LDS).
 //   * Tokens sit on the N dimension: lane (n, kg) = (lane & 15, lane >> 4) holds rows 4 kg .. + 3 of token n of a tile,
 //     so per-token scalars are per-lane scalars. Vectors cross waves through LDS rows [token][feature]; a lane reads
 //     four consecutive features 16 s + 4 kg .. + 3 at once and uses them in four products (the contraction index is
