@@ -1,10 +1,10 @@
 // Elementwise and per-token kernels of the backward pass (Section 4.2.2 "Backward Pass", Appendix B.2). The heavy
-// parts of the backward pass run elsewhere: two solves on the forward kernels (the forward solve for xhat_t and the
-// solve of the incoming gradient, dq_t = CH(H_t + lambda_t I, dxhat_t, r)) and the gated-linear-attention readouts,
-// four of them walking the sequence backwards, which are the reverse recurrences of Section 4.2.2 (Eq. (Ai) and the
-// like for U): one kernel with the state in registers for bf16 tensors, the forward kernels on time-reversed
-// copies for float32 tensors. What remains is here: mixing, conversions, the time reversal (for the latter path),
-// the per-token combination of the pieces and the reverse cumulative sum that gives the gradient of the gates.
+// parts of the backward pass run elsewhere: the two solves (the forward solve for xhat_t and the solve of the incoming
+// gradient, dq_t = CH(H_t + lambda_t I, dxhat_t, r)), the plain readouts and the reverse recurrences of Section 4.2.2
+// (Eq. (Ai) and the like for U). bf16 tensors: both solves in one launch, readouts with the state in registers
+// (gka_readout.hip), the recurrences in one walk backwards over the sequence (gka_reverse.hip). float32 tensors: the
+// forward kernels, for the recurrences on time-reversed copies. What remains is here: mixing, conversions, the time
+// reversal, the per-token combination of the pieces and the reverse cumulative sum that gives the gradient of the gates.
 //
 // All tensors are packed: [B,T,H,d] for vectors, [B,T,H] for scalars.
 #include "gka_device.hpp"

@@ -17,6 +17,13 @@
 // kernel that combined them. PART selects the recurrences: 3 both in one walk (xt = x, i.e. no alpha-connection), 1 -S_t k_t
 // only, 2 the Ubar parts, added to what the call before left in dk (with an alpha-connection the rows of x and of xt do
 // not fit in LDS together).
+//
+// Bound by neither pipe: one workgroup per CU (its LDS), two waves per SIMD at d = 128 and one at d = 64, whose loads, LDS
+// exchanges and barriers do not cover each other (issue 32 %, matrix pipe 23 % of the busy cycles). 64 pairs x 4096 tokens,
+// d = 128: 86 us for the segments' summaries and 365 for the walk (part 1 62 + 152, part 2 50 + 241) and 133 for the kernel that
+// combines its outputs, in place of 657 for the four readouts and 349 for the combination of theirs; d = 64, 64 pairs x 2000
+// tokens 22 + 82. The walk with both recurrences at d = 128 takes 256 registers and spills 44 (part 1 158, part 2 242, d = 64
+// 234: none).
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 

@@ -18,7 +18,10 @@
 // Bound: the matrix pipe (157 TFLOP/s in float32). Measured, microseconds per forward pass, against 32 x 32 x 2 products
 // with two waves per token block that each formed all of P, H_[n] in LDS, one workgroup per chunk: d = 64, 1 pair x 256
 // tokens 62 -> 32; d = 64, 64 x 1024 205 -> 163; d = 128, 16 x 1500 309 -> 197; d = 128, 64 x 1024 664 -> 436
-// (98 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16220 -> 724, of which this kernel 600.
+// (98 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16220 -> 724, of which this kernel 600 (the matrix pipe
+// busy 75 % of it). Registers: capped at 128 up to d = 128 (four waves per SIMD), at 256 at d = 256 (two). With
+// TT = 2 that spills: d = 128 3 (bf16 tensors), 14 (float32), 12 to 29 with the variants or two right-hand sides; d = 256
+// 15 (bf16), 31 (float32), up to 57 with the variants; d = 64 16 with the variants of float32 tensors. With TT = 1 none.
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
