@@ -39,10 +39,18 @@ constexpr int kD = 128;
 constexpr int kOffH = 0;            // [2 chunks] 32 KiB: H_[n] as A fragments [ft 8][fb 4][64 lanes]
                                     //   later: xhat as B fragments [ts 4][hi/lo 2][fb 4][64 lanes]
 constexpr int kOffK = 65536;        // [2] 16 KiB: key rows as A fragments [js 4][fb 4][64]
-                                    //   later (both halves): state part of the readout [ts 4][ft 8][64] float4
+                                    //   later: masked products, tables and the last xhat fragments of the readout (below)
 constexpr int kOffKT = 98304;       // [2] 16 KiB: keys transposed as A fragments [ft 8][jb 2][64]
 constexpr int kOffR = 131072;       // [2] 16 KiB: row-major tile of k rows, later of v rows (64 x 256 B, swizzled)
 constexpr int kLdsBytes = 163840;
+// Readout (the key-row fragments are dead then):
+constexpr int kOffPM = kOffK;               // [2 chunks] 8 KiB: P o M / zeta as B fragments [ts 4][jb 2][64]
+constexpr int kOffVTab = kOffK + 16384;     // the waves' tables of token weights [w 8][slot 4][64] float
+constexpr int kOffZeta = kOffK + 24576;     // [2 chunks][64] float: zeta of the tokens
+constexpr int kOffXLast = kOffK + 28672;    // 4 KiB: remainder of xhat for the last 16 tokens of the second chunk, whose
+                                            // place in kOffH then holds the next iteration's table of gates
+constexpr int kOffGateTab = kOffH + 65536 - 4096;
+constexpr int kOffGateTabSplit = kOffK + 25600;     // SPLIT: there are no key fragments of a second chunk
 // per-token scalars of the Frobenius phase and the partial norms of H_[n]: last KiB of the second row tile
 constexpr int kOffTab = kOffR + 2 * 16384 - 1024;
 
@@ -89,9 +97,11 @@ __device__ __forceinline__ void split8(f32x4 lo, f32x4 hi, bf16x8 &val, bf16x8 &
 }
 __device__ __forceinline__ float sum_over_kg(float x)
 {
-    x += __shfl_xor(x, 16, 64);
-    x += __shfl_xor(x, 32, 64);
-    return x;
+    // (row and half swaps: vector moves, no LDS round trips)
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // U is needed only for the state part of the readout and its own update, once per iteration; in between it is
@@ -146,21 +156,36 @@ __device__ __forceinline__ float *wave_table(const Ctx &c, int byte_off, int slo
 // (Loops that run once per chunk are kept rolled where that costs little: the loop body of the kernel is executed
 // once per iteration, straight through, so its size is paid in instruction fetches.)
 
-// This wave's B fragments of a chunk update: rows of the tile (k or v) transposed, columns 16 w .., each token
-// scaled by its weight (wtab: the weights of the chunk's 64 tokens, a slot of this wave's table).
+// Rows of a tile (k or v) transposed, columns 16 w ..: an operand of either kind whose contraction runs over the chunk's tokens.
 template <class Layout = Rows>
-__device__ __forceinline__ void own_weighted_frags(const Ctx &c, const uint16_t *rows, const float *wtab,
-                                                   bf16x8 (&out)[2], Layout at = Layout())
+__device__ __forceinline__ void own_frags(const Ctx &c, const uint16_t *rows, bf16x8 (&out)[2], Layout at = Layout())
 {
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
         const int t0 = 32 * st + 4 * c.kg;
-        const bf16x8 raw = gather_transposed_bf16(rows, at, 16 * c.w, c.lane, t0, t0 + 16);
+        out[st] = gather_transposed_bf16(rows, at, 16 * c.w, c.lane, t0, t0 + 16);
+    }
+}
+// The same with each token scaled by its weight (wtab: the weights of the chunk's 64 tokens): the B fragments of this wave's
+// columns in a chunk update.
+__device__ __forceinline__ void weight_frags(const Ctx &c, const bf16x8 (&raw)[2], const float *wtab, bf16x8 (&out)[2])
+{
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        const int t0 = 32 * st + 4 * c.kg;
         const f32x4 w0 = *(const f32x4 *)(wtab + t0), w1 = *(const f32x4 *)(wtab + t0 + 16);
         f32x4 lo, hi;
-        unpack8(raw, lo, hi);
+        unpack8(raw[st], lo, hi);
         out[st] = pack8(lo * w0, hi * w1);
     }
+}
+template <class Layout = Rows>
+__device__ __forceinline__ void own_weighted_frags(const Ctx &c, const uint16_t *rows, const float *wtab,
+                                                   bf16x8 (&out)[2], Layout at = Layout())
+{
+    bf16x8 raw[2];
+    own_frags(c, rows, raw, at);
+    weight_frags(c, raw, wtab, out);
 }
 
 // S <- zeta_C S + sum_j w_j k_j a_j^T for this wave's eight tiles (A: transposed keys of chunk g from LDS)
@@ -206,26 +231,47 @@ __device__ __forceinline__ float publish_H(const Ctx &c, const f32x4 (&accH)[8],
     return lane_value(wave_inclusive_scan(ss, c.lane), 63);      // (DPP moves: no LDS round trips)
 }
 
-// State part of the readout for all 64 tokens of chunk g: rows 16 w .. of U_[n] xhat, with U and xhat as rounded
-// value + remainder (three products), to the exchange region at byte offset y_off as [ts][w][lane] float4. The
-// fragments of the next token block are requested before the products of the current one.
-__device__ __forceinline__ void readout_state(const Ctx &c, const f32x4 (&accU)[8], int g, int y_off)
+// xhat of the 16 tokens ts of chunk g as B fragments [fb 4][lane], part 0: rounded value, 1: remainder
+__device__ __forceinline__ bf16x8 *lds_xhat(const Ctx &c, int g, int ts, int part)
+{
+    const int off = (g == 1 && ts == 3 && part == 1) ? kOffXLast : kOffH + g * 32768 + (ts * 2 + part) * 4096;
+    return lds_frags(c, off) + c.lane;
+}
+
+// Readout of chunk g, all 64 tokens, features 16 w ..: y_c = zeta_c (U_[n] xhat_c + V^T (P o M / zeta)_c) with U and xhat as
+// rounded value + remainder (three products), stored as it is formed. Every wave has the rows of U and the columns of v that
+// its features need (vT: raw v columns, the operand of its own update as well), so nothing but the solvers' xhat and P o M
+// crosses waves, and no barrier separates the two chunks' readouts from each other or from the updates of U between them.
+// (The intra-chunk part with the solvers instead, the state part handed to them through LDS in float32: 2 barriers more per
+// iteration, 64 KiB written and read, 16 or 32 transposed reads per wave instead of 4.) The fragments of the next token block
+// are requested before the products of the current one.
+template <int G>
+__device__ __forceinline__ void readout_chunk(const Ctx &c, const f32x4 (&accU)[8], const bf16x8 (&vT)[2], int chunk)
 {
     bf16x8 Uv[4], Ur[4];
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb) split8(accU[2 * fb], accU[2 * fb + 1], Uv[fb], Ur[fb]);
-    const bf16x8 *sX = lds_frags(c, kOffH + g * 32768) + c.lane;
-    f32x4 *sY = (f32x4 *)(c.smem + y_off) + c.w * 64 + c.lane;
-    bf16x8 x[2][8];
+    const bf16x8 *sP = lds_frags(c, kOffPM + G * 8192) + c.lane;
+    const float *sZ = (const float *)(c.smem + kOffZeta) + G * 64 + c.n;
+    bf16x8 x[2][8], pm[2][2];
+    float zeta[2];
+    auto request = [&](auto tsc) {
+        constexpr int ts = decltype(tsc)::value, to = ts & 1;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[0][i] = sX[i * 64];
+        for (int i = 0; i < 8; ++i) x[to][i] = lds_xhat(c, G, ts, i >> 2)[(i & 3) * 64];
 #pragma unroll
-    for (int ts = 0; ts < 4; ++ts) {
-        const int cur = ts & 1;
-        if (ts + 1 < 4) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[cur ^ 1][i] = sX[((ts + 1) * 8 + i) * 64];
-        }
+        for (int jb = 0; jb <= ts / 2; ++jb) pm[to][jb] = sP[(ts * 2 + jb) * 64];
+        zeta[to] = sZ[16 * ts];
+    };
+    // Buffer stores, for which a token that is not to be stored gets an offset beyond the buffer: no branch, and every wave
+    // issues the same number of them (the wait at the top of an iteration counts on that).
+    const int n_tokens = c.T_eff - chunk * kChunk, row_bytes = (int)c.a.stride_t * 2;
+    const buffer_rsrc out = make_raw_buffer((uint16_t *)c.a.o + c.base_bh + (int64_t)chunk * kChunk * c.a.stride_t);
+    const int out_off = c.n * row_bytes + 32 * c.w + 8 * c.kg;
+    request(std::integral_constant<int, 0>{});
+    static_for<0, 4>([&](auto tsc) {
+        constexpr int ts = decltype(tsc)::value, cur = ts & 1;
+        if constexpr (ts + 1 < 4) request(std::integral_constant<int, ts + 1>{});
         f32x4 y0 = zero4(), y1 = zero4(), y2 = zero4();
 #pragma unroll
         for (int fb = 0; fb < 4; ++fb) {
@@ -233,8 +279,14 @@ __device__ __forceinline__ void readout_state(const Ctx &c, const f32x4 (&accU)[
             y1 = mma16(Ur[fb], x[cur][fb], y1);
             y2 = mma16(Uv[fb], x[cur][4 + fb], y2);
         }
-        sY[ts * 8 * 64] = y0 + (y1 + y2);
-    }
+#pragma unroll
+        for (int jb = 0; jb <= ts / 2; ++jb) y1 = mma16(vT[jb], pm[cur][jb], y1);
+        const f32x4 y = zeta[cur] * (y0 + (y1 + y2));
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u16x4 bits = {f32_to_bf16_bits(y[0]), f32_to_bf16_bits(y[1]), f32_to_bf16_bits(y[2]), f32_to_bf16_bits(y[3])};
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, bits), out,
+                                              16 * ts + c.n < n_tokens ? out_off + 16 * ts * row_bytes : -1, 0, 0);
+    });
 }
 
 // ---- solver role -----------------------------------------------------------------------------------------------
@@ -247,7 +299,6 @@ constexpr float kMinSolveZeta = 0x1p-60f;
 
 struct Solver {
     f32x4 mreg[4];                   // decay mask M[j][c], key block js: rows j = 16 js + 4 kg + r (from the passes on: / zeta)
-    f32x4 yi[8];                     // intra-chunk part of the readout (/ zeta)
     float zeta, fro;
     float beta;                      // write gate of this lane's token (1 without the variant)
     int tok;                         // this lane's token (global index)
@@ -609,10 +660,10 @@ __device__ __forceinline__ void solve_tokens(Ctx &c, Solver &s, int g, int ts, c
         const f32x4 qv = IOBF16::cvt4(qraw[ft]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float qe = s.valid ? qv[r] : 0.0f;
+            // (tokens that do not exist take the values of rows that do; nothing of theirs reaches another token or memory)
             xi[ft][r] = 0.0f;
-            dl[ft][r] = s0 * qe;
-            gn[ft][r] = -qe * rz;
+            dl[ft][r] = s0 * qv[r];
+            gn[ft][r] = -rz * qv[r];
         }
     }
     cheb_passes<NJ, SPLIT>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
@@ -639,50 +690,29 @@ __device__ __forceinline__ void solve_tokens(Ctx &c, Solver &s, int g, int ts, c
         }
     }
 
-    // ---- readout, intra-chunk part: sum_{j<=c} M[j,c] v_j (k_j . xhat_c), xhat as value + remainder
+    // ---- readout operands: xhat as value + remainder, and its masked products with the chunk's keys (the intra-chunk
+    // part of y_c is sum_{j<=c} M[j,c] v_j (k_j . xhat_c))
     bf16x8 x[2][4];
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb) split8(xi[2 * fb], xi[2 * fb + 1], x[0][fb], x[1][fb]);
+    park_load(c.park, accU);         // U comes back during the rest of this phase
     f32x4 P[NJ];
     key_products<NJ, 2>(sK, x, P, c.lane);
     constexpr int NJB = NJ / 2;
     bf16x8 pm[NJB];
 #pragma unroll
     for (int jb = 0; jb < NJB; ++jb) pm[jb] = masked_frag(P[2 * jb], P[2 * jb + 1], s.mreg, jb);
-    wait_all_memory();               // this wave's copies of v rows have landed
-    lds_barrier();                   // all of them have; every wave is through its passes: H_[n] is dead
-    bf16x8 *sX = lds_frags(c, kOffH + g * 32768) + c.lane;
+    wait_vector_memory_but<kParkStores>();      // this wave's copies of v rows, older than the loads of U, have landed
+    lds_barrier();                   // all of them have; every wave is through its passes: H_[n] and the key rows are dead
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb) {
-        sX[((ts * 2 + 0) * 4 + fb) * 64] = x[0][fb];
-        sX[((ts * 2 + 1) * 4 + fb) * 64] = x[1][fb];
+        lds_xhat(c, g, ts, 0)[fb * 64] = x[0][fb];
+        lds_xhat(c, g, ts, 1)[fb * 64] = x[1][fb];
     }
-    park_load(c.park, accU);         // U comes back while the last products of this phase run
-    const uint16_t *rowsV = lds_rows(c, g);
+    bf16x8 *sP = lds_frags(c, kOffPM + g * 8192) + c.lane;
 #pragma unroll
-    for (int ft = 0; ft < 8; ++ft) {
-        s.yi[ft] = zero4();
-#pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) {
-            const int t0 = 32 * jb + 4 * c.kg;
-            const bf16x8 vt = gather_transposed_bf16(rowsV, Rows(), 16 * ft, c.lane, t0, t0 + 16);
-            s.yi[ft] = mma16(vt, pm[jb], s.yi[ft]);
-        }
-    }
-}
-
-// y_c = zeta_c U_[n] xhat_c + intra part, stored
-__device__ __forceinline__ void store_output(const Ctx &c, const Solver &s, int ts, int y_off)
-{
-    const f32x4 *sY = (const f32x4 *)(c.smem + y_off);
-    if (!s.valid) return;
-    const int64_t off = c.base_bh + (int64_t)s.tok * c.a.stride_t;
-#pragma unroll
-    for (int ft = 0; ft < 8; ++ft) {
-        const f32x4 ys = sY[(ts * 8 + ft) * 64 + c.lane];
-        const f32x4 y = s.zeta * (ys + s.yi[ft]);          // (yi was formed with the mask divided by zeta)
-        IOBF16::store4(c.a.o, off + 16 * ft + 4 * c.kg, y[0], y[1], y[2], y[3]);
-    }
+    for (int jb = 0; jb < NJB; ++jb) sP[(ts * 2 + jb) * 64] = pm[jb];
+    if (c.kg == 0) ((float *)(c.smem + kOffZeta))[g * 64 + 16 * ts + c.n] = s.zeta;
 }
 
 // ---- data movement ---------------------------------------------------------------------------------------------
@@ -722,40 +752,36 @@ __device__ __forceinline__ void copy_rows_untracked(const Ctx &c, const void *x,
     copy_rows_impl<true>(c, x, g, chunk);
 }
 
-// A fragments of the keys of both chunks from their row tiles: rows (K[js][fb]) and transposed (KT[ft][jb]); each
-// wave builds four of the 32 fragments of either kind.
-// (SPLIT: one chunk, two of its 16 fragments of either kind per wave.)
+// A fragments of the keys of both chunks from their row tiles: rows (K[js][fb]), four of the 32 by each wave, and transposed
+// (KT[ft][jb]), those with ft = w, which this wave also scales for its own columns of the update (kT, on return).
+// (SPLIT: one chunk.)
 template <bool SPLIT>
-__device__ __forceinline__ void build_key_frags(const Ctx &c)
+__device__ __forceinline__ void build_key_frags(const Ctx &c, bf16x8 (&kT)[SPLIT ? 1 : 2][2])
 {
-    constexpr int PER_WAVE = SPLIT ? 2 : 4;
+    constexpr int NG = SPLIT ? 1 : 2, PER_WAVE = 2 * NG;
     // all reads first, then all writes: read-then-write per fragment would be one LDS round trip after the other
-    bf16x8 rowf[PER_WAVE], trf[PER_WAVE];
+    bf16x8 rowf[PER_WAVE];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) own_frags(c, lds_rows(c, g), kT[g]);
 #pragma unroll
     for (int q = 0; q < PER_WAVE; ++q) {
         const int idx = c.w * PER_WAVE + q;
-        const int g = idx >> 4, f = idx & 15;
+        const int g = idx >> 4, js = (idx & 15) >> 2, fb = idx & 3;
         const uint16_t *rows = lds_rows(c, g);
-        {
-            const int js = f >> 2, fb = f & 3;
-            const u16x4 lo = *(const u16x4 *)(rows + Rows()(16 * js + c.n, 32 * fb + 4 * c.kg));
-            const u16x4 hi = *(const u16x4 *)(rows + Rows()(16 * js + c.n, 32 * fb + 16 + 4 * c.kg));
-            const u16x8 u = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            rowf[q] = __builtin_bit_cast(bf16x8, u);
-        }
-        {
-            const int ft = f >> 1, jb = f & 1;
-            const int t0 = 32 * jb + 4 * c.kg;
-            trf[q] = gather_transposed_bf16(rows, Rows(), 16 * ft, c.lane, t0, t0 + 16);
-        }
+        const u16x4 lo = *(const u16x4 *)(rows + Rows()(16 * js + c.n, 32 * fb + 4 * c.kg));
+        const u16x4 hi = *(const u16x4 *)(rows + Rows()(16 * js + c.n, 32 * fb + 16 + 4 * c.kg));
+        const u16x8 u = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        rowf[q] = __builtin_bit_cast(bf16x8, u);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) lds_frags(c, kOffKT + g * 16384)[(c.w * 2 + jb) * 64 + c.lane] = kT[g][jb];
+#pragma unroll
     for (int q = 0; q < PER_WAVE; ++q) {
         const int idx = c.w * PER_WAVE + q;
-        const int g = idx >> 4, f = idx & 15;
-        lds_frags(c, kOffK + g * 16384)[f * 64 + c.lane] = rowf[q];
-        lds_frags(c, kOffKT + g * 16384)[f * 64 + c.lane] = trf[q];
+        lds_frags(c, kOffK + (idx >> 4) * 16384)[(idx & 15) * 64 + c.lane] = rowf[q];
     }
 }
 
@@ -872,14 +898,11 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
         refresh_lane(c);
         // ---- 1
         // Gates of the chunks (fetched during the previous iteration): G_j, the weight of token j in the chunk's
-        // update 2^(G_C - G_j) (times its write gate), and the chunk's decay 2^(G_C). Before the passes one wave per
-        // chunk scans (waves 0 and 1: among the first to arrive here, while others still store their tokens) and
-        // leaves the per-token scalars in a table that all waves read after the barrier; slots of 64 floats: weights
-        // of A, of B, G of A, of B, write gates of A, of B. The table lies in a part of LDS that is free from the last
-        // barrier of the previous iteration to the second of this one (the second chunk's H_[n]; SPLIT: the second
-        // chunk's key fragments, which do not exist).
-        constexpr int kTabBefore = SPLIT ? kOffK + 16384 : kOffH + 32768;
-        constexpr int kTabAfter = kOffK + 16384;             // after the passes: the key-row fragments are dead
+        // update 2^(G_C - G_j) (times its write gate), and the chunk's decay 2^(G_C). One wave per chunk scans (waves 0
+        // and 1) and leaves the per-token scalars in a table that all waves read after the barrier; slots of 64 floats:
+        // weights of A, of B, G of A, of B, write gates of A, of B. The table lies in a part of LDS that nothing else uses
+        // between the second barrier after the passes and the second one of the next iteration.
+        constexpr int kTabBefore = SPLIT ? kOffGateTabSplit : kOffGateTab;
         float *gtab = (float *)(smem + kTabBefore);
         auto scan_chunk = [&](float gm, float bm, int chunk, float &wj, float &zeta) {
             const bool valid = chunk * kChunk + c.lane < c.T_eff;
@@ -904,20 +927,23 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
                 if constexpr (GATED) gtab[5 * 64 + c.lane] = bmB;
             }
         }
-        // This wave's copies of the k rows have landed: they were issued before the kParkStores stores of U that
-        // every wave issues in every iteration, so once no more than that many vector-memory instructions are
-        // outstanding the copies are complete. (The stores of the last tokens, which follow, need not be: waiting
-        // for them cost 3 % of the step.)
-        wait_vector_memory_but<kParkStores>();
+        // This wave's copies of the k rows have landed: they were issued before the stores of the tokens (four per chunk) and
+        // the kParkStores stores of U that every wave issues in every iteration, so once no more than that many
+        // vector-memory instructions are outstanding the copies are complete; the stores need not be.
+        wait_vector_memory_but<kParkStores + 4 * kChunksPerIter>();
         lds_barrier();                   // ... and everybody else's; the table is complete
         // ---- 2
-        zetaA = exp2f(gtab[2 * 64 + 63]);
-        if constexpr (!SPLIT) zetaB = exp2f(gtab[3 * 64 + 63]);
+        zetaA = exp2f(lane_value(gtab[2 * 64 + c.lane], 63));
+        wjA = gtab[c.lane];
+        if constexpr (!SPLIT) {
+            zetaB = exp2f(lane_value(gtab[3 * 64 + c.lane], 63));
+            wjB = gtab[64 + c.lane];
+        }
         const float hnA = publish_H<SPLIT>(c, accH, 0);
-        build_key_frags<SPLIT>(c);
-        bf16x8 wBA[2], wBB[2];
-        own_weighted_frags(c, lds_rows(c, 0), gtab, wBA);
-        if constexpr (!SPLIT) own_weighted_frags(c, lds_rows(c, 1), gtab + 64, wBB);
+        bf16x8 kT[SPLIT ? 1 : 2][2], wBA[2], wBB[2];
+        build_key_frags<SPLIT>(c, kT);
+        weight_frags(c, kT[0], gtab, wBA);
+        if constexpr (!SPLIT) weight_frags(c, kT[1], gtab + 64, wBB);
         // solver inputs of this lane's token
         f32x4 accU[8];
         Solver s;
@@ -968,23 +994,21 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
             // (SPLIT, waves 4-7) this wave's share of the copies of the v rows, the barrier that the solver waves pass
             // after their passes, and U back from its parking place
             copy_rows(c, a.v, 0, c0);
-            wait_all_memory();
-            lds_barrier();
             park_load(c.park, accU);
+            wait_vector_memory_but<kParkStores>();
+            lds_barrier();
         }
-        // (after the passes every wave scans the gates for itself: no barrier separates this from the use of the
-        // results, and the raw gates cost two registers across the passes; the opaque copy keeps the compiler from
-        // merging these scans with those of waves 0 and 1 above)
-        asm volatile("" : "+v"(gmA), "+v"(gmB));
-        scan_chunk(gmA, bmA, c0, wjA, zetaA);
-        if constexpr (!SPLIT) scan_chunk(gmB, bmB, c0 + 1, wjB, zetaB);
-        // this wave's weighted v fragments of the chunks
-        bf16x8 wVA[2], wVB[2];
-        wave_table(c, kTabAfter, 0)[c.lane] = wjA;
-        if constexpr (!SPLIT) wave_table(c, kTabAfter, 1)[c.lane] = wjB;
-        own_weighted_frags(c, lds_rows(c, 0), wave_table(c, kTabAfter, 0), wVA);
-        if constexpr (!SPLIT) own_weighted_frags(c, lds_rows(c, 1), wave_table(c, kTabAfter, 1), wVB);
-        lds_barrier();                   // xhat of the chunks is visible; the key-row fragments are dead
+        // this wave's columns of v of the chunks, and the same with the weights of the update
+        bf16x8 vTA[2], vTB[2], wVA[2], wVB[2];
+        wave_table(c, kOffVTab, 0)[c.lane] = wjA;
+        if constexpr (!SPLIT) wave_table(c, kOffVTab, 1)[c.lane] = wjB;
+        own_frags(c, lds_rows(c, 0), vTA);
+        weight_frags(c, vTA, wave_table(c, kOffVTab, 0), wVA);
+        if constexpr (!SPLIT) {
+            own_frags(c, lds_rows(c, 1), vTB);
+            weight_frags(c, vTB, wave_table(c, kOffVTab, 1), wVB);
+        }
+        lds_barrier();                   // xhat and P o M of the chunks are visible
         // ---- 6
         // k rows of the next chunks: the row tiles are free from here on (every wave has formed its v fragments); the
         // copies land during the readout.
@@ -998,21 +1022,13 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
         gmA = a.gate[c.gate_base + (int64_t)min((c0 + kChunksPerIter) * kChunk + c.lane, a.T - 1) * a.H];
         if constexpr (!SPLIT) gmB = a.gate[c.gate_base + (int64_t)min((c0 + 3) * kChunk + c.lane, a.T - 1) * a.H];
         fetch_beta(c0 + kChunksPerIter);
-        readout_state(c, accU, 0, kOffK);
+        readout_chunk<0>(c, accU, vTA, c0);
         advance_state(c, accU, 0, zetaA, wVA);
-        lds_barrier();
-        // ---- 7: solver A stores while the state part of B is read out into the place of A's xhat
-        if (solver && grp == 0) store_output(c, s, ts, kOffK);
         if constexpr (!SPLIT) {
-            readout_state(c, accU, 1, kOffH);
+            readout_chunk<1>(c, accU, vTB, c0 + 1);
             advance_state(c, accU, 1, zetaB, wVB);
         }
         park_store(c.park, accU);
-        if constexpr (!SPLIT) {
-            lds_barrier();
-            // ---- 8
-            if (grp == 1) store_output(c, s, ts, kOffH);
-        }
     }
     wait_all_memory();               // no copy into this workgroup's LDS may be in flight when it ends
 
