@@ -37,8 +37,9 @@ constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walk
 // Chunk states one launch pair keeps in the workspace unless gka_params::slab_state_bytes says otherwise (tests use
 // that to force several slabs on small problems).
 constexpr size_t kDefaultSlabStateBytes = (size_t)1 << 30;
-// Workgroups the fused kernel should at least have: one per compute unit.
-constexpr int kFusedMinWorkgroups = 256;
+constexpr int kComputeUnits = 256;         // the fused kernels run one workgroup on each
+// Segments are added up to this many workgroups of the fused kernels (four rounds).
+constexpr int kFusedMaxWorkgroups = 4 * kComputeUnits;
 // Above this length d = 256 runs chunk-wise. The line is what callers are asked for, not speed: the chunk states need a
 // workspace, and calls of up to two chunks have always run without one (sizes queried and allocated once by a program
 // would no longer do). Chunk by chunk would be the faster way from 4 to 8 tokens on (us, chunk-wise against token by
@@ -72,6 +73,38 @@ gka_status check_common(const gka_params *p, bool decode)
 
 // head dimensions of the chunk-wise kernels (the others run token by token)
 bool chunked_dim(int d) { return d == 64 || d == 128; }
+
+// Chunks per segment of the fused kernels: the number of segments whose estimated time is the shortest. A launch runs in
+// ceil(workgroups / 256) rounds; a workgroup's walk costs kStart, then kIter + kPass per pass for an iteration (two chunks;
+// split operands: one), and kScan for each earlier segment whose summary its start state is composed of; the summary launch
+// walks every segment but the last once more (constants in us, from launches of 4 to 384 pairs). Measured against the former
+// rule, as few segments as give every CU a workgroup, us per forward pass: 16 pairs x 1337 tokens 66.2 -> 49.2, 36 x 2000
+// 131 -> 103 (288 workgroups -> 216), 48 x 3000 234 -> 173, 80 x 4096 464 -> 382, 100 x 4096 597 -> 497, 300 x 4096 1697 -> 1426,
+// 200 x 4096 944 -> 875; split operands, 12 passes, 48 x 2600 471 -> 352; 64 x 4096 and 32 x 32768 keep their segments.
+int fused_segment(int n_pairs, int n_chunks, int n_iter, bool split)
+{
+    constexpr float kStart = 10.0f, kScan = 1.3f, kSummaryStart = 5.0f, kSummaryChunk = 2.1f;
+    const float iteration = split ? 15.0f + 1.6f * n_iter : 13.5f + 1.15f * n_iter;
+    const int step = split ? 1 : 2;
+    const auto rounds = [](int64_t workgroups) { return (float)((workgroups + kComputeUnits - 1) / kComputeUnits); };
+    int best = n_chunks, last = 0;
+    float best_us = 0.0f;
+    for (int64_t segs = 1; segs <= (n_chunks + step - 1) / step; ++segs) {
+        int len = (int)((n_chunks + segs - 1) / segs);
+        len += len % step;
+        if (len == last) continue;
+        last = len;
+        const int64_t n = (n_chunks + len - 1) / len;
+        if (n > 1 && n * n_pairs > kFusedMaxWorkgroups) break;
+        float us = rounds(n * n_pairs) * (kStart + iteration * (len / step) + kScan * (n - 1));
+        if (n > 1) us += kSummaryStart + rounds((n - 1) * n_pairs) * kSummaryChunk * len;
+        if (segs == 1 || us < best_us) {
+            best = len;
+            best_us = us;
+        }
+    }
+    return best;
+}
 
 gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
 {
@@ -169,9 +202,8 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     // two ping-pong pairs of fp32 (H, U) carried from slab to slab
     const size_t n_carried = pl->slab_chunks < pl->n_chunks ? (size_t)4 * pl->pairs_per_batch : 0;
     pl->total = align_up(pl->off_carry + n_carried * pl->d * pl->d * sizeof(float), 256);
-    // Fused kernel: one workgroup per (pair, segment of the chunk walk). As few segments as give every compute unit a
-    // workgroup (every segment but the last costs a second read of its k and v rows for the summary launch); an even
-    // number of chunks per segment, because a workgroup takes its chunks two at a time.
+    // Fused kernel: one workgroup per (pair, segment of the chunk walk); an even number of chunks per segment, because a
+    // workgroup takes its chunks two at a time.
     pl->fused_shape = pl->io_bf16 && pl->compute_bf16 && pl->d == 128 && !readout_only;
     pl->fused_bytes = 0;
     if (pl->fused_shape) {
@@ -179,17 +211,21 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
         if (p->walk_chunks > 0) {
             seg_len = p->walk_chunks;
         } else {
-            int n_segs = (kFusedMinWorkgroups + pl->n_pairs - 1) / pl->n_pairs;
-            const int min_walk = pl->split ? 1 : 2;
-            if (n_segs > pl->n_chunks / min_walk) n_segs = pl->n_chunks / min_walk;
-            if (n_segs < 1) n_segs = 1;
-            seg_len = (pl->n_chunks + n_segs - 1) / n_segs;
+            seg_len = fused_segment(pl->n_pairs, pl->n_chunks, p->n_iter, pl->split);
         }
         if (!pl->split) seg_len += seg_len & 1;
         pl->fused_seg_len = seg_len;
         pl->fused_n_segs = (pl->n_chunks + seg_len - 1) / seg_len;
         if ((int64_t)pl->n_pairs * pl->fused_n_segs > (int64_t)0x7fffffff) return GKA_ERR_SHAPE;
-        pl->fused_bytes = align_up(gka::fused_workspace_bytes(pl->n_pairs, pl->fused_n_segs), 256);
+        // The size asked for does not shrink with the number of pairs or tokens or depend on the number of passes, as the
+        // segments may: a workspace serves every smaller call.
+        int64_t workgroups = (int64_t)pl->n_pairs * pl->fused_n_segs;
+        if (p->walk_chunks == 0) {
+            const int64_t finest = (int64_t)pl->n_pairs * (pl->split ? pl->n_chunks : (pl->n_chunks + 1) / 2);
+            workgroups = finest < kFusedMaxWorkgroups ? finest : kFusedMaxWorkgroups;
+            if (workgroups < pl->n_pairs) workgroups = pl->n_pairs;
+        }
+        pl->fused_bytes = align_up(gka::fused_workspace_bytes((int)workgroups, 1), 256);
         // (a caller that insists on the fused kernels needs no room for the two-phase kernels' chunk states)
         if (p->path == GKA_PATH_FUSED || pl->split || pl->fused_bytes > pl->total) pl->total = pl->fused_bytes;
     }
