@@ -761,7 +761,34 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         r.reverse = reverse; r.seg_mode = seg_mode;
         return gka::launch_gla_readout(r, p->d_k, p->d_v, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
+    // d = 128 with bf16 operands: the fused kernels' walk solves for both right-hand sides (a caller that asks for the two-phase
+    // kernels or bounds their chunk states gets those)
+    const bool walk = io_bf16 && p->d_k == 128 && p->compute == GKA_COMPUTE_BF16 && p->path == GKA_PATH_AUTO && p->slab_state_bytes == 0;
+    auto walk_both = [&]() {
+        gka::DualSolveArgs d = {};
+        gka::FusedArgs &f = d.f;
+        f.q = q; f.k = k; f.v = v; f.gate = gate; f.lambda = lambda; f.fro_out = rule ? fro : nullptr;
+        f.beta = p->beta; f.alpha = p->alpha; f.lambda_scale = p->lambda_scale;
+        f.H_init = H_init; f.U_init = U_init;
+        f.stride_h = p->d_k; f.stride_t = (int64_t)p->H * p->d_k; f.stride_b = (int64_t)p->T * p->H * p->d_k;
+        f.H = p->H; f.T = p->T; f.n_iter = p->n_iter;
+        f.n_pairs = p->B * p->H; f.n_chunks = (p->T + gka::kChunk - 1) / gka::kChunk;
+        f.seg_len = p->walk_chunks > 0 ? p->walk_chunks + (p->walk_chunks & 1)
+                                       : fused_segment(f.n_pairs, f.n_chunks, 2 * p->n_iter, false);
+        f.n_segs = (f.n_chunks + f.seg_len - 1) / f.seg_len;
+        d.dxt = f32buf(2);
+        d.x_f32 = rule ? xf : nullptr;
+        d.x_hi = io(IO_X); d.x_lo = io(IO_X_LO); d.xt_hi = io(IO_XT); d.xt_lo = io(IO_XT_LO);
+        d.p_f32 = pf32; d.p_hi = io(IO_PR);
+        d.dyy = sbuf;
+        if (!rule) {                          // (with the rule the combination of the vectors follows)
+            d.dq = p->alpha ? dq : nullptr;
+            d.dlambda = dlambda; d.dalpha = dalpha;
+        }
+        return gka::launch_dual_solve(d, fws, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
+    };
     g.natural_order = fused;
+    if (walk && !rule) g.dyy = sbuf;          // (the combination reads and replaces it token by token)
     if (fused) {
         g.dxt_io = f32buf(2);                     // (float32)
         g.phx = phx; g.kd = (float *)(ws + bp.off_m[7]); g.vd = (float *)(ws + bp.off_m[8]);
@@ -773,11 +800,16 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy. (alpha_t dxt_t in bf16 from
         // the readout itself: 97 -> 152 us at 64 pairs x 4096 tokens, its own pass over memory takes 41.)
         GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, 0, f32buf(2), nullptr, nullptr, U_init, true));
-        GKA_TRY(glue(1));
         // x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
-        GKA_TRY(solve_both(io(IO_RHS), io(IO_RHS_LO), rule ? fro : nullptr));
-        // xt in the tensors' dtype (x and p have been written so by the solve); p_t . H_t x_t
-        if (p->alpha) GKA_TRY(glue(0));
+        if (walk) {
+            GKA_TRY(walk_both());
+        } else {
+            GKA_TRY(glue(1));
+            GKA_TRY(solve_both(io(IO_RHS), io(IO_RHS_LO), rule ? fro : nullptr));
+            // xt in the tensors' dtype (x and p have been written so by the solve)
+            if (p->alpha) GKA_TRY(glue(0));
+        }
+        // p_t . H_t x_t
         GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
                         nullptr, pf32, phx));
     } else {

@@ -255,6 +255,17 @@ __global__ __launch_bounds__(256) void bwd_combine_natural_kernel(BackwardGlueAr
     }
 }
 
+// What is left to combine where the solve has formed dq and the dots of its own vectors (gka_fused.hip): scalars.
+__global__ __launch_bounds__(256) void bwd_combine_scalars_kernel(BackwardGlueArgs a)
+{
+    const int64_t tok = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (tok >= a.n_tokens) return;
+    const float be = a.beta ? a.beta[tok] : 1.0f;
+    const float dbeta = 0.5f * (a.vd[tok] + a.kd[tok]);
+    if (a.dbeta) a.dbeta[tok] = dbeta;
+    a.s[tok] = (a.dyy[tok] - a.phx[tok]) - be * dbeta;
+}
+
 // The two reverse scans over a pair's tokens, one workgroup of up to kScanWaves waves per (batch, head) pair:
 //   RULE: C_t = c_t + gate_{t+1}^2 C_{t+1};
 //   else the gate gradient dgate_t = (sum_{s>=t} s_s) / gate_t. A gate of 0 starts a new packed sequence (it wipes the
@@ -368,6 +379,10 @@ static void launch_glue_t(const BackwardGlueArgs &a, int which, hipStream_t stre
     case 1: hipLaunchKernelGGL((bwd_rhs_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;
     case 2: hipLaunchKernelGGL((bwd_reverse_kernel<IO>), dim3(blocks), dim3(256), 0, stream, a); break;
     case 3: {
+        if (a.dyy) {
+            hipLaunchKernelGGL(bwd_combine_scalars_kernel, dim3((unsigned)((a.n_tokens + 255) / 256)), dim3(256), 0, stream, a);
+            break;
+        }
         const int64_t per_block = 4 * (256 / a.d);         // 4 waves of 64 / (d / 4) tokens
         const unsigned tb = (unsigned)((a.n_tokens + per_block - 1) / per_block);
         if constexpr (std::is_same<IO, IOBF16>::value) {

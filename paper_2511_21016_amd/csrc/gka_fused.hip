@@ -325,20 +325,25 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-template <int NJ, bool SPLIT>
+// Operands of the passes. SINGLE: rounded to bf16. SPLIT: H_[n], delta and the masked products P o M as rounded value +
+// remainder. NO_STATE: H_[n] is zero (the first chunk of a sequence without an initial state), so the products with it drop out and
+// delta and P o M, which are all of H_c there, enter as value + remainder.
+enum PassMode { SINGLE, SPLIT_OPERANDS, NO_STATE };
+
+template <int NJ, PassMode MODE>
 struct PassPlan {
     // steps of the loop body, one A fragment each: the tile phase (8 tiles x (HP state + NJB intra fragments)), then
     // the key fragments of the next pass. SPLIT: the state fragments of a tile are the four of the value (each
     // multiplied with the value and with the remainder of delta) and the four of the remainder of H_[n]; a key fragment
     // is multiplied with both parts of delta.
-    static constexpr int NJB = NJ / 2, NP = 4 * NJ, HP = SPLIT ? 8 : 4, PER_TILE = HP + NJB, NT = 8 * PER_TILE,
-                         NS = NT + NP;
+    static constexpr int NJB = NJ / 2, NP = 4 * NJ, HP = MODE == SPLIT_OPERANDS ? 8 : MODE == SINGLE ? 4 : 0,
+                         PER_TILE = HP + NJB, NT = 8 * PER_TILE, NS = NT + NP;
     static constexpr int base(int i) { return i >= NT ? 1 : (i % PER_TILE < HP ? 0 : 2); }
     static constexpr int off(int i)
     {
         if (i >= NT) return (((i - NT) % NJ) * 4 + (i - NT) / NJ) * 64;       // keys [js][fb], fb-major order
         const int t = i / PER_TILE, u = i % PER_TILE;
-        if (u < 4) return (t * 4 + u) * 64;
+        if (u < HP && u < 4) return (t * 4 + u) * 64;
         if (u < HP) return 2048 + (t * 4 + (u - 4)) * 64;                     // remainder of H_[n]: 32 KiB further
         return (t * 2 + (u - HP)) * 64;
     }
@@ -390,13 +395,14 @@ __device__ __forceinline__ void key_products(const bf16x8 *sK, const bf16x8 (&x)
 // of the vector work behind it.
 // `start_copies` is called once, after the last LDS read that the compiler knows of: it issues the copies into LDS
 // that overlap the passes.
-template <int NJ, bool SPLIT, class StartCopies>
+template <int NJ, PassMode MODE, class StartCopies>
 __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, const bf16x8 *sKT, f32x4 (&xi)[8],
                                             f32x4 (&dl)[8], f32x4 (&gn)[8], const f32x4 (&mreg)[4], float s0z,
                                             float s0lam, float rho2, int n_iter, int lane,
                                             StartCopies start_copies)
 {
-    typedef PassPlan<NJ, SPLIT> PL;
+    typedef PassPlan<NJ, MODE> PL;
+    constexpr bool SPLIT = MODE != SINGLE;               // delta and the masked products come with their remainders
     constexpr int NJB = PL::NJB, PER_TILE = PL::PER_TILE, NT = PL::NT, NS = PL::NS, HP = PL::HP;
     static_assert((2048 + 31 * 64 + 63) * 16 < 65536, "the offset field of an LDS read holds 16 bits");
     // A fragments in flight. The request of step i + kDepth goes into the register that step i has just freed, also
@@ -436,7 +442,7 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
     // the first seven tenths of the passes, so that the two finish together (measured: with equal priorities the
     // lighter wave finishes a third earlier, with the priority held throughout it finishes a fifth later; alone on
     // its SIMD a wave runs at half the rate of the two together).
-    constexpr bool kBoost = NJ == 2 && !SPLIT;           // (SPLIT: one solver wave per SIMD)
+    constexpr bool kBoost = NJ == 2 && MODE == SINGLE;   // (SPLIT_OPERANDS: one solver wave per SIMD)
     if (kBoost) __builtin_amdgcn_s_setprio(1);
     const int prio_passes = n_iter / 2;
 #pragma unroll 1
@@ -465,6 +471,7 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
         auto upd_ops = [&](auto ftc, auto fromc, auto toc) {
             static_for<decltype(fromc)::value, decltype(toc)::value>([&](auto opc) { upd_op(ftc, opc); });
         };
+        if constexpr (HP == 0) static_for<0, NJB>(mask_products);
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, NS>([&](auto step) {
             constexpr int i = decltype(step)::value;
@@ -472,7 +479,7 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
             const bf16x8 a = __builtin_bit_cast(bf16x8, q[i % kDepth]);
             if constexpr (i < NT) {
                 constexpr int t = i / PER_TILE, u = i % PER_TILE;
-                if constexpr (u < 4) {
+                if constexpr (u < HP && u < 4) {
                     gn[t] = mma16(a, dB[u], gn[t]);
                     if constexpr (SPLIT) gn[t] = mma16(a, dR[u], gn[t]);
                 } else if constexpr (u < HP) {
@@ -492,8 +499,8 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
             }
             if constexpr (i < NT) {
                 constexpr int t = i / PER_TILE, u = i % PER_TILE;
-                if constexpr (t == 0 && u == 2) mask_products(std::integral_constant<int, 0>{});
-                if constexpr (t == 0 && u == 3 && NJB == 2) mask_products(std::integral_constant<int, NJB - 1>{});
+                if constexpr (HP > 0 && t == 0 && u == 2) mask_products(std::integral_constant<int, 0>{});
+                if constexpr (HP > 0 && t == 0 && u == 3 && NJB == 2) mask_products(std::integral_constant<int, NJB - 1>{});
                 if constexpr (t >= 1) {
                     // step u of the tile takes the operations [16 u / PER_TILE, 16 (u + 1) / PER_TILE)
                     upd_ops(std::integral_constant<int, t - 1>{}, std::integral_constant<int, 16 * u / PER_TILE>{},
@@ -666,7 +673,7 @@ __device__ __forceinline__ void solve_tokens(Ctx &c, Solver &s, int g, int ts, c
             gn[ft][r] = -rz * qv[r];
         }
     }
-    cheb_passes<NJ, SPLIT>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+    cheb_passes<NJ, SPLIT ? SPLIT_OPERANDS : SINGLE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
         // v rows of the iteration's chunks replace the k rows; they land during the passes
         copy_rows(c, c.a.v, 0, c0);
         if constexpr (!SPLIT) copy_rows(c, c.a.v, 1, c0 + 1);
@@ -785,14 +792,16 @@ __device__ __forceinline__ void build_key_frags(const Ctx &c, bf16x8 (&kT)[SPLIT
     }
 }
 
-// Start state of this wave's tiles: the caller's initial state advanced over the segments before this one.
-__device__ __forceinline__ void load_start_state(const Ctx &c, f32x4 (&accH)[8], f32x4 (&accU)[8], int pair, int seg)
+// Start state of this wave's tiles: the caller's initial state advanced over the segments before this one. (accU: absent
+// in a walk that needs H alone.)
+template <class... AccU>
+__device__ __forceinline__ void load_start_state(const Ctx &c, int pair, int seg, f32x4 (&accH)[8], AccU &...accU)
 {
     const FusedArgs &a = c.a;
 #pragma unroll
     for (int jt = 0; jt < 8; ++jt) {
         accH[jt] = zero4();
-        accU[jt] = zero4();
+        ((accU[jt] = zero4()), ...);
     }
     if (a.H_init) {
         const float *Hi = a.H_init + (int64_t)pair * kD * kD;
@@ -807,7 +816,7 @@ __device__ __forceinline__ void load_start_state(const Ctx &c, f32x4 (&accH)[8],
             } else {
                 accH[jt] = *(const f32x4 *)(Hi + (int64_t)(16 * c.w + c.n) * kD + 16 * jt + 4 * c.kg);
             }
-            accU[jt] = *(const f32x4 *)(Ui + (int64_t)(16 * c.w + c.n) * kD + 16 * jt + 4 * c.kg);
+            ((accU[jt] = *(const f32x4 *)(Ui + (int64_t)(16 * c.w + c.n) * kD + 16 * jt + 4 * c.kg)), ...);
         }
     }
     for (int sg = 0; sg < seg; ++sg) {
@@ -816,7 +825,7 @@ __device__ __forceinline__ void load_start_state(const Ctx &c, f32x4 (&accH)[8],
 #pragma unroll
         for (int jt = 0; jt < 8; ++jt) {
             accH[jt] = decay * accH[jt] + t[jt * 64];
-            accU[jt] = decay * accU[jt] + t[4096 + jt * 64];
+            ((accU[jt] = decay * accU[jt] + t[4096 + jt * 64]), ...);
         }
     }
 }
@@ -868,7 +877,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
     f32x4 accH[8];
     {
         f32x4 accU[8];
-        load_start_state(c, accH, accU, pair, seg);
+        load_start_state(c, pair, seg, accH, accU);
         park_store(c.park, accU);
     }
     copy_rows(c, a.k, 0, chunk_begin);
@@ -1045,6 +1054,275 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
     }
 }
 
+// ---- the two solves of the backward pass -----------------------------------------------------------------------
+namespace {
+
+// The lane's values of a token in two neighbouring tiles (x[0]: features 16 ft + 4 kg .., x[1]: 16 further) as bf16: lanes
+// of neighbouring kg exchange runs of four, so that a lane stores eight features at once. dst: the token's row.
+__device__ __forceinline__ void store_tile_pair(void *dst, int64_t row, int ft, int kg, const u16x4 (&x)[2])
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 a = __builtin_bit_cast(u32x2, x[0]), b = __builtin_bit_cast(u32x2, x[1]);
+    const auto r0 = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto r1 = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    // (odd kg of the first operand against even kg of the second: even kg holds the first tile, odd kg the second)
+    *(u32x4 *)((uint16_t *)dst + row + 16 * (ft + (kg & 1)) + 8 * (kg >> 1)) = u32x4{r0[0], r1[0], r0[1], r1[1]};
+}
+__device__ __forceinline__ u16x4 bf16_bits4(f32x4 x)
+{
+    return u16x4{f32_to_bf16_bits(x[0]), f32_to_bf16_bits(x[1]), f32_to_bf16_bits(x[2]), f32_to_bf16_bits(x[3])};
+}
+// A token's vector as bf16 value and, unless lo is nullptr, remainder.
+__device__ __forceinline__ void store_token_bf16(void *hi, void *lo, int64_t row, int kg, const f32x4 (&x)[8])
+{
+#pragma unroll
+    for (int ft = 0; ft < 8; ft += 2) {
+        const u16x4 v[2] = {bf16_bits4(x[ft]), bf16_bits4(x[ft + 1])};
+        store_tile_pair(hi, row, ft, kg, v);
+        if (lo) {
+            const u16x4 rem[2] = {bf16_bits4(x[ft] - IOBF16::cvt4(v[0])), bf16_bits4(x[ft + 1] - IOBF16::cvt4(v[1]))};
+            store_tile_pair(lo, row, ft, kg, rem);
+        }
+    }
+}
+__device__ __forceinline__ float dot4(f32x4 a, f32x4 b, float sum)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum = __builtin_fmaf(a[r], b[r], sum);
+    return sum;
+}
+
+// Both solves for the 16 tokens of this wave and what follows from them token by token: x_t, xt_t = alpha_t x_t + (1 -
+// alpha_t) q_t and p_t in the forms that the backward pass's readouts take, dlambda_t = -x_t . p_t, dalpha_t = dxt_t . (x_t - q_t),
+// dy_t . y_t = dxt_t . xt_t. The second solve's right-hand side alpha_t dxt_t is taken in float32.
+template <int NJ, PassMode MODE, bool GATED>
+__device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d, Solver &s, int g, int ts,
+                                                  const typename IOBF16::raw4 (&qraw)[8], float lam, int c0)
+{
+    const bf16x8 *sH = lds_frags(c, kOffH + g * 32768);
+    const bf16x8 *sK = lds_frags(c, kOffK + g * 16384);
+    const bf16x8 *sKT = lds_frags(c, kOffKT + g * 16384);
+    const float L = s.fro + lam, mu = lam;
+    const float rcp = __builtin_amdgcn_rcpf(L + mu);
+    const float s0 = 2.0f * rcp;
+    const float rho = (L - mu) * rcp;
+    s.zeta = fmaxf(s.zeta, kMinSolveZeta);               // (as in solve_tokens)
+    const float rz = 1.0f / s.zeta;
+#pragma unroll
+    for (int js = 0; js < 4; ++js) s.mreg[js] *= rz;
+    f32x4 xi[8], dl[8], gn[8];
+    auto start = [&](int ft, f32x4 rhs) {
+        xi[ft] = zero4();
+        dl[ft] = s0 * rhs;
+        gn[ft] = -rz * rhs;
+    };
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) start(ft, IOBF16::cvt4(qraw[ft]));
+    cheb_passes<NJ, MODE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+        // k rows of the next iteration's chunks (the row tiles are free); they land during the passes
+        copy_rows_untracked(c, c.a.k, 0, c0 + 2);
+        copy_rows_untracked(c, c.a.k, 1, c0 + 3);
+    });
+    wait_all_memory();                       // those copies (and stores of the chunks before) are long complete
+    refresh_lane(c);
+    const int tokc = min(s.tok, c.a.T - 1);
+    const int64_t tok_index = c.gate_base + (int64_t)tokc * c.a.H, row = tok_index * kD;
+    f32x4 dxt[8];
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) dxt[ft] = *(const f32x4 *)(d.dxt + row + 16 * ft + 4 * c.kg);
+    float al = 1.0f;
+    if constexpr (GATED) {
+        if (c.a.alpha) al = c.a.alpha[tok_index];
+    }
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) xi[ft] += dl[ft];
+    if (s.valid) {
+        if (d.x_f32) {
+#pragma unroll
+            for (int ft = 0; ft < 8; ++ft) *(f32x4 *)(d.x_f32 + row + 16 * ft + 4 * c.kg) = xi[ft];
+        }
+    }
+    // (all lanes take part in the exchanges of neighbouring kg; a token is valid on all four of its lanes or on none)
+    if (s.valid) store_token_bf16(d.x_hi, d.x_lo, row, c.kg, xi);
+    float dyy = 0.0f, dal = 0.0f;
+    if (!GATED || (!c.a.alpha && !d.dalpha)) {
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) dyy = dot4(dxt[ft], xi[ft], dyy);
+    } else {
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) {
+            const f32x4 qv = IOBF16::load4(c.a.q, row + 16 * ft + 4 * c.kg);
+            dal = dot4(dxt[ft], xi[ft] - qv, dal);
+            xi[ft] = al * xi[ft] + (1.0f - al) * qv;
+            dyy = dot4(dxt[ft], xi[ft], dyy);
+        }
+        if (s.valid && c.a.alpha) store_token_bf16(d.xt_hi, d.xt_lo, row, c.kg, xi);
+        dal = sum_over_kg(dal);
+        if (d.dalpha && s.valid && c.kg == 0) d.dalpha[tok_index] = dal;
+    }
+    dyy = sum_over_kg(dyy);
+    if (s.valid && c.kg == 0) d.dyy[tok_index] = dyy;
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) start(ft, GATED ? al * dxt[ft] : dxt[ft]);
+    cheb_passes<NJ, MODE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [] {});
+    refresh_lane(c);
+    const int tokc2 = min(s.tok, c.a.T - 1);
+    const int64_t tok_index2 = c.gate_base + (int64_t)tokc2 * c.a.H, row2 = tok_index2 * kD;
+    // x_t again, as it was stored (lanes of this wave did, before the passes; value + remainder)
+    wait_vector_memory_but<0>();
+    IOBF16::raw4 xh[8], xl[8];
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) {
+        xh[ft] = IOBF16::load_raw4(d.x_hi, row2 + 16 * ft + 4 * c.kg);
+        xl[ft] = IOBF16::load_raw4(d.x_lo, row2 + 16 * ft + 4 * c.kg);
+    }
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) xi[ft] += dl[ft];
+    if (s.valid) {
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) *(f32x4 *)(d.p_f32 + row2 + 16 * ft + 4 * c.kg) = xi[ft];
+        store_token_bf16(d.p_hi, nullptr, row2, c.kg, xi);
+    }
+    float xp = 0.0f;
+#pragma unroll
+    for (int ft = 0; ft < 8; ++ft) xp = dot4(IOBF16::cvt4(xh[ft]) + IOBF16::cvt4(xl[ft]), xi[ft], xp);
+    xp = sum_over_kg(xp);
+    if (d.dlambda && s.valid && c.kg == 0) d.dlambda[tok_index2] = -xp;
+    if constexpr (GATED) {
+        // (alpha_t is not read again: dalpha may have replaced it)
+        if (d.dq && s.valid) {               // dq_t = p_t + (1 - alpha_t) dxt_t (without an alpha-connection p_f32 is dq)
+#pragma unroll
+            for (int ft = 0; ft < 8; ++ft) {
+                const f32x4 dx = *(const f32x4 *)(d.dxt + row2 + 16 * ft + 4 * c.kg);
+                *(f32x4 *)(d.dq + row2 + 16 * ft + 4 * c.kg) = xi[ft] + (1.0f - al) * dx;
+            }
+        }
+    }
+}
+
+}  // namespace
+
+// x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r) in the fused forward kernel's walk: the
+// same eight waves and roles with H alone, so U, its parking place, the v rows and the readout drop out, and the second solve
+// reuses everything in front of the first one's passes. Replaces a state pass that wrote the chunk states to memory and a
+// solve kernel that read them, the pass that rounded alpha dxt, and, for a lambda that is given, the combination of the vectors
+// afterwards (the dots are formed here, where the vectors are in registers). Packed tensors. Bound as the forward kernel is, the
+// passes most of its cycles. 64 pairs x 4096 tokens, 10 passes: 358 us and 34 for the summaries, in place of 48 + 78 (state pass),
+// 507 (two-phase solve), 43 (rounding of alpha dxt) and 80 (combination, 5 left); the whole backward pass 1385 -> 1118.
+// Errors against the oracle (2-norm, mean over 16 sequences of 150 and 420 tokens, two-phase -> here): dk 3.6 -> 3.0e-3, with
+// the rule 5.6 -> 4.5e-3; dq 1.3 -> 1.2e-3, dv 1.8 -> 1.5e-3, dlambda 3.45 -> 3.35e-3, gate gradient 3.3 -> 2.7e-3.
+template <bool GATED>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dual_solve_kernel(DualSolveArgs d)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const FusedArgs &a = d.f;
+    Ctx c{d.f, smem};
+    c.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    refresh_lane(c);
+    const int pair = blockIdx.x % a.n_pairs, seg = blockIdx.x / a.n_pairs;
+    const int b = pair / a.H, h = pair % a.H;
+    c.base_bh = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
+    c.gate_base = (int64_t)b * a.T * a.H + h;
+    const int chunk_begin = seg * a.seg_len;
+    const int chunk_end = min(chunk_begin + a.seg_len, a.n_chunks);
+    if (chunk_begin >= chunk_end) return;
+    c.T_eff = min(a.T, chunk_end * kChunk);
+    const int grp = (c.w >> 1) & 1;                      // roles as in fused_forward_kernel
+    const int ts = (c.w < 4 ? 2 : 0) + (c.w & 1);
+    const bool wide = ts >= 2;
+
+    f32x4 accH[8];
+    load_start_state(c, pair, seg, accH);
+    copy_rows(c, a.k, 0, chunk_begin);
+    copy_rows(c, a.k, 1, chunk_begin + 1);
+    float *sTab = (float *)(smem + kOffTab);
+    float *gtab = (float *)(smem + kOffGateTab);
+    // gates and write gates of the chunks' tokens, lane j: token j
+    float gmA, gmB, bmA = 1.0f, bmB = 1.0f;
+    auto fetch_gates = [&](int chunk0) {
+        const int64_t atA = c.gate_base + (int64_t)min(chunk0 * kChunk + c.lane, a.T - 1) * a.H;
+        const int64_t atB = c.gate_base + (int64_t)min((chunk0 + 1) * kChunk + c.lane, a.T - 1) * a.H;
+        gmA = a.gate[atA];
+        gmB = a.gate[atB];
+        if constexpr (GATED) {
+            if (a.beta) {
+                bmA = a.beta[atA];
+                bmB = a.beta[atB];
+            }
+        }
+    };
+    fetch_gates(chunk_begin);
+    wait_all_memory();
+#pragma unroll 1
+    for (int c0 = chunk_begin; c0 < chunk_end; c0 += 2) {
+        refresh_lane(c);
+        // Per-token scalars of the chunks by waves 0 and 1 (see fused_forward_kernel), scanned before the barrier and written
+        // after it: the table lies in the second chunk's H_[n], which the others' passes may still read.
+        float G = 0.0f, wj = 0.0f;
+        if (c.w < 2) {
+            const bool valid = (c0 + c.w) * kChunk + c.lane < c.T_eff;
+            G = wave_inclusive_scan(valid ? log2_gate(c.w ? gmB : gmA) : 0.0f, c.lane);
+            wj = valid ? exp2f(lane_value(G, 63) - G) * (c.w ? bmB : bmA) : 0.0f;
+        }
+        lds_barrier();                       // everybody is through the passes, and everybody's copies have landed
+        if (c.w < 2) {
+            gtab[c.w * 64 + c.lane] = wj;
+            gtab[(2 + c.w) * 64 + c.lane] = G;
+            if constexpr (GATED) gtab[(4 + c.w) * 64 + c.lane] = c.w ? bmB : bmA;
+        }
+        lds_barrier();
+        const float zetaA = exp2f(lane_value(gtab[2 * 64 + c.lane], 63));
+        const float zetaB = exp2f(lane_value(gtab[3 * 64 + c.lane], 63));
+        const float hnA = publish_H<false>(c, accH, 0);
+        bf16x8 kT[2][2], wBA[2], wBB[2];
+        build_key_frags<false>(c, kT);
+        weight_frags(c, kT[0], gtab, wBA);
+        weight_frags(c, kT[1], gtab + 64, wBB);
+        Solver s;
+        s.tok = (c0 + grp) * kChunk + 16 * ts + c.n;
+        s.valid = s.tok < c.T_eff;
+        const int64_t tok_off = c.base_bh + (int64_t)min(s.tok, a.T - 1) * a.stride_t;
+        IOBF16::raw4 qraw[8];
+        float lam = 1.0f;
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) qraw[ft] = IOBF16::load_raw4(a.q, tok_off + 16 * ft + 4 * c.kg);
+        if (!GATED || a.lambda) lam = a.lambda[c.gate_base + (int64_t)min(s.tok, a.T - 1) * a.H];
+        build_mask<GATED>(c, s, gtab + (2 + grp) * 64, gtab + (4 + grp) * 64, ts);
+        lds_barrier();
+        advance_state(c, accH, 0, zetaA, wBA);
+        const float hnB = publish_H<false>(c, accH, 1);
+        advance_state(c, accH, 1, zetaB, wBB);
+        if (c.lane == 0) {
+            sTab[128 + c.w] = hnA;
+            sTab[128 + 8 + c.w] = hnB;
+        }
+        lds_barrier();
+        if (wide) frobenius_terms<4, GATED>(c, s, grp, ts);
+        else frobenius_terms<2, GATED>(c, s, grp, ts);
+        lds_barrier();
+        s.fro = wide ? frobenius_norm<4>(c, s, grp) : frobenius_norm<2>(c, s, grp);
+        if (a.fro_out && s.valid && c.kg == 0) a.fro_out[c.gate_base + (int64_t)s.tok * a.H] = s.fro;
+        if constexpr (GATED) {
+            if (!a.lambda) lam = a.lambda_scale * s.fro;
+        }
+        if (!s.valid) lam = 1.0f;
+        lds_barrier();                       // the table is dead: the row tiles may be overwritten
+        // The first tokens of a sequence are where p is least accurate with single operands (a state of low rank, whose
+        // masked products the solves amplify, and the gradient of the first keys is a difference of large terms): the chunk without a
+        // state before it takes value + remainder operands and, with nothing to multiply by H_[n], fewer products all the same.
+        const bool no_state = c0 + grp == 0 && !a.H_init;
+        if (no_state) {
+            if (wide) dual_solve_tokens<4, NO_STATE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+            else dual_solve_tokens<2, NO_STATE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+        } else {
+            if (wide) dual_solve_tokens<4, SINGLE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+            else dual_solve_tokens<2, SINGLE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+        }
+        fetch_gates(c0 + 2);
+    }
+    wait_all_memory();                       // no copy into this workgroup's LDS may be in flight when it ends
+}
+
 // Summary (prod gamma, Delta H, Delta U from a zero state) of every segment but the last: the start states of the
 // fused kernel's workgroups follow from these by a short scan. One chunk per iteration; its k and v rows were fetched
 // kSummaryAhead iterations earlier into registers and are stored into the other half of a double buffer, so an
@@ -1164,13 +1442,18 @@ size_t fused_workspace_bytes(int n_pairs, int n_segs)
     return n * (2 * kD * kD * sizeof(float)) + ((n * sizeof(float) + 255) / 256) * 256 + n * (kD * kD * sizeof(float));
 }
 
-hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_t stream, int which, bool split)
+static void carve_fused_workspace(FusedArgs &a, void *workspace)
 {
-    FusedArgs a = a0;
     a.seg_buf = (float *)workspace;
     const size_t n = (size_t)a.n_pairs * a.n_segs;
     a.seg_logdecay = (float *)((char *)workspace + n * (2 * kD * kD * sizeof(float)));
     a.park = (float *)((char *)a.seg_logdecay + ((n * sizeof(float) + 255) / 256) * 256);
+}
+
+hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_t stream, int which, bool split)
+{
+    FusedArgs a = a0;
+    carve_fused_workspace(a, workspace);
     // (the attribute is kept per device)
     static bool attr_set_on[64] = {};
     int dev = 0;
@@ -1207,6 +1490,28 @@ hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_
         else if (gated) hipLaunchKernelGGL((fused_forward_kernel<false, true>), grid, block, kLdsBytes, stream, a);
         else hipLaunchKernelGGL((fused_forward_kernel<false, false>), grid, block, kLdsBytes, stream, a);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_dual_solve(const DualSolveArgs &d0, void *workspace, hipStream_t stream)
+{
+    DualSolveArgs d = d0;
+    FusedArgs &a = d.f;
+    carve_fused_workspace(a, workspace);
+    static bool lds_raised[kMaxLdsDevices] = {};
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)dual_solve_kernel<false>, kLdsBytes},
+                                                 {(const void *)dual_solve_kernel<true>, kLdsBytes},
+                                                 {(const void *)fused_summary_kernel, kSummaryLds}});
+    if (e != hipSuccess) return e;
+    if (a.n_segs > 1) {
+        hipLaunchKernelGGL(fused_summary_kernel, dim3((unsigned)(a.n_pairs * (a.n_segs - 1))), dim3(kFusedThreads),
+                           kSummaryLds, stream, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid((unsigned)(a.n_pairs * a.n_segs)), block(kFusedThreads);
+    if (a.beta || a.alpha || !a.lambda || d.dalpha) hipLaunchKernelGGL(dual_solve_kernel<true>, grid, block, kLdsBytes, stream, d);
+    else hipLaunchKernelGGL(dual_solve_kernel<false>, grid, block, kLdsBytes, stream, d);
     return hipGetLastError();
 }
 

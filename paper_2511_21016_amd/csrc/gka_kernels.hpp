@@ -117,6 +117,7 @@ struct BackwardGlueArgs {
     const void *dxt_io, *y_io, *hx_io;                     // U_t^T dy_t; float32 tensors: forward output, H_t x_t
     const float *phx;             // bf16 tensors: p_t . H_t x_t,
     const float *kd, *vd;         //   k . dk / beta, v . dv / beta (gka_reverse.hip)
+    const float *dyy;             // dy_t . y_t where the solve has formed it (and dq, dlambda, dalpha): combination of scalars
     void *k_rev, *v_rev, *dy_rev, *x_rev, *p_rev, *xt_rev; // time-reversed copies
     float *gate_rev, *zeros;      // gates of the reverse recurrences; an all-zero alpha
     const void *r1, *r2, *r3, *r4;                         // reversed passes: A k, A^T k, Ubar^T v, Ubar k
@@ -265,6 +266,23 @@ size_t fused_workspace_bytes(int n_pairs, int n_segs);
 // and the masked products as bf16 value + remainder. (beta, alpha or a missing lambda select the kernels' variant with
 // the write gate, the alpha-connection and the rule for lambda.)
 hipError_t launch_fused_forward(const FusedArgs &a, void *workspace, hipStream_t stream, int which, bool split);
+
+// Both solves of the backward pass in the fused kernel's walk (bf16 tensors and operands, d = 128, packed tensors): x_t =
+// CH(H_t + lambda_t I, q_t, r), p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r). f: q, k, v (for the segments' summaries), gates,
+// lambda or its rule, initial states, sizes; fro_out optional. Vectors [B,T,H,d], scalars [B,T,H].
+struct DualSolveArgs {
+    FusedArgs f;
+    const float *dxt;             // U_t^T dy_t
+    float *x_f32;                 // x in float32, or nullptr
+    void *x_hi, *x_lo;            // x as bf16 value and remainder
+    void *xt_hi, *xt_lo;          // alpha x + (1 - alpha) q likewise (written with alpha only)
+    float *p_f32;
+    void *p_hi;                   // p in bf16
+    float *dq;                    // p + (1 - alpha) dxt, or nullptr (without alpha it is p)
+    float *dlambda, *dalpha;      // -x . p and dxt . (x - q), each nullptr or written
+    float *dyy;                   // dxt . xt
+};
+hipError_t launch_dual_solve(const DualSolveArgs &d, void *workspace, hipStream_t stream);
 
 // Workspace sizes in bytes per (pair, chunk).
 size_t ws_H_bytes_per_chunk(int d, bool compute_bf16);
