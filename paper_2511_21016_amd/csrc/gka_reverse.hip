@@ -19,11 +19,11 @@
 // not fit in LDS together).
 //
 // Bound by neither pipe: one workgroup per CU (its LDS), two waves per SIMD at d = 128 and one at d = 64, whose loads, LDS
-// exchanges and barriers do not cover each other (issue 32 %, matrix pipe 23 % of the busy cycles). 64 pairs x 4096 tokens,
-// d = 128: 86 us for the segments' summaries and 365 for the walk (part 1 62 + 152, part 2 50 + 241) and 133 for the kernel that
-// combines its outputs, in place of 657 for the four readouts and 349 for the combination of theirs; d = 64, 64 pairs x 2000
-// tokens 22 + 82. The walk with both recurrences at d = 128 takes 256 registers and spills 44 (part 1 158, part 2 242, d = 64
-// 234: none).
+// exchanges and barriers do not cover each other. 64 pairs x 4096 tokens, d = 128: 75 us for the segments' summaries and 246
+// for the walk. (With the rows of the next chunk fetched into registers behind the output stores, 48 of them, 44 spilled:
+// 80 + 352, a fifth of it spent where those loads were issued; copies straight into LDS without the touch of the next chunk's
+// lines: 268.) With an alpha-connection, 64 pairs x 2000 tokens: part 1 (two chunks' tiles) 33 + 70, part 2 27 + 117. All
+// variants fit in 231 registers without spills.
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
@@ -49,9 +49,13 @@ struct ReverseShape {
     static constexpr int UNITS = 6;                    // causal (token tile, pair of key tiles)
     static constexpr size_t p_bytes = (size_t)N_MATS * UNITS * 2 * 64 * 16;   // value and remainder
     static constexpr size_t tab_bytes = (2 + 2 * NW) * kChunk * 4;            // G, weights; partial dots
-    static constexpr size_t lds_main = N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes;
-    static constexpr size_t lds_summary = N_SUMMARY * tile_elems * 2 + 2 * kChunk * 4;
-    static constexpr int PIECES = kChunk * D / 8 / NT; // 16-byte pieces of a tensor's chunk per thread (2)
+    // Two chunks' tiles where they fit (d = 64; -S_t k_t alone at d = 128), so that a chunk's copies have a whole chunk's work
+    // to land in; else one, whose tiles are filled again as they fall free.
+    static constexpr bool TWO_MAIN = 2 * N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes <= 160 * 1024;
+    static constexpr size_t lds_main = (TWO_MAIN ? 2 : 1) * N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes;
+    static constexpr size_t lds_summary = 2 * N_SUMMARY * tile_elems * 2 + NW * kChunk * 4;   // two chunks; the waves' weights
+    // a copy instruction of a wave moves 1 KiB: ROWS rows; two instructions per wave and tensor
+    static constexpr int ROWS = 512 / D, COPIES = kChunk / ROWS / NW;
     typedef SwizzledRows<D * 2, 2> Rows;
 };
 
@@ -79,6 +83,23 @@ __device__ __forceinline__ frag negate(frag x)
 
 }  // namespace
 
+// Units of the masked key products that wave w takes. d = 128 with all three matrices: waves 0-5 one of [0] and one other, waves
+// 6 and 7 three others each; else one after the other.
+template <int D, int PART>
+__device__ __forceinline__ int reverse_units(int w)
+{
+    typedef ReverseShape<D, PART> SH;
+    if (D == 128 && SH::N_MATS == 3) return w < 6 ? 2 : 3;
+    return (SH::N_MATS * SH::UNITS - w + SH::NW - 1) / SH::NW;
+}
+template <int D, int PART>
+__device__ __forceinline__ int reverse_unit(int w, int i)
+{
+    typedef ReverseShape<D, PART> SH;
+    if (D == 128 && SH::N_MATS == 3) return w < 6 ? w + SH::UNITS * i : SH::UNITS + 6 + 3 * (w - 6) + i;
+    return w + SH::NW * i;
+}
+
 template <int D, int PART, bool SUMMARY>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void reverse_kernel(ReverseArgs a)
 {
@@ -96,8 +117,10 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
     uint16_t *sDY = tiles + (2 + DO_S) * SH::tile_elems;                       // dy (U)
     uint16_t *sK = tiles + (2 + DO_S + DO_U) * SH::tile_elems;
     uint16_t *sV = tiles + (3 + DO_S + DO_U) * SH::tile_elems;
-    frag *sP = (frag *)(tiles + NTEN * SH::tile_elems);
-    float *sG = SUMMARY ? (float *)sP : (float *)((unsigned char *)sP + SH::p_bytes);
+    constexpr bool TWO = SUMMARY || SH::TWO_MAIN;                              // two chunks' tiles
+    constexpr int TOUCH = TWO ? 0 : ((2 + DO_S + DO_U) * kChunk * D * 2 / 128 + NT - 1) / NT;
+    frag *sP = (frag *)(tiles + (TWO ? 2 : 1) * NTEN * SH::tile_elems);
+    float *sG = (float *)((unsigned char *)sP + SH::p_bytes);
     float *sW = sG + kChunk;
     float *sDot = sW + kChunk;                                                 // [2][NW][64]
 
@@ -151,39 +174,44 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
         }
     }
 
-    // ---- rows of a chunk: global -> registers (one chunk ahead) -> LDS
-    struct Fetch {
-        u32x4_t r[NTEN][SH::PIECES];
-        float gate;
-    };
+    // ---- rows of a chunk: direct copies global -> LDS (no staging registers: 48 for six tensors, which spilled and, read a chunk
+    // ahead behind the output stores, held every wave up for a fifth of the walk). The lane picks the 16 source bytes that belong
+    // at its place of the swizzled row. The compiler does not track these copies: they are awaited before the barrier that
+    // hands their tiles over.
     auto source = [&](int i) {
         if (i < 2) return i == 0 ? a.x : a.x_lo;
         if (i < 2 + DO_S + DO_U) return DO_S && i == 2 ? a.p : a.dy;
         return i == 2 + DO_S + DO_U ? a.k : a.v;
     };
-    auto fetch = [&](Fetch &f, int c) {
-        // one uniform base per tensor, 32-bit offsets within the chunk
-        const int t_low = max(a.T - 1 - (c * kChunk + kChunk - 1), 0);
-        const int64_t chunk_base = base + t_low * row_stride;
+    const uint32_t tiles_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)tiles;
+    auto copy_rows = [&](int first, int last, int c, int buffer) {
+        constexpr int PER_ROW = 64 / SH::ROWS;           // 16-byte pieces of a row
 #pragma unroll
-        for (int j = 0; j < SH::PIECES; ++j) {
-            const int piece = j * NT + tid;
-            const uint32_t off = (uint32_t)(tensor_token(c * kChunk + piece / (D / 8)) - t_low) * (uint32_t)row_stride +
-                                 8 * (piece % (D / 8));
+        for (int j = 0; j < SH::COPIES; ++j) {
+            const int idx = j * NW + w, row0 = idx * SH::ROWS;
+            const int row = row0 + lane / PER_ROW;
+            // (one uniform base per instruction, 32-bit offsets within its rows)
+            const int t_low = max(a.T - 1 - (c * kChunk + row0 + SH::ROWS - 1), 0);
+            const int64_t at0 = base + t_low * row_stride;
+            const int off = (int)((uint32_t)(tensor_token(c * kChunk + row) - t_low) * (uint32_t)row_stride * 2u) +
+                            (((lane % PER_ROW) * 16) ^ ((row & Rows::kMask) << 5));
 #pragma unroll
-            for (int i = 0; i < NTEN; ++i) f.r[i][j] = *(const u32x4_t *)((const uint16_t *)source(i) + chunk_base + off);
+            for (int i = 0; i < NTEN; ++i)
+                if (i >= first && i < last)
+                    async_copy16_to_lds_untracked(tiles_addr + ((buffer * NTEN + i) * (uint32_t)SH::tile_elems + idx * 512) * 2,
+                                                  raw_buffer_words((const uint16_t *)source(i) + at0), off);
         }
-        const int tau = min(c * kChunk + (tid & 63), a.T - 1);
-        f.gate = tau == 0 ? 1.0f : a.gate[gate_base + (int64_t)(a.T - tau) * a.H];   // gate'_tau = gate_{T - tau}
     };
-    auto stage = [&](const Fetch &f) {
-#pragma unroll
-        for (int j = 0; j < SH::PIECES; ++j) {
-            const int piece = j * NT + tid;
-            const int e = at(piece / (D / 8), 8 * (piece % (D / 8)));
-#pragma unroll
-            for (int i = 0; i < NTEN; ++i) *(u32x4_t *)(tiles + i * SH::tile_elems + e) = f.r[i][j];
-        }
+    auto gate_of = [&](int c) {                          // gate'_tau = gate_{T - tau}
+        const int tau = min(c * kChunk + lane, a.T - 1);
+        return tau == 0 ? 1.0f : a.gate[gate_base + (int64_t)(a.T - tau) * a.H];
+    };
+    // decays of a chunk, lane j: token j: G_j, the weight of token j in the states after the chunk
+    float G = 0.0f, wj = 0.0f;
+    auto scan = [&](int c, float gate) {
+        const bool valid = c * kChunk + lane < a.T;
+        G = wave_inclusive_scan(valid ? log2_gate(gate) : 0.0f, lane);
+        wj = valid ? exp2f(lane_value(G, 63) - G) : 0.0f;
     };
     // operand fragment of row 16 t + n of a tile: features 32 ks + 4 kg .. + 3 and 16 further
     auto row_frag = [&](const uint16_t *tile, int t, int ks) {
@@ -198,8 +226,8 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
     };
 
     float Gseg = 0.0f;
-    Fetch rows;
-    fetch(rows, chunk_begin);
+    float gate_next = gate_of(chunk_begin);
+    copy_rows(0, NTEN, chunk_begin, 0);
     for (int c = chunk_begin; c < chunk_end; ++c) {
         // (the lane index passes through an opaque copy in every chunk: addresses formed from it are not kept in registers
         // across the loop)
@@ -207,18 +235,47 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
         asm volatile("" : "+v"(lane));
         n = lane & 15;
         kg = lane >> 4;
-        // ---- decays of the chunk (every wave for itself): lane j holds token j
+        // ---- decays of the chunk (every wave for itself)
         const bool valid = c * kChunk + lane < a.T;
-        const float G = wave_inclusive_scan(valid ? log2_gate(rows.gate) : 0.0f, lane);
+        scan(c, gate_next);
         const float Gtot = lane_value(G, 63);
         Gseg += Gtot;
-        lds_barrier();                                 // the previous chunk's tiles have been read
-        stage(rows);
-        if (w == 0) {
-            sG[lane] = G;
-            sW[lane] = valid ? exp2f(Gtot - G) : 0.0f; // weight of token j in the states after the chunk
+        const int buffer = TWO ? (c - chunk_begin) & 1 : 0;
+        if constexpr (TWO) {
+            sX = tiles + (size_t)buffer * NTEN * SH::tile_elems;
+            sXL = sX + SH::tile_elems;
+            sPr = sX + 2 * SH::tile_elems;
+            sDY = sX + (2 + DO_S) * SH::tile_elems;
+            sK = sX + (2 + DO_S + DO_U) * SH::tile_elems;
+            sV = sX + (3 + DO_S + DO_U) * SH::tile_elems;
         }
-        lds_barrier();
+        if constexpr (SUMMARY) {
+            sW = (float *)sP + w * kChunk;             // (of its own for every wave)
+            sW[lane] = wj;
+        } else if (w == 0) {
+            sG[lane] = G;
+            sW[lane] = wj;
+        }
+        wait_vector_memory_but<0>();                   // this wave's copies have landed
+        lds_barrier();                                 // ... and everybody's; the table is complete
+        gate_next = gate_of(c + 1);
+        // One set of tiles: the next chunk's lines of the tensors that can only be copied at the end of this one are asked for now,
+        // a word of each, so that the copies find them in L2.
+        uint32_t touched[TOUCH > 0 ? TOUCH : 1];
+        if constexpr (TOUCH > 0) {
+            constexpr int LINES = kChunk * D * 2 / 128;  // of a tensor
+#pragma unroll
+            for (int j = 0; j < TOUCH; ++j) {
+                const int line = min(j * NT + tid, (2 + DO_S + DO_U) * LINES - 1);
+                const int i = line / LINES, row = line % LINES / (D * 2 / 128), part = line % (D * 2 / 128);
+                const int tok = tensor_token(min((c + 1) * kChunk + row, chunk_end * kChunk - 1));
+                const uint16_t *src = (const uint16_t *)(i < 2 ? (i == 0 ? a.x : a.x_lo) : DO_S && i == 2 ? a.p : a.dy);
+                touched[j] = *(const uint32_t *)(src + base + tok * row_stride + part * 64);
+            }
+        }
+        if constexpr (TWO) {
+            if (c + 1 < chunk_end) copy_rows(0, NTEN, c + 1, buffer ^ 1);
+        }
 
         // this wave's columns of the row tensors, transposed: A operand of the intra-chunk products and, weighted, B
         // operand of the state updates
@@ -234,8 +291,10 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
         if constexpr (!SUMMARY) {
             // ---- masked key products, (token tile tt, key tiles 2 m, 2 m + 1) per unit, dealt out over the waves:
             // [0] x . k, [1] p . k (S), last: dy . v (U)
-            for (int u0 = w; u0 < SH::N_MATS * UNITS; u0 += NW) {
-                const int mat = u0 / UNITS, u = u0 - mat * UNITS;
+            // (a unit of [0], two products for every one of the others', counts twice: dealt out so that every wave has the same)
+            const int n_units = reverse_units<D, PART>(w);
+            for (int i = 0; i < n_units; ++i) {
+                const int u0 = reverse_unit<D, PART>(w, i), mat = u0 / UNITS, u = u0 - mat * UNITS;
                 const int tt = u < 2 ? u : u < 4 ? 2 : 3, m = u < 2 ? 0 : u & 1;
                 const bool is_u = DO_U && mat == SH::N_MATS - 1;
                 const uint16_t *keys = mat == 0 ? sX : is_u ? sDY : sPr, *query = is_u ? sV : sK;
@@ -373,10 +432,27 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
             }
         }
 
-        // the next chunk's rows are requested here: behind the outputs their registers are free, and the update covers
-        // their latency
-        __builtin_amdgcn_sched_barrier(0);
-        if (c + 1 < chunk_end) fetch(rows, c + 1);
+        if constexpr (TOUCH > 0) {
+#pragma unroll
+            for (int j = 0; j < TOUCH; ++j) asm volatile("" ::"v"(touched[j]));
+        }
+        if constexpr (!SUMMARY) {
+            lds_barrier();                             // the queries' tiles are free; the partial dots are complete
+            if (!TWO && c + 1 < chunk_end) copy_rows(2 + DO_S + DO_U, NTEN, c + 1, 0);
+            if constexpr (DO_U) {
+                if (w == 0 && valid) {
+                    float kd = 0.0f, vd = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) {
+                        kd += sDot[i * kChunk + lane];
+                        vd += sDot[(NW + i) * kChunk + lane];
+                    }
+                    const int64_t g = gate_base + (int64_t)tensor_token(c * kChunk + lane) * a.H;
+                    a.kd[g] = kd;
+                    a.vd[g] = vd;
+                }
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- state <- zeta_C state + sum of weighted outer products
@@ -435,22 +511,12 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
                 }
             }
         }
-        if constexpr (!SUMMARY && DO_U) {
-            // the partial dots of this chunk (written before the update; the next chunk's are two barriers away)
-            lds_barrier();
-            if (w == 0 && valid) {
-                float kd = 0.0f, vd = 0.0f;
-#pragma unroll
-                for (int i = 0; i < NW; ++i) {
-                    kd += sDot[i * kChunk + lane];
-                    vd += sDot[(NW + i) * kChunk + lane];
-                }
-                const int64_t g = gate_base + (int64_t)tensor_token(c * kChunk + lane) * a.H;
-                a.kd[g] = kd;
-                a.vd[g] = vd;
-            }
+        if constexpr (!SUMMARY) {
+            lds_barrier();                             // the other tiles and the table are free
+            if (!TWO && c + 1 < chunk_end) copy_rows(0, 2 + DO_S + DO_U, c + 1, 0);
         }
     }
+    wait_all_memory();                                 // no copy into this workgroup's LDS may be in flight when it ends
 
     if constexpr (SUMMARY) {
 #pragma unroll
