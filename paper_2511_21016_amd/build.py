@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgka.so")
-SOURCES = ["gka_api.hip", "gka_state_pass.hip", "gka_chunk_solve.hip", "gka_solve_f32.hip",
+SOURCES = ["gka_api.hip", "gka_state_pass.hip", "gka_chunk_solve.hip", "gka_solve_f32.hip", "gka_solve_wide.hip",
            "gka_fused.hip", "gka_decode.hip", "gka_backward.hip", "gka_readout.hip", "gka_reverse.hip",
            "gka_sketch.hip", "gka_small_dim.hip"]
 HIPCC_FLAGS = [

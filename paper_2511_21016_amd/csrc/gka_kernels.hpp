@@ -242,6 +242,10 @@ hipError_t launch_chunk_solve(const SolveArgs &a, int n_pairs, int d, bool io_bf
                               hipStream_t stream);
 // The same with float32 products (gka_solve_f32.hip; d = 64, 128, 256): what launch_chunk_solve calls for float32 operands.
 hipError_t launch_solve_f32(const SolveArgs &a, int d, bool io_bf16, hipStream_t stream);
+// d = 256, bf16 tensors: float32's precision from 16-bit pieces (gka_solve_wide.hip), which launch_solve_f32 selects where it can;
+// tiles: token tiles per workgroup, 1 or 2.
+bool solve_wide_takes(const SolveArgs &a, int d, bool io_bf16);
+hipError_t launch_solve_wide(const SolveArgs &a, int tiles, hipStream_t stream);
 hipError_t launch_decode_step(const DecodeArgs &a, int n_pairs, int d, bool io_bf16, hipStream_t stream);
 
 // Forward pass in one kernel with the states in registers (bf16 tensors and operands, d = 128, Eq. (CH) as printed).

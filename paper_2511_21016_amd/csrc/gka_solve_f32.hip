@@ -502,6 +502,7 @@ static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
     // 1024 chunks 472 / 436; d = 256: 20 chunks 119 / 181, 88 chunks 210 / 209, 160 chunks 240 / 227, 512 chunks 834 / 724.
     // (TT = 4 at d = 128, 1024 chunks: 460; at d = 256 the state rows leave no registers for it.)
     const int64_t chunks = (int64_t)a.n_pairs * a.n_chunks;
+    if (solve_wide_takes(a, D, std::is_same<IO, IOBF16>::value)) return launch_solve_wide(a, chunks <= 96 ? 1 : 2, stream);
     if (chunks <= (D == 256 ? 96 : 192)) return launch_solve_f32_t<IO, D, 1, MODE>(a, stream);
     return launch_solve_f32_t<IO, D, 2, MODE>(a, stream);
 }
