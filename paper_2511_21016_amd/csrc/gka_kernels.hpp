@@ -84,6 +84,7 @@ struct SolveArgs {
     void *xhat_hi, *xhat_lo, *xhat2_hi;
     bool init_states;             // the sequence starts from given states (else the states before chunk 0 are zero)
     int skip_blocks;              // float32 products: token blocks at the chunks' ends that launches before this one took
+                                  // (gka_solve_wide.hip: -1 if this one takes them all)
 };
 
 struct DecodeArgs {

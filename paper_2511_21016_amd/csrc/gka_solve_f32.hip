@@ -18,8 +18,8 @@
 // Bound: the matrix pipe (157 TFLOP/s in float32). Measured, microseconds per forward pass, against 32 x 32 x 2 products
 // with two waves per token block that each formed all of P, H_[n] in LDS, one workgroup per chunk: d = 64, 1 pair x 256
 // tokens 62 -> 32; d = 64, 64 x 1024 205 -> 163; d = 128, 16 x 1500 309 -> 197; d = 128, 64 x 1024 664 -> 436
-// (98 TFLOP/s). d = 256, 32 x 1024 against the token-by-token kernel: 16220 -> 724, of which this kernel 600 (the matrix pipe
-// busy 75 % of it). Registers: capped at 128 up to d = 128 (four waves per SIMD), at 256 at d = 256 (two). With
+// (98 TFLOP/s). d = 256, 32 x 1024 float32 tensors against the token-by-token kernel: 16220 -> 724, of which this kernel 600 (the
+// matrix pipe busy 75 % of it); bf16 tensors there: gka_solve_wide.hip. Registers: capped at 128 up to d = 128 (four waves per SIMD), at 256 at d = 256 (two). With
 // TT = 2 that spills: d = 128 3 (bf16 tensors), 14 (float32), 12 to 29 with the variants or two right-hand sides; d = 256
 // 15 (bf16), 31 (float32), up to 57 with the variants; d = 64 16 with the variants of float32 tensors. With TT = 1 none.
 #include "gka_device.hpp"
@@ -502,7 +502,10 @@ static hipError_t launch_solve_f32_d(const SolveArgs &a, hipStream_t stream)
     // 1024 chunks 472 / 436; d = 256: 20 chunks 119 / 181, 88 chunks 210 / 209, 160 chunks 240 / 227, 512 chunks 834 / 724.
     // (TT = 4 at d = 128, 1024 chunks: 460; at d = 256 the state rows leave no registers for it.)
     const int64_t chunks = (int64_t)a.n_pairs * a.n_chunks;
-    if (solve_wide_takes(a, D, std::is_same<IO, IOBF16>::value)) return launch_solve_wide(a, chunks <= 96 ? 1 : 2, stream);
+    // (gka_solve_wide.hip: one round of workgroups either way up to 64 and 128 chunks. Whole forward pass, TT = 1 / 2: 20 chunks
+    // 57 / 79, 64 chunks 68 / 91, 88 chunks 114 / 100, 128 chunks 106 / 93, 160 chunks 136 / 133, 512 chunks 399 / 347; with
+    // float32 products 119, 134, 210, 193, 228, 717)
+    if (solve_wide_takes(a, D, std::is_same<IO, IOBF16>::value)) return launch_solve_wide(a, chunks <= 64 ? 1 : 2, stream);
     if (chunks <= (D == 256 ? 96 : 192)) return launch_solve_f32_t<IO, D, 1, MODE>(a, stream);
     return launch_solve_f32_t<IO, D, 2, MODE>(a, stream);
 }

@@ -12,7 +12,11 @@
 // Operands of all contractions over features sit in LDS as fragments of v_mfma_f32_16x16x32: lane (n, kg) = (lane & 15,
 // lane >> 4), eight values, slot p <-> feature 32 s + 16 (p / 4) + 4 kg + p % 4. A wave's rows of a vector are one such
 // fragment.
-// Measured: FIGURES
+// Measured, 32 pairs x 1024 tokens, 10 passes, us: this kernel 313 in place of 610 with float32 products, the whole forward pass
+// (with the state pass on pieces too) 724 -> 374; 4 pairs x 300 tokens 119 -> 57. Two thirds of a workgroup's time are its
+// states on their way from memory (512 KiB, nothing beside it on the CU) and what surrounds the passes; a pass is 7.4 k
+// cycles, of which the matrix pipe needs 4.4 k and LDS 3.2 k. Against the oracle: the solve's result 3.4e-7 -> 2.2e-7 (2-norm;
+// 2.9e-6 both with lambda a hundredth), ||H_t||_F 3.5e-7 -> 2.5e-7, the output its own rounding both.
 #include "gka_device.hpp"
 #include "gka_kernels.hpp"
 
@@ -115,10 +119,15 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
-    // (order of the workgroups as in gka_solve_f32.hip: later token tiles, which see more keys, first)
-    const int per_tb = a.n_pairs * a.n_chunks;
-    const int tb = TB - 1 - a.skip_blocks - (int)blockIdx.x / per_tb;
-    const int within = (int)blockIdx.x % per_tb;
+    // The workgroups of a chunk read the same 512 KiB of states. They get block indices equal modulo 8, next to each other: the
+    // same XCD, whose L2 then serves all but the first, at about the same time. (All of one token block before the next:
+    // states read from HBM once for each,
+    // 32 pairs x 1024 tokens 426 us per forward pass instead of 409; U_[n]'s lines asked for during the passes: 428.) Within a chunk the later tokens, which see more keys, come first.
+    const int n_all = a.n_pairs * a.n_chunks, blocks = a.skip_blocks < 0 ? TB : 1;
+    const int group = (int)blockIdx.x / (8 * blocks), in_group = min(8, n_all - 8 * group);
+    const int rest = (int)blockIdx.x - group * 8 * blocks;
+    const int tb = TB - 1 - max(a.skip_blocks, 0) - rest / in_group;
+    const int within = 8 * group + rest % in_group;
     const int pair = within % a.n_pairs, chunk_local = within / a.n_pairs;
     const int chunk = a.chunk0 + chunk_local;
     const int b = (a.pair0 + pair) / a.H, h = (a.pair0 + pair) % a.H;
@@ -533,11 +542,11 @@ static hipError_t launch_solve_wide_t(const SolveArgs &a, hipStream_t stream)
     hipError_t e = raise_lds_limits(lds_raised, {{(const void *)solve_wide_kernel<TT, GATED>, SH::lds_bytes}});
     if (e != hipSuccess) return e;
     // (outputs that replace rows of k or v: the token blocks of a chunk one launch after the other, as in gka_solve_f32.hip)
-    const int blocks = a.o == a.v || a.o == a.k ? 1 : SH::TB;
+    const bool over_rows = a.o == a.v || a.o == a.k;
     SolveArgs args = a;
-    for (args.skip_blocks = 0; args.skip_blocks < SH::TB; args.skip_blocks += blocks) {
-        hipLaunchKernelGGL((solve_wide_kernel<TT, GATED>), dim3((unsigned)(a.n_pairs * a.n_chunks * blocks)), dim3(kWideThreads),
-                           SH::lds_bytes, stream, args);
+    for (args.skip_blocks = over_rows ? 0 : -1; args.skip_blocks < (over_rows ? SH::TB : 0); ++args.skip_blocks) {
+        hipLaunchKernelGGL((solve_wide_kernel<TT, GATED>), dim3((unsigned)(a.n_pairs * a.n_chunks * (over_rows ? 1 : SH::TB))),
+                           dim3(kWideThreads), SH::lds_bytes, stream, args);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

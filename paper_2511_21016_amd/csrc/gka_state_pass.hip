@@ -84,6 +84,15 @@ __device__ __forceinline__ void store_end_state(const StatePassArgs &a, const f3
 // DOH: this workgroup owns the H slab (else the U slab); WRITE: chunk states are written to the workspace. Both are
 // compile-time so that the chunk loop is straight-line code and the in-flight prefetches are never drained by a
 // conservative wait.
+// Float32 operands of bf16 tensors at d = 256: the k rows are bf16 as they are, and the weighted rows of a in three bf16 pieces
+// have float32's 24 bits, so a float32 product is three bf16 ones, at a fifth of the matrix pipe's time and with half the LDS;
+// the k rows carry no weight. 32 pairs x 1024 tokens: 131 -> 76 us, of which 268 MB of states take 53.
+template <class MMA, class IO, int D>
+constexpr bool state_pass_by_pieces()
+{
+    return std::is_same<MMA, MmaF32>::value && std::is_same<IO, IOBF16>::value && D == 256;
+}
+
 template <class MMA, class IO, int D, bool DOH, bool WRITE, bool GATED>
 __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, int group,
                                                 typename MMA::elem_t *s_k, typename MMA::elem_t *s_v)
@@ -96,6 +105,10 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
     constexpr int RSV = 32 + MMA::kRowPad;
     constexpr int KP = kChunk * (D / 4) / NT;     // 4-element pieces of k per thread (= 8)
     constexpr int VP = kChunk * 8 / NT;           // 4-element pieces of the v slab per thread
+    constexpr bool PIECES = state_pass_by_pieces<MMA, IO, D>();
+    // PIECES: k rows as they are, then the slab's columns of the weighted a rows, three pieces
+    constexpr int RSB = D + MmaBF16::kRowPad, RSA = 32 + MmaBF16::kRowPad;
+    uint16_t *t_k = (uint16_t *)s_k, *t_a = (uint16_t *)s_v;
     typedef typename MMA::frag frag;
     typedef typename MMA::elem_t elem_t;
 
@@ -142,13 +155,13 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
             const int t = min(c * kChunk + row, a.T - 1);
             f.k[i] = IO::load_raw4(a.k, base_bh + (int64_t)t * a.stride_t + 4 * c4);
         }
-        if (!doH) {
+        if (!doH || PIECES) {
 #pragma unroll
             for (int i = 0; i < VP; ++i) {
                 const int piece = i * NT + tid;
                 const int row = piece / 8, c4 = piece % 8;
                 const int t = min(c * kChunk + row, a.T - 1);
-                f.v[i] = IO::load_raw4(a.v, base_bh + (int64_t)t * a.stride_t + 32 * rb + 4 * c4);
+                f.v[i] = IO::load_raw4(doH ? a.k : a.v, base_bh + (int64_t)t * a.stride_t + 32 * rb + 4 * c4);
             }
         }
         const int t = min(c * kChunk + lane, a.T - 1);
@@ -165,11 +178,17 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
         Gseg += Gtot;
         float swd = exp2f(0.5f * (Gtot - G));          // lane j: sqrt(beta_j zeta_C / zeta_j)
         if constexpr (GATED) swd *= sqrtf(a.beta ? f.beta : 1.0f);
+        float wd = PIECES ? exp2f(Gtot - G) : 0.0f;    // the whole weight
+        if constexpr (GATED) wd *= a.beta ? f.beta : 1.0f;
         lds_barrier();                          // previous chunk's LDS readers are done
 #pragma unroll
         for (int i = 0; i < KP; ++i) {
             const int piece = i * NT + tid;
             const int row = piece / (D / 4);
+            if constexpr (PIECES) {
+                *(u16x4 *)(t_k + row * RSB + 4 * (piece % (D / 4))) = c * kChunk + row >= a.T ? u16x4{0, 0, 0, 0} : f.k[i];
+                continue;
+            }
             f32x4 kv = IO::cvt4(f.k[i]);
             if (c * kChunk + row >= a.T) kv = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             // the wave's 64 pieces of this sweep lie in two consecutive rows
@@ -178,7 +197,23 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
                                            : __shfl(swd, row, 64);
             MMA::store4(s_k + row * RS + 4 * (piece % (D / 4)), kv * sw);
         }
-        if (!doH) {
+        if constexpr (PIECES) {
+#pragma unroll
+            for (int i = 0; i < VP; ++i) {
+                const int piece = i * NT + tid;
+                const int row = piece / 8;
+                f32x4 vv = IO::cvt4(f.v[i]);
+                if (c * kChunk + row >= a.T) vv = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                vv *= __shfl(wd, row, 64);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const u16x4 bits = {f32_to_bf16_bits(vv[0]), f32_to_bf16_bits(vv[1]), f32_to_bf16_bits(vv[2]),
+                                        f32_to_bf16_bits(vv[3])};
+                    *(u16x4 *)(t_a + (p * kChunk + row) * RSA + 4 * (piece % 8)) = bits;
+                    vv -= IOBF16::cvt4(bits);
+                }
+            }
+        } else if (!doH) {
 #pragma unroll
             for (int i = 0; i < VP; ++i) {
                 const int piece = i * NT + tid;
@@ -216,6 +251,19 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
         // ---- S <- zeta_C S + sum_j w_j a_j k_j^T
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] *= zetaC;
+        if constexpr (PIECES) {
+            const int sub = 16 * ((lane >> 4) & 1);
+#pragma unroll
+            for (int s = 0; s < kChunk / 16; ++s) {
+                const int j0 = 16 * s + 8 * g;
+                const bf16x8 fa = gather_transposed_bf16(t_k, PaddedRows{RSB}, 32 * w + sub, lane, j0, j0 + 4);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    acc = MmaBF16::mma(fa, gather_transposed_bf16(t_a + p * kChunk * RSA, PaddedRows{RSA}, sub, lane, j0, j0 + 4),
+                                       acc);
+            }
+            return;
+        }
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             // lane (n, g): tokens j = s*2*VEC + g*VEC + p of the chunk
@@ -589,8 +637,11 @@ __global__ __launch_bounds__(D * 2) __attribute__((amdgpu_waves_per_eu(kStateWav
     if (a.only_h && (sub & 1)) return;             // ... or its U states
     const int rb = sub >> 1;                       // slab index (row block of H0 / U0)
     typedef typename MMA::elem_t elem_t;
-    __shared__ __attribute__((aligned(1024))) elem_t s_k[kChunk * (D + MMA::kRowPad)];
-    __shared__ __attribute__((aligned(16))) elem_t s_v[kChunk * (32 + MMA::kRowPad)];
+    constexpr bool PIECES = state_pass_by_pieces<MMA, IO, D>();
+    constexpr size_t k_bytes = PIECES ? kChunk * (D + MmaBF16::kRowPad) * 2 : kChunk * (D + MMA::kRowPad) * sizeof(elem_t);
+    constexpr size_t v_bytes = PIECES ? 3 * kChunk * (32 + MmaBF16::kRowPad) * 2 : kChunk * (32 + MMA::kRowPad) * sizeof(elem_t);
+    __shared__ __attribute__((aligned(1024))) elem_t s_k[k_bytes / sizeof(elem_t)];
+    __shared__ __attribute__((aligned(16))) elem_t s_v[v_bytes / sizeof(elem_t)];
     if (a.write_frags) {
         if (sub & 1) state_pass_body<MMA, IO, D, false, true, GATED>(a, rb, group, s_k, s_v);
         else state_pass_body<MMA, IO, D, true, true, GATED>(a, rb, group, s_k, s_v);
