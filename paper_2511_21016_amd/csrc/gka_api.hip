@@ -570,6 +570,27 @@ void plan_reverse_segments(int n_pairs, int n_chunks, int *n_segs, int *seg_len)
     *n_segs = (n_chunks + *seg_len - 1) / *seg_len;
 }
 
+// Segments of the two solves' walk (gka_fused.hip) and the finer parts of them whose summaries are formed: the readouts, which
+// start from the same summaries, walk a part each. seg_len is a multiple of sum_len and even.
+struct WalkSegments {
+    int seg_len, n_segs, sum_len, n_sums;
+};
+WalkSegments plan_walk_segments(int n_pairs, int n_chunks, int n_iter, int walk_chunks)
+{
+    int rs_n, rs_len;
+    plan_readout_segments(n_pairs, n_chunks, &rs_n, &rs_len);
+    int len = walk_chunks > 0 ? walk_chunks + (walk_chunks & 1) : fused_segment(n_pairs, n_chunks, 2 * n_iter, false);
+    int parts = (len + rs_len - 1) / rs_len;
+    if (parts > len / 2) parts = len / 2;            // (two chunks at least)
+    WalkSegments s;
+    s.sum_len = (len + parts - 1) / parts;
+    if (s.sum_len * parts % 2) ++s.sum_len;
+    s.seg_len = s.sum_len * parts;
+    s.n_segs = (n_chunks + s.seg_len - 1) / s.seg_len;
+    s.n_sums = (n_chunks + s.sum_len - 1) / s.sum_len;
+    return s;
+}
+
 // Tensors of the backward pass in the tensors' dtype: those of float32 tensors alone, those of both, those of bf16 tensors.
 enum { IO_Y, IO_DXT, IO_HX, IO_KR, IO_VR, IO_DYR, IO_XR, IO_XTR, IO_R1, IO_R2, IO_R3, IO_R4,
        IO_RHS, IO_BF16_FIRST = IO_RHS, IO_X, IO_XT, IO_PR, IO_SCRATCH, IO_HK, IO_VPR, IO_R5,
@@ -631,6 +652,12 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
     plan_reverse_segments(p->B * p->H, (p->T + gka::kChunk - 1) / gka::kChunk, &rs_n, &rs_len);
     const size_t vbytes = align_up(gka::reverse_workspace_bytes(p->B * p->H, rs_n, p->d_k), 256);
     if (vbytes > bp->fwd_bytes) bp->fwd_bytes = vbytes;
+    // (the solves' walk keeps no more than one summary for every two chunks, and at most about kReadoutMinWorkgroups)
+    int64_t sums = (int64_t)p->B * p->H * ((((p->T + gka::kChunk - 1) / gka::kChunk) + 1) / 2);
+    const int64_t most = (int64_t)kFusedMaxWorkgroups + p->B * p->H;
+    if (sums > most) sums = most;
+    const size_t sbytes = align_up(gka::fused_summary_bytes((int)sums, 1), 256);
+    if (p->d_k == 128 && p->io_dtype == GKA_BF16 && sbytes > bp->fwd_bytes) bp->fwd_bytes = sbytes;
     bp->total = off + bp->fwd_bytes;
     return GKA_OK;
 }
@@ -733,6 +760,30 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     auto glue = [&](int which) {
         return gka::launch_backward_glue(g, which, io_bf16, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
+    // d = 128 with bf16 operands: the fused kernels' walk solves for both right-hand sides (a caller that asks for the two-phase
+    // kernels or bounds their chunk states gets those)
+    const bool walk = io_bf16 && p->d_k == 128 && p->compute == GKA_COMPUTE_BF16 && p->path == GKA_PATH_AUTO && p->slab_state_bytes == 0;
+    gka::DualSolveArgs d = {};
+    if (walk) {
+        gka::FusedArgs &f = d.f;
+        f.q = q; f.k = k; f.v = v; f.gate = gate; f.lambda = lambda; f.fro_out = rule ? fro : nullptr;
+        f.beta = p->beta; f.alpha = p->alpha; f.lambda_scale = p->lambda_scale;
+        f.H_init = H_init; f.U_init = U_init;
+        f.stride_h = p->d_k; f.stride_t = (int64_t)p->H * p->d_k; f.stride_b = (int64_t)p->T * p->H * p->d_k;
+        f.H = p->H; f.T = p->T; f.n_iter = p->n_iter;
+        f.n_pairs = p->B * p->H; f.n_chunks = (p->T + gka::kChunk - 1) / gka::kChunk;
+        const WalkSegments s = plan_walk_segments(f.n_pairs, f.n_chunks, p->n_iter, p->walk_chunks);
+        f.seg_len = s.seg_len; f.n_segs = s.n_segs; f.n_sums = s.n_sums; f.sums_per_seg = s.seg_len / s.sum_len;
+        d.dxt = f32buf(2);
+        d.x_f32 = rule ? xf : nullptr;
+        d.x_hi = io(IO_X); d.x_lo = io(IO_X_LO); d.xt_hi = io(IO_XT); d.xt_lo = io(IO_XT_LO);
+        d.p_f32 = pf32; d.p_hi = io(IO_PR);
+        d.dyy = sbuf;
+        if (!rule) {                          // (with the rule the combination of the vectors follows)
+            d.dq = p->alpha ? dq : nullptr;
+            d.dlambda = dlambda; d.dalpha = dalpha;
+        }
+    }
     // the plain readout y_t = U_t qq_t, U_t = gate_t U_{t-1} + beta_t vv_t kk_t^T, in one kernel with the state in
     // registers (bf16 tensors); `reverse`: the recurrence runs from the last token to the first
     // (bf16 tensors: whatever operands the two solves use, the readouts take the stored bf16 tensors as they are)
@@ -756,36 +807,14 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         r.qk_stride_h = r.stride_h; r.qk_stride_t = r.stride_t; r.qk_stride_b = r.stride_b;
         r.H = p->H; r.T = p->T; r.n_pairs = p->B * p->H;
         plan_readout_segments(r.n_pairs, (p->T + gka::kChunk - 1) / gka::kChunk, &r.n_segs, &r.seg_len);
+        if (seg_mode >= 2) {                         // the summaries of the solves' walk
+            r.n_segs = d.f.n_sums;
+            r.seg_len = d.f.seg_len / d.f.sums_per_seg;
+        }
         r.seg_buf = (float *)fws;
-        r.seg_logdecay = r.seg_buf + (size_t)r.n_pairs * r.n_segs * p->d_k * p->d_v;
+        r.seg_logdecay = r.seg_buf + (size_t)r.n_pairs * r.n_segs * (seg_mode >= 2 ? 2 : 1) * p->d_k * p->d_v;
         r.reverse = reverse; r.seg_mode = seg_mode;
         return gka::launch_gla_readout(r, p->d_k, p->d_v, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
-    };
-    // d = 128 with bf16 operands: the fused kernels' walk solves for both right-hand sides (a caller that asks for the two-phase
-    // kernels or bounds their chunk states gets those)
-    const bool walk = io_bf16 && p->d_k == 128 && p->compute == GKA_COMPUTE_BF16 && p->path == GKA_PATH_AUTO && p->slab_state_bytes == 0;
-    auto walk_both = [&]() {
-        gka::DualSolveArgs d = {};
-        gka::FusedArgs &f = d.f;
-        f.q = q; f.k = k; f.v = v; f.gate = gate; f.lambda = lambda; f.fro_out = rule ? fro : nullptr;
-        f.beta = p->beta; f.alpha = p->alpha; f.lambda_scale = p->lambda_scale;
-        f.H_init = H_init; f.U_init = U_init;
-        f.stride_h = p->d_k; f.stride_t = (int64_t)p->H * p->d_k; f.stride_b = (int64_t)p->T * p->H * p->d_k;
-        f.H = p->H; f.T = p->T; f.n_iter = p->n_iter;
-        f.n_pairs = p->B * p->H; f.n_chunks = (p->T + gka::kChunk - 1) / gka::kChunk;
-        f.seg_len = p->walk_chunks > 0 ? p->walk_chunks + (p->walk_chunks & 1)
-                                       : fused_segment(f.n_pairs, f.n_chunks, 2 * p->n_iter, false);
-        f.n_segs = (f.n_chunks + f.seg_len - 1) / f.seg_len;
-        d.dxt = f32buf(2);
-        d.x_f32 = rule ? xf : nullptr;
-        d.x_hi = io(IO_X); d.x_lo = io(IO_X_LO); d.xt_hi = io(IO_XT); d.xt_lo = io(IO_XT_LO);
-        d.p_f32 = pf32; d.p_hi = io(IO_PR);
-        d.dyy = sbuf;
-        if (!rule) {                          // (with the rule the combination of the vectors follows)
-            d.dq = p->alpha ? dq : nullptr;
-            d.dlambda = dlambda; d.dalpha = dalpha;
-        }
-        return gka::launch_dual_solve(d, fws, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
     g.natural_order = fused;
     if (walk && !rule) g.dyy = sbuf;          // (the combination reads and replaces it token by token)
@@ -799,10 +828,12 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     if (fused) {
         // dxt_t = U_t^T dy_t: the recurrence with the roles of k and v exchanged, read out with dy. (alpha_t dxt_t in bf16 from
         // the readout itself: 97 -> 152 us at 64 pairs x 4096 tokens, its own pass over memory takes 41.)
-        GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, 0, f32buf(2), nullptr, nullptr, U_init, true));
+        // (With the solves' walk the readouts start from its summaries: of U^T here, of H below; a summary launch less for each.)
+        if (walk && gka::launch_dual_solve_summaries(d, fws, stream) != hipSuccess) return GKA_ERR_LAUNCH;
+        GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, walk ? 3 : 0, f32buf(2), nullptr, nullptr, U_init, true));
         // x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
         if (walk) {
-            GKA_TRY(walk_both());
+            if (gka::launch_dual_solve(d, fws, stream) != hipSuccess) return GKA_ERR_LAUNCH;
         } else {
             GKA_TRY(glue(1));
             GKA_TRY(solve_both(io(IO_RHS), io(IO_RHS_LO), rule ? fro : nullptr));
@@ -810,7 +841,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
             if (p->alpha) GKA_TRY(glue(0));
         }
         // p_t . H_t x_t
-        GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
+        GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, walk ? 2 : 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
                         nullptr, pf32, phx));
     } else {
         // the forward solve and output; then x, xt in the tensors' dtype, the all-zero alpha and the reversed gates
@@ -825,7 +856,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     if (rule) {
         GKA_TRY(glue(5));
         GKA_TRY(glue(6));
-        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), 1, nullptr, nullptr, nullptr, H_init));
+        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), walk ? 2 : 1, nullptr, nullptr, nullptr, H_init));
         else GKA_TRY(fwd(k, k, k, gate, p->beta, zeros, 0, io(IO_HK), nullptr));
     }
     // reverse recurrences: A_t k_t, A_t^T k_t, Ubar_t^T v_t, Ubar_t k_t (no write gate inside them)

@@ -387,6 +387,15 @@ __device__ __forceinline__ float wave_sum(float x)
     return x;
 }
 
+// Sum over the four lanes n, 16 + n, 32 + n, 48 + n, to all of them (row and half swaps: vector moves, no LDS round trips).
+__device__ __forceinline__ float sum_over_kg(float x)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // log2(gamma) with the documented floor. Decays are kept in base-2 log space (the hardware's exp and log are
 // base 2): cumulative sums of these, and exp2 of their differences.
 __device__ __forceinline__ float log2_gate(float gamma) { return fmaxf(log2f(gamma), kMinLog2Gate); }

@@ -95,14 +95,6 @@ __device__ __forceinline__ void split8(f32x4 lo, f32x4 hi, bf16x8 &val, bf16x8 &
     unpack8(val, bl, bh);
     rem = pack8(lo - bl, hi - bh);
 }
-__device__ __forceinline__ float sum_over_kg(float x)
-{
-    // (row and half swaps: vector moves, no LDS round trips)
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
 
 // U is needed only for the state part of the readout and its own update, once per iteration; in between it is
 // parked in a scratch block of this workgroup in global memory (1 KiB per wave and tile, written and read by the same
@@ -179,13 +171,18 @@ __device__ __forceinline__ void weight_frags(const Ctx &c, const bf16x8 (&raw)[2
         out[st] = pack8(lo * w0, hi * w1);
     }
 }
-template <class Layout = Rows>
-__device__ __forceinline__ void own_weighted_frags(const Ctx &c, const uint16_t *rows, const float *wtab,
-                                                   bf16x8 (&out)[2], Layout at = Layout())
+// ... and what their rounding left over
+__device__ __forceinline__ void weight_frags_split(const Ctx &c, const bf16x8 (&raw)[2], const float *wtab, bf16x8 (&val)[2],
+                                                   bf16x8 (&rem)[2])
 {
-    bf16x8 raw[2];
-    own_frags(c, rows, raw, at);
-    weight_frags(c, raw, wtab, out);
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        const int t0 = 32 * st + 4 * c.kg;
+        const f32x4 w0 = *(const f32x4 *)(wtab + t0), w1 = *(const f32x4 *)(wtab + t0 + 16);
+        f32x4 lo, hi;
+        unpack8(raw[st], lo, hi);
+        split8(lo * w0, hi * w1, val[st], rem[st]);
+    }
 }
 
 // S <- zeta_C S + sum_j w_j k_j a_j^T for this wave's eight tiles (A: transposed keys of chunk g from LDS)
@@ -819,9 +816,9 @@ __device__ __forceinline__ void load_start_state(const Ctx &c, int pair, int seg
             ((accU[jt] = *(const f32x4 *)(Ui + (int64_t)(16 * c.w + c.n) * kD + 16 * jt + 4 * c.kg)), ...);
         }
     }
-    for (int sg = 0; sg < seg; ++sg) {
-        const f32x4 *t = (const f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_segs + sg) * 2) * 4096 + (c.w * 8) * 64 + c.lane;
-        const float decay = exp2f(a.seg_logdecay[pair * a.n_segs + sg]);
+    for (int sg = 0; sg < seg * a.sums_per_seg; ++sg) {
+        const f32x4 *t = (const f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_sums + sg) * 2) * 4096 + (c.w * 8) * 64 + c.lane;
+        const float decay = exp2f(a.seg_logdecay[pair * a.n_sums + sg]);
 #pragma unroll
         for (int jt = 0; jt < 8; ++jt) {
             accH[jt] = decay * accH[jt] + t[jt * 64];
@@ -1334,6 +1331,12 @@ constexpr int kSummaryTile = kChunk * kSummaryRowElems * 2; // bytes
 constexpr int kSummaryAhead = 2;                           // chunks whose rows are in flight
 constexpr int kSummaryTables = 2 * 2 * kSummaryTile;       // offset of the waves' tables of per-token weights
 constexpr int kSummaryLds = kSummaryTables + 8 * 4 * 64 * 4;   // [buffer][k, v] row tiles + tables
+// PRECISE: the weighted rows as value + remainder, for the readouts of the backward pass, which start from the same summaries and
+// whose outputs enter a long cumulative sum of differences; U transposed, as they need it.
+// (64 pairs x 4096 tokens, 8 summaries per pair: 57 us, in place of 35 for four rounded ones and 2 x 32 of the readouts' own;
+// backward pass 1045 -> 1011. Errors against the oracle, with the start states more precise: dlambda 3.35 -> 2.85e-3, dq 1.17 ->
+// 1.05e-3, the others as before. U read transposed by the readouts instead: 109 us for one in place of 97.)
+template <bool PRECISE>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fused_summary_kernel(FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -1403,11 +1406,15 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
             const float zetaC = exp2f(Gtot);
             const uint16_t *rowsK = (const uint16_t *)tiles;
             const uint16_t *rowsV = (const uint16_t *)(tiles + kSummaryTile);
-            bf16x8 wK[2], wV[2];
+            bf16x8 raw[2], wK[2], wV[2], wKr[2], wVr[2];
             float *wtab = wave_table(c, kSummaryTables, buf);
             wtab[c.lane] = wj;
-            own_weighted_frags(c, rowsK, wtab, wK, at);
-            own_weighted_frags(c, rowsV, wtab, wV, at);
+            own_frags(c, rowsK, raw, at);
+            if constexpr (PRECISE) weight_frags_split(c, raw, wtab, wK, wKr);
+            else weight_frags(c, raw, wtab, wK);
+            own_frags(c, rowsV, raw, at);
+            if constexpr (PRECISE) weight_frags_split(c, raw, wtab, wV, wVr);
+            else weight_frags(c, raw, wtab, wV);
 #pragma unroll
             for (int jt = 0; jt < 8; ++jt) {
                 // (operand reads of four tiles at a time in flight: more would take the registers of the prefetch)
@@ -1420,6 +1427,10 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
                     const bf16x8 kt = gather_transposed_bf16(rowsK, at, 16 * jt, c.lane, t0, t0 + 16);
                     accH[jt] = mma16(kt, wK[ks], accH[jt]);
                     accU[jt] = mma16(kt, wV[ks], accU[jt]);
+                    if constexpr (PRECISE) {
+                        accH[jt] = mma16(kt, wKr[ks], accH[jt]);
+                        accU[jt] = mma16(kt, wVr[ks], accU[jt]);
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1429,7 +1440,16 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
     for (int jt = 0; jt < 8; ++jt) {
         t[jt * 64] = accH[jt];
-        t[4096 + jt * 64] = accU[jt];
+        if constexpr (PRECISE) {
+            // U^T in the order of the tiles: element (row 16 jt + 4 kg + r, column 16 w + n) of the accumulators, U[16 w + n][..], is
+            // component n % 4 of lane (4 kg + r, n / 4) of tile w of wave jt (read several times, and as it is used then)
+            float *u = (float *)(a.seg_buf + ((int64_t)(pair * a.n_segs + seg) * 2 + 1) * (kD * kD)) +
+                       ((jt * 8 + c.w) * 64 + 16 * (c.n >> 2) + 4 * c.kg) * 4 + (c.n & 3);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r * 4] = accU[jt][r];
+        } else {
+            t[4096 + jt * 64] = accU[jt];
+        }
     }
     if (c.tid == 0) a.seg_logdecay[pair * a.n_segs + seg] = Gseg;
 }
@@ -1445,14 +1465,21 @@ size_t fused_workspace_bytes(int n_pairs, int n_segs)
 static void carve_fused_workspace(FusedArgs &a, void *workspace)
 {
     a.seg_buf = (float *)workspace;
-    const size_t n = (size_t)a.n_pairs * a.n_segs;
+    const size_t n = (size_t)a.n_pairs * a.n_sums;
     a.seg_logdecay = (float *)((char *)workspace + n * (2 * kD * kD * sizeof(float)));
     a.park = (float *)((char *)a.seg_logdecay + ((n * sizeof(float) + 255) / 256) * 256);
+}
+size_t fused_summary_bytes(int n_pairs, int n_sums)
+{
+    const size_t n = (size_t)n_pairs * n_sums;
+    return n * (2 * kD * kD * sizeof(float)) + ((n * sizeof(float) + 255) / 256) * 256;
 }
 
 hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_t stream, int which, bool split)
 {
     FusedArgs a = a0;
+    a.n_sums = a.n_segs;
+    a.sums_per_seg = 1;
     carve_fused_workspace(a, workspace);
     // (the attribute is kept per device)
     static bool attr_set_on[64] = {};
@@ -1471,12 +1498,12 @@ hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_
             e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
             if (e != hipSuccess) return e;
         }
-        e = hipFuncSetAttribute((const void *)fused_summary_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kSummaryLds);
+        e = hipFuncSetAttribute((const void *)fused_summary_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSummaryLds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     if (a.n_segs > 1 && (which & 1)) {
-        hipLaunchKernelGGL(fused_summary_kernel, dim3((unsigned)(a.n_pairs * (a.n_segs - 1))), dim3(kFusedThreads),
+        hipLaunchKernelGGL(fused_summary_kernel<false>, dim3((unsigned)(a.n_pairs * (a.n_segs - 1))), dim3(kFusedThreads),
                            kSummaryLds, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1493,6 +1520,21 @@ hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_
     return hipGetLastError();
 }
 
+hipError_t launch_dual_solve_summaries(const DualSolveArgs &d, void *workspace, hipStream_t stream)
+{
+    FusedArgs a = d.f;
+    if (a.n_sums <= 1) return hipSuccess;
+    carve_fused_workspace(a, workspace);
+    a.seg_len /= a.sums_per_seg;
+    a.n_segs = a.n_sums;
+    static bool lds_raised[kMaxLdsDevices] = {};
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)fused_summary_kernel<true>, kSummaryLds}});
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fused_summary_kernel<true>, dim3((unsigned)(a.n_pairs * (a.n_segs - 1))), dim3(kFusedThreads), kSummaryLds,
+                       stream, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_dual_solve(const DualSolveArgs &d0, void *workspace, hipStream_t stream)
 {
     DualSolveArgs d = d0;
@@ -1500,15 +1542,8 @@ hipError_t launch_dual_solve(const DualSolveArgs &d0, void *workspace, hipStream
     carve_fused_workspace(a, workspace);
     static bool lds_raised[kMaxLdsDevices] = {};
     hipError_t e = raise_lds_limits(lds_raised, {{(const void *)dual_solve_kernel<false>, kLdsBytes},
-                                                 {(const void *)dual_solve_kernel<true>, kLdsBytes},
-                                                 {(const void *)fused_summary_kernel, kSummaryLds}});
+                                                 {(const void *)dual_solve_kernel<true>, kLdsBytes}});
     if (e != hipSuccess) return e;
-    if (a.n_segs > 1) {
-        hipLaunchKernelGGL(fused_summary_kernel, dim3((unsigned)(a.n_pairs * (a.n_segs - 1))), dim3(kFusedThreads),
-                           kSummaryLds, stream, a);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     const dim3 grid((unsigned)(a.n_pairs * a.n_segs)), block(kFusedThreads);
     if (a.beta || a.alpha || !a.lambda || d.dalpha) hipLaunchKernelGGL(dual_solve_kernel<true>, grid, block, kLdsBytes, stream, d);
     else hipLaunchKernelGGL(dual_solve_kernel<false>, grid, block, kLdsBytes, stream, d);

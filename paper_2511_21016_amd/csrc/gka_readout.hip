@@ -148,6 +148,19 @@ __global__ __launch_bounds__(DV * 2)
             }
             for (int sg = 0; sg < seg; ++sg) {
                 const float decay = exp2f(a.seg_logdecay[pair * a.n_segs + sg]);
+                if (DK == 128 && DV == 128 && a.seg_mode >= 2) {
+                    // the fused kernels' summaries: H, then U^T, element [16 wave + n][16 tile + 4 kg + r] of either at float4
+                    // (wave * 8 + tile) * 64 + 16 kg + n, component r
+                    const float *s = a.seg_buf + ((int64_t)(pair * a.n_segs + sg) * 2 + (a.seg_mode - 2)) * (128 * 128);
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const f32x4 d = *(const f32x4 *)(s + (((2 * w + (n >> 4)) * 8 + 2 * jb + (q4 >> 1)) * 64 +
+                                                              16 * (2 * (q4 & 1) + g) + (n & 15)) * 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[jb][4 * q4 + e] = decay * acc[jb][4 * q4 + e] + d[e];
+                    }
+                    continue;
+                }
                 const float *t = summary_tile<DK, DV>(a, pair, sg, w, jb);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[jb][r] = decay * acc[jb][r] + t[r * 64 + lane];

@@ -414,10 +414,8 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
                         kd += kv[r] * zk[tt][r];
                         vd += vv[r] * zv[tt][r];
                     }
-                    kd += __shfl_xor(kd, 16, 64);
-                    kd += __shfl_xor(kd, 32, 64);
-                    vd += __shfl_xor(vd, 16, 64);
-                    vd += __shfl_xor(vd, 32, 64);
+                    kd = sum_over_kg(kd);
+                    vd = sum_over_kg(vd);
                     if (kg == 0) {
                         sDot[w * kChunk + 16 * tt + n] = kd;
                         sDot[(NW + w) * kChunk + 16 * tt + n] = vd;

@@ -89,15 +89,6 @@ __device__ __forceinline__ void split8(f32x4 lo, f32x4 hi, bf16x8 &val, bf16x8 &
     unpack8(val, bl, bh);
     rem = pack8(lo - bl, hi - bh);
 }
-// sum over the four lanes that share n: rows of 16 lanes are exchanged in the register file (as shuffles they would be
-// two LDS round trips)
-__device__ __forceinline__ float sum_over_kg(float x)
-{
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 // The lane's number, formed anew wherever it is asked for: values derived from it are then not kept (or spilled)
 // across the code in between.
 __device__ __forceinline__ int fresh_lane()
