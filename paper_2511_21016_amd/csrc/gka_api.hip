@@ -38,8 +38,14 @@ constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walk
 // that to force several slabs on small problems).
 constexpr size_t kDefaultSlabStateBytes = (size_t)1 << 30;
 constexpr int kComputeUnits = 256;         // the fused kernels run one workgroup on each
-// Segments are added up to this many workgroups of the fused kernels (four rounds).
+// Segments are added up to this many workgroups of the fused kernels (four rounds), or as many as a caller's bound on the
+// workspace (gka_params::slab_state_bytes) has room for, one round at least.
 constexpr int kFusedMaxWorkgroups = 4 * kComputeUnits;
+int fused_max_workgroups(int64_t slab_state_bytes)
+{
+    const int64_t fit = slab_state_bytes / (int64_t)gka::fused_workspace_bytes(1, 1);
+    return slab_state_bytes <= 0 || fit > kFusedMaxWorkgroups ? kFusedMaxWorkgroups : fit < kComputeUnits ? kComputeUnits : (int)fit;
+}
 // Above this length d = 256 runs chunk-wise. The line is what callers are asked for, not speed: the chunk states need a
 // workspace, and calls of up to two chunks have always run without one (sizes queried and allocated once by a program
 // would no longer do). Chunk by chunk would be the faster way from 4 to 8 tokens on (us, chunk-wise against token by
@@ -81,7 +87,7 @@ bool chunked_dim(int d) { return d == 64 || d == 128; }
 // rule, as few segments as give every CU a workgroup, us per forward pass: 16 pairs x 1337 tokens 66.2 -> 49.2, 36 x 2000
 // 131 -> 103 (288 workgroups -> 216), 48 x 3000 234 -> 173, 80 x 4096 464 -> 382, 100 x 4096 597 -> 497, 300 x 4096 1697 -> 1426,
 // 200 x 4096 944 -> 875; split operands, 12 passes, 48 x 2600 471 -> 352; 64 x 4096 and 32 x 32768 keep their segments.
-int fused_segment(int n_pairs, int n_chunks, int n_iter, bool split)
+int fused_segment(int n_pairs, int n_chunks, int n_iter, bool split, int max_workgroups)
 {
     constexpr float kStart = 10.0f, kScan = 1.3f, kSummaryStart = 5.0f, kSummaryChunk = 2.1f;
     const float iteration = split ? 15.0f + 1.6f * n_iter : 13.5f + 1.15f * n_iter;
@@ -95,7 +101,7 @@ int fused_segment(int n_pairs, int n_chunks, int n_iter, bool split)
         if (len == last) continue;
         last = len;
         const int64_t n = (n_chunks + len - 1) / len;
-        if (n > 1 && n * n_pairs > kFusedMaxWorkgroups) break;
+        if (n > 1 && n * n_pairs > max_workgroups) break;
         float us = rounds(n * n_pairs) * (kStart + iteration * (len / step) + kScan * (n - 1));
         if (n > 1) us += kSummaryStart + rounds((n - 1) * n_pairs) * kSummaryChunk * len;
         if (segs == 1 || us < best_us) {
@@ -208,10 +214,11 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     pl->fused_bytes = 0;
     if (pl->fused_shape) {
         int seg_len;
+        const int max_workgroups = fused_max_workgroups(p->slab_state_bytes);
         if (p->walk_chunks > 0) {
             seg_len = p->walk_chunks;
         } else {
-            seg_len = fused_segment(pl->n_pairs, pl->n_chunks, p->n_iter, pl->split);
+            seg_len = fused_segment(pl->n_pairs, pl->n_chunks, p->n_iter, pl->split, max_workgroups);
         }
         if (!pl->split) seg_len += seg_len & 1;
         pl->fused_seg_len = seg_len;
@@ -222,7 +229,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
         int64_t workgroups = (int64_t)pl->n_pairs * pl->fused_n_segs;
         if (p->walk_chunks == 0) {
             const int64_t finest = (int64_t)pl->n_pairs * (pl->split ? pl->n_chunks : (pl->n_chunks + 1) / 2);
-            workgroups = finest < kFusedMaxWorkgroups ? finest : kFusedMaxWorkgroups;
+            workgroups = finest < max_workgroups ? finest : max_workgroups;
             if (workgroups < pl->n_pairs) workgroups = pl->n_pairs;
         }
         pl->fused_bytes = align_up(gka::fused_workspace_bytes((int)workgroups, 1), 256);
@@ -579,7 +586,7 @@ WalkSegments plan_walk_segments(int n_pairs, int n_chunks, int n_iter, int walk_
 {
     int rs_n, rs_len;
     plan_readout_segments(n_pairs, n_chunks, &rs_n, &rs_len);
-    int len = walk_chunks > 0 ? walk_chunks + (walk_chunks & 1) : fused_segment(n_pairs, n_chunks, 2 * n_iter, false);
+    int len = walk_chunks > 0 ? walk_chunks + (walk_chunks & 1) : fused_segment(n_pairs, n_chunks, 2 * n_iter, false, kFusedMaxWorkgroups);
     int parts = (len + rs_len - 1) / rs_len;
     if (parts > len / 2) parts = len / 2;            // (two chunks at least)
     WalkSegments s;
