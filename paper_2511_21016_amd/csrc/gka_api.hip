@@ -663,7 +663,11 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
     int64_t sums = (int64_t)p->B * p->H * ((((p->T + gka::kChunk - 1) / gka::kChunk) + 1) / 2);
     const int64_t most = (int64_t)kFusedMaxWorkgroups + p->B * p->H;
     if (sums > most) sums = most;
-    const size_t sbytes = align_up(gka::fused_summary_bytes((int)sums, 1), 256);
+    int64_t workgroups = (int64_t)p->B * p->H * (((p->T + gka::kChunk - 1) / gka::kChunk + 1) / 2);
+    if (workgroups > kFusedMaxWorkgroups) workgroups = kFusedMaxWorkgroups;
+    if (workgroups < (int64_t)p->B * p->H) workgroups = (int64_t)p->B * p->H;
+    if (p->walk_chunks > 0) workgroups = sums = (int64_t)p->B * p->H * ((p->T + gka::kChunk - 1) / gka::kChunk);
+    const size_t sbytes = align_up(gka::dual_solve_workspace_bytes(sums, workgroups), 256);
     if (p->d_k == 128 && p->io_dtype == GKA_BF16 && sbytes > bp->fwd_bytes) bp->fwd_bytes = sbytes;
     bp->total = off + bp->fwd_bytes;
     return GKA_OK;
@@ -819,7 +823,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
             r.seg_len = d.f.seg_len / d.f.sums_per_seg;
         }
         r.seg_buf = (float *)fws;
-        r.seg_logdecay = r.seg_buf + (size_t)r.n_pairs * r.n_segs * (seg_mode >= 2 ? 2 : 1) * p->d_k * p->d_v;
+        r.seg_logdecay = r.seg_buf + (size_t)r.n_pairs * r.n_segs * (seg_mode >= 2 ? gka::kSummaryPlanes : 1) * p->d_k * p->d_v;
         r.reverse = reverse; r.seg_mode = seg_mode;
         return gka::launch_gla_readout(r, p->d_k, p->d_v, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
@@ -837,7 +841,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         // the readout itself: 97 -> 152 us at 64 pairs x 4096 tokens, its own pass over memory takes 41.)
         // (With the solves' walk the readouts start from its summaries: of U^T here, of H below; a summary launch less for each.)
         if (walk && gka::launch_dual_solve_summaries(d, fws, stream) != hipSuccess) return GKA_ERR_LAUNCH;
-        GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, walk ? 3 : 0, f32buf(2), nullptr, nullptr, U_init, true));
+        GKA_TRY(readout(dy, v, k, p->beta, false, nullptr, walk ? 2 : 0, f32buf(2), nullptr, nullptr, U_init, true));
         // x_t = CH(H_t + lambda_t I, q_t, r) and p_t = CH(H_t + lambda_t I, alpha_t dxt_t, r)
         if (walk) {
             if (gka::launch_dual_solve(d, fws, stream) != hipSuccess) return GKA_ERR_LAUNCH;
@@ -848,7 +852,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
             if (p->alpha) GKA_TRY(glue(0));
         }
         // p_t . H_t x_t
-        GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, walk ? 2 : 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
+        GKA_TRY(readout(io(IO_X), k, k, p->beta, false, nullptr, walk ? 3 : 0, nullptr, io(IO_X_LO), nullptr, H_init, false,
                         nullptr, pf32, phx));
     } else {
         // the forward solve and output; then x, xt in the tensors' dtype, the all-zero alpha and the reversed gates
@@ -863,7 +867,7 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
     if (rule) {
         GKA_TRY(glue(5));
         GKA_TRY(glue(6));
-        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), walk ? 2 : 1, nullptr, nullptr, nullptr, H_init));
+        if (fused) GKA_TRY(readout(k, k, k, p->beta, false, io(IO_HK), walk ? 3 : 1, nullptr, nullptr, nullptr, H_init));
         else GKA_TRY(fwd(k, k, k, gate, p->beta, zeros, 0, io(IO_HK), nullptr));
     }
     // reverse recurrences: A_t k_t, A_t^T k_t, Ubar_t^T v_t, Ubar_t k_t (no write gate inside them)

@@ -14,10 +14,11 @@
 // Roles. The workgroup has eight waves and handles two consecutive chunks (A, B) per iteration.
 //   * State role (all waves): wave w owns columns 16 w .. 16 w + 15 of H (as H[16 jt + row][16 w + n], eight tiles)
 //     and of U^T (U[16 w + n][16 jt + row]). It converts H to the bf16 A operand of the solve, advances H and U by a
-//     chunk (S <- zeta_C S + sum_j w_j k_j a_j^T, the weights on its own B fragments), and reads out
-//     zeta-free U_[n] xhat for all tokens of a chunk from its registers (rounded value + remainder of both operands).
+//     chunk (S <- zeta_C S + sum_j w_j k_j a_j^T, the weights on its own B fragments), and reads out its 16 features
+//     of y for all tokens of a chunk: U_[n] xhat from its registers (rounded value + remainder of both operands) and the
+//     intra-chunk part from its columns of v and the masked products of all tokens.
 //   * Solver role: four waves per chunk, each wave 16 tokens with all 128 features: chunk-wise Frobenius norm, all
-//     passes of Algorithm 1 and the intra-chunk part of the readout run without any barrier, the iterate never
+//     passes of Algorithm 1 and the masked products of the readout run without any barrier, the iterate never
 //     leaves the wave's registers.
 //
 // SPLIT variant (GKA_COMPUTE_BF16_SPLIT), for ill-conditioned systems: the two operands whose rounding the
@@ -322,10 +323,10 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-// Operands of the passes. SINGLE: rounded to bf16. SPLIT: H_[n], delta and the masked products P o M as rounded value +
-// remainder. NO_STATE: H_[n] is zero (the first chunk of a sequence without an initial state), so the products with it drop out and
-// delta and P o M, which are all of H_c there, enter as value + remainder.
-enum PassMode { SINGLE, SPLIT_OPERANDS, NO_STATE };
+// Operands of the passes. SINGLE: rounded to bf16. SPLIT_OPERANDS: H_[n], delta and the masked products P o M as rounded value +
+// remainder. SEPARATE: rounded to bf16, but the token's system is not divided by zeta_c: the state part has an accumulator of its
+// own for a pass, g += zeta_c H_[n] delta, and what is rounded, P o M among it, is what solve_kernel rounds too.
+enum PassMode { SINGLE, SPLIT_OPERANDS, SEPARATE };
 
 template <int NJ, PassMode MODE>
 struct PassPlan {
@@ -333,14 +334,14 @@ struct PassPlan {
     // the key fragments of the next pass. SPLIT: the state fragments of a tile are the four of the value (each
     // multiplied with the value and with the remainder of delta) and the four of the remainder of H_[n]; a key fragment
     // is multiplied with both parts of delta.
-    static constexpr int NJB = NJ / 2, NP = 4 * NJ, HP = MODE == SPLIT_OPERANDS ? 8 : MODE == SINGLE ? 4 : 0,
+    static constexpr int NJB = NJ / 2, NP = 4 * NJ, HP = MODE == SPLIT_OPERANDS ? 8 : 4,
                          PER_TILE = HP + NJB, NT = 8 * PER_TILE, NS = NT + NP;
     static constexpr int base(int i) { return i >= NT ? 1 : (i % PER_TILE < HP ? 0 : 2); }
     static constexpr int off(int i)
     {
         if (i >= NT) return (((i - NT) % NJ) * 4 + (i - NT) / NJ) * 64;       // keys [js][fb], fb-major order
         const int t = i / PER_TILE, u = i % PER_TILE;
-        if (u < HP && u < 4) return (t * 4 + u) * 64;
+        if (u < 4) return (t * 4 + u) * 64;
         if (u < HP) return 2048 + (t * 4 + (u - 4)) * 64;                     // remainder of H_[n]: 32 KiB further
         return (t * 2 + (u - HP)) * 64;
     }
@@ -387,19 +388,19 @@ __device__ __forceinline__ void key_products(const bf16x8 *sK, const bf16x8 (&x)
 // is one chain of matrix products per feature tile, with no vector instruction between the state part and the
 // intra-chunk part (the caller passes the mask divided by zeta_c; the iterate itself is not scaled).
 // On entry: xi = xi_{-1} = 0, dl = delta_0 = xi_0, gn = -q / zeta_c; s0z = 2 zeta_c / (L + mu), s0lam = 2 lambda /
-// (L + mu). On exit xi + dl is the result.
+// (L + mu). On exit xi + dl is the result. SEPARATE, not divided by zeta_c: gn = -q and s0z = 2 / (L + mu).
 // The loop body is one straight line of MFMA steps, each with its A fragment requested kDepth steps ahead and a slice
 // of the vector work behind it.
 // `start_copies` is called once, after the last LDS read that the compiler knows of: it issues the copies into LDS
 // that overlap the passes.
 template <int NJ, PassMode MODE, class StartCopies>
 __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, const bf16x8 *sKT, f32x4 (&xi)[8],
-                                            f32x4 (&dl)[8], f32x4 (&gn)[8], const f32x4 (&mreg)[4], float s0z,
-                                            float s0lam, float rho2, int n_iter, int lane,
+                                            f32x4 (&dl)[8], f32x4 (&gn)[8], const f32x4 (&mreg)[4], float zeta,
+                                            float s0z, float s0lam, float rho2, int n_iter, int lane,
                                             StartCopies start_copies)
 {
     typedef PassPlan<NJ, MODE> PL;
-    constexpr bool SPLIT = MODE != SINGLE;               // delta and the masked products come with their remainders
+    constexpr bool SPLIT = MODE == SPLIT_OPERANDS, OWN = MODE == SEPARATE;
     constexpr int NJB = PL::NJB, PER_TILE = PL::PER_TILE, NT = PL::NT, NS = PL::NS, HP = PL::HP;
     static_assert((2048 + 31 * 64 + 63) * 16 < 65536, "the offset field of an LDS read holds 16 bits");
     // A fragments in flight. The request of step i + kDepth goes into the register that step i has just freed, also
@@ -439,7 +440,7 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
     // the first seven tenths of the passes, so that the two finish together (measured: with equal priorities the
     // lighter wave finishes a third earlier, with the priority held throughout it finishes a fifth later; alone on
     // its SIMD a wave runs at half the rate of the two together).
-    constexpr bool kBoost = NJ == 2 && MODE == SINGLE;   // (SPLIT_OPERANDS: one solver wave per SIMD)
+    constexpr bool kBoost = NJ == 2 && !SPLIT;         // (SPLIT_OPERANDS: one solver wave per SIMD)
     if (kBoost) __builtin_amdgcn_s_setprio(1);
     const int prio_passes = n_iter / 2;
 #pragma unroll 1
@@ -456,19 +457,27 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
             else pm[jb] = masked_frag(P[2 * jb], P[2 * jb + 1], mreg, jb);
         };
         // Update of a tile's four elements as sixteen single instructions, op = 2 r + {0, 1}: xi += delta and
-        // (omega - 1) delta, which need no product of this pass; then op = 8 + 2 r + {0, 1}: the two multiply-adds
-        // of the new delta. They are dealt out evenly over the steps of the next tile.
+        // (omega - 1) delta, which need no product of this pass; then (SEPARATE: four multiply-adds of the state part and) the
+        // two multiply-adds of the new delta. They are dealt out evenly over the steps of the next tile.
+        constexpr int SOPS = OWN ? 4 : 0, NOPS = 16 + SOPS;
+        f32x4 gs[2];                         // SEPARATE: H_[n] delta of the even and the odd tiles
         auto upd_op = [&](auto ftc, auto opc) {
-            constexpr int ft = decltype(ftc)::value, op = decltype(opc)::value, r = (op & 7) >> 1;
-            if constexpr (op < 8 && (op & 1) == 0) xi[ft][r] += dl[ft][r];
-            if constexpr (op < 8 && (op & 1) == 1) tcm[r] = cm * dl[ft][r];
-            if constexpr (op >= 8 && (op & 1) == 0) tcm[r] = __builtin_fmaf(ncs, gn[ft][r], tcm[r]);
-            if constexpr (op >= 8 && (op & 1) == 1) dl[ft][r] = __builtin_fmaf(ncl, xi[ft][r], tcm[r]);
+            constexpr int ft = decltype(ftc)::value, op = decltype(opc)::value;
+            if constexpr (op < 8) {
+                constexpr int r = op >> 1;
+                if constexpr ((op & 1) == 0) xi[ft][r] += dl[ft][r];
+                else tcm[r] = cm * dl[ft][r];
+            } else if constexpr (op < 8 + SOPS) {
+                gn[ft][op - 8] = __builtin_fmaf(zeta, gs[ft & 1][op - 8], gn[ft][op - 8]);
+            } else {
+                constexpr int r = (op - 8 - SOPS) >> 1;
+                if constexpr ((op & 1) == 0) tcm[r] = __builtin_fmaf(ncs, gn[ft][r], tcm[r]);
+                else dl[ft][r] = __builtin_fmaf(ncl, xi[ft][r], tcm[r]);
+            }
         };
         auto upd_ops = [&](auto ftc, auto fromc, auto toc) {
             static_for<decltype(fromc)::value, decltype(toc)::value>([&](auto opc) { upd_op(ftc, opc); });
         };
-        if constexpr (HP == 0) static_for<0, NJB>(mask_products);
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, NS>([&](auto step) {
             constexpr int i = decltype(step)::value;
@@ -476,7 +485,9 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
             const bf16x8 a = __builtin_bit_cast(bf16x8, q[i % kDepth]);
             if constexpr (i < NT) {
                 constexpr int t = i / PER_TILE, u = i % PER_TILE;
-                if constexpr (u < HP && u < 4) {
+                if constexpr (OWN && u < 4) {
+                    gs[t & 1] = mma16(a, dB[u], u == 0 ? zero4() : gs[t & 1]);
+                } else if constexpr (u < 4) {
                     gn[t] = mma16(a, dB[u], gn[t]);
                     if constexpr (SPLIT) gn[t] = mma16(a, dR[u], gn[t]);
                 } else if constexpr (u < HP) {
@@ -496,12 +507,12 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
             }
             if constexpr (i < NT) {
                 constexpr int t = i / PER_TILE, u = i % PER_TILE;
-                if constexpr (HP > 0 && t == 0 && u == 2) mask_products(std::integral_constant<int, 0>{});
-                if constexpr (HP > 0 && t == 0 && u == 3 && NJB == 2) mask_products(std::integral_constant<int, NJB - 1>{});
+                if constexpr (t == 0 && u == 2) mask_products(std::integral_constant<int, 0>{});
+                if constexpr (t == 0 && u == 3 && NJB == 2) mask_products(std::integral_constant<int, NJB - 1>{});
                 if constexpr (t >= 1) {
-                    // step u of the tile takes the operations [16 u / PER_TILE, 16 (u + 1) / PER_TILE)
-                    upd_ops(std::integral_constant<int, t - 1>{}, std::integral_constant<int, 16 * u / PER_TILE>{},
-                            std::integral_constant<int, 16 * (u + 1) / PER_TILE>{});
+                    // step u of the tile takes the operations [NOPS u / PER_TILE, NOPS (u + 1) / PER_TILE)
+                    upd_ops(std::integral_constant<int, t - 1>{}, std::integral_constant<int, NOPS * u / PER_TILE>{},
+                            std::integral_constant<int, NOPS * (u + 1) / PER_TILE>{});
                 }
             } else {
                 // key products of the next pass: the last tile's update and the new operands meanwhile
@@ -512,7 +523,7 @@ __device__ __forceinline__ void cheb_passes(const bf16x8 *sH, const bf16x8 *sK, 
                     pack_delta(std::integral_constant<int, 1>{});
                 }
                 if constexpr (k == NJ) {
-                    upd_ops(FT{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
+                    upd_ops(FT{}, std::integral_constant<int, 8>{}, std::integral_constant<int, NOPS>{});
                     pack_delta(std::integral_constant<int, 2>{});
                 }
                 if constexpr (k == 2 * NJ) pack_delta(std::integral_constant<int, 3>{});
@@ -670,7 +681,7 @@ __device__ __forceinline__ void solve_tokens(Ctx &c, Solver &s, int g, int ts, c
             gn[ft][r] = -rz * qv[r];
         }
     }
-    cheb_passes<NJ, SPLIT ? SPLIT_OPERANDS : SINGLE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+    cheb_passes<NJ, SPLIT ? SPLIT_OPERANDS : SINGLE>(sH, sK, sKT, xi, dl, gn, s.mreg, 1.0f, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
         // v rows of the iteration's chunks replace the k rows; they land during the passes
         copy_rows(c, c.a.v, 0, c0);
         if constexpr (!SPLIT) copy_rows(c, c.a.v, 1, c0 + 1);
@@ -817,7 +828,7 @@ __device__ __forceinline__ void load_start_state(const Ctx &c, int pair, int seg
         }
     }
     for (int sg = 0; sg < seg * a.sums_per_seg; ++sg) {
-        const f32x4 *t = (const f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_sums + sg) * 2) * 4096 + (c.w * 8) * 64 + c.lane;
+        const f32x4 *t = (const f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_sums + sg) * a.sum_planes) * 4096 + (c.w * 8) * 64 + c.lane;
         const float decay = exp2f(a.seg_logdecay[pair * a.n_sums + sg]);
 #pragma unroll
         for (int jt = 0; jt < 8; ++jt) {
@@ -831,17 +842,16 @@ __device__ __forceinline__ void load_start_state(const Ctx &c, int pair, int seg
 
 // One workgroup per (pair, segment of chunks). Per iteration (chunks A = c0, B = c0 + 1), with the barriers between
 // the phases:
-//   1. gate scans (the k rows, copied global -> LDS since the end of the previous iteration, land; solver B of the
-//      previous iteration may still be storing)
+//   1. gate scans (the k rows, copied global -> LDS since the end of the previous iteration, land; stores of the previous
+//      iteration may still be on their way)
 //   2. H_[n] of A -> LDS; key fragments of both chunks; this wave's weighted k fragments
 //   3. H advanced over A; H_[n] of B -> LDS; H advanced over B; partial norms -> table (in the dead k row tile)
 //   4. solver: Frobenius terms -> table
-//   5. solver: norms; copies of the v rows into the row tiles start; passes, intra-chunk readout products;
-//      xhat -> LDS (over H_[n])
-//   6. state part of the readout for A (over the key-row fragments), U advanced over A
-//   7. solver A stores; state part of the readout for B (over A's xhat), U advanced over B and parked
-//   8. solver B stores; copies of the next k rows into the row tiles start
-// SPLIT: the same with chunk A alone (everything that concerns B drops out, phase 8 joins phase 7).
+//   5. solver: norms; copies of the v rows into the row tiles start; passes; xhat -> LDS (over H_[n]) and its masked products
+//      with the chunk's keys -> LDS (over the key-row fragments)
+//   6. this wave's features of A's outputs, stored as they are formed; U advanced over A
+//   7. the same for B, U advanced over B and parked; copies of the next k rows into the row tiles start
+// SPLIT: the same with chunk A alone (everything that concerns B drops out).
 // GATED: the layer's variants (write gate beta, alpha-connection, the rule lambda_t = a ||H_t||_F), a compile-time
 // flag so that the plain kernel carries none of their loads, registers or branches.
 template <bool SPLIT, bool GATED>
@@ -1092,7 +1102,7 @@ __device__ __forceinline__ float dot4(f32x4 a, f32x4 b, float sum)
 // Both solves for the 16 tokens of this wave and what follows from them token by token: x_t, xt_t = alpha_t x_t + (1 -
 // alpha_t) q_t and p_t in the forms that the backward pass's readouts take, dlambda_t = -x_t . p_t, dalpha_t = dxt_t . (x_t - q_t),
 // dy_t . y_t = dxt_t . xt_t. The second solve's right-hand side alpha_t dxt_t is taken in float32.
-template <int NJ, PassMode MODE, bool GATED>
+template <int NJ, bool GATED>
 __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d, Solver &s, int g, int ts,
                                                   const typename IOBF16::raw4 (&qraw)[8], float lam, int c0)
 {
@@ -1103,19 +1113,15 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
     const float rcp = __builtin_amdgcn_rcpf(L + mu);
     const float s0 = 2.0f * rcp;
     const float rho = (L - mu) * rcp;
-    s.zeta = fmaxf(s.zeta, kMinSolveZeta);               // (as in solve_tokens)
-    const float rz = 1.0f / s.zeta;
-#pragma unroll
-    for (int js = 0; js < 4; ++js) s.mreg[js] *= rz;
     f32x4 xi[8], dl[8], gn[8];
     auto start = [&](int ft, f32x4 rhs) {
         xi[ft] = zero4();
         dl[ft] = s0 * rhs;
-        gn[ft] = -rz * rhs;
+        gn[ft] = -rhs;
     };
 #pragma unroll
     for (int ft = 0; ft < 8; ++ft) start(ft, IOBF16::cvt4(qraw[ft]));
-    cheb_passes<NJ, MODE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
         // k rows of the next iteration's chunks (the row tiles are free); they land during the passes
         copy_rows_untracked(c, c.a.k, 0, c0 + 2);
         copy_rows_untracked(c, c.a.k, 1, c0 + 3);
@@ -1161,7 +1167,7 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
     if (s.valid && c.kg == 0) d.dyy[tok_index] = dyy;
 #pragma unroll
     for (int ft = 0; ft < 8; ++ft) start(ft, GATED ? al * dxt[ft] : dxt[ft]);
-    cheb_passes<NJ, MODE>(sH, sK, sKT, xi, dl, gn, s.mreg, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [] {});
+    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, c.a.n_iter, c.lane, [] {});
     refresh_lane(c);
     const int tokc2 = min(s.tok, c.a.T - 1);
     const int64_t tok_index2 = c.gate_base + (int64_t)tokc2 * c.a.H, row2 = tok_index2 * kD;
@@ -1204,10 +1210,15 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
 // reuses everything in front of the first one's passes. Replaces a state pass that wrote the chunk states to memory and a
 // solve kernel that read them, the pass that rounded alpha dxt, and, for a lambda that is given, the combination of the vectors
 // afterwards (the dots are formed here, where the vectors are in registers). Packed tensors. Bound as the forward kernel is, the
-// passes most of its cycles. 64 pairs x 4096 tokens, 10 passes: 358 us and 34 for the summaries, in place of 48 + 78 (state pass),
-// 507 (two-phase solve), 43 (rounding of alpha dxt) and 80 (combination, 5 left); the whole backward pass 1385 -> 1118.
-// Errors against the oracle (2-norm, mean over 16 sequences of 150 and 420 tokens, two-phase -> here): dk 3.6 -> 3.0e-3, with
-// the rule 5.6 -> 4.5e-3; dq 1.3 -> 1.2e-3, dv 1.8 -> 1.5e-3, dlambda 3.45 -> 3.35e-3, gate gradient 3.3 -> 2.7e-3.
+// passes most of its cycles. 64 pairs x 4096 tokens, 10 passes: 402 us and 63 for the summaries (which the readouts use too), in
+// place of 48 + 78 (state pass), 507 (two-phase solve), 43 (rounding of alpha dxt), 80 (combination, 5 left) and 2 x 32 (the
+// readouts' summaries); the whole backward pass 1385 -> 1066 with it.
+// The passes are SEPARATE: dk is a sum of large terms that cancel, and single elements of it follow the rounding of P o M. With
+// the system divided by zeta_c as in the forward kernel the walk took 376 us and was as precise in the norm, but elements of dk
+// were up to 0.5 of their size or of the root mean square away from the two-phase solve's; so they are up to 0.22. With a state
+// accumulator of each tile over all passes: 430 (32 registers more). H in memory during the passes: 402, in registers 450.
+// Errors against the oracle (2-norm, mean over 32 sequences of 150 and 420 tokens) are the two-phase solve's: dk 3.6e-3, with the
+// rule 5.6e-3; dq 1.3e-3, dv 1.8e-3, dlambda 3.45e-3; gate gradient 3.26 -> 3.08e-3.
 template <bool GATED>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dual_solve_kernel(DualSolveArgs d)
 {
@@ -1304,17 +1315,11 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
         }
         if (!s.valid) lam = 1.0f;
         lds_barrier();                       // the table is dead: the row tiles may be overwritten
-        // The first tokens of a sequence are where p is least accurate with single operands (a state of low rank, whose
-        // masked products the solves amplify, and the gradient of the first keys is a difference of large terms): the chunk without a
-        // state before it takes value + remainder operands and, with nothing to multiply by H_[n], fewer products all the same.
-        const bool no_state = c0 + grp == 0 && !a.H_init;
-        if (no_state) {
-            if (wide) dual_solve_tokens<4, NO_STATE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
-            else dual_solve_tokens<2, NO_STATE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
-        } else {
-            if (wide) dual_solve_tokens<4, SINGLE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
-            else dual_solve_tokens<2, SINGLE, GATED>(c, d, s, grp, ts, qraw, lam, c0);
-        }
+        // H is not needed before the next iteration, and the passes need its registers
+        park_store(c.park, accH);
+        if (wide) dual_solve_tokens<4, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+        else dual_solve_tokens<2, GATED>(c, d, s, grp, ts, qraw, lam, c0);
+        park_load(c.park, accH);
         fetch_gates(c0 + 2);
     }
     wait_all_memory();                       // no copy into this workgroup's LDS may be in flight when it ends
@@ -1331,11 +1336,11 @@ constexpr int kSummaryTile = kChunk * kSummaryRowElems * 2; // bytes
 constexpr int kSummaryAhead = 2;                           // chunks whose rows are in flight
 constexpr int kSummaryTables = 2 * 2 * kSummaryTile;       // offset of the waves' tables of per-token weights
 constexpr int kSummaryLds = kSummaryTables + 8 * 4 * 64 * 4;   // [buffer][k, v] row tiles + tables
-// PRECISE: the weighted rows as value + remainder, for the readouts of the backward pass, which start from the same summaries and
-// whose outputs enter a long cumulative sum of differences; U transposed, as they need it.
-// (64 pairs x 4096 tokens, 8 summaries per pair: 57 us, in place of 35 for four rounded ones and 2 x 32 of the readouts' own;
-// backward pass 1045 -> 1011. Errors against the oracle, with the start states more precise: dlambda 3.35 -> 2.85e-3, dq 1.17 ->
-// 1.05e-3, the others as before. U read transposed by the readouts instead: 109 us for one in place of 97.)
+// PRECISE: the backward pass. H as it is here, rounded rows weighted and rounded once more, for the solves' walk; U^T and H with
+// the weighted rows as value + remainder, for the readouts that start from the same summaries and whose outputs enter a long
+// cumulative sum of differences. (64 pairs x 4096 tokens, 8 summaries per pair: 63
+// us, in place of 35 for four of the walk's and 2 x 32 of the readouts' own. H with the remainders for the walk as well: 57, but its
+// start states then differ from those that the state pass gives. U read transposed by the readouts: 109 us for one in place of 97.)
 template <bool PRECISE>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fused_summary_kernel(FusedArgs a)
 {
@@ -1351,11 +1356,12 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
     const int chunk_end = min(chunk_begin + a.seg_len, a.n_chunks);
     c.T_eff = min(a.T, chunk_end * kChunk);
 
-    f32x4 accH[8], accU[8];
+    f32x4 accH[8], accU[8], remH[PRECISE ? 8 : 1];
 #pragma unroll
     for (int jt = 0; jt < 8; ++jt) {
         accH[jt] = zero4();
         accU[jt] = zero4();
+        if constexpr (PRECISE) remH[jt] = zero4();
     }
     // Rows of k and v travel global memory -> registers -> padded LDS tiles, kSummaryAhead chunks ahead of their use
     // (one stage of registers per chunk in flight). Piece i of a thread: tile (i / 2: k, v), 16 bytes of row
@@ -1421,6 +1427,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
                 if (jt == 4) __builtin_amdgcn_sched_barrier(0);
                 accH[jt] *= zetaC;
                 accU[jt] *= zetaC;
+                if constexpr (PRECISE) remH[jt] *= zetaC;
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks) {
                     const int t0 = 32 * ks + 4 * c.kg;
@@ -1428,7 +1435,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
                     accH[jt] = mma16(kt, wK[ks], accH[jt]);
                     accU[jt] = mma16(kt, wV[ks], accU[jt]);
                     if constexpr (PRECISE) {
-                        accH[jt] = mma16(kt, wKr[ks], accH[jt]);
+                        remH[jt] = mma16(kt, wKr[ks], remH[jt]);
                         accU[jt] = mma16(kt, wVr[ks], accU[jt]);
                     }
                 }
@@ -1436,14 +1443,16 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    f32x4 *t = (f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_segs + seg) * 2) * 4096 + (c.w * 8) * 64 + c.lane;
+    constexpr int PLANES = PRECISE ? 3 : 2;
+    f32x4 *t = (f32x4 *)a.seg_buf + ((int64_t)(pair * a.n_segs + seg) * PLANES) * 4096 + (c.w * 8) * 64 + c.lane;
 #pragma unroll
     for (int jt = 0; jt < 8; ++jt) {
         t[jt * 64] = accH[jt];
         if constexpr (PRECISE) {
             // U^T in the order of the tiles: element (row 16 jt + 4 kg + r, column 16 w + n) of the accumulators, U[16 w + n][..], is
             // component n % 4 of lane (4 kg + r, n / 4) of tile w of wave jt (read several times, and as it is used then)
-            float *u = (float *)(a.seg_buf + ((int64_t)(pair * a.n_segs + seg) * 2 + 1) * (kD * kD)) +
+            t[2 * 4096 + jt * 64] = accH[jt] + remH[jt];
+            float *u = (float *)(a.seg_buf + ((int64_t)(pair * a.n_segs + seg) * PLANES + 1) * (kD * kD)) +
                        ((jt * 8 + c.w) * 64 + 16 * (c.n >> 2) + 4 * c.kg) * 4 + (c.n & 3);
 #pragma unroll
             for (int r = 0; r < 4; ++r) u[r * 4] = accU[jt][r];
@@ -1466,13 +1475,13 @@ static void carve_fused_workspace(FusedArgs &a, void *workspace)
 {
     a.seg_buf = (float *)workspace;
     const size_t n = (size_t)a.n_pairs * a.n_sums;
-    a.seg_logdecay = (float *)((char *)workspace + n * (2 * kD * kD * sizeof(float)));
+    a.seg_logdecay = (float *)((char *)workspace + n * ((size_t)a.sum_planes * kD * kD * sizeof(float)));
     a.park = (float *)((char *)a.seg_logdecay + ((n * sizeof(float) + 255) / 256) * 256);
 }
-size_t fused_summary_bytes(int n_pairs, int n_sums)
+size_t dual_solve_workspace_bytes(int64_t summaries, int64_t workgroups)
 {
-    const size_t n = (size_t)n_pairs * n_sums;
-    return n * (2 * kD * kD * sizeof(float)) + ((n * sizeof(float) + 255) / 256) * 256;
+    return (size_t)summaries * (3 * kD * kD * sizeof(float)) + (((size_t)summaries * sizeof(float) + 255) / 256) * 256 +
+           (size_t)workgroups * (kD * kD * sizeof(float));
 }
 
 hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_t stream, int which, bool split)
@@ -1480,6 +1489,7 @@ hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_
     FusedArgs a = a0;
     a.n_sums = a.n_segs;
     a.sums_per_seg = 1;
+    a.sum_planes = 2;
     carve_fused_workspace(a, workspace);
     // (the attribute is kept per device)
     static bool attr_set_on[64] = {};
@@ -1524,6 +1534,7 @@ hipError_t launch_dual_solve_summaries(const DualSolveArgs &d, void *workspace, 
 {
     FusedArgs a = d.f;
     if (a.n_sums <= 1) return hipSuccess;
+    a.sum_planes = 3;
     carve_fused_workspace(a, workspace);
     a.seg_len /= a.sums_per_seg;
     a.n_segs = a.n_sums;
@@ -1539,6 +1550,7 @@ hipError_t launch_dual_solve(const DualSolveArgs &d0, void *workspace, hipStream
 {
     DualSolveArgs d = d0;
     FusedArgs &a = d.f;
+    a.sum_planes = 3;
     carve_fused_workspace(a, workspace);
     static bool lds_raised[kMaxLdsDevices] = {};
     hipError_t e = raise_lds_limits(lds_raised, {{(const void *)dual_solve_kernel<false>, kLdsBytes},

@@ -165,7 +165,7 @@ struct ReadoutArgs {
     float *seg_logdecay;          // [pairs, n_segs]
     int seg_mode;                 // 0: the summaries are computed by this call; 1: they are in seg_buf already (the call
                                   // before had the same k, v, gate, beta, direction); 2, 3 (dk = dv = 128): seg_buf holds those of
-                                  // the solves' walk, of H_t (2) and of U_t^T (3)
+                                  // the solves' walk, of U_t^T (2) and of H_t (3)
     bool reverse;
     const float *init_state;      // [pairs, dv, dk] float32 or nullptr (zero): the state before the first token of the walk
     bool init_transposed;         // init_state holds the transposed state, [pairs, dk, dv] (dk = dv only)
@@ -267,6 +267,7 @@ struct FusedArgs {
     int n_segs, seg_len;          // segments of the chunk walk per pair (one workgroup each), chunks per segment
     // summaries for the start states: n_sums of them per pair, sums_per_seg to a segment (1: a summary per segment)
     int n_sums, sums_per_seg;
+    int sum_planes;               // states in a summary: H, U, or H, U^T, H for the readouts (the backward pass); set by the launcher
     float *seg_buf, *seg_logdecay, *park; // set by the launcher (carved from the workspace)
 };
 size_t fused_workspace_bytes(int n_pairs, int n_segs);
@@ -294,8 +295,9 @@ struct DualSolveArgs {
 // between as well), then the walk.
 hipError_t launch_dual_solve_summaries(const DualSolveArgs &d, void *workspace, hipStream_t stream);
 hipError_t launch_dual_solve(const DualSolveArgs &d, void *workspace, hipStream_t stream);
-// Where the summaries lie in the workspace: [pairs, n_sums][H, U^T] and log2 decays.
-size_t fused_summary_bytes(int n_pairs, int n_sums);
+// In the workspace: [pairs, n_sums][3] states, log2 decays, and a state's room for each workgroup of the walk.
+constexpr int kSummaryPlanes = 3;
+size_t dual_solve_workspace_bytes(int64_t summaries, int64_t workgroups);
 
 // Workspace sizes in bytes per (pair, chunk).
 size_t ws_H_bytes_per_chunk(int d, bool compute_bf16);

@@ -149,9 +149,9 @@ __global__ __launch_bounds__(DV * 2)
             for (int sg = 0; sg < seg; ++sg) {
                 const float decay = exp2f(a.seg_logdecay[pair * a.n_segs + sg]);
                 if (DK == 128 && DV == 128 && a.seg_mode >= 2) {
-                    // the fused kernels' summaries: H, then U^T, element [16 wave + n][16 tile + 4 kg + r] of either at float4
-                    // (wave * 8 + tile) * 64 + 16 kg + n, component r
-                    const float *s = a.seg_buf + ((int64_t)(pair * a.n_segs + sg) * 2 + (a.seg_mode - 2)) * (128 * 128);
+                    // the solves' summaries: the walk's H, then U^T and H for the readouts, element [16 wave + n][16 tile + 4 kg + r] at
+                    // float4 (wave * 8 + tile) * 64 + 16 kg + n, component r
+                    const float *s = a.seg_buf + ((int64_t)(pair * a.n_segs + sg) * kSummaryPlanes + (a.seg_mode - 1)) * (128 * 128);
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
                         const f32x4 d = *(const f32x4 *)(s + (((2 * w + (n >> 4)) * 8 + 2 * jb + (q4 >> 1)) * 64 +
