@@ -41,9 +41,9 @@ constexpr int kComputeUnits = 256;         // the fused kernels run one workgrou
 // Segments are added up to this many workgroups of the fused kernels (four rounds), or as many as a caller's bound on the
 // workspace (gka_params::slab_state_bytes) has room for, one round at least.
 constexpr int kFusedMaxWorkgroups = 4 * kComputeUnits;
-int fused_max_workgroups(int64_t slab_state_bytes)
+int fused_max_workgroups(int64_t slab_state_bytes, bool split)
 {
-    const int64_t fit = slab_state_bytes / (int64_t)gka::fused_workspace_bytes(1, 1);
+    const int64_t fit = slab_state_bytes / (int64_t)gka::fused_workspace_bytes(1, 1, split);
     return slab_state_bytes <= 0 || fit > kFusedMaxWorkgroups ? kFusedMaxWorkgroups : fit < kComputeUnits ? kComputeUnits : (int)fit;
 }
 // Above this length d = 256 runs chunk-wise. The line is what callers are asked for, not speed: the chunk states need a
@@ -214,7 +214,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     pl->fused_bytes = 0;
     if (pl->fused_shape) {
         int seg_len;
-        const int max_workgroups = fused_max_workgroups(p->slab_state_bytes);
+        const int max_workgroups = fused_max_workgroups(p->slab_state_bytes, pl->split);
         if (p->walk_chunks > 0) {
             seg_len = p->walk_chunks;
         } else {
@@ -232,7 +232,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
             workgroups = finest < max_workgroups ? finest : max_workgroups;
             if (workgroups < pl->n_pairs) workgroups = pl->n_pairs;
         }
-        pl->fused_bytes = align_up(gka::fused_workspace_bytes((int)workgroups, 1), 256);
+        pl->fused_bytes = align_up(gka::fused_workspace_bytes((int)workgroups, 1, pl->split), 256);
         // (a caller that insists on the fused kernels needs no room for the two-phase kernels' chunk states)
         if (p->path == GKA_PATH_FUSED || pl->split || pl->fused_bytes > pl->total) pl->total = pl->fused_bytes;
     }

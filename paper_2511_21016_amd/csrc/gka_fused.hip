@@ -873,6 +873,12 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
     if (chunk_begin >= chunk_end) return;
     c.T_eff = min(a.T, chunk_end * kChunk);
     constexpr int kChunksPerIter = SPLIT ? 1 : 2;
+    // SPLIT: H waits beside U in the workgroup's scratch while it is not needed, from the Frobenius terms to the end of the
+    // readout: the passes with two operands each leave no 32 registers for it (spills 111-123 -> 3-5; 16 pairs x 8192 tokens, 16
+    // passes: 374 -> 357 us). The plain passes do, and there it costs (22 spills outside of them -> none, but 64 pairs x 4096
+    // tokens 303 -> 317 us for the traffic).
+    constexpr bool PARK_H = SPLIT;
+    const int64_t parkH = (int64_t)gridDim.x * (8 * 8 * 64);
     // Solver role: chunk of the pair and token block. Waves w and w + 4 share a SIMD, whose arbiter prefers the older
     // one: waves 0-3 take the token blocks with more key blocks (ts = 2, 3), waves 4-7 the others. SPLIT: waves 0-3
     // take the four token blocks of the one chunk, waves 4-7 none.
@@ -946,7 +952,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
         // This wave's copies of the k rows have landed: they were issued before the stores of the tokens (four per chunk) and
         // the kParkStores stores of U that every wave issues in every iteration, so once no more than that many
         // vector-memory instructions are outstanding the copies are complete; the stores need not be.
-        wait_vector_memory_but<kParkStores + 4 * kChunksPerIter>();
+        wait_vector_memory_but<(PARK_H ? 2 : 1) * kParkStores + 4 * kChunksPerIter>();
         lds_barrier();                   // ... and everybody else's; the table is complete
         // ---- 2
         zetaA = exp2f(lane_value(gtab[2 * 64 + c.lane], 63));
@@ -982,6 +988,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
             hnB = publish_H<false>(c, accH, 1);
             advance_state(c, accH, 1, zetaB, wBB);
         }
+        if constexpr (PARK_H) park_store(c.park + parkH, accH);
         if (c.lane == 0) {
             sTab[128 + c.w] = hnA;
             if constexpr (!SPLIT) sTab[128 + 8 + c.w] = hnB;
@@ -1044,6 +1051,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
             readout_chunk<1>(c, accU, vTB, c0 + 1);
             advance_state(c, accU, 1, zetaB, wVB);
         }
+        if constexpr (PARK_H) park_load(c.park + parkH, accH);
         park_store(c.park, accU);
     }
     wait_all_memory();               // no copy into this workgroup's LDS may be in flight when it ends
@@ -1463,12 +1471,13 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
     if (c.tid == 0) a.seg_logdecay[pair * a.n_segs + seg] = Gseg;
 }
 
-size_t fused_workspace_bytes(int n_pairs, int n_segs)
+size_t fused_workspace_bytes(int n_pairs, int n_segs, bool split)
 {
     // per (pair, segment): Delta H, Delta U in the kernels' tile order, the segment's log2 decay, and the scratch
-    // block that holds U between its uses
+    // block that holds U (SPLIT: and H) between its uses
     const size_t n = (size_t)n_pairs * n_segs;
-    return n * (2 * kD * kD * sizeof(float)) + ((n * sizeof(float) + 255) / 256) * 256 + n * (kD * kD * sizeof(float));
+    return n * (2 * kD * kD * sizeof(float)) + ((n * sizeof(float) + 255) / 256) * 256 +
+           n * ((split ? 2 : 1) * kD * kD * sizeof(float));
 }
 
 static void carve_fused_workspace(FusedArgs &a, void *workspace)

@@ -270,7 +270,7 @@ struct FusedArgs {
     int sum_planes;               // states in a summary: H, U, or H, U^T, H for the readouts (the backward pass); set by the launcher
     float *seg_buf, *seg_logdecay, *park; // set by the launcher (carved from the workspace)
 };
-size_t fused_workspace_bytes(int n_pairs, int n_segs);
+size_t fused_workspace_bytes(int n_pairs, int n_segs, bool split);
 // which: bit 0 the summary launch (segment summaries for the start states), bit 1 the chunk walk; split: H_[n], delta
 // and the masked products as bf16 value + remainder. (beta, alpha or a missing lambda select the kernels' variant with
 // the write gate, the alpha-connection and the rule for lambda.)
