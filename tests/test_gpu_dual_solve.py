@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # Bounds of test_gpu_backward.py, of a gradient's largest value: 2e-2 against the oracle, 5e-2 for dk of short sequences under
 # the rule, 3e-2 for dalpha of a single token. Between two paths that both meet them: twice that. Where random systems are
 # conditioned so badly that the two-phase kernels miss a bound (lambda of 0.01, 8 passes), 1.25 times their error is allowed: the
-# roundings are the same in kind and number, not in place.
+# operands are rounded alike, the sums and the start states are not formed in the same order.
 TOL, TOL_DK_RULE, TOL_DALPHA_ONE = 2e-2, 5e-2, 3e-2
 
 
@@ -109,3 +109,19 @@ def test_gradients_of_scalars_over_their_inputs():
     want = run(w, x, dy, binding.GKA_PATH_AUTO, variants=True)
     for n in want:
         assert (got[n] == want[n]).all(), n
+
+
+@pytest.mark.parametrize("T", [200, 390])
+def test_operands_are_rounded_as_the_two_phase_solve_rounds_them(T):
+    """The error is that of the bf16 operands. With the same operands on both paths most of it is common to them: they are nearer
+    to each other than half the error. Other roundings (of a system divided by zeta_c, say) would leave independent errors of
+    the same size, 1.4 times it apart."""
+    w, x, dy = problem(2, 3, T, seed=50)
+    got = run(w, x, dy, binding.GKA_PATH_AUTO)
+    other = run(w, x, dy, binding.GKA_PATH_TWO_PHASE)
+    want = bwd.backward(x["q"], x["k"], x["v"], x["gate"], x["lam"], dy, w.n_iter)
+    for n in ("dq", "dk", "dv", "dlam"):
+        ref = np.asarray(want[n], dtype=np.float64)
+        apart, err = np.linalg.norm(got[n] - other[n]), np.linalg.norm(other[n] - ref)
+        print(T, n, apart / err, flush=True)
+        assert apart <= 0.5 * err, (n, apart / err)
