@@ -582,20 +582,38 @@ void plan_reverse_segments(int n_pairs, int n_chunks, int *n_segs, int *seg_len)
 struct WalkSegments {
     int seg_len, n_segs, sum_len, n_sums;
 };
+// Most summaries and most segments of all pairs together, whatever the number of passes: what the workspace has room for. A part
+// of a segment has two chunks at least.
+struct WalkRoom {
+    int64_t sums, segs;
+};
+WalkRoom walk_room(int n_pairs, int n_chunks, int walk_chunks)
+{
+    const int64_t finest = (int64_t)n_pairs * ((n_chunks + 1) / 2);
+    if (walk_chunks > 0) return {finest, finest};
+    const int64_t segs = n_pairs > kFusedMaxWorkgroups ? n_pairs : kFusedMaxWorkgroups;
+    const int64_t sums = (int64_t)kFusedMaxWorkgroups + n_pairs;
+    return {finest < sums ? finest : sums, finest < segs ? finest : segs};
+}
 WalkSegments plan_walk_segments(int n_pairs, int n_chunks, int n_iter, int walk_chunks)
 {
     int rs_n, rs_len;
     plan_readout_segments(n_pairs, n_chunks, &rs_n, &rs_len);
-    int len = walk_chunks > 0 ? walk_chunks + (walk_chunks & 1) : fused_segment(n_pairs, n_chunks, 2 * n_iter, false, kFusedMaxWorkgroups);
-    int parts = (len + rs_len - 1) / rs_len;
+    int len = walk_chunks > 0 ? walk_chunks : fused_segment(n_pairs, n_chunks, 2 * n_iter, false, kFusedMaxWorkgroups);
+    // (a segment of more chunks than there are has no more parts for it)
+    int parts = ((len < n_chunks ? len : n_chunks) + rs_len - 1) / rs_len;
+    len += len & 1;
     if (parts > len / 2) parts = len / 2;            // (two chunks at least)
-    WalkSegments s;
-    s.sum_len = (len + parts - 1) / parts;
-    if (s.sum_len * parts % 2) ++s.sum_len;
-    s.seg_len = s.sum_len * parts;
-    s.n_segs = (n_chunks + s.seg_len - 1) / s.seg_len;
-    s.n_sums = (n_chunks + s.sum_len - 1) / s.sum_len;
-    return s;
+    const WalkRoom room = walk_room(n_pairs, n_chunks, walk_chunks);
+    for (;; --parts) {                               // (with one part a summary is a segment, for which there is room)
+        WalkSegments s;
+        s.sum_len = (len + parts - 1) / parts;
+        if (s.sum_len * parts % 2) ++s.sum_len;
+        s.seg_len = s.sum_len * parts;
+        s.n_segs = (n_chunks + s.seg_len - 1) / s.seg_len;
+        s.n_sums = (n_chunks + s.sum_len - 1) / s.sum_len;
+        if (parts == 1 || (int64_t)n_pairs * s.n_sums <= room.sums) return s;
+    }
 }
 
 // Tensors of the backward pass in the tensors' dtype: those of float32 tensors alone, those of both, those of bf16 tensors.
@@ -659,15 +677,8 @@ gka_status make_backward_plan(const gka_params *p, BackwardPlan *bp)
     plan_reverse_segments(p->B * p->H, (p->T + gka::kChunk - 1) / gka::kChunk, &rs_n, &rs_len);
     const size_t vbytes = align_up(gka::reverse_workspace_bytes(p->B * p->H, rs_n, p->d_k), 256);
     if (vbytes > bp->fwd_bytes) bp->fwd_bytes = vbytes;
-    // (the solves' walk keeps no more than one summary for every two chunks, and at most about kReadoutMinWorkgroups)
-    int64_t sums = (int64_t)p->B * p->H * ((((p->T + gka::kChunk - 1) / gka::kChunk) + 1) / 2);
-    const int64_t most = (int64_t)kFusedMaxWorkgroups + p->B * p->H;
-    if (sums > most) sums = most;
-    int64_t workgroups = (int64_t)p->B * p->H * (((p->T + gka::kChunk - 1) / gka::kChunk + 1) / 2);
-    if (workgroups > kFusedMaxWorkgroups) workgroups = kFusedMaxWorkgroups;
-    if (workgroups < (int64_t)p->B * p->H) workgroups = (int64_t)p->B * p->H;
-    if (p->walk_chunks > 0) workgroups = sums = (int64_t)p->B * p->H * ((p->T + gka::kChunk - 1) / gka::kChunk);
-    const size_t sbytes = align_up(gka::dual_solve_workspace_bytes(sums, workgroups), 256);
+    const WalkRoom room = walk_room(p->B * p->H, (p->T + gka::kChunk - 1) / gka::kChunk, p->walk_chunks);
+    const size_t sbytes = align_up(gka::dual_solve_workspace_bytes(room.sums, room.segs), 256);
     if (p->d_k == 128 && p->io_dtype == GKA_BF16 && sbytes > bp->fwd_bytes) bp->fwd_bytes = sbytes;
     bp->total = off + bp->fwd_bytes;
     return GKA_OK;
@@ -785,6 +796,8 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         f.n_pairs = p->B * p->H; f.n_chunks = (p->T + gka::kChunk - 1) / gka::kChunk;
         const WalkSegments s = plan_walk_segments(f.n_pairs, f.n_chunks, p->n_iter, p->walk_chunks);
         f.seg_len = s.seg_len; f.n_segs = s.n_segs; f.n_sums = s.n_sums; f.sums_per_seg = s.seg_len / s.sum_len;
+        if (gka::dual_solve_workspace_bytes((int64_t)f.n_pairs * s.n_sums, (int64_t)f.n_pairs * s.n_segs) > bp.fwd_bytes)
+            return GKA_ERR_WORKSPACE;
         d.dxt = f32buf(2);
         d.x_f32 = rule ? xf : nullptr;
         d.x_hi = io(IO_X); d.x_lo = io(IO_X_LO); d.xt_hi = io(IO_XT); d.xt_lo = io(IO_XT_LO);

@@ -2,21 +2,26 @@
  * and writes down what the library asked for. One line per call on the file of recorder_open():
  *   launch <kernel's mangled name> <grid> <block> <dynamic LDS bytes>
  *   attribute <kernel's mangled name> <attribute> <value> <device>
+ * and after recorder_words(n), behind each launch, the first n 8-byte words of its first argument (the kernels take one struct,
+ * which the launch has copied to the stack; what follows a shorter one are the callers' variables):
+ *   words <value> ...
  */
 #include <stdio.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <string.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
 
 static struct { const void *host; const char *name; } kernels[4096];
-static int n_kernels, device;
+static int n_kernels, device, n_words;
 static FILE *out;
 static struct { dim3_t grid, block; size_t lds; void *stream; } pushed;
 
 void recorder_open(const char *path) { out = fopen(path, "w"); }
 void recorder_close(void) { if (out) fclose(out); out = NULL; }
 void recorder_set_device(int d) { device = d; }
+void recorder_words(int n) { n_words = n; }
 
 static const char *name_of(const void *host)
 {
@@ -49,8 +54,17 @@ int __hipPopCallConfiguration(dim3_t *grid, dim3_t *block, size_t *lds, void **s
 }
 int hipLaunchKernel(const void *host, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
 {
-    (void)args; (void)stream;
+    (void)stream;
     if (out) fprintf(out, "launch %s %u %u %zu\n", name_of(host), grid.x, block.x, lds);
+    if (out && n_words > 0) {
+        uint64_t word;
+        fprintf(out, "words");
+        for (int i = 0; i < n_words; ++i) {
+            memcpy(&word, (const char *)args[0] + 8 * i, 8);
+            fprintf(out, " %llu", (unsigned long long)word);
+        }
+        fprintf(out, "\n");
+    }
     return 0;
 }
 int hipFuncSetAttribute(const void *host, int attribute, int value)

@@ -21,6 +21,7 @@ from paper_2511_21016_amd import binding
 binding.load_library()
 recorder = ctypes.CDLL({recorder!r})
 set_device = recorder.recorder_set_device
+recorder.recorder_words({words})
 recorder.recorder_open({out!r}.encode())
 """
 
@@ -34,15 +35,16 @@ def kernel_name(mangled):
     return mangled
 
 
-def record(body):
-    """Executes the source `body` with `binding` and `set_device` in scope. Returns the recorded calls as dicts."""
+def record(body, words=0):
+    """Executes the source `body` with `binding` and `set_device` in scope. Returns the recorded calls as dicts; with `words`,
+    launches have the first so many 8-byte words of their argument in "words"."""
     from paper_2511_21016_amd import binding, build
     if not os.path.exists(binding.LIB_PATH):
         build.build_library(verbose=False)
     with tempfile.TemporaryDirectory() as tmp:
         recorder, out = os.path.join(tmp, "hip_recorder.so"), os.path.join(tmp, "calls")
         subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", recorder, os.path.join(HERE, "hip_recorder.c")], check=True)
-        source = _PRELUDE.format(root=ROOT, recorder=recorder, out=out) + body + "\nrecorder.recorder_close()\n"
+        source = _PRELUDE.format(root=ROOT, recorder=recorder, out=out, words=words) + body + "\nrecorder.recorder_close()\n"
         env = dict(os.environ)
         env["LD_PRELOAD"] = (recorder + " " + env.get("LD_PRELOAD", "")).strip()
         pr = subprocess.run([sys.executable, "-c", source], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
@@ -50,6 +52,9 @@ def record(body):
         assert pr.returncode == 0, pr.stdout
         calls = []
         for line in open(out):
+            if line.startswith("words"):
+                calls[-1]["words"] = [int(x) for x in line.split()[1:]]
+                continue
             kind, name, a, b, c = line.split()
             call = {"kind": kind, "kernel": kernel_name(name), "mangled": name}
             call.update(grid=int(a), block=int(b), lds=int(c)) if kind == "launch" else call.update(value=int(b), device=int(c))

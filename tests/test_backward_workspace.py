@@ -2,7 +2,10 @@
 within it and takes nothing from what it held before."""
 import pytest
 
+from hip_recorder import record
 from paper_2511_21016_amd import binding
+
+STATE_BYTES = 128 * 128 * 4
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
@@ -17,6 +20,36 @@ def test_query(dtype, d):
     scratch = chunks * (3 * d * d * 4 + 4096) + (1 << 20)
     total = binding.backward_workspace_bytes(p)
     assert total <= (17 if dtype == "bf16" else 23) * tensor + scalars + states + scratch
+
+
+PAIRS = ((1, 1), (1, 4), (2, 3), (3, 16), (5, 20), (8, 32), (10, 30), (16, 32), (19, 31), (24, 32), (32, 32), (41, 25), (33, 32),
+         (48, 32), (64, 32), (128, 24), (128, 32))
+CHUNKS = (1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 15, 16, 17, 23, 32, 39, 63, 64, 65, 129)
+
+
+@pytest.mark.parametrize("n_iter,walk_chunks", [(0, 0), (10, 0), (40, 0), (10, 1), (10, 5)])
+def test_the_solves_walk_keeps_within_it(n_iter, walk_chunks):
+    """From the arguments of the launches: the blocks in which the workgroups of the solves' walk park their states, the last
+    thing in the workspace, end within what the query asked for, and the query does not depend on the passes."""
+    cases = [(B, H, 64 * n - n % 2) for B, H in PAIRS for n in CHUNKS]
+    calls = record(f"""
+for i, (B, H, T) in enumerate({cases}):
+    p = binding.make_params(B, H, T, 128, {n_iter}, binding.GKA_BF16, binding.GKA_COMPUTE_BF16, walk_chunks={walk_chunks})
+    q, k, v, gate, lam, dy, dq, dk, dv, dgate = (n << 32 for n in range(1, 11))
+    W, size = (i + 1) << 44, binding.backward_workspace_bytes(p)
+    assert size < 1 << 44
+    st = binding.backward_raw(p, q, k, v, gate, lam, dy, dq, dk, dv, dgate, dlam=dq, workspace=W, workspace_bytes=size)
+    assert st == binding.GKA_OK, binding.status_string(st)
+""", words=48)
+    walks = [c for c in calls if c["kind"] == "launch" and c["kernel"] == "dual_solve_kernel"]
+    assert len(walks) == len(cases)
+    for i, (B, H, T) in enumerate(cases):
+        size = binding.backward_workspace_bytes(binding.make_params(B, H, T, 128, 10, binding.GKA_BF16, binding.GKA_COMPUTE_BF16,
+                                                                    walk_chunks=walk_chunks))
+        W, walk = (i + 1) << 44, walks[i]
+        assert 0 < walk["grid"] <= max(1024, B * H) or walk_chunks
+        parked = max(x for x in walk["words"] if W <= x < W + (1 << 44))
+        assert parked - W + walk["grid"] * STATE_BYTES <= size, (B, H, T, walk["grid"])
 
 
 @pytest.mark.gpu

@@ -125,3 +125,31 @@ def test_operands_are_rounded_as_the_two_phase_solve_rounds_them(T):
         apart, err = np.linalg.norm(got[n] - other[n]), np.linalg.norm(other[n] - ref)
         print(T, n, apart / err, flush=True)
         assert apart <= 0.5 * err, (n, apart / err)
+
+
+def test_more_pairs_than_workgroups_in_four_rounds():
+    """1088 pairs of three chunks: each pair's gradients are those of a call with fewer pairs and the same segments, bit for bit,
+    and the pass keeps within a workspace of the size that the query gives."""
+    import torch
+    B, H, T = 64, 17, 150
+    w = synth.CFG2.scaled(B=2, H=H, T=T, d=128, n_iter=4, seed=6400)
+    x = synth.make_inputs(w)
+    dy = synth.round_to_bf16(np.random.default_rng(w.seed).standard_normal(x["v"].shape).astype(np.float32))
+    dev = upload_inputs(x, "bf16")
+    few = [dev[n] for n in ("q", "k", "v", "gate", "lam")] + [to_device(dy, "bf16")]
+    many = [t.repeat(B // 2, *[1] * (t.dim() - 1)).contiguous() for t in few]
+    p = binding.make_params(B, H, T, 128, w.n_iter, binding.GKA_BF16, binding.GKA_COMPUTE_BF16)
+    nbytes = binding.backward_workspace_bytes(p)
+    ws = torch.full((nbytes + (64 << 20),), 255, dtype=torch.uint8, device="cuda")
+    ws[nbytes:] = 77
+    print("backward pass of", B * H, "pairs", flush=True)
+    got = binding.gka_backward(*many, w.n_iter, workspace=ws[:nbytes])
+    torch.cuda.synchronize()
+    assert bool((ws[nbytes:] == 77).all())
+    want = run(w, x, dy, binding.GKA_PATH_AUTO, walk_chunks=3)
+    for n, a in got.items():
+        a = to_host(a)
+        assert all((a[i:i + 2] == want[n]).all() for i in range(0, B, 2)), n
+    x1 = {n: a[:1, :, :2] for n, a in x.items()}
+    ref = bwd.backward(x1["q"], x1["k"], x1["v"], x1["gate"], x1["lam"], dy[:1, :, :2], w.n_iter)
+    compare({n: a[:1, :, :2] for n, a in want.items()}, ref, T, 0.0)
