@@ -216,7 +216,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
         int seg_len;
         const int max_workgroups = fused_max_workgroups(p->slab_state_bytes, pl->split);
         if (p->walk_chunks > 0) {
-            seg_len = p->walk_chunks;
+            seg_len = p->walk_chunks < pl->n_chunks ? p->walk_chunks : pl->n_chunks;
         } else {
             seg_len = fused_segment(pl->n_pairs, pl->n_chunks, p->n_iter, pl->split, max_workgroups);
         }
@@ -599,7 +599,8 @@ WalkSegments plan_walk_segments(int n_pairs, int n_chunks, int n_iter, int walk_
 {
     int rs_n, rs_len;
     plan_readout_segments(n_pairs, n_chunks, &rs_n, &rs_len);
-    int len = walk_chunks > 0 ? walk_chunks : fused_segment(n_pairs, n_chunks, 2 * n_iter, false, kFusedMaxWorkgroups);
+    int len = walk_chunks <= 0 ? fused_segment(n_pairs, n_chunks, 2 * n_iter, false, kFusedMaxWorkgroups)
+                               : walk_chunks < n_chunks ? walk_chunks : n_chunks;
     // (a segment of more chunks than there are has no more parts for it)
     int parts = ((len < n_chunks ? len : n_chunks) + rs_len - 1) / rs_len;
     len += len & 1;

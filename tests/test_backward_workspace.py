@@ -27,7 +27,7 @@ PAIRS = ((1, 1), (1, 4), (2, 3), (3, 16), (5, 20), (8, 32), (10, 30), (16, 32), 
 CHUNKS = (1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 15, 16, 17, 23, 32, 39, 63, 64, 65, 129)
 
 
-@pytest.mark.parametrize("n_iter,walk_chunks", [(0, 0), (10, 0), (40, 0), (10, 1), (10, 5)])
+@pytest.mark.parametrize("n_iter,walk_chunks", [(0, 0), (10, 0), (40, 0), (10, 1), (10, 5), (10, 2 ** 31 - 1)])
 def test_the_solves_walk_keeps_within_it(n_iter, walk_chunks):
     """From the arguments of the launches: the blocks in which the workgroups of the solves' walk park their states, the last
     thing in the workspace, end within what the query asked for, and the query does not depend on the passes."""
