@@ -42,7 +42,7 @@ typedef enum {
     GKA_ERR_UNSUPPORTED = 3,  /* head dimension, chunk, dtype or compute mode not supported   */
     GKA_ERR_WORKSPACE = 4,    /* workspace NULL, misaligned or smaller than the query says    */
     GKA_ERR_LAUNCH = 5,       /* a HIP call or kernel launch reported an error                */
-    GKA_ERR_STATIC_SCRATCH = 6 /* gka_forward_static: the problem needs more than GKA_STATIC_SCRATCH_BYTES */
+    GKA_ERR_STATIC_SCRATCH = 6 /* gka_forward_static: the problem takes more than 341 workgroups */
 } gka_status;
 
 typedef enum { GKA_F32 = 0, GKA_BF16 = 1 } gka_dtype;
@@ -179,16 +179,17 @@ gka_status gka_forward(const gka_params *p,
 
 /* gka_forward for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc. The same arguments as gka_forward without the
- * workspace, the same kernels and the same results; the scratch that the kernels need (segment summaries of the chunk
- * walk and the parked states, 196,612 bytes per workgroup) lives in an array of GKA_STATIC_SCRATCH_BYTES
- * that the library's code object reserves on every GPU it is loaded on, until the process ends. The call allocates
- * and frees nothing, on the device or through any library.
+ * workspace and the same kernels; the scratch that the kernels need (segment summaries of the chunk
+ * walk and the parked states, 196,612 bytes per workgroup and, with split operands, 65,536 more) lives in an array of
+ * GKA_STATIC_SCRATCH_BYTES and 65,536 bytes for each workgroup that they hold, which the library's code object reserves on
+ * every GPU it is loaded on, until the process ends. The call allocates and frees nothing, on the device or through any
+ * library. The results are gka_forward's, to the last bit where both cut the walk alike (with p->walk_chunks given, say).
  *   Supported: what the fused kernels cover (see gka_path: GKA_BF16 tensors, GKA_COMPUTE_BF16 or _SPLIT, d = 128, no
  *   xhat_out, GKA_PHASE_ALL, path not GKA_PATH_TWO_PHASE), else GKA_ERR_UNSUPPORTED.
- *   Size limit: (number of (batch, head) pairs) x (segments of the chunk walk) x 196,612 bytes (+ padding) must not
- *   exceed GKA_STATIC_SCRATCH_BYTES: at most 341 workgroups. The library cuts the walk into ceil(256 / (B H))
- *   segments (fewer for short sequences); p->walk_chunks >= ceil(T / 64) asks for a single segment, with which any
- *   B H <= 341 fits. Larger: GKA_ERR_STATIC_SCRATCH, nothing is launched.
+ *   Size limit: at most 341 workgroups, GKA_STATIC_SCRATCH_BYTES / 196,612, with either kind of operands; a workgroup walks one
+ *   segment of one (batch, head) pair. The library cuts the walk into no more segments than that leaves room for, so any B H <= 341
+ *   fits; with p->walk_chunks given, (B H) x (segments of that length) must not exceed it. Larger: GKA_ERR_STATIC_SCRATCH,
+ *   nothing is launched.
  *   Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (two streams, two threads) race and
  *   give wrong results; calls on one stream, or ordered by events, are safe. Nothing in the array needs clearing
  *   between calls: every word a call reads it has written before.

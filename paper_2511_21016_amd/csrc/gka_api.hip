@@ -112,7 +112,9 @@ int fused_segment(int n_pairs, int n_chunks, int n_iter, bool split, int max_wor
     return best;
 }
 
-gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
+// most_workgroups: of the fused kernels, where their scratch has a fixed size (0: the library's choice); fused_bytes is then what
+// this plan takes.
+gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false, int most_workgroups = 0)
 {
     gka_status s = check_common(p, false);
     if (s != GKA_OK) return s;
@@ -214,7 +216,8 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
     pl->fused_bytes = 0;
     if (pl->fused_shape) {
         int seg_len;
-        const int max_workgroups = fused_max_workgroups(p->slab_state_bytes, pl->split);
+        int max_workgroups = fused_max_workgroups(p->slab_state_bytes, pl->split);
+        if (most_workgroups > 0 && max_workgroups > most_workgroups) max_workgroups = most_workgroups;
         if (p->walk_chunks > 0) {
             seg_len = p->walk_chunks < pl->n_chunks ? p->walk_chunks : pl->n_chunks;
         } else {
@@ -227,7 +230,7 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false)
         // The size asked for does not shrink with the number of pairs or tokens or depend on the number of passes, as the
         // segments may: a workspace serves every smaller call.
         int64_t workgroups = (int64_t)pl->n_pairs * pl->fused_n_segs;
-        if (p->walk_chunks == 0) {
+        if (p->walk_chunks == 0 && most_workgroups == 0) {
             const int64_t finest = (int64_t)pl->n_pairs * (pl->split ? pl->n_chunks : (pl->n_chunks + 1) / 2);
             workgroups = finest < max_workgroups ? finest : max_workgroups;
             if (workgroups < pl->n_pairs) workgroups = pl->n_pairs;
@@ -289,10 +292,10 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
                         const float *lambda, void *o, const float *H_init, const float *U_init, float *H_final,
                         float *U_final, float *fro_out, void *workspace, size_t workspace_bytes,
                         void *hip_stream, PhaseEvents *prof, bool readout_only = false, bool solve_only = false,
-                        const SecondRhs *second = nullptr)
+                        const SecondRhs *second = nullptr, int most_workgroups = 0)
 {
     Plan pl;
-    gka_status s = make_plan(p, &pl, readout_only);
+    gka_status s = make_plan(p, &pl, readout_only, most_workgroups);
     if (s != GKA_OK) return s;
     if (!q || !k || !v || !gate || !o) return GKA_ERR_NULL;
     if (!lambda && !(p->lambda_scale > 0.0f)) return GKA_ERR_NULL;      // neither lambda_t nor the rule for it
@@ -473,10 +476,14 @@ gka_status gka_forward_profile(const gka_params *p, const void *q, const void *k
 
 // ---- gka_forward_static: the fused kernels with their scratch in a fixed device array --------------------------
 namespace {
-// Segment summaries and parked states of the fused kernels. Every GPU the library runs on holds its own copy until
-// the process ends. In host code the array's name is only a handle: its device address comes from
+// Segment summaries and parked states of the fused kernels: GKA_STATIC_SCRATCH_BYTES of summaries and parked U for as many
+// workgroups as they hold, and room for the H that each of them parks beside U with split operands. Every GPU the library runs
+// on holds its own copy until the process ends. In host code the array's name is only a handle: its device address comes from
 // hipGetSymbolAddress, once per device, and is what kernels and copies are given.
-static __device__ __align__(256) unsigned char scratch[GKA_STATIC_SCRATCH_BYTES];
+constexpr size_t kStateBytes = 128 * 128 * sizeof(float);
+constexpr int kStaticWorkgroups = GKA_STATIC_SCRATCH_BYTES / (3 * kStateBytes + sizeof(float));
+constexpr size_t kStaticBytes = GKA_STATIC_SCRATCH_BYTES + kStaticWorkgroups * kStateBytes;
+static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices] = {};
@@ -501,17 +508,17 @@ gka_status gka_forward_static(const gka_params *p, const void *q, const void *k,
                               float *U_final, float *fro_out, void *hip_stream)
 {
     Plan pl;
-    gka_status s = make_plan(p, &pl);
+    gka_status s = make_plan(p, &pl, false, kStaticWorkgroups);
     if (s != GKA_OK) return s;
     if (!pl.fused_shape || p->path == GKA_PATH_TWO_PHASE) return GKA_ERR_UNSUPPORTED;
-    if (pl.fused_bytes > (size_t)GKA_STATIC_SCRATCH_BYTES) return GKA_ERR_STATIC_SCRATCH;
+    if ((int64_t)pl.n_pairs * pl.fused_n_segs > kStaticWorkgroups) return GKA_ERR_STATIC_SCRATCH;
     void *ws = nullptr;
     s = static_scratch(&ws);
     if (s != GKA_OK) return s;
     gka_params pf = *p;
     pf.path = GKA_PATH_FUSED;            // (anything the fused kernels do not cover: GKA_ERR_UNSUPPORTED)
-    return forward_impl(&pf, q, k, v, gate, lambda, o, H_init, U_init, H_final, U_final, fro_out, ws,
-                        GKA_STATIC_SCRATCH_BYTES, hip_stream, nullptr);
+    return forward_impl(&pf, q, k, v, gate, lambda, o, H_init, U_init, H_final, U_final, fro_out, ws, kStaticBytes, hip_stream,
+                        nullptr, false, false, nullptr, kStaticWorkgroups);
 }
 
 namespace {

@@ -2,6 +2,7 @@
  * and writes down what the library asked for. One line per call on the file of recorder_open():
  *   launch <kernel's mangled name> <grid> <block> <dynamic LDS bytes>
  *   attribute <kernel's mangled name> <attribute> <value> <device>
+ *   variable <device variable's name> <bytes> 0 0     (when its address, RECORDER_VARIABLE, is asked for)
  * and after recorder_words(n), behind each launch, the first n 8-byte words of its first argument (the kernels take one struct,
  * which the launch has copied to the stack; what follows a shorter one are the callers' variables):
  *   words <value> ...
@@ -11,10 +12,14 @@
 #include <stdint.h>
 #include <string.h>
 
+#define RECORDER_VARIABLE ((uintptr_t)1 << 60)
+
 typedef struct { uint32_t x, y, z; } dim3_t;
 
 static struct { const void *host; const char *name; } kernels[4096];
 static int n_kernels, device, n_words;
+static struct { const void *host; const char *name; size_t size; } variables[64];
+static int n_variables;
 static FILE *out;
 static struct { dim3_t grid, block; size_t lds; void *stream; } pushed;
 
@@ -40,7 +45,8 @@ void __hipRegisterFunction(void **modules, const void *host, char *device_functi
 }
 void __hipRegisterVar(void **modules, void *var, char *host, char *dev, int ext, size_t size, int constant, int global)
 {
-    (void)modules; (void)var; (void)host; (void)dev; (void)ext; (void)size; (void)constant; (void)global;
+    (void)modules; (void)host; (void)ext; (void)constant; (void)global;
+    if (n_variables < 64) { variables[n_variables].host = var; variables[n_variables].name = dev; variables[n_variables++].size = size; }
 }
 int __hipPushCallConfiguration(dim3_t grid, dim3_t block, size_t lds, void *stream)
 {
@@ -74,7 +80,13 @@ int hipFuncSetAttribute(const void *host, int attribute, int value)
 }
 int hipGetDevice(int *d) { *d = device; return 0; }
 int hipGetLastError(void) { return 0; }
-int hipGetSymbolAddress(void **p, const void *symbol) { (void)symbol; *p = (void *)0x100000; return 0; }
+int hipGetSymbolAddress(void **p, const void *symbol)
+{
+    for (int i = 0; i < n_variables; ++i)
+        if (variables[i].host == symbol && out) fprintf(out, "variable %s %zu 0 0\n", variables[i].name, variables[i].size);
+    *p = (void *)RECORDER_VARIABLE;
+    return 0;
+}
 int hipEventCreate(void **e) { *e = (void *)1; return 0; }
 int hipEventDestroy(void *e) { (void)e; return 0; }
 int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }

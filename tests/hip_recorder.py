@@ -9,6 +9,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
+VARIABLE = 1 << 60            # address of every device variable
+
 # (the binding asks torch for its dtypes and the stream query only; torch itself would find the recorder for a runtime)
 _PRELUDE = """
 import ctypes, sys, types
@@ -57,6 +59,11 @@ def record(body, words=0):
                 continue
             kind, name, a, b, c = line.split()
             call = {"kind": kind, "kernel": kernel_name(name), "mangled": name}
-            call.update(grid=int(a), block=int(b), lds=int(c)) if kind == "launch" else call.update(value=int(b), device=int(c))
+            if kind == "launch":
+                call.update(grid=int(a), block=int(b), lds=int(c))
+            elif kind == "variable":
+                call.update(bytes=int(a))
+            else:
+                call.update(value=int(b), device=int(c))
             calls.append(call)
         return calls
