@@ -371,7 +371,7 @@ def main():
         for name, shape, path, kernel in (
                 ("d16_197_tokens", dict(B=256, H=24, T=197, d=16), binding.GKA_PATH_AUTO, "small_walk_kernel (one wave per pair, 16 tokens at a time)"),
                 ("d16_197_tokens_recurrent", dict(B=256, H=24, T=197, d=16), rec, "decode_step_kernel_d16 (path recurrent)"),
-                ("d256", dict(B=4, H=8, T=1024, d=256), binding.GKA_PATH_AUTO, "pieces::solve_f32_kernel (chunk-wise, products of 16-bit pieces)")):
+                ("d256", dict(B=4, H=8, T=1024, d=256), binding.GKA_PATH_AUTO, "solve_wide_kernel (chunk-wise, products of 16-bit pieces)")):
             wd = w.scaled(seed=w.seed + 50, **shape)
             xd = upload_inputs(synth.make_inputs(wd), "bf16")
             od = torch.empty_like(xd["v"])

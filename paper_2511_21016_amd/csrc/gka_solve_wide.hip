@@ -94,11 +94,9 @@ __device__ __forceinline__ u16x4 bits4(f32x4 x)
 // most 16 (2 i + 1) of its largest element, which is below 2^5: 2^9 (2 i + 1) < 65504.
 constexpr int kMaxPasses = 60;
 
-// (launch plans know the solve with float32's precision by this name)
-namespace pieces {
 // GATED: the layer's variants (write gate, alpha-connection, lambda_t = a ||H_t||_F) and the solve's result as an output.
 template <int TT, bool GATED>
-__global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void solve_f32_kernel(SolveArgs a)
+__global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void solve_wide_kernel(SolveArgs a)
 {
     typedef WideShape<TT> SH;
     typedef IOBF16 IO;
@@ -536,20 +534,18 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                 IO::store4(a.o, tok_off[tt] + 16 * rt, gS[rt][tt][0], gS[rt][tt][1], gS[rt][tt][2], gS[rt][tt][3]);
 }
 
-}  // namespace pieces
-
 template <int TT, bool GATED>
 static hipError_t launch_solve_wide_t(const SolveArgs &a, hipStream_t stream)
 {
     typedef WideShape<TT> SH;
     static bool lds_raised[kMaxLdsDevices] = {};
-    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)pieces::solve_f32_kernel<TT, GATED>, SH::lds_bytes}});
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)solve_wide_kernel<TT, GATED>, SH::lds_bytes}});
     if (e != hipSuccess) return e;
     // (outputs that replace rows of k or v: the token blocks of a chunk one launch after the other, as in gka_solve_f32.hip)
     const bool over_rows = a.o == a.v || a.o == a.k;
     SolveArgs args = a;
     for (args.skip_blocks = over_rows ? 0 : -1; args.skip_blocks < (over_rows ? SH::TB : 0); ++args.skip_blocks) {
-        hipLaunchKernelGGL((pieces::solve_f32_kernel<TT, GATED>), dim3((unsigned)(a.n_pairs * a.n_chunks * (over_rows ? 1 : SH::TB))),
+        hipLaunchKernelGGL((solve_wide_kernel<TT, GATED>), dim3((unsigned)(a.n_pairs * a.n_chunks * (over_rows ? 1 : SH::TB))),
                            dim3(kWideThreads), SH::lds_bytes, stream, args);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

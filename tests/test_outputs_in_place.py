@@ -1,29 +1,41 @@
 """gka_forward whose outputs replace its values (o == v) or keys (o == k), where a workgroup or wave reads rows of a chunk that
-others solve: float32 products (a chunk's token blocks in workgroups of their own) and d = 16 and 32 (waves that advance the
-states over tiles of other waves). Launch plans on the CPU, results on the GPU."""
+others solve: float32 products, or those of 16-bit pieces at d = 256 (a chunk's token blocks in workgroups of their own), and d =
+16 and 32 (waves that advance the states over tiles of other waves). Launch plans on the CPU, results on the GPU."""
 import pytest
 
 from hip_recorder import record
 
 _CALL = """
 Q, K, V, O, X, W = (n << 36 for n in range(1, 7))
-p = binding.make_params({B}, {H}, {T}, {d}, 5, binding.{io}, binding.{compute})
+p = binding.make_params({B}, {H}, {T}, {d}, {n_iter}, binding.{io}, binding.{compute})
 st = binding.forward_raw(p, Q, K, V, X, X, {o}, workspace=W, workspace_bytes=1 << 42)
 assert st == binding.GKA_OK, binding.status_string(st)
 """
 
 
-def _launches(d, B, H, T, dtype, o):
+def _launches(d, B, H, T, dtype, o, n_iter=5):
     io, compute = {"f32": ("GKA_F32", "GKA_COMPUTE_F32"), "bf16": ("GKA_BF16", "GKA_COMPUTE_BF16")}[dtype]
-    return [c for c in record(_CALL.format(d=d, B=B, H=H, T=T, io=io, compute=compute, o=o)) if c["kind"] == "launch"]
+    return [c for c in record(_CALL.format(d=d, B=B, H=H, T=T, io=io, compute=compute, o=o, n_iter=n_iter))
+            if c["kind"] == "launch"]
 
 
 @pytest.mark.parametrize("o", ["V", "K"])
-@pytest.mark.parametrize("d,B,H,T,dtype,blocks", [(64, 1, 2, 130, "f32", 4), (64, 4, 8, 500, "f32", 2), (128, 1, 3, 200, "f32", 4),
-                                                  (256, 1, 2, 300, "bf16", 4), (256, 4, 8, 300, "f32", 2)])
-def test_float32_products(d, B, H, T, dtype, blocks, o):
+@pytest.mark.parametrize("d,B,H,T,dtype,n_iter,blocks,kernel", [(64, 1, 2, 130, "f32", 5, 4, "solve_f32_kernel"),
+                                                                (64, 4, 8, 500, "f32", 5, 2, "solve_f32_kernel"),
+                                                                (128, 1, 3, 200, "f32", 5, 4, "solve_f32_kernel"),
+                                                                (256, 1, 2, 300, "f32", 5, 4, "solve_f32_kernel"),
+                                                                (256, 4, 8, 300, "f32", 5, 2, "solve_f32_kernel"),
+                                                                (256, 1, 2, 300, "bf16", 5, 4, "solve_wide_kernel"),
+                                                                (256, 4, 8, 300, "bf16", 60, 2, "solve_wide_kernel"),
+                                                                (256, 1, 2, 300, "bf16", 61, 4, "solve_f32_kernel"),
+                                                                (256, 4, 8, 300, "bf16", 61, 2, "solve_f32_kernel")])
+def test_float32_products(d, B, H, T, dtype, n_iter, blocks, kernel, o):
     chunks = B * H * ((T + 63) // 64)
-    solves = lambda dst: [c["grid"] for c in _launches(d, B, H, T, dtype, dst) if c["kernel"] == "solve_f32_kernel"]
+
+    def solves(dst):
+        plan = [c for c in _launches(d, B, H, T, dtype, dst, n_iter) if c["kernel"].startswith("solve")]
+        assert {c["kernel"] for c in plan} == {kernel}
+        return [c["grid"] for c in plan]
     assert solves("O") == [chunks * blocks]
     assert solves(o) == [chunks] * blocks            # one token block of every chunk per launch
 
