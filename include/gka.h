@@ -50,7 +50,9 @@ typedef enum { GKA_F32 = 0, GKA_BF16 = 1 } gka_dtype;
 /* Arithmetic of the matrix products.
  * GKA_COMPUTE_F32 : float32 operands on the float32 MFMA path (required for GKA_F32 tensors).
  * GKA_COMPUTE_BF16: bf16 operands with float32 accumulation on the bf16 MFMA path; the Chebyshev
- *                   iterate, the residual and all per-token scalars stay float32.
+ *                   iterate, the residual and all per-token scalars stay float32. (d = 256 above 128 tokens: float32
+ *                   operands cut into 16-bit pieces, about float32's precision on the 16-bit MFMA path; above 60 passes the
+ *                   solve runs on the float32 one. Up to 128 tokens: float32 whatever this says, see GKA_PATH_RECURRENT.)
  * GKA_COMPUTE_BF16_SPLIT: the bf16 MFMA path for ill-conditioned systems (lambda_t orders of magnitude below
  *                   ||H_t||_F, where the iteration amplifies the rounding of its operands): the chunk's initial state
  *                   H_[n], the update of the iterate and the masked intra-chunk products enter their products as
@@ -93,7 +95,7 @@ typedef enum { GKA_STATE_FULL = 0, GKA_STATE_H_LOWER_BLOCKS = 1 } gka_state_layo
  *                     kernel of gka_decode_tokens), float32 arithmetic whatever p->compute says. Every head dimension,
  *                     dtype, stride and variant, with xhat_out and fro_out; GKA_PHASE_ALL only. It is the only path
  *                     for float32 tensors or operands at d = 16 and 32 and for d = 256 up to 128 tokens (what
- *                     GKA_PATH_AUTO selects there; longer sequences at d = 256 run chunk-wise with float32 products)
+ *                     GKA_PATH_AUTO selects there; longer sequences at d = 256 run chunk-wise with float32 operands)
  *                     and its parallelism is the number of pairs: meant for short sequences over many heads
  *                     and as a float32 cross-check of the chunk-wise kernels, not for long sequences over few
  *                     pairs. Gates are used as given (no floor at exp(-100)). */

@@ -18,7 +18,8 @@ struct Plan {
     int pairs_per_batch;          // (batch, head) pairs per launch
     int slab_chunks;              // chunks of every pair per launch
     bool recurrent;               // token-by-token kernel: no chunks, no launch plan
-    bool wide;                    // d = 256 chunk-wise: the two-phase kernels with float32 products
+    bool wide;                    // d = 256 chunk-wise: the two-phase kernels with float32 operands
+    bool pieces;                  // ... which are 16-bit pieces where the tensors and the caller's operands are bf16
     bool small;                   // chunk-wise kernels of the head dimensions 16 and 32 (bf16 tensors and operands)
     bool split;                   // GKA_COMPUTE_BF16_SPLIT (fused kernel only)
     bool fused_shape;             // dtype, operands and head dimension of the fused kernel
@@ -128,9 +129,10 @@ gka_status make_plan(const gka_params *p, Plan *pl, bool readout_only = false, i
     // GKA_PATH_TWO_PHASE select there), else token by token
     pl->small = pl->d <= 32 && pl->io_bf16 && p->compute == GKA_COMPUTE_BF16 && !readout_only &&
                 (p->path == GKA_PATH_AUTO || p->path == GKA_PATH_TWO_PHASE);
-    // d = 256: GKA_PATH_AUTO takes the chunk-wise kernels with float32 products (the token-by-token kernel's arithmetic)
+    // d = 256: GKA_PATH_AUTO takes the chunk-wise kernels with float32 operands (the token-by-token kernel's arithmetic)
     // above kWideMinTokens
     pl->wide = pl->d == 256 && p->path == GKA_PATH_AUTO && p->T > kWideMinTokens && !pl->split && !readout_only;
+    pl->pieces = pl->wide && pl->io_bf16 && p->compute == GKA_COMPUTE_BF16;
     pl->recurrent = !pl->small && !pl->wide && (p->path == GKA_PATH_RECURRENT || !chunked_dim(pl->d));
     if (pl->recurrent && (p->path == GKA_PATH_TWO_PHASE || p->path == GKA_PATH_FUSED || readout_only))
         return GKA_ERR_UNSUPPORTED;
@@ -391,6 +393,7 @@ gka_status forward_impl(const gka_params *p, const void *q, const void *k, const
     so.stride_b = pl.stride_b; so.stride_t = pl.stride_t; so.stride_h = pl.stride_h;
     so.H = p->H; so.T = p->T; so.n_iter = p->n_iter;
     so.init_states = H_init != nullptr;
+    sa.pieces = so.pieces = pl.pieces;
     // d = 256 with the final states in the buffers of the initial ones: one segment, whose workgroups read the part of a state
     // that they write. (With several segments the last one's workgroups would write what the others may not have read yet;
     // several slabs read and write them in different launches.)

@@ -56,6 +56,7 @@ struct StatePassArgs {
     int write_frags;              // store chunk states to ws_H / ws_U / ws_hn
     bool only_u;                  // float32 operands: the H states are not needed (plain readout y_t = U_t q_t): their workgroups exit
     bool only_h;                  // the U states are not needed (solve without readout): their workgroups exit
+    bool pieces;                  // d = 256, bf16 tensors: float32 operands as 16-bit pieces
 };
 
 struct SolveArgs {
@@ -82,6 +83,7 @@ struct SolveArgs {
     // with q2: the results as the readouts of the backward pass take them, bf16 value and remainder of the first, value of the
     // second (packed [B,T,H,d])
     void *xhat_hi, *xhat_lo, *xhat2_hi;
+    bool pieces;                  // d = 256, bf16 tensors: float32 operands as 16-bit pieces where they can be
     bool init_states;             // the sequence starts from given states (else the states before chunk 0 are zero)
     int skip_blocks;              // float32 products: token blocks at the chunks' ends that launches before this one took
                                   // (gka_solve_wide.hip: -1 if this one takes them all)
@@ -244,7 +246,7 @@ hipError_t launch_chunk_solve(const SolveArgs &a, int n_pairs, int d, bool io_bf
                               hipStream_t stream);
 // The same with float32 products (gka_solve_f32.hip; d = 64, 128, 256): what launch_chunk_solve calls for float32 operands.
 hipError_t launch_solve_f32(const SolveArgs &a, int d, bool io_bf16, hipStream_t stream);
-// d = 256, bf16 tensors: float32's precision from 16-bit pieces (gka_solve_wide.hip), which launch_solve_f32 selects where it can;
+// d = 256, bf16 tensors and operands: float32's precision from 16-bit pieces (gka_solve_wide.hip), which launch_solve_f32 selects where it can;
 // tiles: token tiles per workgroup, 1 or 2.
 bool solve_wide_takes(const SolveArgs &a, int d, bool io_bf16);
 hipError_t launch_solve_wide(const SolveArgs &a, int tiles, hipStream_t stream);

@@ -553,7 +553,10 @@ static hipError_t launch_solve_wide_t(const SolveArgs &a, hipStream_t stream)
     return hipSuccess;
 }
 
-bool solve_wide_takes(const SolveArgs &a, int d, bool io_bf16) { return d == kWideD && io_bf16 && a.n_iter <= kMaxPasses; }
+bool solve_wide_takes(const SolveArgs &a, int d, bool io_bf16)
+{
+    return a.pieces && d == kWideD && io_bf16 && a.n_iter <= kMaxPasses;
+}
 
 hipError_t launch_solve_wide(const SolveArgs &a, int tiles, hipStream_t stream)
 {

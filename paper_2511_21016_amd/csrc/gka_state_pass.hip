@@ -81,18 +81,15 @@ __device__ __forceinline__ void store_end_state(const StatePassArgs &a, const f3
     }
 }
 
+// Float32 operands by 16-bit pieces, of bf16 tensors (StatePassArgs::pieces): the k rows are bf16 as they are, and the weighted rows
+// of a in three bf16 pieces have float32's 24 bits, so a float32 product is three bf16 ones, at a fifth of the matrix pipe's time
+// and with half the LDS; the k rows carry no weight. d = 256, 32 pairs x 1024 tokens: 131 -> 76 us, of which 268 MB of states
+// take 53.
+struct MmaPieces : MmaF32 {};
+
 // DOH: this workgroup owns the H slab (else the U slab); WRITE: chunk states are written to the workspace. Both are
 // compile-time so that the chunk loop is straight-line code and the in-flight prefetches are never drained by a
 // conservative wait.
-// Float32 operands of bf16 tensors at d = 256: the k rows are bf16 as they are, and the weighted rows of a in three bf16 pieces
-// have float32's 24 bits, so a float32 product is three bf16 ones, at a fifth of the matrix pipe's time and with half the LDS;
-// the k rows carry no weight. 32 pairs x 1024 tokens: 131 -> 76 us, of which 268 MB of states take 53.
-template <class MMA, class IO, int D>
-constexpr bool state_pass_by_pieces()
-{
-    return std::is_same<MMA, MmaF32>::value && std::is_same<IO, IOBF16>::value && D == 256;
-}
-
 template <class MMA, class IO, int D, bool DOH, bool WRITE, bool GATED>
 __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, int group,
                                                 typename MMA::elem_t *s_k, typename MMA::elem_t *s_v)
@@ -105,7 +102,7 @@ __device__ __forceinline__ void state_pass_body(const StatePassArgs &a, int rb, 
     constexpr int RSV = 32 + MMA::kRowPad;
     constexpr int KP = kChunk * (D / 4) / NT;     // 4-element pieces of k per thread (= 8)
     constexpr int VP = kChunk * 8 / NT;           // 4-element pieces of the v slab per thread
-    constexpr bool PIECES = state_pass_by_pieces<MMA, IO, D>();
+    constexpr bool PIECES = std::is_same<MMA, MmaPieces>::value;
     // PIECES: k rows as they are, then the slab's columns of the weighted a rows, three pieces
     constexpr int RSB = D + MmaBF16::kRowPad, RSA = 32 + MmaBF16::kRowPad;
     uint16_t *t_k = (uint16_t *)s_k, *t_a = (uint16_t *)s_v;
@@ -637,7 +634,7 @@ __global__ __launch_bounds__(D * 2) __attribute__((amdgpu_waves_per_eu(kStateWav
     if (a.only_h && (sub & 1)) return;             // ... or its U states
     const int rb = sub >> 1;                       // slab index (row block of H0 / U0)
     typedef typename MMA::elem_t elem_t;
-    constexpr bool PIECES = state_pass_by_pieces<MMA, IO, D>();
+    constexpr bool PIECES = std::is_same<MMA, MmaPieces>::value;
     constexpr size_t k_bytes = PIECES ? kChunk * (D + MmaBF16::kRowPad) * 2 : kChunk * (D + MMA::kRowPad) * sizeof(elem_t);
     constexpr size_t v_bytes = PIECES ? 3 * kChunk * (32 + MmaBF16::kRowPad) * 2 : kChunk * (32 + MMA::kRowPad) * sizeof(elem_t);
     __shared__ __attribute__((aligned(1024))) elem_t s_k[k_bytes / sizeof(elem_t)];
@@ -714,6 +711,7 @@ hipError_t launch_state_pass(const StatePassArgs &a, int n_pairs, int d, bool io
         return launch_state_pass_t<MmaBF16, IOBF16, 64>(a, n_pairs, stream);
     }
     if (io_bf16) {
+        if (d == 256 && a.pieces) return launch_state_pass_t<MmaPieces, IOBF16, 256>(a, n_pairs, stream);
         if (d == 256) return launch_state_pass_t<MmaF32, IOBF16, 256>(a, n_pairs, stream);
         if (d == 128) return launch_state_pass_t<MmaF32, IOBF16, 128>(a, n_pairs, stream);
         return launch_state_pass_t<MmaF32, IOBF16, 64>(a, n_pairs, stream);

@@ -14,15 +14,15 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-5
 
 
-def both(x, n_iter, variants=None, **kw):
+def both(x, n_iter, variants=None, of=("bf16", "f32"), compute=None, **kw):
     import torch
     out = []
-    for dtype in ("bf16", "f32"):
+    for dtype in of:
         dev = {n: to_device(x[n], dtype) for n in ("q", "k", "v")}
         opt = {n: to_device(v, "f32") for n, v in (variants or {}).items()}
         o, ex = binding.gka_forward(dev["q"], dev["k"], dev["v"], to_device(x["gate"], "f32"),
                                     None if "lambda_scale" in kw else to_device(x["lam"], "f32"), n_iter, return_xhat=True,
-                                    return_fro=True, return_state=True, compute=None, **opt, **kw)
+                                    return_fro=True, return_state=True, compute=compute, **opt, **kw)
         torch.cuda.synchronize()
         out.append({"o": to_host(o), **{n: to_host(t) for n, t in ex.items()}})
     return out
@@ -51,6 +51,17 @@ def test_against_float32_products(B, H, T, variants):
         check(*both(x, 8, variants={n: g[n] for n in ("beta", "alpha")}, lambda_scale=0.05))
     else:
         check(*both(x, 8))
+
+
+@pytest.mark.parametrize("B,H,T", [(1, 2, 175), (4, 8, 300)])
+def test_float32_operands_of_bf16_tensors(B, H, T):
+    """GKA_COMPUTE_F32 is the float32 MFMA path for either type of tensors: the same bits up to the output's rounding."""
+    w = synth.CFG2.scaled(B=B, H=H, T=T, d=256, n_iter=8, seed=950 + T)
+    x = synth.make_inputs(w)
+    got, want = both(x, 8, compute=binding.GKA_COMPUTE_F32)
+    for n in ("xhat", "fro", "H_final", "U_final"):
+        assert (got[n] == want[n]).all(), n
+    assert (got["o"] == synth.round_to_bf16(want["o"].astype(np.float32))).all()
 
 
 @pytest.mark.parametrize("n_iter", [0, 1, 60, 61])

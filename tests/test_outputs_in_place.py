@@ -14,7 +14,8 @@ assert st == binding.GKA_OK, binding.status_string(st)
 
 
 def _launches(d, B, H, T, dtype, o, n_iter=5):
-    io, compute = {"f32": ("GKA_F32", "GKA_COMPUTE_F32"), "bf16": ("GKA_BF16", "GKA_COMPUTE_BF16")}[dtype]
+    io, compute = {"f32": ("GKA_F32", "GKA_COMPUTE_F32"), "bf16": ("GKA_BF16", "GKA_COMPUTE_BF16"),
+                   "bf16, f32": ("GKA_BF16", "GKA_COMPUTE_F32")}[dtype]
     return [c for c in record(_CALL.format(d=d, B=B, H=H, T=T, io=io, compute=compute, o=o, n_iter=n_iter))
             if c["kind"] == "launch"]
 
@@ -25,6 +26,8 @@ def _launches(d, B, H, T, dtype, o, n_iter=5):
                                                                 (128, 1, 3, 200, "f32", 5, 4, "solve_f32_kernel"),
                                                                 (256, 1, 2, 300, "f32", 5, 4, "solve_f32_kernel"),
                                                                 (256, 4, 8, 300, "f32", 5, 2, "solve_f32_kernel"),
+                                                                (256, 1, 2, 300, "bf16, f32", 5, 4, "solve_f32_kernel"),
+                                                                (256, 4, 8, 300, "bf16, f32", 5, 2, "solve_f32_kernel"),
                                                                 (256, 1, 2, 300, "bf16", 5, 4, "solve_wide_kernel"),
                                                                 (256, 4, 8, 300, "bf16", 60, 2, "solve_wide_kernel"),
                                                                 (256, 1, 2, 300, "bf16", 61, 4, "solve_f32_kernel"),
