@@ -4,9 +4,10 @@
 // that keep float32's precision, at an eighth to a fifth of the matrix pipe's time:
 //   * states and vectors as two binary16 pieces, x s = hi + lo with a power of two s (22 bits of the largest element's scale and
 //     of everything within 2^-10 of it; 2^-34 of the largest for what is smaller): S x ~ Sh xh + Sl xh + Sh xl, what is left out is
-//     2^-22 of the product, less than the rounding of a float32 sum of 256 terms. s is chosen per wave for its rows of a
-//     state (largest element to [2^9, 2^10)), per token for the solve's updates (largest element of the first to [2^4, 2^5):
-//     the passes may grow them, see kMaxPasses) and once more for the readout's operand.
+//     2^-22 of the product, less than the rounding of a float32 sum of 256 terms. s is chosen per row of a state (largest
+//     element to [2^9, 2^10); per wave, for its 32 rows, small rows beside large ones kept few digits), per token for the
+//     solve's updates (largest element of the first to [2^4, 2^5): the passes may grow them, see kMaxPasses) and once more for
+//     the readout's operand.
 //   * keys are exact in either 16-bit type: binary16 with a power of two per key for K x (two products), bf16 as stored for
 //     K^T (P o M) and V^T (P o M), whose other operand, the masked products, is cut into three bf16 pieces (24 bits).
 // Operands of all contractions over features sit in LDS as fragments of v_mfma_f32_16x16x32: lane (n, kg) = (lane & 15,
@@ -39,7 +40,7 @@ struct WideShape {
     static constexpr size_t row_bytes = (size_t)kChunk * kRowStride * 2;          // k rows, later v rows, bf16
     static constexpr size_t x_bytes = (size_t)TT * 2 * kSteps * 64 * 16;          // operand fragments [tt][hi, lo][s][lane]
     static constexpr size_t p_bytes = (size_t)TT * 2 * 3 * 64 * 16;               // masked products [tt][jb][piece][lane]
-    static constexpr size_t tab_bytes = (kChunk + 2 * kWideWaves * 16 * TT) * 4;  // scales of the keys, maxima of the tokens
+    static constexpr size_t tab_bytes = (kChunk + 2 * kWideWaves * 16 * TT + kWideD) * 4;  // scales of keys, maxima of tokens, scales of state rows
     static constexpr size_t lds_bytes = k_bytes + row_bytes + x_bytes + p_bytes + tab_bytes;
     static_assert((2 * kWideWaves + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand fragments");
 };
@@ -119,6 +120,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
+    float *sScale = sMax + 2 * NW * 16 * TT + 32 * w;    // [NW][32] inverse scales of this wave's rows of a state
     // The workgroups of a chunk read the same 512 KiB of states. They get block indices equal modulo 8, next to each other: the
     // same XCD, whose L2 then serves all but the first, at about the same time. (All of one token block before the next:
     // states read from HBM once for each,
@@ -167,29 +169,31 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     load_rows(a.k);
     // this wave's rows of a state as A fragments: element [32 w + 16 rt + n][32 s + 16 (p / 4) + 4 kg + p % 4] times the scale
     f16x8 shi[2][kSteps], slo[2][kSteps];
-    int sexp = 0;
+    // inverse scales of rows 32 w + 16 rt + 4 kg .. (from LDS wherever they are needed: no registers for them across the passes)
+    auto state_scale = [&](int rt) { return *(const f32x4 *)(sScale + 16 * rt + 4 * kg); };
     auto load_state = [&](const void *ws) {
         if (!stated) return;
         const f32x4 *src = (const f32x4 *)ws + chunk_id * (kWideD * kWideD / 4) + (int64_t)w * 2 * 16 * 64 + lane;
         f32x4 x[2][2 * kSteps];
-        float m = 0.0f;
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
             for (int s = 0; s < 2 * kSteps; ++s) x[rt][s] = src[(rt * 2 * kSteps + s) * 64];
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < 2; ++rt) {
+            float m = 0.0f;
 #pragma unroll
             for (int s = 0; s < 2 * kSteps; ++s)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(x[rt][s][e]));
-        sexp = __builtin_amdgcn_readfirstlane(scale_exponent(wave_max(m), 9));
-        const float sc = pow2(sexp);
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+            const int sexp = scale_exponent(max_kg(m), 9);
+            const float sc = pow2(sexp);
 #pragma unroll
             for (int s = 0; s < kSteps; ++s) split_f16(sc * x[rt][2 * s], sc * x[rt][2 * s + 1], shi[rt][s], slo[rt][s]);
+            sScale[16 * rt + n] = pow2(-sexp);           // (the same from the four lanes of a row)
+        }
     };
+    sScale[lane & 31] = 1.0f;
     load_state(a.ws_H);
     int c_loc[TT];                                       // this lane's tokens
     int64_t tok_off[TT];
@@ -276,7 +280,6 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     // ---------------- chunk-wise Frobenius norm (as in gka_solve_f32.hip) ----------------
     float fro[TT];
     {
-        const float sinv = pow2(-sexp);
         for (int jt = 0; jt < JT; ++jt) {
             float part = 0.0f;
             const float ksj = sKs[16 * jt + n];          // (column n: key 16 jt + n)
@@ -293,10 +296,12 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                 }
                 const f16x8 kr = sK[(jt * kSteps + w) * 64 + lane];               // this wave's features of the keys
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
+                for (int rt = 0; rt < 2; ++rt) {
+                    acc[rt] *= state_scale(rt);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) part += acc[rt][r] * (float)kr[4 * rt + r];
-                part = sum_kg(part) * sinv * ksj * ksj;
+                }
+                part = sum_kg(part) * ksj * ksj;
             }
             if (kg == 0) sA[w * 64 + 16 * jt + n] = part;
         }
@@ -467,7 +472,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     token_scales(dl, 4, sMax);                                 // (its barrier: the norm's scratch is free for the operands)
     float zs[TT];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) zs[tt] = zeta[tt] * pow2(-sexp) * pow2(-xexp[tt]);
+    for (int tt = 0; tt < TT; ++tt) zs[tt] = zeta[tt] * pow2(-xexp[tt]);
     for (int it = 0; it < a.n_iter; ++it) {
         publish(dl);
         lds_barrier();                                   // delta visible; the masked products of the last pass are used up
@@ -480,13 +485,15 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
             omega[tt] = 4.0f / (4.0f - rho2[tt] * omega[tt]);                     // weight schedule
             const float cm = omega[tt] - 1.0f, cs = -omega[tt] * s0[tt];
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
+            for (int rt = 0; rt < 2; ++rt) {
+                const f32x4 zsr = zs[tt] * state_scale(rt);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float res = zs[tt] * gS[rt][tt][r] + gI[rt][tt][r] + lam[tt] * xi[rt][tt][r];   // -r_{i-1}
+                    const float res = zsr[r] * gS[rt][tt][r] + gI[rt][tt][r] + lam[tt] * xi[rt][tt][r];   // -r_{i-1}
                     dl[rt][tt][r] = cm * dl[rt][tt][r] + cs * res;
                     xi[rt][tt][r] += dl[rt][tt][r];
                 }
+            }
         }
     }
     if (GATED && a.xhat_out) {
@@ -524,7 +531,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) gS[rt][tt] *= zeta[tt] * pow2(-sexp) * pow2(-xexp[tt]);
+        for (int tt = 0; tt < TT; ++tt) gS[rt][tt] *= zeta[tt] * pow2(-xexp[tt]) * state_scale(rt);
     intra_product(gS);
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)

@@ -86,6 +86,21 @@ def test_scales(scale_q, scale_k, scale_v):
     check(*both(x, 8))
 
 
+def test_features_of_other_scales():
+    """Single features of q, k and v are 2^-32 of the others: their rows of the states are as small, and what the solve and the
+    readout make of them has float32's and the output's precision by itself."""
+    w = synth.CFG2.scaled(B=1, H=2, T=200, d=256, n_iter=8, seed=80)
+    x = synth.make_inputs(w)
+    few = [5, 40, 200]
+    for n in ("q", "k", "v"):
+        x[n][..., few] *= np.float32(2.0 ** -32)
+    got, want = both(x, 8)
+    check(got, want)
+    for n, tol in (("xhat", TOL), ("o", 2.0 ** -8)):
+        scale = np.abs(want[n][..., few]).max(axis=1, keepdims=True)
+        assert (np.abs(got[n][..., few] - want[n][..., few]) / scale).max() <= tol, n
+
+
 def test_a_wiped_state_and_a_tiny_key_behind_it():
     w = synth.CFG2.scaled(B=1, H=2, T=200, d=256, n_iter=8, seed=79)
     x = synth.make_inputs(w)
