@@ -3,13 +3,14 @@
 // a wave in its registers, vectors cross waves through LDS) with every float32 product replaced by products of 16-bit pieces
 // that keep float32's precision, at an eighth to a fifth of the matrix pipe's time:
 //   * states and vectors as two binary16 pieces, x s = hi + lo with a power of two s (22 bits of the largest element's scale and
-//     of everything within 2^-10 of it; 2^-34 of the largest for what is smaller): S x ~ Sh xh + Sl xh + Sh xl, what is left out is
+//     of what is not much smaller; else within 2^-34 of the largest, 2^-29 for the updates): S x ~ Sh xh + Sl xh + Sh xl, what is left out is
 //     2^-22 of the product, less than the rounding of a float32 sum of 256 terms. s is chosen per row of a state (largest
 //     element to [2^9, 2^10); per wave, for its 32 rows, small rows beside large ones kept few digits), per token for the
 //     solve's updates (largest element of the first to [2^4, 2^5): the passes may grow them, see kMaxPasses) and once more for
 //     the readout's operand.
-//   * keys are exact in either 16-bit type: binary16 with a power of two per key for K x (two products), bf16 as stored for
-//     K^T (P o M) and V^T (P o M), whose other operand, the masked products, is cut into three bf16 pieces (24 bits).
+//   * keys are one binary16 piece with a power of two per key for K x (two products; largest element to [2^14, 2^15): exact down to
+//     2^-31 of it, below that within 2^-39 of it), and bf16 as stored for K^T (P o M) and V^T (P o M), whose other operand, the
+//     masked products, is cut into three bf16 pieces (24 bits).
 // Operands of all contractions over features sit in LDS as fragments of v_mfma_f32_16x16x32: lane (n, kg) = (lane & 15,
 // lane >> 4), eight values, slot p <-> feature 32 s + 16 (p / 4) + 4 kg + p % 4. A wave's rows of a vector are one such
 // fragment.
@@ -241,7 +242,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
         unit_j = u;
         unit_m = unit_t < TT ? mask4(u, 16 * (TT * tb + unit_t) + n, false) : zero4();
     }
-    // keys to LDS: bf16 rows, and binary16 fragments with a power of two per key (largest element to [1, 2))
+    // keys to LDS: bf16 rows, and binary16 fragments with a power of two per key (largest element to [2^14, 2^15): sums of 256
+    // products with the updates' 2^16 stay below 2^40)
     store_rows();
 #pragma unroll
     for (int i = 0; i < NP; ++i)
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
             const int row = i * NW + w;
             f32x4 x = IO::cvt4(rows[i]);
             if (tok0 + row >= a.T) x = zero4();
-            const int e = scale_exponent(wave_max(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])))), 0);
+            const int e = scale_exponent(wave_max(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])))), 14);
             const float sc = pow2(e);
             f16x4 y;
 #pragma unroll

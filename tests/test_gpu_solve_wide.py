@@ -101,6 +101,18 @@ def test_features_of_other_scales():
         assert (np.abs(got[n][..., few] - want[n][..., few]) / scale).max() <= tol, n
 
 
+def test_small_elements_of_keys():
+    """Queries live where every key is 2^-22 of its largest element: the products of keys and vectors are sums of those small
+    elements, which count with all their bits. (Lambda is so large that the solve does not turn the vectors to the others, where
+    elements 2^-28 of the largest would count.)"""
+    w = synth.CFG2.scaled(B=1, H=2, T=200, d=256, n_iter=8, seed=81)
+    x = synth.make_inputs(w)
+    x["q"][..., :128] = 0.0
+    x["k"][..., 128:] *= np.float32(2.0 ** -22)
+    x["lam"] += np.float32(4096.0)
+    check(*both(x, 8))
+
+
 def test_a_wiped_state_and_a_tiny_key_behind_it():
     w = synth.CFG2.scaled(B=1, H=2, T=200, d=256, n_iter=8, seed=79)
     x = synth.make_inputs(w)
