@@ -1153,6 +1153,8 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
             for (int ft = 0; ft < 8; ++ft) *(f32x4 *)(d.x_f32 + row + 16 * ft + 4 * c.kg) = xi[ft];
         }
     }
+    f32x4 *park_x = c.park + (int64_t)gridDim.x * (8 * 8 * 64);
+    if (d.dlambda) park_store(park_x, xi);   // (as it is, until the second solve is through)
     // (all lanes take part in the exchanges of neighbouring kg; a token is valid on all four of its lanes or on none)
     if (s.valid) store_token_bf16(d.x_hi, d.x_lo, row, c.kg, xi);
     float dyy = 0.0f, dal = 0.0f;
@@ -1179,26 +1181,22 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
     refresh_lane(c);
     const int tokc2 = min(s.tok, c.a.T - 1);
     const int64_t tok_index2 = c.gate_base + (int64_t)tokc2 * c.a.H, row2 = tok_index2 * kD;
-    // x_t again, as it was stored (lanes of this wave did, before the passes; value + remainder)
-    wait_vector_memory_but<0>();
-    IOBF16::raw4 xh[8], xl[8];
-#pragma unroll
-    for (int ft = 0; ft < 8; ++ft) {
-        xh[ft] = IOBF16::load_raw4(d.x_hi, row2 + 16 * ft + 4 * c.kg);
-        xl[ft] = IOBF16::load_raw4(d.x_lo, row2 + 16 * ft + 4 * c.kg);
-    }
 #pragma unroll
     for (int ft = 0; ft < 8; ++ft) xi[ft] += dl[ft];
+    if (d.dlambda) {
+        f32x4 x[8];
+        park_load(park_x, x);
+        float xp = 0.0f;
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) xp = dot4(x[ft], xi[ft], xp);
+        xp = sum_over_kg(xp);
+        if (s.valid && c.kg == 0) d.dlambda[tok_index2] = -xp;
+    }
     if (s.valid) {
 #pragma unroll
         for (int ft = 0; ft < 8; ++ft) *(f32x4 *)(d.p_f32 + row2 + 16 * ft + 4 * c.kg) = xi[ft];
         store_token_bf16(d.p_hi, nullptr, row2, c.kg, xi);
     }
-    float xp = 0.0f;
-#pragma unroll
-    for (int ft = 0; ft < 8; ++ft) xp = dot4(IOBF16::cvt4(xh[ft]) + IOBF16::cvt4(xl[ft]), xi[ft], xp);
-    xp = sum_over_kg(xp);
-    if (d.dlambda && s.valid && c.kg == 0) d.dlambda[tok_index2] = -xp;
     if constexpr (GATED) {
         // (alpha_t is not read again: dalpha may have replaced it)
         if (d.dq && s.valid) {               // dq_t = p_t + (1 - alpha_t) dxt_t (without an alpha-connection p_f32 is dq)
@@ -1490,7 +1488,7 @@ static void carve_fused_workspace(FusedArgs &a, void *workspace)
 size_t dual_solve_workspace_bytes(int64_t summaries, int64_t workgroups)
 {
     return (size_t)summaries * (3 * kD * kD * sizeof(float)) + (((size_t)summaries * sizeof(float) + 255) / 256) * 256 +
-           (size_t)workgroups * (kD * kD * sizeof(float));
+           (size_t)workgroups * (2 * kD * kD * sizeof(float));
 }
 
 hipError_t launch_fused_forward(const FusedArgs &a0, void *workspace, hipStream_t stream, int which, bool split)

@@ -297,7 +297,8 @@ struct DualSolveArgs {
 // between as well), then the walk.
 hipError_t launch_dual_solve_summaries(const DualSolveArgs &d, void *workspace, hipStream_t stream);
 hipError_t launch_dual_solve(const DualSolveArgs &d, void *workspace, hipStream_t stream);
-// In the workspace: [pairs, n_sums][3] states, log2 decays, and a state's room for each workgroup of the walk.
+// In the workspace: [pairs, n_sums][3] states, log2 decays, and two states' room for each workgroup of the walk: H, and x of the
+// 128 tokens at hand.
 constexpr int kSummaryPlanes = 3;
 size_t dual_solve_workspace_bytes(int64_t summaries, int64_t workgroups);
 

@@ -29,8 +29,8 @@ CHUNKS = (1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 15, 16, 17, 23, 32, 39, 63, 64, 65, 129
 
 @pytest.mark.parametrize("n_iter,walk_chunks", [(0, 0), (10, 0), (40, 0), (10, 1), (10, 5), (10, 2 ** 31 - 1)])
 def test_the_solves_walk_keeps_within_it(n_iter, walk_chunks):
-    """From the arguments of the launches: the blocks in which the workgroups of the solves' walk park their states, the last
-    thing in the workspace, end within what the query asked for, and the query does not depend on the passes."""
+    """From the arguments of the launches: the blocks in which the workgroups of the solves' walk park their states and vectors, the
+    last thing in the workspace, end within what the query asked for, and the query does not depend on the passes."""
     cases = [(B, H, 64 * n - n % 2) for B, H in PAIRS for n in CHUNKS]
     calls = record(f"""
 for i, (B, H, T) in enumerate({cases}):
@@ -49,7 +49,7 @@ for i, (B, H, T) in enumerate({cases}):
         W, walk = (i + 1) << 44, walks[i]
         assert 0 < walk["grid"] <= max(1024, B * H) or walk_chunks
         parked = max(x for x in walk["words"] if W <= x < W + (1 << 44))
-        assert parked - W + walk["grid"] * STATE_BYTES <= size, (B, H, T, walk["grid"])
+        assert parked - W + walk["grid"] * 2 * STATE_BYTES <= size, (B, H, T, walk["grid"])
 
 
 @pytest.mark.gpu

@@ -153,3 +153,18 @@ def test_more_pairs_than_workgroups_in_four_rounds():
     x1 = {n: a[:1, :, :2] for n, a in x.items()}
     ref = bwd.backward(x1["q"], x1["k"], x1["v"], x1["gate"], x1["lam"], dy[:1, :, :2], w.n_iter)
     compare({n: a[:1, :, :2] for n, a in want.items()}, ref, T, 0.0)
+
+
+def test_lambda_gradient_takes_x_in_float32():
+    """Without passes x_t = 2 q_t / (L + mu), p_t is dq_t, and dlambda_t = -x_t . p_t can be formed from them: 128 float32
+    products and sums, a relative 2^-24 for each rounding of a partial sum and for the common factor. x as bf16 value +
+    remainder, 2^-18 of every element, would leave three to five times as much."""
+    w, x, dy = problem(2, 4, 300, n_iter=0, seed=90)
+    x["lam"] = (x["lam"] + 1024.0).astype(np.float32)
+    got = run(w, x, dy, binding.GKA_PATH_AUTO)
+    dev = upload_inputs(x, "bf16")
+    fro = to_host(binding.gka_forward(*(dev[n] for n in ("q", "k", "v", "gate", "lam")), 0, return_fro=True)[1]["fro"])
+    terms = 2.0 * x["q"].astype(np.float64) / (fro + 2.0 * x["lam"])[..., None] * got["dq"]
+    err = np.abs(got["dlam"] + terms.sum(axis=-1)) / np.abs(terms).sum(axis=-1)
+    print("dlambda", err.max(), np.sqrt((err ** 2).mean()), flush=True)
+    assert err.max() <= 2e-7
