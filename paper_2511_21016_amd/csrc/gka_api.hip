@@ -38,7 +38,7 @@ constexpr int kStateMaxWalk = 64;          // chunks a state-pass workgroup walk
 // Chunk states one launch pair keeps in the workspace unless gka_params::slab_state_bytes says otherwise (tests use
 // that to force several slabs on small problems).
 constexpr size_t kDefaultSlabStateBytes = (size_t)1 << 30;
-constexpr int kComputeUnits = 256;         // the fused kernels run one workgroup on each
+using gka::kComputeUnits;                  // the fused kernels run one workgroup on each
 // Segments are added up to this many workgroups of the fused kernels (four rounds), or as many as a caller's bound on the
 // workspace (gka_params::slab_state_bytes) has room for, one round at least.
 constexpr int kFusedMaxWorkgroups = 4 * kComputeUnits;

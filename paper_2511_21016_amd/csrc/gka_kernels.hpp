@@ -31,6 +31,8 @@ inline hipError_t raise_lds_limits(bool (&done)[kMaxLdsDevices], std::initialize
     return hipSuccess;
 }
 
+constexpr int kComputeUnits = 256;
+
 struct StatePassArgs {
     const void *k, *v;            // [B,T,H,d] tensors (element strides below)
     const float *gate;            // [B,T,H]

@@ -51,8 +51,10 @@ struct ReverseShape {
     static constexpr size_t tab_bytes = (2 + 2 * NW) * kChunk * 4;            // G, weights; partial dots
     // Two chunks' tiles where they fit (d = 64; -S_t k_t alone at d = 128), so that a chunk's copies have a whole chunk's work
     // to land in; else one, whose tiles are filled again as they fall free.
-    static constexpr bool TWO_MAIN = 2 * N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes <= 160 * 1024;
-    static constexpr size_t lds_main = (TWO_MAIN ? 2 : 1) * N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes;
+    static constexpr size_t lds_main(bool two) { return (two ? 2 : 1) * N_TENSORS * tile_elems * 2 + p_bytes + tab_bytes; }
+    static constexpr bool TWO_FITS = lds_main(true) <= 160 * 1024;
+    // (one recurrence at d = 64) two workgroups on a CU with one chunk's tiles each
+    static constexpr bool TWO_GROUPS = NT == 256 && TWO_FITS && 2 * lds_main(false) <= 160 * 1024;
     static constexpr size_t lds_summary = 2 * N_SUMMARY * tile_elems * 2 + NW * kChunk * 4;   // two chunks; the waves' weights
     // a copy instruction of a wave moves 1 KiB: ROWS rows; two instructions per wave and tensor
     static constexpr int ROWS = 512 / D, COPIES = kChunk / ROWS / NW;
@@ -100,7 +102,8 @@ __device__ __forceinline__ int reverse_unit(int w, int i)
     return w + SH::NW * i;
 }
 
-template <int D, int PART, bool SUMMARY>
+// TWO: two chunks' tiles in LDS.
+template <int D, int PART, bool SUMMARY, bool TWO>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void reverse_kernel(ReverseArgs a)
 {
     typedef ReverseShape<D, PART> SH;
@@ -117,7 +120,6 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
     uint16_t *sDY = tiles + (2 + DO_S) * SH::tile_elems;                       // dy (U)
     uint16_t *sK = tiles + (2 + DO_S + DO_U) * SH::tile_elems;
     uint16_t *sV = tiles + (3 + DO_S + DO_U) * SH::tile_elems;
-    constexpr bool TWO = SUMMARY || SH::TWO_MAIN;                              // two chunks' tiles
     constexpr int TOUCH = TWO ? 0 : ((2 + DO_S + DO_U) * kChunk * D * 2 / 128 + NT - 1) / NT;
     frag *sP = (frag *)(tiles + (TWO ? 2 : 1) * NTEN * SH::tile_elems);
     float *sG = (float *)((unsigned char *)sP + SH::p_bytes);
@@ -539,17 +541,25 @@ template <int D, int PART>
 hipError_t launch_reverse_t(const ReverseArgs &a, hipStream_t stream)
 {
     typedef ReverseShape<D, PART> SH;
+    // d = 64, one recurrence, more workgroups than CUs: two of them on a CU with one chunk's tiles each. Whole backward pass,
+    // two chunks' tiles and one workgroup / this: 257 pairs x 500 tokens 479 / 409 us, 300 x 1000 994 / 854, 1000 x 150 487 / 430; up
+    // to a workgroup for each CU two chunks' tiles (256 x 500: 371, 382 with rows fetched into registers).
+    constexpr bool ONE = !SH::TWO_FITS || SH::TWO_GROUPS;
+    const bool two = SH::TWO_FITS && !(SH::TWO_GROUPS && (int64_t)a.n_pairs * a.n_segs > kComputeUnits);
     static bool lds_raised[kMaxLdsDevices] = {};
-    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)reverse_kernel<D, PART, false>, SH::lds_main},
-                                                 {(const void *)reverse_kernel<D, PART, true>, SH::lds_summary}});
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)reverse_kernel<D, PART, false, SH::TWO_FITS>, SH::lds_main(SH::TWO_FITS)},
+                                                 {(const void *)reverse_kernel<D, PART, false, !ONE>, SH::lds_main(!ONE)},
+                                                 {(const void *)reverse_kernel<D, PART, true, true>, SH::lds_summary}});
     if (e != hipSuccess) return e;
     if (a.n_segs > 1) {                                // summaries of every segment but the last, from zero states
-        hipLaunchKernelGGL((reverse_kernel<D, PART, true>), dim3(a.n_pairs * (a.n_segs - 1)), dim3(SH::NT), SH::lds_summary,
+        hipLaunchKernelGGL((reverse_kernel<D, PART, true, true>), dim3(a.n_pairs * (a.n_segs - 1)), dim3(SH::NT), SH::lds_summary,
                            stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((reverse_kernel<D, PART, false>), dim3(a.n_pairs * a.n_segs), dim3(SH::NT), SH::lds_main, stream, a);
+    const dim3 grid(a.n_pairs * a.n_segs), block(SH::NT);
+    if (two) hipLaunchKernelGGL((reverse_kernel<D, PART, false, SH::TWO_FITS>), grid, block, SH::lds_main(true), stream, a);
+    else hipLaunchKernelGGL((reverse_kernel<D, PART, false, !ONE>), grid, block, SH::lds_main(!ONE), stream, a);
     return hipGetLastError();
 }
 }  // namespace
