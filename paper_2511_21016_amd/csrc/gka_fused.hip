@@ -647,6 +647,16 @@ __device__ __forceinline__ float frobenius_norm(const Ctx &c, const Solver &s, i
 
 __device__ __forceinline__ void copy_rows(const Ctx &c, const void *x, int g, int chunk);
 
+// Passes for the 16 tokens ts of a chunk: none where the sequence ends before them (a last chunk without a second one beside it, or
+// one of less than 64 tokens), which leaves issue slots and LDS to the tokens that there are. Forward pass with the layer's
+// variants, us: 1024 pairs x 64 tokens 120 -> 105, x 1 token 114 -> 81, 512 x 150 119 -> 101; backward pass, 1000 pairs x 1 258 ->
+// 223, 520 x 150 539 -> 453. Longer even sequences are indifferent, but for the forward kernel without variants, which runs all
+// passes: with a count of each wave's own 64 pairs x 4096 tokens took 303 instead of 298.
+__device__ __forceinline__ int passes_of_block(const Ctx &c, int chunk, int ts)
+{
+    return chunk * kChunk + 16 * ts < c.T_eff ? c.a.n_iter : 0;
+}
+
 // Everything between the Frobenius table and the published result: the passes, then (after the workgroup has
 // passed the barrier inside) xhat to LDS and the intra-chunk part of the readout.
 template <int NJ, bool SPLIT, bool GATED>
@@ -681,7 +691,7 @@ __device__ __forceinline__ void solve_tokens(Ctx &c, Solver &s, int g, int ts, c
             gn[ft][r] = -rz * qv[r];
         }
     }
-    cheb_passes<NJ, SPLIT ? SPLIT_OPERANDS : SINGLE>(sH, sK, sKT, xi, dl, gn, s.mreg, 1.0f, s0 * s.zeta, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+    cheb_passes<NJ, SPLIT ? SPLIT_OPERANDS : SINGLE>(sH, sK, sKT, xi, dl, gn, s.mreg, 1.0f, s0 * s.zeta, s0 * lam, rho * rho, GATED ? passes_of_block(c, c0 + g, ts) : c.a.n_iter, c.lane, [&]() {
         // v rows of the iteration's chunks replace the k rows; they land during the passes
         copy_rows(c, c.a.v, 0, c0);
         if constexpr (!SPLIT) copy_rows(c, c.a.v, 1, c0 + 1);
@@ -1047,7 +1057,9 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2
         fetch_beta(c0 + kChunksPerIter);
         readout_chunk<0>(c, accU, vTA, c0);
         advance_state(c, accU, 0, zetaA, wVA);
-        if constexpr (!SPLIT) {
+        // (Where there is a second chunk. No iteration follows one without, so the count at the top holds. 1024 pairs x 64 tokens 115 ->
+        // 110 us; 64 pairs x 4096 tokens 298 either way.)
+        if (!SPLIT && c0 + 1 < chunk_end) {
             readout_chunk<1>(c, accU, vTB, c0 + 1);
             advance_state(c, accU, 1, zetaB, wVB);
         }
@@ -1129,7 +1141,8 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
     };
 #pragma unroll
     for (int ft = 0; ft < 8; ++ft) start(ft, IOBF16::cvt4(qraw[ft]));
-    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, c.a.n_iter, c.lane, [&]() {
+    const int passes = passes_of_block(c, c0 + g, ts);
+    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, passes, c.lane, [&]() {
         // k rows of the next iteration's chunks (the row tiles are free); they land during the passes
         copy_rows_untracked(c, c.a.k, 0, c0 + 2);
         copy_rows_untracked(c, c.a.k, 1, c0 + 3);
@@ -1177,7 +1190,7 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
     if (s.valid && c.kg == 0) d.dyy[tok_index] = dyy;
 #pragma unroll
     for (int ft = 0; ft < 8; ++ft) start(ft, GATED ? al * dxt[ft] : dxt[ft]);
-    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, c.a.n_iter, c.lane, [] {});
+    cheb_passes<NJ, SEPARATE>(sH, sK, sKT, xi, dl, gn, s.mreg, s.zeta, s0, s0 * lam, rho * rho, passes, c.lane, [] {});
     refresh_lane(c);
     const int tokc2 = min(s.tok, c.a.T - 1);
     const int64_t tok_index2 = c.gate_base + (int64_t)tokc2 * c.a.H, row2 = tok_index2 * kD;
