@@ -794,8 +794,12 @@ gka_status gka_backward_from_state(const gka_params *p, const void *q, const voi
         return gka::launch_backward_glue(g, which, io_bf16, stream) == hipSuccess ? GKA_OK : GKA_ERR_LAUNCH;
     };
     // d = 128 with bf16 operands: the fused kernels' walk solves for both right-hand sides (a caller that asks for the two-phase
-    // kernels or bounds their chunk states gets those)
-    const bool walk = io_bf16 && p->d_k == 128 && p->compute == GKA_COMPUTE_BF16 && p->path == GKA_PATH_AUTO && p->slab_state_bytes == 0;
+    // kernels or bounds their chunk states gets those). Not for sequences of one chunk in more than one round of workgroups, which
+    // would each have half of their work: whole backward pass, us, walk / two-phase, 257 pairs x 64 tokens 139 / 134, x 40
+    // 133 / 126, 1000 pairs x 64 311 / 304, x 40 278 / 255, x 1 226 / 213 (x 16 230 / 230); 256 pairs x 64 88 / 102, x 1 72 / 76;
+    // two chunks, 257 pairs x 65 180 / 203.
+    const bool walk = io_bf16 && p->d_k == 128 && p->compute == GKA_COMPUTE_BF16 && p->path == GKA_PATH_AUTO && p->slab_state_bytes == 0 &&
+                      (p->T > gka::kChunk || (int64_t)p->B * p->H <= kComputeUnits);
     gka::DualSolveArgs d = {};
     if (walk) {
         gka::FusedArgs &f = d.f;

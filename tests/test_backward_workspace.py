@@ -31,7 +31,7 @@ CHUNKS = (1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 15, 16, 17, 23, 32, 39, 63, 64, 65, 129
 def test_the_solves_walk_keeps_within_it(n_iter, walk_chunks):
     """From the arguments of the launches: the blocks in which the workgroups of the solves' walk park their states and vectors, the
     last thing in the workspace, end within what the query asked for, and the query does not depend on the passes."""
-    cases = [(B, H, 64 * n - n % 2) for B, H in PAIRS for n in CHUNKS]
+    cases = [(B, H, 64 * n - n % 2) for B, H in PAIRS for n in CHUNKS if n > 1 or B * H <= 256]      # (else no walk)
     calls = record(f"""
 for i, (B, H, T) in enumerate({cases}):
     p = binding.make_params(B, H, T, 128, {n_iter}, binding.GKA_BF16, binding.GKA_COMPUTE_BF16, walk_chunks={walk_chunks})
