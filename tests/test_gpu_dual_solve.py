@@ -1,6 +1,5 @@
 """Both solves of the backward pass in the fused kernels' walk (bf16 tensors, d = 128): against the oracle around the edges of
-chunks and chunk pairs, with every option; against the two-phase kernels in segments and from initial states; gradients that
-replace their inputs."""
+chunks and chunk pairs, with every option, in segments and from initial states; gradients that replace their inputs."""
 import numpy as np
 import pytest
 
@@ -11,10 +10,14 @@ from gka_testutil import to_device, to_host, upload_inputs
 pytestmark = pytest.mark.gpu
 
 # Bounds of test_gpu_backward.py, of a gradient's largest value: 2e-2 against the oracle, 5e-2 for dk of short sequences under
-# the rule, 3e-2 for dalpha of a single token. Between two paths that both meet them: twice that. Where random systems are
-# conditioned so badly that the two-phase kernels miss a bound (lambda of 0.01, 8 passes), 1.25 times their error is allowed: the
-# operands are rounded alike, the sums and the start states are not formed in the same order.
+# the rule, 3e-2 for dalpha of a single token. Between two paths that both meet them: twice that. Some of the random systems here
+# are conditioned so badly (lambda of 0.01, 8 passes) that the rounding of their bf16 operands alone exceeds these bounds; there the
+# error of the two-phase solve, which rounds the same operands, was measured before the walk was there, and a quarter more is
+# allowed: the sums and the start states are not formed in the same order. (T, variants, rule): {gradient: that error}
 TOL, TOL_DK_RULE, TOL_DALPHA_ONE = 2e-2, 5e-2, 3e-2
+ILL_CONDITIONED = {(1, False, 0.0): {"dk": 0.0299}, (1, True, 0.0): {"dk": 0.0322, "dalpha": 0.1388},
+                   (1, True, 0.05): {"dk": 0.0859, "dv": 0.0316, "dalpha": 0.1869}, (129, False, 0.0): {"dk": 0.0206},
+                   (200, False, 0.0): {"dlam": 0.0416}}
 
 
 def run(w, x, dy, path, walk_chunks=0, variants=False, rule=0.0, in_place=False, states=None):
@@ -54,7 +57,7 @@ def problem(B, H, T, n_iter=8, seed=0):
     return w, x, dy
 
 
-def compare(got, want, T, rule, factor=1, other=None):
+def compare(got, want, T, rule, factor=1, known={}):
     for n in got:
         if n == "dgate" and T == 1:          # the gate multiplies a zero state: what is left of terms of order one
             assert np.abs(got[n]).max() <= 2e-3
@@ -62,8 +65,8 @@ def compare(got, want, T, rule, factor=1, other=None):
         tol = TOL_DK_RULE if n == "dk" and rule else TOL_DALPHA_ONE if n == "dalpha" and T == 1 else TOL
         tol *= factor
         err = np.abs(got[n] - want[n]).max() / np.abs(want[n]).max()
-        if other and err > tol:
-            tol = 1.25 * np.abs(other[n] - want[n]).max() / np.abs(want[n]).max()
+        if n in known:
+            tol = 1.25 * known[n]
         assert np.isfinite(got[n]).all() and err <= tol, (n, err, tol)
 
 
@@ -76,7 +79,7 @@ def test_against_the_oracle(T, variants, rule):
     opt = synth.make_gates(w) if variants else {}
     want = bwd.backward(x["q"], x["k"], x["v"], x["gate"], None if rule else x["lam"], dy, w.n_iter, lambda_scale=rule,
                         **{n: opt[n] for n in ("beta", "alpha") if n in opt})
-    compare(got, want, T, rule, other=run(w, x, dy, binding.GKA_PATH_TWO_PHASE, variants=variants, rule=rule))
+    compare(got, want, T, rule, known=ILL_CONDITIONED.get((T, variants, rule), {}))
 
 
 @pytest.mark.parametrize("walk", [2, 4, 6])
@@ -92,8 +95,11 @@ def test_segments_initial_states_and_wiped_states(walk):
     Ui = 0.1 * torch.randn((1, 3, 128, 128), generator=gen, device="cuda")
     for states in (None, (Hi, Ui)):
         got = run(w, x, dy, binding.GKA_PATH_AUTO, walk_chunks=walk, states=states)
-        want = run(w, x, dy, binding.GKA_PATH_TWO_PHASE, states=states)
-        compare(got, want, 700, 0.0, factor=2)
+        compare(got, run(w, x, dy, binding.GKA_PATH_TWO_PHASE, states=states), 700, 0.0, factor=2)
+        H, U = (s.cpu().numpy() for s in states) if states else (None, None)
+        want = bwd.backward(x["q"], x["k"], x["v"], x["gate"], x["lam"], dy, w.n_iter, H_init=H, U_init=U)
+        want["dgate"][x["gate"] == 0.0] = 0.0                # (reported as 0 at a gate of 0)
+        compare(got, want, 700, 0.0)
 
 
 @pytest.mark.parametrize("n_iter", [0, 1])
@@ -125,6 +131,12 @@ def test_operands_are_rounded_as_the_two_phase_solve_rounds_them(T):
         apart, err = np.linalg.norm(got[n] - other[n]), np.linalg.norm(other[n] - ref)
         print(T, n, apart / err, flush=True)
         assert apart <= 0.5 * err, (n, apart / err)
+    # The gate gradient is a cumulative sum in which almost everything cancels: what is left follows the order of the sums and of the
+    # start states, so that the two errors are of one size but independent, 1.4 times it apart (half as much again for six pairs)
+    ref = np.asarray(want["dgate"], dtype=np.float64)
+    errs = [np.linalg.norm(a["dgate"] - ref) for a in (got, other)]
+    print(T, "dgate", errs[0] / errs[1], flush=True)
+    assert np.linalg.norm(got["dgate"] - other["dgate"]) <= 2.1 * errs[1] and errs[0] <= 2.0 * errs[1]
 
 
 def test_more_pairs_than_workgroups_in_four_rounds():
