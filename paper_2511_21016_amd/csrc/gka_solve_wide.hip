@@ -49,12 +49,7 @@ struct WideShape {
 __device__ __forceinline__ f32x4 mma_h(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f32x4 mma_b(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
-// over the four lanes that hold the rows of one token
-__device__ __forceinline__ float sum_kg(float x)
-{
-    x += __shfl_xor(x, 16, 64);
-    return x + __shfl_xor(x, 32, 64);
-}
+// largest over the four lanes that hold the rows of one token
 __device__ __forceinline__ float max_kg(float x)
 {
     x = fmaxf(x, __shfl_xor(x, 16, 64));
@@ -303,7 +298,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
                     for (int r = 0; r < 4; ++r) part += acc[rt][r] * (float)kr[4 * rt + r];
                 }
-                part = sum_kg(part) * ksj * ksj;
+                part = sum_over_kg(part) * ksj * ksj;
             }
             if (kg == 0) sA[w * 64 + 16 * jt + n] = part;
         }
@@ -320,8 +315,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                 bp += m[r] * g2;
                 dp += (4 * kg + r == n) ? g2 : 0.0f;
             }
-            bp = sum_kg(bp);
-            dp = sum_kg(dp);
+            bp = sum_over_kg(bp);
+            dp = sum_over_kg(dp);
             if (kg == 0) {
                 sB[it * 64 + 16 * jt + n] = bp;
                 if (it == jt) sDg[16 * jt + n] = dp;
