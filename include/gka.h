@@ -133,13 +133,17 @@ typedef struct {
                           /*   (before the alpha-connection). With q := an incoming gradient this is the    */
                           /*   solve of the backward pass, CH(H_t + lambda_t I, dxhat_t, r) (Section 4.2.2). */
                           /*   Ignored by the decode entry points.                                          */
-    /* Launch plan of gka_forward (0 everywhere = the library's choices; results do not depend on these beyond
-     * rounding). They exist so that callers and tests can bound the workspace or force short walks. */
+    /* Launch plan of gka_forward and gka_backward (0 everywhere = the library's choices; results do not depend on these
+     * beyond rounding). They exist so that callers and tests can bound the workspace or force short walks. */
     int64_t slab_state_bytes; /* two-phase kernels: bytes of chunk states one launch pair keeps in the workspace  */
-                              /*   (0 = 1 GiB); larger problems run as several launches, states carried in fp32   */
-    int32_t walk_chunks;      /* fused kernel: chunks one workgroup walks (rounded up to an even number); the     */
-                              /*   sequence is cut into such segments, whose start states come from a summary     */
-                              /*   launch. 0 = as few segments as fill the GPU                                    */
+                              /*   (0 = 1 GiB); larger problems run as several launches, states carried in fp32.  */
+                              /*   Fused kernels: the sequences are cut into no more segments than this has room  */
+                              /*   for, or than fill the GPU once if that is more. gka_backward: not 0 = the two  */
+                              /*   solves on the two-phase kernels, within this bound                             */
+    int32_t walk_chunks;      /* fused kernels: chunks one workgroup walks (rounded up to an even number with     */
+                              /*   GKA_COMPUTE_BF16); the sequence is cut into such segments, whose start states  */
+                              /*   come from a summary launch. 0 = the segments whose estimated time is shortest, */
+                              /*   up to 1024 workgroups                                                          */
     int32_t path;             /* gka_path                                                                         */
 } gka_params;
 
@@ -149,7 +153,9 @@ typedef struct {
  * chunks at a time: large problems are processed as a sequence of such launches, the running states
  * carried from slab to slab in float32, so that the workspace stays bounded (about 1 GiB of chunk
  * states; p->slab_state_bytes overrides that budget). The fused kernel (gka_path) needs only the segment summaries
- * of its chunk walk; the query returns the larger of the two sizes. The chunk-wise kernels of d = 16 and 32 keep four
+ * of its chunk walk and the parked states: 192 KiB (split operands: 256) for each of up to 1024 workgroups, or for one per
+ * (batch, head) pair where there are more; the query returns the larger of the two sizes, whatever the number
+ * of passes. The chunk-wise kernels of d = 16 and 32 keep four
  * d x d float32 states per chunk. The token-by-token path (GKA_PATH_RECURRENT) keeps
  * its states in registers: 256 bytes, plus one U state per pair at d = 256. Above 128 tokens d = 256 runs chunk-wise: at
  * most 1 GiB of chunk states as well and, where a sequence takes several slabs, 1 MiB of carried states for each of the up to
@@ -256,11 +262,12 @@ gka_status gka_decode_tokens(const gka_params *p,
  * dy_t = dL/dy_t, the gradients at q, k, v, the gates and lambda (and at the write gate and the alpha-connection if
  * they are in use). The forward solve's result is treated as the exact solution of its system and both solves run
  * r passes of Algorithm 1 (dq_t = CH(H_t + lambda_t I, dxhat_t, r)), as in the paper. GKA_BF16 tensors: both
- * solves share one pass over the forward pass's chunk states, two gated-linear-attention readouts give U_t^T dy_t and
+ * solves run in one launch over the same chunk states (d = 128 with GKA_COMPUTE_BF16, GKA_PATH_AUTO and no bound on the chunk
+ * states: in the fused forward kernel's walk; else behind the two-phase kernels' state pass), two gated-linear-attention readouts give U_t^T dy_t and
  * p_t . H_t xhat_t (the rule for lambda: two more), and one walk over the sequence from its end forms the reverse
  * recurrences of Section 4.2.2 (two walks with an alpha-connection). GKA_F32 tensors: the forward kernels for two solves
- * and six readouts (eight with the rule), four of them on reversed copies. Either way a few elementwise kernels: about five
- * times the cost of gka_forward with bf16 tensors and operands; the paper's chunk-wise backward kernels are not reproduced.
+ * and six readouts (eight with the rule), four of them on reversed copies. Either way a few elementwise kernels. bf16
+ * tensors and operands at d = 128: about 3.8 times the cost of gka_forward; the paper's chunk-wise backward kernels are not reproduced.
  *   Supported: lambda given or NULL with p->lambda_scale > 0 (the rule lambda_t = a ||H_t||_F, whose w_t H_t terms
  *   of the Lemma in Section 4.2.2 cost two more readouts), zero initial states (gka_backward_from_state takes
  *   others), p->beta and p->alpha as in gka_forward. Explicit strides apply to q, k, v and dy (multiples of 16
@@ -272,7 +279,8 @@ gka_status gka_decode_tokens(const gka_params *p,
  *   dq, dk, dv   [B,T,H,d] float32, 16-byte aligned (written);  dgate [B,T,H] float32 (written)
  *   dlambda, dbeta, dalpha [B,T,H] float32, each written if not NULL (dlambda only when lambda is given)
  *   workspace: gka_backward_workspace_bytes(p) bytes, 256-byte aligned (GKA_BF16 tensors: the size of 17 tensors like q,
- *   GKA_F32 tensors: of 23, plus the forward workspace); contents unspecified afterwards. */
+ *   GKA_F32 tensors: of 23, plus the forward workspace or, if that is more, the solves' walk's: 192 KiB a summary, of which there
+ *   are up to 1024 and one per pair, and 128 KiB a workgroup); contents unspecified afterwards. */
 size_t gka_backward_workspace_bytes(const gka_params *p);
 gka_status gka_backward(const gka_params *p,
                         const void *q, const void *k, const void *v,

@@ -1229,15 +1229,16 @@ __device__ __forceinline__ void dual_solve_tokens(Ctx &c, const DualSolveArgs &d
 // reuses everything in front of the first one's passes. Replaces a state pass that wrote the chunk states to memory and a
 // solve kernel that read them, the pass that rounded alpha dxt, and, for a lambda that is given, the combination of the vectors
 // afterwards (the dots are formed here, where the vectors are in registers). Packed tensors. Bound as the forward kernel is, the
-// passes most of its cycles. 64 pairs x 4096 tokens, 10 passes: 402 us and 63 for the summaries (which the readouts use too), in
+// passes most of its cycles. 64 pairs x 4096 tokens, 10 passes: 396 us and 62 for the summaries (which the readouts use too), in
 // place of 48 + 78 (state pass), 507 (two-phase solve), 43 (rounding of alpha dxt), 80 (combination, 5 left) and 2 x 32 (the
-// readouts' summaries); the whole backward pass 1385 -> 1066 with it.
+// readouts' summaries); the whole backward pass 1387 -> 1036 with it and the present gka_reverse.hip.
 // The passes are SEPARATE: dk is a sum of large terms that cancel, and single elements of it follow the rounding of P o M. With
 // the system divided by zeta_c as in the forward kernel the walk took 376 us and was as precise in the norm, but elements of dk
 // were up to 0.5 of their size or of the root mean square away from the two-phase solve's; so they are up to 0.22. With a state
 // accumulator of each tile over all passes: 430 (32 registers more). H in memory during the passes: 402, in registers 450.
-// Errors against the oracle (2-norm, mean over 32 sequences of 150 and 420 tokens) are the two-phase solve's: dk 3.6e-3, with the
-// rule 5.6e-3; dq 1.3e-3, dv 1.8e-3, dlambda 3.45e-3; gate gradient 3.26 -> 3.08e-3.
+// Errors against the oracle (2-norm; root mean square over 32 sequences of 777 tokens, 10 passes) are the two-phase solve's: dk 3.64e-3
+// (two-phase 3.66e-3), with the rule 1.21e-2 (1.21e-2), dq 1.44e-3, dv 1.82e-3, dlambda 7.26e-3 (all the same); gate gradient
+// 4.01e-3 (4.23e-3), with the variants 2.16e-3 (2.13e-3), with the rule 0.99e-2 (1.03e-2): the two are independent there.
 template <bool GATED>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dual_solve_kernel(DualSolveArgs d)
 {

@@ -14,8 +14,8 @@
 // Operands of all contractions over features sit in LDS as fragments of v_mfma_f32_16x16x32: lane (n, kg) = (lane & 15,
 // lane >> 4), eight values, slot p <-> feature 32 s + 16 (p / 4) + 4 kg + p % 4. A wave's rows of a vector are one such
 // fragment.
-// Measured, 32 pairs x 1024 tokens, 10 passes, us: this kernel 313 in place of 610 with float32 products, the whole forward pass
-// (with the state pass on pieces too) 724 -> 374; 4 pairs x 300 tokens 119 -> 57. Two thirds of a workgroup's time are its
+// Measured, 32 pairs x 1024 tokens, 10 passes, us: this kernel 299 in place of 610 with float32 products, the whole forward pass
+// (with the state pass on pieces too) 724 -> 381; 4 pairs x 300 tokens 119 -> 57. Two thirds of a workgroup's time are its
 // states on their way from memory (512 KiB, nothing beside it on the CU) and what surrounds the passes; a pass is 7.4 k
 // cycles, of which the matrix pipe needs 4.4 k and LDS 3.2 k. Against the oracle: the solve's result 3.4e-7 -> 2.2e-7 (2-norm;
 // 2.9e-6 both with lambda a hundredth), ||H_t||_F 3.5e-7 -> 2.5e-7, the output its own rounding both.
