@@ -6,8 +6,8 @@
 //     of what is not much smaller; else within 2^-34 of the largest, 2^-29 for the updates): S x ~ Sh xh + Sl xh + Sh xl, what is left out is
 //     2^-22 of the product, less than the rounding of a float32 sum of 256 terms. s is chosen per row of a state (largest
 //     element to [2^9, 2^10); per wave, for its 32 rows, small rows beside large ones kept few digits), per token for the
-//     solve's updates (largest element of the first to [2^4, 2^5): the passes may grow them, see kMaxPasses) and once more for
-//     the readout's operand.
+//     solve's updates (largest element of the first to [2^4, 2^5): the passes may grow them, see kMaxPasses and kRescaleAbove)
+//     and once more for the readout's operand.
 //   * keys are one binary16 piece with a power of two per key for K x (two products; largest element to [2^14, 2^15): exact down to
 //     2^-31 of it, below that within 2^-39 of it), and bf16 as stored for K^T (P o M) and V^T (P o M), whose other operand, the
 //     masked products, is cut into three bf16 pieces (24 bits).
@@ -41,7 +41,7 @@ struct WideShape {
     static constexpr size_t row_bytes = (size_t)kChunk * kRowStride * 2;          // k rows, later v rows, bf16
     static constexpr size_t x_bytes = (size_t)TT * 2 * kSteps * 64 * 16;          // operand fragments [tt][hi, lo][s][lane]
     static constexpr size_t p_bytes = (size_t)TT * 2 * 3 * 64 * 16;               // masked products [tt][jb][piece][lane]
-    static constexpr size_t tab_bytes = (kChunk + 2 * kWideWaves * 16 * TT + kWideD) * 4;  // scales of keys, maxima of tokens, scales of state rows
+    static constexpr size_t tab_bytes = (kChunk + 2 * kWideWaves * 16 * TT + kWideD + 2 * 16 * TT) * 4;  // scales of keys, maxima of tokens, scales of state rows, flags
     static constexpr size_t lds_bytes = k_bytes + row_bytes + x_bytes + p_bytes + tab_bytes;
     static_assert((2 * kWideWaves + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand fragments");
 };
@@ -90,9 +90,17 @@ __device__ __forceinline__ u16x4 bits4(f32x4 x)
 // the 2-norm, so delta_i = (omega_i - 1) delta_{i-1} + omega_i 2 / (L + mu) r_{i-1}, omega_i < 2, is at most (2 i + 1) |delta_0|, at
 // most 16 (2 i + 1) of its largest element, which is below 2^5: 2^9 (2 i + 1) < 65504.
 constexpr int kMaxPasses = 60;
+// A token whose update has an element above this in a pass has the next one scaled down by 2^kRescale. Systems of the layer hardly get
+// there; from an initial state that is not positive semidefinite the updates grow, in the 2-norm at most sevenfold in a pass (A delta
+// is at most (L + lambda) |delta|, the step 2 / (L + mu), omega < 2), in their largest element at most 16 times as much: below
+// 2^9 * 112 < 65504, and by less than 2^kRescale.
+constexpr float kRescaleAbove = 0x1p9f;
+constexpr int kRescale = 8;
 
-// GATED: the layer's variants (write gate, alpha-connection, lambda_t = a ||H_t||_F) and the solve's result as an output.
-template <int TT, bool GATED>
+// GATED: the layer's variants (write gate, alpha-connection, lambda_t = a ||H_t||_F) and the solve's result as an output. GIVEN: the
+// sequence starts from given states, which nobody has looked at: updates that grow are scaled down. (32 pairs x 1024 tokens 366 -> 373
+// us with it; from zero states every H_t is positive semidefinite.)
+template <int TT, bool GATED, bool GIVEN>
 __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void solve_wide_kernel(SolveArgs a)
 {
     typedef WideShape<TT> SH;
@@ -117,6 +125,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
     float *sScale = sMax + 2 * NW * 16 * TT + 32 * w;    // [NW][32] inverse scales of this wave's rows of a state
+    int *sGrown = (int *)(sMax + 2 * NW * 16 * TT + kWideD);                      // [even, odd pass][16 TT] update above kRescaleAbove
+    if (GIVEN && tid < 2 * 16 * TT) sGrown[tid] = 0;
     // The workgroups of a chunk read the same 512 KiB of states. They get block indices equal modulo 8, next to each other: the
     // same XCD, whose L2 then serves all but the first, at about the same time. (All of one token block before the next:
     // states read from HBM once for each,
@@ -472,10 +482,31 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     for (int tt = 0; tt < TT; ++tt) zs[tt] = zeta[tt] * pow2(-xexp[tt]);
     for (int it = 0; it < a.n_iter; ++it) {
         publish(dl);
+        int *flags = sGrown + (it & 1) * 16 * TT + n;
+        if constexpr (GIVEN) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                float largest = 0.0f;
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) largest = fmaxf(largest, fabsf(dl[rt][tt][r]));
+                if (largest * pow2(xexp[tt]) > kRescaleAbove) flags[16 * tt] = 1;
+            }
+        }
         lds_barrier();                                   // delta visible; the masked products of the last pass are used up
+        int grown[TT] = {};
+        if constexpr (GIVEN) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) grown[tt] = flags[16 * tt];
+        }
         masked_key_products();
         state_product(gS);
         lds_barrier();
+        if (GIVEN && w == 0 && kg == 0) {                // (everybody has read them; they are written again two barriers from here)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) flags[16 * tt] = 0;
+        }
         intra_product(gI);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
@@ -490,6 +521,16 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                     dl[rt][tt][r] = cm * dl[rt][tt][r] + cs * res;
                     xi[rt][tt][r] += dl[rt][tt][r];
                 }
+            }
+        }
+        if constexpr (GIVEN) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                const int down = xexp[tt] > kRescale - 126 && grown[tt] ? kRescale : 0;
+                xexp[tt] -= down;
+                zs[tt] *= pow2(down);
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) gS[rt][tt] *= pow2(-down);
             }
         }
     }
@@ -538,18 +579,18 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                 IO::store4(a.o, tok_off[tt] + 16 * rt, gS[rt][tt][0], gS[rt][tt][1], gS[rt][tt][2], gS[rt][tt][3]);
 }
 
-template <int TT, bool GATED>
+template <int TT, bool GATED, bool GIVEN>
 static hipError_t launch_solve_wide_t(const SolveArgs &a, hipStream_t stream)
 {
     typedef WideShape<TT> SH;
     static bool lds_raised[kMaxLdsDevices] = {};
-    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)solve_wide_kernel<TT, GATED>, SH::lds_bytes}});
+    hipError_t e = raise_lds_limits(lds_raised, {{(const void *)solve_wide_kernel<TT, GATED, GIVEN>, SH::lds_bytes}});
     if (e != hipSuccess) return e;
     // (outputs that replace rows of k or v: the token blocks of a chunk one launch after the other, as in gka_solve_f32.hip)
     const bool over_rows = a.o == a.v || a.o == a.k;
     SolveArgs args = a;
     for (args.skip_blocks = over_rows ? 0 : -1; args.skip_blocks < (over_rows ? SH::TB : 0); ++args.skip_blocks) {
-        hipLaunchKernelGGL((solve_wide_kernel<TT, GATED>), dim3((unsigned)(a.n_pairs * a.n_chunks * (over_rows ? 1 : SH::TB))),
+        hipLaunchKernelGGL((solve_wide_kernel<TT, GATED, GIVEN>), dim3((unsigned)(a.n_pairs * a.n_chunks * (over_rows ? 1 : SH::TB))),
                            dim3(kWideThreads), SH::lds_bytes, stream, args);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -565,8 +606,12 @@ bool solve_wide_takes(const SolveArgs &a, int d, bool io_bf16)
 hipError_t launch_solve_wide(const SolveArgs &a, int tiles, hipStream_t stream)
 {
     const bool gated = a.beta || a.alpha || !a.lambda || a.xhat_out;
-    if (tiles == 2) return gated ? launch_solve_wide_t<2, true>(a, stream) : launch_solve_wide_t<2, false>(a, stream);
-    return gated ? launch_solve_wide_t<1, true>(a, stream) : launch_solve_wide_t<1, false>(a, stream);
+    if (a.init_states) {
+        if (tiles == 2) return gated ? launch_solve_wide_t<2, true, true>(a, stream) : launch_solve_wide_t<2, false, true>(a, stream);
+        return gated ? launch_solve_wide_t<1, true, true>(a, stream) : launch_solve_wide_t<1, false, true>(a, stream);
+    }
+    if (tiles == 2) return gated ? launch_solve_wide_t<2, true, false>(a, stream) : launch_solve_wide_t<2, false, false>(a, stream);
+    return gated ? launch_solve_wide_t<1, true, false>(a, stream) : launch_solve_wide_t<1, false, false>(a, stream);
 }
 
 }  // namespace gka

@@ -120,3 +120,30 @@ def test_a_wiped_state_and_a_tiny_key_behind_it():
     x["k"][0, 100:] *= 2.0 ** -13
     x["lam"][0, 100:] *= 2.0 ** -26
     check(*both(x, 8), tol=1e-4)          # (what exp(-100) leaves of the old state is not negligible beside 2^-26 in the same way)
+
+
+@pytest.mark.parametrize("T,n_iter", [(150, 20), (200, 30), (129, 60)])
+@pytest.mark.parametrize("variants", [False, True])
+def test_initial_states_that_are_not_positive_semidefinite(T, n_iter, variants):
+    """Eigenvalues below zero lie outside the interval that the iteration is made for and its updates grow, thousandfold in ten
+    passes: they are scaled down on the way, and what comes out is what float32 products give. A pass's products are right to
+    2^-22 of their operands' size on either side; where everything grows these errors add up, n_iter of them (a factor of four
+    for their number and for elements that are larger than the common size). Behind a wiped state in the same chunk nothing grows."""
+    w = synth.CFG2.scaled(B=1, H=2, T=T, d=256, n_iter=n_iter, seed=82)
+    x = synth.make_inputs(w)
+    x["gate"][:] = 1.0 - 2.0 ** -12                  # (the initial state stays,
+    x["gate"][0, 100, 1] = 0.0                       # but for the second pair's)
+    A = np.random.default_rng(82).standard_normal((1, 2, 256, 256)).astype(np.float32)
+    kw = dict(H_init=to_device(A + A.transpose(0, 1, 3, 2), "f32"), U_init=to_device(A, "f32"))
+    if variants:
+        g = synth.make_gates(w)
+        kw["variants"] = {n: g[n] for n in ("beta", "alpha")}
+    print("not semidefinite", T, n_iter, variants, flush=True)
+    got, want = both(x, n_iter, **kw)
+    first = np.abs(2.0 * x["q"] / (want["fro"] + 2.0 * x["lam"])[..., None])
+    for pair, tokens in ((0, slice(0, T)), (1, slice(0, 100)), (1, slice(100, 128))):
+        a, b = (y["xhat"][0, tokens, pair] for y in (got, want))
+        grown, err = np.abs(b).max() / first[0, tokens, pair].max(), np.abs(a - b).max() / np.abs(b).max()
+        print(pair, tokens, grown, err, flush=True)
+        assert np.isfinite(b).all() and (grown > 2.0 ** 14) == (tokens.start == 0)
+        assert np.isfinite(got["o"]).all() and err <= n_iter * 2.0 ** -20
