@@ -22,8 +22,7 @@
 // matrix pipe busy 75 % of it); bf16 tensors there: gka_solve_wide.hip. Registers: capped at 128 up to d = 128 (four waves per SIMD), at 256 at d = 256 (two). With
 // TT = 2 that spills: d = 128 3 (bf16 tensors), 14 (float32), 12 to 29 with the variants or two right-hand sides; d = 256
 // 15 (bf16), 31 (float32), up to 57 with the variants; d = 64 16 with the variants of float32 tensors. With TT = 1 none.
-#include "gka_device.hpp"
-#include "gka_kernels.hpp"
+#include "gka_solve_shared.hpp"
 
 namespace gka {
 
@@ -40,7 +39,7 @@ struct SolveF32Shape {
     static constexpr size_t x_bytes = (size_t)16 * TT * (D + 4) * 4;
     static constexpr size_t p_bytes = (size_t)16 * TT * (kChunk + 4) * 4;
     static constexpr size_t lds_bytes = k_bytes + x_bytes + p_bytes;
-    static_assert((2 * NW + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand rows");
+    static_assert(NormScratch<NW>::bytes <= x_bytes, "the scratch of the norm fits the operand rows");
 };
 
 // float4 index of columns 4 c4 .. + 3 of a row in a tile of rows of W floats. Rows are padded by 16 bytes: sixteen rows at
@@ -56,7 +55,6 @@ __device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
 // sum over the four lanes that hold the rows of one token
 __device__ __forceinline__ float sum_kg(float x)
 {
@@ -77,11 +75,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
     f32x4 *sX = (f32x4 *)(smem + SH::k_bytes);         // operand rows [16 TT][D]
     f32x4 *sP = (f32x4 *)(smem + SH::k_bytes + SH::x_bytes);   // masked key products [16 TT][64]
     // scratch of the norm, in the operand rows
-    float *sA = (float *)sX;                           // [NW][64] k_j^T H k_j, a wave's rows
-    float *sB = sA + NW * 64;                          // [4][64]  sum of m[i,j] G_ij^2 over a tile of i
-    float *sDg = sB + 4 * 64;                          // [64]     G_jj^2
-    float *sW = sDg + 64;                              // [64]     w_j
-    float *sF = sW + 64;                               // [NW][64] sum of m[j,c]^2 w_j over a wave's share of j
+    const NormScratch<NW> norm(sX);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -176,19 +170,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
     float zeta[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) zeta[tt] = exp2f(__shfl(Gall, c_loc[tt], 64));
-    // beta_j M[j,c] for rows j = 16 jt + 4 kg + r and the column c; strict: j < c
-    auto mask4 = [&](int jt, int c, bool strict) {
-        const float Gc = __shfl(Gall, c, 64);
-        f32x4 m;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 16 * jt + 4 * kg + r;
-            float x = __builtin_amdgcn_exp2f(Gc - __shfl(Gall, j, 64));
-            if constexpr (GATED) x *= __shfl(ball, j, 64);
-            m[r] = (strict ? j < c : j <= c) ? x : 0.0f;
-        }
-        return m;
-    };
+    auto mask4 = [&](int jt, int c, bool strict) { return mask_rows<GATED>(Gall, ball, kg, jt, c, strict); };
     // this wave's (key tile, token tile) pairs of the masked key products
     int unit_j[MAXU], unit_t[MAXU];                    // token tile TT: no such pair
     f32x4 unit_m[MAXU];
@@ -217,10 +199,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
         return c0 + c1;
     };
 
-    // ---------------- chunk-wise Frobenius norm ----------------
-    // ||H_c||^2 = zeta_c^2 ||H_[n]||^2 + sum_{j<=c} m[j,c]^2 w_j,
-    // w_j = 2 (zeta_j k_j^T H_[n] k_j + sum_{i<j} m[i,j] G_ij^2) / beta_j + G_jj^2,  G = K K^T
-    // (the folded three-term expansion, see gka_chunk_solve.hip)
+    // ---------------- chunk-wise Frobenius norm (gka_solve_shared.hpp) ----------------
     float fro[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) fro[tt] = 0.0f;
@@ -247,7 +226,7 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
                 }
                 part = sum_kg(part);
             }
-            if (kg == 0) sA[w * 64 + 16 * jt + n] = part;
+            if (kg == 0) norm.sA[w * 64 + 16 * jt + n] = part;
         }
         for (int u0 = w; u0 < JT * (JT + 1) / 2; u0 += NW) {
             int it = u0, jt = 0;
@@ -264,38 +243,16 @@ __device__ __forceinline__ void solve_f32_body(const SolveArgs &a)
             bp = sum_kg(bp);
             dp = sum_kg(dp);
             if (kg == 0) {
-                sB[it * 64 + 16 * jt + n] = bp;
-                if (it == jt) sDg[16 * jt + n] = dp;
+                norm.sB[it * 64 + 16 * jt + n] = bp;
+                if (it == jt) norm.sDg[16 * jt + n] = dp;
             }
         }
-        lds_barrier();
-        if (tid < 16 * JT) {                           // (the first wave: lane j = token j)
-            float as = 0.0f, bs = 0.0f;
-#pragma unroll
-            for (int i = 0; i < NW; ++i) as += sA[i * 64 + tid];
-            for (int i = 0; i <= tid >> 4; ++i) bs += sB[i * 64 + tid];
-            const float cross = 2.0f * (exp2f(Gall) * as + bs);
-            sW[tid] = GATED ? (ball > 0.0f ? cross / ball + sDg[tid] : 0.0f) : cross + sDg[tid];
-        }
-        lds_barrier();
-        float f = 0.0f;                                // lane c = token c; keys dealt out over the waves
-#pragma unroll
-        for (int i = 0; i < 64 / NW; ++i) {
-            const int j = i * NW + w;
-            if (j < 16 * JT) {
-                float m = __builtin_amdgcn_exp2f(Gall - lane_value(Gall, j));
-                if constexpr (GATED) m *= lane_value(ball, j);
-                m = j <= lane ? m : 0.0f;
-                f += m * m * sW[j];
-            }
-        }
-        sF[w * 64 + lane] = f;
-        lds_barrier();
+        sum_norm_terms<NW, GATED>(norm, tid, w, JT, Gall, ball);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             float fs = 0.0f;
 #pragma unroll
-            for (int i = 0; i < NW; ++i) fs += sF[i * 64 + c_loc[tt]];
+            for (int i = 0; i < NW; ++i) fs += norm.sF[i * 64 + c_loc[tt]];
             fro[tt] = sqrtf(fmaxf(zeta[tt] * zeta[tt] * hn2 + fs, 0.0f));
             if (a.fro_out && valid[tt] && w == 0 && kg == 0)
                 a.fro_out[gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H] = fro[tt];

@@ -19,8 +19,7 @@
 // states on their way from memory (512 KiB, nothing beside it on the CU) and what surrounds the passes; a pass is 7.4 k
 // cycles, of which the matrix pipe needs 4.4 k and LDS 3.2 k. Against the oracle: the solve's result 3.4e-7 -> 2.2e-7 (2-norm;
 // 2.9e-6 both with lambda a hundredth), ||H_t||_F 3.5e-7 -> 2.5e-7, the output its own rounding both.
-#include "gka_device.hpp"
-#include "gka_kernels.hpp"
+#include "gka_solve_shared.hpp"
 
 namespace gka {
 
@@ -43,12 +42,11 @@ struct WideShape {
     static constexpr size_t p_bytes = (size_t)TT * 2 * 3 * 64 * 16;               // masked products [tt][jb][piece][lane]
     static constexpr size_t tab_bytes = (kChunk + 2 * kWideWaves * 16 * TT + kWideD + 2 * 16 * TT) * 4;  // scales of keys, maxima of tokens, scales of state rows, flags
     static constexpr size_t lds_bytes = k_bytes + row_bytes + x_bytes + p_bytes + tab_bytes;
-    static_assert((2 * kWideWaves + 6) * 64 * 4 <= x_bytes, "the scratch of the norm fits the operand fragments");
+    static_assert(NormScratch<kWideWaves>::bytes <= x_bytes, "the scratch of the norm fits the operand fragments");
 };
 
 __device__ __forceinline__ f32x4 mma_h(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f32x4 mma_b(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
 // largest over the four lanes that hold the rows of one token
 __device__ __forceinline__ float max_kg(float x)
 {
@@ -114,11 +112,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     float *sKs = (float *)((unsigned char *)sP + SH::p_bytes);                    // [64]
     float *sMax = sKs + kChunk;                                                   // [updates, readout][NW][16 TT]
     // scratch of the norm, in the operand fragments
-    float *sA = (float *)sX;                             // [NW][64] k_j^T H k_j, a wave's rows
-    float *sB = sA + NW * 64;                            // [4][64]  sum of m[i,j] G_ij^2 over a tile of i
-    float *sDg = sB + 4 * 64;                            // [64]     G_jj^2
-    float *sW = sDg + 64;                                // [64]     w_j
-    float *sF = sW + 64;                                 // [NW][64] sum of m[j,c]^2 w_j over a wave's share of j
+    const NormScratch<NW> norm(sX);
     const PaddedRows at{kRowStride};
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -225,19 +219,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     float zeta[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) zeta[tt] = exp2f(__shfl(Gall, c_loc[tt], 64));
-    // beta_j M[j,c] for rows j = 16 jt + 4 kg + r and the column c; strict: j < c
-    auto mask4 = [&](int jt, int c, bool strict) {
-        const float Gc = __shfl(Gall, c, 64);
-        f32x4 m;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 16 * jt + 4 * kg + r;
-            float x = __builtin_amdgcn_exp2f(Gc - __shfl(Gall, j, 64));
-            if constexpr (GATED) x *= __shfl(ball, j, 64);
-            m[r] = (strict ? j < c : j <= c) ? x : 0.0f;
-        }
-        return m;
-    };
+    auto mask4 = [&](int jt, int c, bool strict) { return mask_rows<GATED>(Gall, ball, kg, jt, c, strict); };
     // this wave's (key tile, token tile) pair of the masked key products (token tile TT: none)
     int unit_j, unit_t = 0;
     f32x4 unit_m;
@@ -284,7 +266,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
     typedef std::integral_constant<int, 1> One;
     typedef std::integral_constant<int, 2> Two;
 
-    // ---------------- chunk-wise Frobenius norm (as in gka_solve_f32.hip) ----------------
+    // ---------------- chunk-wise Frobenius norm (gka_solve_shared.hpp) ----------------
     float fro[TT];
     {
         for (int jt = 0; jt < JT; ++jt) {
@@ -310,7 +292,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
                 }
                 part = sum_over_kg(part) * ksj * ksj;
             }
-            if (kg == 0) sA[w * 64 + 16 * jt + n] = part;
+            if (kg == 0) norm.sA[w * 64 + 16 * jt + n] = part;
         }
         for (int u0 = w; u0 < JT * (JT + 1) / 2; u0 += NW) {
             int it = u0, jt = 0;
@@ -328,38 +310,16 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
             bp = sum_over_kg(bp);
             dp = sum_over_kg(dp);
             if (kg == 0) {
-                sB[it * 64 + 16 * jt + n] = bp;
-                if (it == jt) sDg[16 * jt + n] = dp;
+                norm.sB[it * 64 + 16 * jt + n] = bp;
+                if (it == jt) norm.sDg[16 * jt + n] = dp;
             }
         }
-        lds_barrier();
-        if (tid < 16 * JT) {                             // (the first wave: lane j = token j)
-            float as = 0.0f, bs = 0.0f;
-#pragma unroll
-            for (int i = 0; i < NW; ++i) as += sA[i * 64 + tid];
-            for (int i = 0; i <= tid >> 4; ++i) bs += sB[i * 64 + tid];
-            const float cross = 2.0f * (exp2f(Gall) * as + bs);
-            sW[tid] = GATED ? (ball > 0.0f ? cross / ball + sDg[tid] : 0.0f) : cross + sDg[tid];
-        }
-        lds_barrier();
-        float f = 0.0f;                                  // lane c = token c; keys dealt out over the waves
-#pragma unroll
-        for (int i = 0; i < 64 / NW; ++i) {
-            const int j = i * NW + w;
-            if (j < 16 * JT) {
-                float m = __builtin_amdgcn_exp2f(Gall - lane_value(Gall, j));
-                if constexpr (GATED) m *= lane_value(ball, j);
-                m = j <= lane ? m : 0.0f;
-                f += m * m * sW[j];
-            }
-        }
-        sF[w * 64 + lane] = f;
-        lds_barrier();
+        sum_norm_terms<NW, GATED>(norm, tid, w, JT, Gall, ball);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             float fs = 0.0f;
 #pragma unroll
-            for (int i = 0; i < NW; ++i) fs += sF[i * 64 + c_loc[tt]];
+            for (int i = 0; i < NW; ++i) fs += norm.sF[i * 64 + c_loc[tt]];
             fro[tt] = sqrtf(fmaxf(zeta[tt] * zeta[tt] * hn2 + fs, 0.0f));
             if (a.fro_out && valid[tt] && w == 0 && kg == 0)
                 a.fro_out[gate_base + (int64_t)(tok0 + c_loc[tt]) * a.H] = fro[tt];
